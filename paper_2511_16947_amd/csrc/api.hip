@@ -25,8 +25,10 @@ int check_shape(const fine_shape* s) {
     return FINE_OK;
 }
 
+// the matrix-core kernels keep byte offsets inside a row tile and inside 32 k-rows of a weight matrix in 32 bits
 bool use_mfma(const fine_shape& s) {
-    return s.dtype == FINE_BF16 && !(s.flags & FINE_FLAG_SIMPLE_FFN);
+    if (s.flags & FINE_FLAG_SIMPLE_FFN) return false;
+    return s.dtype == FINE_BF16 || (s.d <= (1 << 20) && s.f <= (1 << 20));
 }
 
 }  // namespace
@@ -176,6 +178,9 @@ int fine_grouped_ffn(const fine_shape* shape, int32_t rank, const void* x_perm, 
         return FINE_INVALID_ARG;
     if (ws_bytes < ffn_ws_layout(*shape).total) return FINE_WORKSPACE_TOO_SMALL;
     const int lo = rank < 0 ? 0 : rank, hi = rank < 0 ? shape->G : rank + 1;
+    if (use_mfma(*shape) && shape->dtype == FINE_F32)
+        return launch_ffn_f32(*shape, lo, hi, x_perm, w_gate, w_up, w_down, seg_off, y_perm, act_save, (char*)ws,
+                              (hipStream_t)stream);
     if (use_mfma(*shape))
         return launch_ffn_mfma(*shape, lo, hi, x_perm, w_gate, w_up, w_down, seg_off, y_perm, act_save, (char*)ws,
                                (hipStream_t)stream);

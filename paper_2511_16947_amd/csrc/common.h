@@ -6,6 +6,7 @@
 #include <stdint.h>
 #include <stddef.h>
 
+#include <algorithm>
 #include <atomic>
 
 #include "../../include/finemoe.h"
@@ -180,6 +181,9 @@ int launch_tile_map(const fine_shape& s, const int32_t* seg_off, int rank_lo, in
 int launch_ffn_simple(const fine_shape& s, int rank_lo, int rank_hi, const void* x_perm,
                       const void* wg, const void* wu, const void* wd, const int32_t* seg_off,
                       void* y_perm, void* act_save, char* ws, hipStream_t st);
+int launch_ffn_f32(const fine_shape& s, int rank_lo, int rank_hi, const void* x_perm,
+                   const void* wg, const void* wu, const void* wd, const int32_t* seg_off,
+                   void* y_perm, void* act_save, char* ws, hipStream_t st);
 int launch_ffn_mfma(const fine_shape& s, int rank_lo, int rank_hi, const void* x_perm,
                     const void* wg, const void* wu, const void* wd, const int32_t* seg_off,
                     void* y_perm, void* act_save, char* ws, hipStream_t st);

@@ -2,14 +2,21 @@
 // The experts are picked in descending logit order (equal logits: lower index first), and
 // the combine weights are the softmax over the K selected logits.
 //
-// bf16 layers with E a multiple of 8 up to 256: the logits of 32 tokens are a skinny GEMM on
+// bf16 layers of up to 256 experts: the logits of 32 tokens are a skinny GEMM on
 // v_mfma_f32_32x32x16_bf16 with the router weights as the row operand, so that each lane ends
 // up with the logits of ITS token (lane & 31) in registers.  Token fragments are 16-byte global
 // loads; the router weights [d, E] lie the wrong way for a fragment, so 64-k slabs of them
 // are staged in LDS as they are and read with the transposing LDS read (lane layout: see
-// gemm_w8.h).  A block is 32 tokens; its four waves split the k range (E <= 64) or the experts
-// (larger E), so that T / 32 blocks of four busy waves stream x.
-// Everything else (fp32 layers, other E): each wave owns TB tokens; lane l accumulates the
+// gemm_w8.h).  A block is 32 tokens; its waves split the k range (E <= 64) or the experts
+// (larger E), so that T / 32 blocks of busy waves stream x.  E need not be a multiple of 8: a
+// 16-byte piece that reaches past a row's end brings the next row's first weights into columns
+// that no expert owns (they are masked before the selection); only the matrix's last pieces, which
+// would reach past its end, are fetched from further left and shifted (1305 tokens, d 1088, 20 experts: 184 us with
+// the lane-per-expert kernel, 8 us here).
+// fp32 layers of up to 256 experts: the same on v_mfma_f32_32x32x2_f32, whose row operand takes one
+// weight per lane, 32 neighbouring experts at a time: both operands come straight from memory (2048
+// tokens, d 1024, 16 experts: 135 us with the lane-per-expert kernel, 14 us here; 256 tokens, d 128: 28 and 5.5 us).
+// More than 256 experts (or a router matrix of 2^31 weights): each wave owns TB tokens; lane l accumulates the
 // logits of experts l, l+64, ... in fp32 while the token rows stream through LDS, then K
 // rounds of a cross-lane argmax.
 #include <cfloat>
@@ -178,7 +185,25 @@ __device__ inline void select_topk(mfma::f32x16 (&acc)[NT], const float* __restr
 }
 
 
-template <int NT>
+// 16 bytes of router weights from an address that is a multiple of 2 only
+// (ODD: E is not a multiple of 8) or of 16; `last`: the last piece that lies inside the matrix.  (Two instantiations
+// because the clamp and the 2-byte alignment cost the aligned case 4-12 %: 256 experts, d 7168: 50 -> 54 us.)
+typedef mfma::u32x4 __attribute__((aligned(2))) u32x4_a2;
+template <bool ODD>
+__device__ inline mfma::u32x4 load_piece(const uint16_t* w, size_t k_off, uint32_t piece, uint32_t last) {
+    if constexpr (ODD) return *reinterpret_cast<const u32x4_a2*>(w + min((uint32_t)k_off + piece, last));
+    else return *reinterpret_cast<const mfma::u32x4*>(w + k_off + (int)piece);
+}
+
+// A piece that was fetched `over` elements left of where it belongs (the end of the matrix): its elements
+// from `over` on go to the places they belong to.
+__device__ inline void store_shifted(char* lds, const mfma::u32x4& v, int over) {
+#pragma unroll
+    for (int j = 1; j < 8; ++j)
+        if (j >= over) *reinterpret_cast<uint16_t*>(lds + 2 * (j - over)) = (uint16_t)(v[j >> 1] >> (16 * (j & 1)));
+}
+
+template <int NT, bool ODD>
 __global__ __launch_bounds__(256) void k_topk_mfma(const uint16_t* __restrict__ x, const uint16_t* __restrict__ w_router,
                                                    const float* __restrict__ bias, int Tn, int d, int E, int K,
                                                    int32_t* __restrict__ topk_idx, float* __restrict__ topk_w) {
@@ -211,15 +236,18 @@ __global__ __launch_bounds__(256) void k_topk_mfma(const uint16_t* __restrict__ 
     // kk are 32 h + 8 kk .. + 7, matching the 64 contiguous bytes each lane loads of its token
     const int g = lane >> 4, i4 = lane & 15;
     const int tr_off = (32 * (g >> 1) + (i4 >> 2)) * PITCH + (16 * (g & 1) + 4 * (i4 & 3)) * 2;
-    const int chunks_per_row = E / 8;                 // 16-byte pieces of a router-weight row
+    const int chunks_per_row = (E + 7) / 8;           // 16-byte pieces of a router-weight row
     const int nsteps = d / 64;
+
+    const uint32_t last_piece = (uint32_t)d * E - 8;      // (d * E < 2^31: checked by the launcher)
 
     char* slab = s_slab + wave * (kSlabBytes / 4);
     // Each lane moves up to PITCH / 16 pieces of 16 bytes of a slab; the next step's pieces and
     // token values are fetched into registers before the current step is computed, so that a
     // step does not cost a whole memory latency.
     constexpr int MAXP = PITCH / 16;
-    int w_off[MAXP], s_off[MAXP];
+    uint32_t w_off[MAXP];
+    int s_off[MAXP];
 #pragma unroll
     for (int p = 0; p < MAXP; ++p) {
         const int c = lane + 64 * p, kr = c / max(1, chunks_per_row), ce = c - kr * chunks_per_row;
@@ -231,7 +259,7 @@ __global__ __launch_bounds__(256) void k_topk_mfma(const uint16_t* __restrict__ 
     auto fetch = [&](int k0) {
 #pragma unroll
         for (int p = 0; p < MAXP; ++p)
-            if (p < chunks_per_row) wreg[p] = *reinterpret_cast<const u32x4*>(w_router + (size_t)k0 * E + w_off[p]);
+            if (p < chunks_per_row) wreg[p] = load_piece<ODD>(w_router, (size_t)k0 * E, w_off[p], last_piece);
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) xnext[kk] = *reinterpret_cast<const bf16x8*>(xrow + k0 + 8 * kk);
     };
@@ -240,6 +268,13 @@ __global__ __launch_bounds__(256) void k_topk_mfma(const uint16_t* __restrict__ 
 #pragma unroll
         for (int p = 0; p < MAXP; ++p)
             if (p < chunks_per_row) *reinterpret_cast<u32x4*>(slab + s_off[p]) = wreg[p];
+        if (ODD && step == nsteps - 1) {
+#pragma unroll
+            for (int p = 0; p < MAXP; ++p) {
+                const int over = (int)((uint32_t)step * 64 * E + w_off[p] - last_piece);
+                if (p < chunks_per_row && over > 0) store_shifted(slab + s_off[p], wreg[p], over);
+            }
+        }
         bf16x8 xf[4];
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) xf[kk] = xnext[kk];
@@ -286,7 +321,7 @@ __global__ __launch_bounds__(256) void k_topk_mfma(const uint16_t* __restrict__ 
 // With a few thousand tokens even that leaves CUs idle and every block a long chain of dependent
 // steps; then gridDim.y blocks share a token tile, each over its own part of k, and write their
 // partial logits to `partial` [gridDim.y][tiles * 32][NT * 32] floats for k_topk_select.
-template <int NT>
+template <int NT, bool ODD>
 __global__ __launch_bounds__(256) void k_topk_mfma_esplit(const uint16_t* __restrict__ x, const uint16_t* __restrict__ w_router,
                                                           const float* __restrict__ bias, int Tn, int d, int E, int K,
                                                           int32_t* __restrict__ topk_idx, float* __restrict__ topk_w,
@@ -320,7 +355,8 @@ __global__ __launch_bounds__(256) void k_topk_mfma_esplit(const uint16_t* __rest
         for (int q = 0; q < 16; ++q) acc[nt][q] = 0.f;
     const int g = lane >> 4, i4 = lane & 15;
     const int tr_off = (32 * (g >> 1) + (i4 >> 2)) * PITCH + (16 * (g & 1) + 4 * (i4 & 3)) * 2;
-    const int chunks = max(0, min(EPW, E - e0)) / 8;  // 16-byte pieces of this wave's part of a router-weight row
+    const int chunks = (max(0, min(EPW, E - e0)) + 7) / 8;      // 16-byte pieces of this wave's part of a router-weight row
+    const uint32_t last_piece = (uint32_t)d * E - 8;      // (d * E < 2^31: checked by the launcher)
     char* slab = s_mem + wave * SLAB;
     // Pieces of router-weight rows and token values are fetched DEPTH steps ahead of the step that
     // uses them: with one block of four waves per CU nothing else hides the latency of a step's
@@ -331,7 +367,8 @@ __global__ __launch_bounds__(256) void k_topk_mfma_esplit(const uint16_t* __rest
     constexpr int MAXP = PITCH / 16, DEPTH = 3;
     const int steps_all = d / 64, steps_blk = (steps_all + (int)gridDim.y - 1) / (int)gridDim.y;
     const int k_begin = min(steps_all, (int)blockIdx.y * steps_blk) * 64, k_end = min(steps_all, ((int)blockIdx.y + 1) * steps_blk) * 64;
-    int w_off[MAXP], s_off[MAXP];
+    uint32_t w_off[MAXP];
+    int s_off[MAXP];
 #pragma unroll
     for (int p = 0; p < MAXP; ++p) {
         const int c = lane + 64 * p, kr = c / max(1, chunks), ce = c - kr * chunks;
@@ -345,7 +382,7 @@ __global__ __launch_bounds__(256) void k_topk_mfma_esplit(const uint16_t* __rest
     auto fetch = [&](auto slot, int k0) {
         const int kc = min(k0, d - 64);                // past this block's part: some valid step again, never used
 #pragma unroll
-        for (int p = 0; p < MAXP; ++p) wreg[slot.value][p] = *reinterpret_cast<const u32x4*>(w_router + (size_t)kc * E + w_off[p]);
+        for (int p = 0; p < MAXP; ++p) wreg[slot.value][p] = load_piece<ODD>(w_router, (size_t)kc * E, w_off[p], last_piece);
         xreg[slot.value] = *reinterpret_cast<const u32x4*>(xsrc + kc);
     };
     static_for<DEPTH>([&](auto sl) { fetch(sl, k_begin + 64 * sl.value); });
@@ -353,6 +390,13 @@ __global__ __launch_bounds__(256) void k_topk_mfma_esplit(const uint16_t* __rest
         const int xb = ((k0 >> 6) & 1) * kXbytes;
 #pragma unroll
         for (int p = 0; p < MAXP; ++p) *reinterpret_cast<u32x4*>(s_mem + s_off[p]) = wreg[sl.value][p];
+        if (ODD && k0 == d - 64) {
+#pragma unroll
+            for (int p = 0; p < MAXP; ++p) {
+                const int over = (int)((uint32_t)k0 * E + w_off[p] - last_piece);
+                if (p < chunks && over > 0) store_shifted(s_mem + s_off[p], wreg[sl.value][p], over);
+            }
+        }
         *reinterpret_cast<u32x4*>(s_mem + x_st + xb) = xreg[sl.value];
         fetch(sl, k0 + 64 * DEPTH);
         // everybody's piece of this step's token tile is in LDS; the other tile buffer is free again once
@@ -409,6 +453,86 @@ __global__ __launch_bounds__(256) void k_topk_mfma_esplit(const uint16_t* __rest
     select_topk<NT>(all, bias, E, K, t0 + r, Tn, s_val, topk_idx, topk_w);
 }
 
+// fp32 layers.  A block is 32 tokens, its NW waves split k in pieces of 32.  Both MFMA operands come
+// straight from memory: lane (l & 31, h = l >> 5) supplies expert / token (l & 31) and the k-values
+// 8 j + 4 h + 0 .. 3 of a piece (its token's as one 16-byte load, each weight a 4-byte load that 32 lanes make of
+// neighbouring experts).  k-values past d are zeros, experts past E are masked before the selection.
+template <int NT, int NW>
+__global__ __launch_bounds__(64 * NW) void k_topk_f32(const float* __restrict__ x, const float* __restrict__ w_router,
+                                                      const float* __restrict__ bias, int Tn, int d, int E, int K,
+                                                      int32_t* __restrict__ topk_idx, float* __restrict__ topk_w) {
+    using namespace mfma;
+    __shared__ float s_red[NW * NT * 16 * 64];
+    __shared__ float s_val[32][33];
+    typedef f32x4 __attribute__((aligned(4))) f32x4_a4;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, r = lane & 31, h = lane >> 5;
+    const int t0 = blockIdx.x * 32;
+    const float* xrow = x + (size_t)min(t0 + r, Tn - 1) * d;
+    int e_of[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) e_of[nt] = min(32 * nt + r, E - 1);
+    f32x16 acc[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int q = 0; q < 16; ++q) acc[nt][q] = 0.f;
+    constexpr int J = NT <= 2 ? 4 : 1;               // groups of 8 k-values whose loads are in flight together
+    auto group = [&](int k0, auto checked) {
+        f32x4 xv[J];
+        float wv[J][NT][4];
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const int k = k0 + 8 * j + 4 * h;
+            if constexpr (checked.value) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float v = xrow[min(k + q, d - 1)];
+                    xv[j][q] = k + q < d ? v : 0.f;
+                }
+            } else {
+                xv[j] = *reinterpret_cast<const f32x4_a4*>(xrow + k);
+            }
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float v = w_router[(size_t)(checked.value ? min(k + q, d - 1) : k + q) * E + e_of[nt]];
+                    wv[j][nt][q] = checked.value && k + q >= d ? 0.f : v;
+                }
+        }
+#pragma unroll
+        for (int j = 0; j < J; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+                    acc[nt] = __builtin_amdgcn_mfma_f32_32x32x2f32(wv[j][nt][q], xv[j][q], acc[nt], 0, 0, 0);
+    };
+    for (int k0 = wave * 8 * J; k0 < d; k0 += NW * 8 * J) {
+        if (k0 + 8 * J <= d) group(k0, std::false_type{});
+        else group(k0, std::true_type{});
+    }
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int q = 0; q < 16; ++q) s_red[((wave * NT + nt) * 16 + q) * 64 + lane] = acc[nt][q];
+    __syncthreads();
+    for (int i = threadIdx.x; i < NT * 16 * 64; i += 64 * NW) {      // the waves' sums in wave order
+        float sum = s_red[i];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) sum += s_red[w * NT * 16 * 64 + i];
+        s_red[i] = sum;
+    }
+    __syncthreads();
+    if (wave != 0) return;
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int q = 0; q < 16; ++q) acc[nt][q] = s_red[(nt * 16 + q) * 64 + lane];
+    select_topk<NT>(acc, bias, E, K, t0 + r, Tn, s_val, topk_idx, topk_w);
+}
+
+// more than 256 experts, or a router matrix of 2^31 weights
 template <typename T>
 int dispatch(const fine_shape& s, const void* x, const void* w, const float* bias,
              int32_t* idx, float* tw, hipStream_t st) {
@@ -416,9 +540,7 @@ int dispatch(const fine_shape& s, const void* x, const void* w, const float* bia
 #define FINE_TOPK_CASE(TB, EPL)                                                                        \
     hipLaunchKernelGGL((k_topk<T, TB, EPL>), dim3(cdiv(s.T, 4 * TB)), dim3(256), 0, st, (const T*)x,   \
                        (const T*)w, bias, s.T, s.d, s.E, s.K, idx, tw)
-    if (epl == 1) FINE_TOPK_CASE(8, 1);
-    else if (epl == 2) FINE_TOPK_CASE(8, 2);
-    else if (epl <= 4) FINE_TOPK_CASE(8, 4);
+    if (epl <= 4) FINE_TOPK_CASE(8, 4);
     else if (epl <= 8) FINE_TOPK_CASE(4, 8);
     else FINE_TOPK_CASE(2, 16);
 #undef FINE_TOPK_CASE
@@ -488,7 +610,7 @@ __global__ __launch_bounds__(256) void k_topk_select(const float* __restrict__ p
 // Parts of k that blocks of one token tile split among themselves: enough blocks for two per CU,
 // at least eight steps of 64 k each, at most eight parts.
 int topk_parts(const fine_shape& s) {
-    if (s.dtype != FINE_BF16 || s.E <= 64 || s.E > 256 || s.E % 8 != 0 || s.d % 64 != 0 || s.T == 0) return 1;
+    if (s.dtype != FINE_BF16 || s.E <= 64 || s.E > 256 || s.T == 0 || (long long)s.d * s.E >= (1ll << 31)) return 1;
     const int tiles = cdiv(s.T, 32);
     return max(1, min(min(8, cdiv(512, tiles)), s.d / 64 / 8));
 }
@@ -502,34 +624,52 @@ size_t topk_ws_bytes(const fine_shape& s) {
 int launch_topk(const fine_shape& s, const void* x, const void* w_router, const float* bias,
                 int32_t* topk_idx, float* topk_w, void* ws, size_t ws_bytes, hipStream_t st) {
     if (s.T == 0) return FINE_OK;
-    if (s.dtype == FINE_F32) return dispatch<float>(s, x, w_router, bias, topk_idx, topk_w, st);
-    if (s.E % 8 == 0 && s.E <= 256 && s.d % 64 == 0) {
-#define FINE_TOPK_MFMA(KERNEL)                                                                                  \
-    hipLaunchKernelGGL((KERNEL), dim3(cdiv(s.T, 32)), dim3(256), 0, st, (const uint16_t*)x,                     \
-                       (const uint16_t*)w_router, bias, s.T, s.d, s.E, s.K, topk_idx, topk_w)
-#define FINE_TOPK_ESPLIT(NT)                                                                                    \
-    do {                                                                                                        \
-        hipLaunchKernelGGL((k_topk_mfma_esplit<NT>), dim3(cdiv(s.T, 32), parts), dim3(256), 0, st,              \
-                           (const uint16_t*)x, (const uint16_t*)w_router, bias, s.T, s.d, s.E, s.K, topk_idx,  \
-                           topk_w, parts > 1 ? (float*)ws : nullptr);                                           \
-        if (parts > 1) {                                                                                        \
-            FINE_LAUNCH_CHECK();                                                                                \
-            hipLaunchKernelGGL((k_topk_select<2 * NT>), dim3(cdiv(s.T, 16)), dim3(256), 0, st, (const float*)ws, \
-                               parts, cdiv(s.T, 32) * 32, NT * 32, bias, s.T, s.E, s.K, topk_idx, topk_w);      \
-        }                                                                                                       \
-    } while (0)
-        // without the workspace for the partial logits every token tile is one block's
-        const int parts = (ws != nullptr && ws_bytes >= topk_ws_bytes(s)) ? topk_parts(s) : 1;
-        if (s.E <= 32) FINE_TOPK_MFMA(k_topk_mfma<1>);
-        else if (s.E <= 64) FINE_TOPK_MFMA(k_topk_mfma<2>);
-        else if (s.E <= 128) FINE_TOPK_ESPLIT(4);
-        else FINE_TOPK_ESPLIT(8);
-#undef FINE_TOPK_MFMA
-#undef FINE_TOPK_ESPLIT
+    if (s.E > 256 || (long long)s.d * s.E >= (1ll << 31))
+        return s.dtype == FINE_F32 ? dispatch<float>(s, x, w_router, bias, topk_idx, topk_w, st)
+                                   : dispatch<uint16_t>(s, x, w_router, bias, topk_idx, topk_w, st);
+    const int blocks = cdiv(s.T, 32);
+    if (s.dtype == FINE_F32) {
+#define FINE_TOPK_F32(NT, NW)                                                                                   \
+    hipLaunchKernelGGL((k_topk_f32<NT, NW>), dim3(blocks), dim3(64 * NW), 0, st, (const float*)x,               \
+                       (const float*)w_router, bias, s.T, s.d, s.E, s.K, topk_idx, topk_w)
+        if (s.E <= 32) FINE_TOPK_F32(1, 8);
+        else if (s.E <= 64) FINE_TOPK_F32(2, 8);
+        else if (s.E <= 128) FINE_TOPK_F32(4, 4);
+        else FINE_TOPK_F32(8, 4);
+#undef FINE_TOPK_F32
         FINE_LAUNCH_CHECK();
         return FINE_OK;
     }
-    return dispatch<uint16_t>(s, x, w_router, bias, topk_idx, topk_w, st);
+    const bool odd = s.E % 8 != 0;
+#define FINE_TOPK_MFMA(NT)                                                                                      \
+    hipLaunchKernelGGL((odd ? k_topk_mfma<NT, true> : k_topk_mfma<NT, false>), dim3(blocks), dim3(256), 0, st,  \
+                       (const uint16_t*)x, (const uint16_t*)w_router, bias, s.T, s.d, s.E, s.K, topk_idx, topk_w)
+#define FINE_TOPK_ESPLIT(NT)                                                                                    \
+    do {                                                                                                        \
+        hipLaunchKernelGGL((odd ? k_topk_mfma_esplit<NT, true> : k_topk_mfma_esplit<NT, false>),                \
+                           dim3(blocks, parts), dim3(256), 0, st, (const uint16_t*)x, (const uint16_t*)w_router,     \
+                           bias, s.T, s.d, s.E, s.K, topk_idx, topk_w, parts > 1 ? (float*)ws : nullptr);                                           \
+        if (parts > 1) {                                                                                        \
+            FINE_LAUNCH_CHECK();                                                                                \
+            hipLaunchKernelGGL((k_topk_select<2 * NT>), dim3(cdiv(s.T, 16)), dim3(256), 0, st, (const float*)ws, \
+                               parts, blocks * 32, NT * 32, bias, s.T, s.E, s.K, topk_idx, topk_w);      \
+        }                                                                                                       \
+    } while (0)
+    // without the workspace for the partial logits every token tile is one block's
+    const int parts = (ws != nullptr && ws_bytes >= topk_ws_bytes(s)) ? topk_parts(s) : 1;
+    if (s.E <= 32) {
+        FINE_TOPK_MFMA(1);
+    } else if (s.E <= 64) {
+        FINE_TOPK_MFMA(2);
+    } else if (s.E <= 128) {
+        FINE_TOPK_ESPLIT(4);
+    } else {
+        FINE_TOPK_ESPLIT(8);
+    }
+#undef FINE_TOPK_MFMA
+#undef FINE_TOPK_ESPLIT
+    FINE_LAUNCH_CHECK();
+    return FINE_OK;
 }
 
 }  // namespace fine

@@ -416,7 +416,7 @@ int launch_backward(const fine_shape& s, int rank_lo, int rank_hi, const void* d
         auto* act_ws = reinterpret_cast<uint16_t*>(ws + L.act);
         if (on(1))
             FINE_TRY(launch_ffn_parts(s, rank_lo, rank_hi, x_perm, wg, wu, wd, seg_off, h, nullptr, act_ws, tiles, count,
-                                      L.max_tiles, reinterpret_cast<float*>(ws + L.sk), true, false, st));
+                                      L.max_tiles, reinterpret_cast<float*>(ws + L.sk), true, false, true, st));
         act = act_ws;
     }
     const double P = (double)s.T * s.K;

@@ -92,12 +92,12 @@ struct SchedWs {
 };
 SchedWs sched_ws_layout(const fine_shape& s);
 
-// Work list of the grouped GEMMs: one entry per (segment, row tile).
+// Work list of the grouped GEMMs: one entry per row tile of a run of segments (k_tile_map).
 struct TileEntry {
     int32_t expert;
     int32_t row0;      // first row of the tile (absolute row of the permuted buffer)
     int32_t rows;      // valid rows in the tile (1..BM)
-    int32_t seg_rows;  // rows of the whole segment
+    int32_t alone;     // 1: the only tile of its run
 };
 
 // The count block: int32 number of row tiles, from int32 index kSkCounterOffset on 256 arrival
@@ -188,10 +188,14 @@ int launch_ffn_mfma(const fine_shape& s, int rank_lo, int rank_hi, const void* x
                     const void* wg, const void* wu, const void* wd, const int32_t* seg_off,
                     void* y_perm, void* act_save, char* ws, hipStream_t st);
 
+int launch_ffn_stream(const fine_shape& s, int rank_lo, int rank_hi, const void* x_perm, const void* wg, const void* wu,
+                      const void* wd, const int32_t* seg_off, void* h_buf, void* y_perm, void* act_save, TileEntry* tiles,
+                      int32_t* count, int max_tiles, bool gemm1, bool gemm2, hipStream_t st);
+
 int launch_ffn_parts(const fine_shape& s, int rank_lo, int rank_hi, const void* x_perm, const void* wg,
                      const void* wu, const void* wd, const int32_t* seg_off, void* h_buf, void* y_perm,
                      void* act_save, TileEntry* tiles, int32_t* count, int max_tiles, float* sk_partials, bool gemm1, bool gemm2,
-                     hipStream_t st);
+                     bool any_ranks, hipStream_t st);
 
 int launch_backward(const fine_shape& s, int rank_lo, int rank_hi, const void* d_out, const void* x_perm, const void* y_perm,
                     const void* act_save, const void* wg, const void* wu, const void* wd,

@@ -20,21 +20,17 @@ __device__ inline float silu_mul(float a, float b) { return a * b * __builtin_am
 
 // EPI 0: GEMM 1 (A = x_perm, B0/B1 = Wg/Wu [E,Kd,N]; C = H [P,N]; act [P,2N] optional)
 // EPI 1: GEMM 2 (A = H, B0 = Wd [E,Kd,N]; C = y_perm [P,N])
-// 4 waves: every thread loads its share of both operand tiles, whole tiles only.
-// 8 waves: see gemm_w8.h; the tiles that do not fill a whole round of the grid are cut along
+// 8 waves (see gemm_w8.h); the tiles that do not fill a whole round of the grid are cut along
 // k so that every block gets the same number of k-steps (sk_partials, sk_counters below).
 template <int WAVES_M, int WAVES_N, int WM, int WN, int EPI>
 __device__ __forceinline__ void ffn_gemm_body(const uint16_t* __restrict__ A, int lda, const uint16_t* __restrict__ B0,
                                               const uint16_t* __restrict__ B1, size_t b_expert_stride, int Kd, int N,
                                               uint16_t* __restrict__ C, int ldc, uint16_t* __restrict__ act,
                                               const TileEntry* __restrict__ tiles, int32_t* __restrict__ count,
-                                              float* __restrict__ sk_partials) {
+                                              float* __restrict__ sk_partials, int may_cut) {
     constexpr int BM = WAVES_M * WM * 32, BN = WAVES_N * WN * 32;
     constexpr int BNC = (EPI == 0) ? BN / 2 : BN;      // output columns per block
-    constexpr bool W8 = WAVES_M * WAVES_N == 8;
-    static_assert(WAVES_M * WAVES_N == 4 || (W8 && WAVES_M == 2 && WAVES_N == 4 && (WM == 4 || WM == 2) && WN == 2),
-                  "4 waves, or 2 x 4 waves on 256 x 256 or 128 x 256");
-    static_assert(EPI != 0 || WN % 2 == 0, "gate/up pairs");
+    static_assert(WAVES_M == 2 && WAVES_N == 4 && (WM == 4 || WM == 2) && WN == 2, "2 x 4 waves on 256 x 256 or 128 x 256");
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
     const int ntn = (N + BNC - 1) / BNC;
@@ -51,45 +47,28 @@ __device__ __forceinline__ void ffn_gemm_body(const uint16_t* __restrict__ A, in
         const int n0 = tn * BNC;
         const uint16_t* Bg = B0 + (size_t)te.expert * b_expert_stride;
         const uint16_t* Bu = (EPI == 0) ? B1 + (size_t)te.expert * b_expert_stride : nullptr;
-        auto a_row = [&](int r) { return (size_t)min(r, te.rows - 1) * lda; };
         auto k_tile = [&](int kt) { return KTile{(ptrdiff_t)(kb + kt) * BK, (ptrdiff_t)(kb + kt) * BK, Kd, 0}; };
-        if constexpr (W8) {
-            const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-            RowDmaOperand<WM, BM> oa;
-            // rows past the tile's last lie beyond the descriptor's size: the DMA writes zeros for them
-            // and asks memory for nothing (their results are never stored)
-            oa.init(A + (size_t)te.row0 * lda, [&](int r) { return (size_t)r * lda; },
-                    (uint32_t)((size_t)te.rows * lda * 2), (wave / WAVES_N) * WM * 32);
-            DmaOperand<WN> ob;
-            const int wn = wave % WAVES_N;
-            if constexpr (EPI == 0) {
-                // panel 0 = 128 gate columns, panel 1 = the matching up columns; a wave's two
-                // fragments are the same 32 columns of both
-                ob.init(Bg, Bu, [&](int, int c) { return min(n0 + 8 * c, N - 8); }, (size_t)N,
-                        [&](int f) { return 128 * f + 32 * wn; });
-            } else {
-                ob.init(Bg, Bg, [&](int p, int c) { return min(n0 + 128 * p + 8 * c, N - 8); }, (size_t)N,
-                        [&](int f) { return 64 * wn + 32 * f; });
-            }
-            // fragments of the wave that hold valid rows (the rest of a short last tile is skipped)
-            const int nf = min(WM, max(0, (te.rows - (wave / WAVES_N) * WM * 32 + 31) / 32));
-            if (te.rows == BM) k_loop8<false, 4>(kn, smem, acc, oa, ob, k_tile);
-            else k_loop8<true, 4>(kn, smem, acc, oa, ob, k_tile, nf);
+        const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+        RowDmaOperand<WM, BM> oa;
+        // rows past the tile's last lie beyond the descriptor's size: the DMA writes zeros for them
+        // and asks memory for nothing (their results are never stored)
+        oa.init(A + (size_t)te.row0 * lda, [&](int r) { return (size_t)r * lda; },
+                (uint32_t)((size_t)te.rows * lda * 2), (wave / WAVES_N) * WM * 32);
+        DmaOperand<WN> ob;
+        const int wn = wave % WAVES_N;
+        if constexpr (EPI == 0) {
+            // panel 0 = 128 gate columns, panel 1 = the matching up columns; a wave's two
+            // fragments are the same 32 columns of both
+            ob.init(Bg, Bu, [&](int, int c) { return min(n0 + 8 * c, N - 8); }, (size_t)N,
+                    [&](int f) { return 128 * f + 32 * wn; });
         } else {
-            LoaderKC<BM> la;
-            la.init([&](int r) { return A + (size_t)te.row0 * lda + a_row(r); });
-            LoaderMC<BN, false> lb;
-            lb.init([&](int r8) {
-                const int nb = r8 * 8;
-                if (EPI == 0) {
-                    const int q = nb >> 5, within = nb & 31;
-                    return ((q & 1) ? Bu : Bg) + min(n0 + (q >> 1) * 32 + within, N - 8);
-                } else {
-                    return Bg + min(n0 + nb, N - 8);
-                }
-            }, (size_t)N);
-            k_loop<WAVES_M, WAVES_N, WM, WN, (WM * WN >= 16 ? 1 : 2)>(kn, smem, acc, la, lb, k_tile);
+            ob.init(Bg, Bg, [&](int p, int c) { return min(n0 + 128 * p + 8 * c, N - 8); }, (size_t)N,
+                    [&](int f) { return 64 * wn + 32 * f; });
         }
+        // fragments of the wave that hold valid rows (the rest of a short last tile is skipped)
+        const int nf = min(WM, max(0, (te.rows - (wave / WAVES_N) * WM * 32 + 31) / 32));
+        if (te.rows == BM) k_loop8<false, 4>(kn, smem, acc, oa, ob, k_tile);
+        else k_loop8<true, 4>(kn, smem, acc, oa, ob, k_tile, nf);
     };
 
     // LDS-staged epilogue of tile `work`, 8-byte coalesced stores
@@ -122,8 +101,7 @@ __device__ __forceinline__ void ffn_gemm_body(const uint16_t* __restrict__ A, in
         }
     };
 
-    // Whole tiles first: as many full rounds of the grid as there are (4 waves: all tiles).
-    // 8 waves: the remaining rest < nblk tiles are rest * nk k-steps, cut into nblk parts: part p is
+    // Whole tiles first: as many full rounds of the grid as there are.  The remaining rest < nblk tiles are rest * nk k-steps, cut into nblk parts: part p is
     // steps [p * per, (p+1) * per) of that sequence.  Whoever computes only part of a tile's k
     // range counts itself in when its k-loop is done; all but the last to do so write their
     // accumulators to their part's slot (two per part: a range begins and ends inside at most one
@@ -139,8 +117,8 @@ __device__ __forceinline__ void ffn_gemm_body(const uint16_t* __restrict__ A, in
     // break-even: about 16 steps on the 256-row tile (GEMM 2 of a rank with 128 tiles of 224 steps
     // gains 30 %, half a round of 64-step GEMM 1 tiles a little); on the 128-row tile, whose
     // workloads stream weights from HBM, the cut only pays for long k ranges (32 steps).
-    const int whole_rounds = (total / nblk) * nblk;
-    const bool cut_even = W8 && (long long)nk * (nblk - (total - whole_rounds)) > (long long)(WM == 4 ? 16 : 32) * nblk;
+    const int whole_rounds = may_cut ? (total / nblk) * nblk : total;
+    const bool cut_even = total > whole_rounds && (long long)nk * (nblk - (total - whole_rounds)) > (long long)(WM == 4 ? 16 : 32) * nblk;
     // Below that break-even a small rest would still cost a whole extra round (24 of 280 tiles of 32
     // steps: one more tile time with 232 CUs idle).  Spreading so few steps over the whole grid would
     // leave each tile in ten parts for its last block to add up; instead every rest tile is cut into 2
@@ -155,13 +133,13 @@ __device__ __forceinline__ void ffn_gemm_body(const uint16_t* __restrict__ A, in
     // with n whole row tiles at the training shape's GEMM 2 (8 column tiles, 128 k-steps) the even cut took
     // 192-241 us for n = 17 ... 22 where its step count says 110-145.
     int grp = 0;
-    if (W8 && WM == 4 && 2 * rest_if > nblk && rest_if < nblk) {
+    if (WM == 4 && 2 * rest_if > nblk && rest_if < nblk) {
         const int q = (rest_if + (nblk - rest_if) - 1) / (nblk - rest_if);
         if (nk > 16 * (q + 1)) grp = q;      // what a part saves against a whole tile, nk / (q + 1) steps, must pay for a partial tile
     }
     const bool cut = cut_even && grp == 0;
     int few = 0;
-    if (W8 && !cut && grp == 0 && rest_if > 0)
+    if (!cut && grp == 0 && rest_if > 0)
         for (int p = 4; p >= 2 && few == 0; p >>= 1)
             if (rest_if * p <= nblk && nk % p == 0 && nk / p >= 8) few = p;
     const int full = (cut || few || grp) ? whole_rounds : total;
@@ -205,9 +183,9 @@ __device__ __forceinline__ void ffn_gemm_body(const uint16_t* __restrict__ A, in
         __builtin_amdgcn_make_buffer_rsrc((void*)sk_partials, 0, (int)(2 * 256 * (size_t)kSlotBytes), 0x00020000);
 
     // Who computes what: the units of a launch are its whole tiles [0, full) and then its parts
-    // [full, full + nparts); 8 waves: handed out by UnitQueue (counters zeroed by k_tile_map).
+    // [full, full + nparts), handed out by UnitQueue (counters zeroed by k_tile_map).
     UnitQueue uq;
-    uq.init(count + kQueueOffset + (EPI * 8) * kQueueStride, kQueueStride, full + nparts, bid, W8);
+    uq.init(count + kQueueOffset + (EPI * 8) * kQueueStride, kQueueStride, full + nparts, bid, true);
     auto request = [&]() { uq.request(); };
 
     // k-tiles [kb, kb + kn) of tile `work`; part: the part this piece belongs to (-1: a whole tile);
@@ -217,119 +195,102 @@ __device__ __forceinline__ void ffn_gemm_body(const uint16_t* __restrict__ A, in
         run_tile(work, kb, kn);
         if (ask) request();
         bool finish = true;
-        if constexpr (W8) {
-            if (kn != nk) {
-                const int t = work - full;
-                // the parts that hold pieces of tile t: first, first + step, ... (n_parts of them)
-                const int first = few ? t : grp ? (t / grp) * (grp + 1) + t % grp : (t * nk) / per;
-                const int step = few ? rest : 1;
-                const int n_parts = few ? few : grp ? 2 : (t * nk + nk - 1) / per - first + 1;
-                // Whoever arrives last (everybody else has left its k-loop by then) adds the parts up; the
-                // others write theirs to their slots and then count themselves ready.  The tile is
-                // part 0 + part 1 + part 2 + ... in that order whoever adds: if the last one holds part 0 or
-                // part 1 it keeps it in its accumulators (x + y = y + x to the bit, so the chain may start
-                // from either of the two) and reads only the others; if it holds a later part it writes that
-                // one too and reads them all.
-                if (threadIdx.x == 0)
-                    s_last = __hip_atomic_fetch_add(&counters[t], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
-                             n_parts - 1;
-                __syncthreads();
-                finish = s_last != 0;
-                const int my_idx = (part - first) / step;
-                const bool keep = finish && my_idx <= 1;
-                if (!keep) {
-                    const int mine = slot_of(part, t);
-                    static_for<WM * WN>([&](auto m) {
-                        static_for<4>([&](auto q) {
-                            const f32x16& v = acc[m.value / WN][m.value % WN];
-                            const f32x4 val = {v[4 * q.value], v[4 * q.value + 1], v[4 * q.value + 2], v[4 * q.value + 3]};
-                            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, val), sk_rs, threadIdx.x * 16,
-                                                                   mine * kSlotBytes + (m.value * 4 + q.value) * kThreadsBlk * 16,
-                                                                   kCoherent);
-                        });
+        if (kn != nk) {
+            const int t = work - full;
+            // the parts that hold pieces of tile t: first, first + step, ... (n_parts of them)
+            const int first = few ? t : grp ? (t / grp) * (grp + 1) + t % grp : (t * nk) / per;
+            const int step = few ? rest : 1;
+            const int n_parts = few ? few : grp ? 2 : (t * nk + nk - 1) / per - first + 1;
+            // Whoever arrives last (everybody else has left its k-loop by then) adds the parts up; the
+            // others write theirs to their slots and then count themselves ready.  The tile is
+            // part 0 + part 1 + part 2 + ... in that order whoever adds: if the last one holds part 0 or
+            // part 1 it keeps it in its accumulators (x + y = y + x to the bit, so the chain may start
+            // from either of the two) and reads only the others; if it holds a later part it writes that
+            // one too and reads them all.
+            if (threadIdx.x == 0)
+                s_last = __hip_atomic_fetch_add(&counters[t], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+                         n_parts - 1;
+            __syncthreads();
+            finish = s_last != 0;
+            const int my_idx = (part - first) / step;
+            const bool keep = finish && my_idx <= 1;
+            if (!keep) {
+                const int mine = slot_of(part, t);
+                static_for<WM * WN>([&](auto m) {
+                    static_for<4>([&](auto q) {
+                        const f32x16& v = acc[m.value / WN][m.value % WN];
+                        const f32x4 val = {v[4 * q.value], v[4 * q.value + 1], v[4 * q.value + 2], v[4 * q.value + 3]};
+                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, val), sk_rs, threadIdx.x * 16,
+                                                               mine * kSlotBytes + (m.value * 4 + q.value) * kThreadsBlk * 16,
+                                                               kCoherent);
                     });
-                    __builtin_amdgcn_s_waitcnt(0x0070);      // vmcnt(0): this thread's partial sums have been written
-                    __syncthreads();
-                    if (!finish && threadIdx.x == 0)
-                        __hip_atomic_fetch_add(&ready[t], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                }
-                if (finish) {
-                    // The others are past their k-loops and on their way through the lines above, which wait
-                    // for nothing but their own stores: this wait ends.  (The bound only keeps a mistake
-                    // elsewhere from hanging the launch: the sums would then be wrong, not the GPU stuck.)
-                    if (threadIdx.x == 0) {
-                        int polls = 0;
-                        while (__hip_atomic_load(&ready[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < n_parts - 1 &&
-                               ++polls < (1 << 20))
-                            __builtin_amdgcn_s_sleep(4);
-                        ready[t] = 0;          // both counters are zero again for the next launch
-                        counters[t] = 0;
-                    }
-                    __syncthreads();
-                    auto add_part = [&](int i, auto assign) {
-                        const int sl = slot_of(first + i * step, t);
-                        static_for<WM * WN / 2>([&](auto mp) {
-                            u32x4 v[8];
-                            static_for<8>([&](auto g) {
-                                v[g.value] = __builtin_amdgcn_raw_buffer_load_b128(
-                                    sk_rs, threadIdx.x * 16, sl * kSlotBytes + (mp.value * 8 + g.value) * kThreadsBlk * 16, kCoherent);
-                            });
-                            static_for<8>([&](auto g) {
-                                constexpr int m = mp.value * 2 + g.value / 4, q = g.value % 4;
-                                const f32x4 val = __builtin_bit_cast(f32x4, v[g.value]);
-                                f32x16& a = acc[m / WN][m % WN];
-                                if constexpr (assign.value) {
-                                    a[4 * q] = val[0]; a[4 * q + 1] = val[1]; a[4 * q + 2] = val[2]; a[4 * q + 3] = val[3];
-                                } else {
-                                    a[4 * q] += val[0]; a[4 * q + 1] += val[1]; a[4 * q + 2] += val[2]; a[4 * q + 3] += val[3];
-                                }
-                            });
-                            __builtin_amdgcn_sched_barrier(0);      // keeps the loads from piling up in registers
-                        });
-                    };
-                    if (!keep) add_part(0, std::true_type{});
-                    for (int i = keep ? 0 : 1; i < n_parts; ++i)
-                        if (!(keep && i == my_idx)) add_part(i, std::false_type{});
+                });
+                __builtin_amdgcn_s_waitcnt(0x0070);      // vmcnt(0): this thread's partial sums have been written
+                __syncthreads();
+                if (!finish && threadIdx.x == 0)
+                    __hip_atomic_fetch_add(&ready[t], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            if (finish) {
+                // The others are past their k-loops and on their way through the lines above, which wait
+                // for nothing but their own stores: this wait ends.  (The bound only keeps a mistake
+                // elsewhere from hanging the launch: the sums would then be wrong, not the GPU stuck.)
+                if (threadIdx.x == 0) {
+                    int polls = 0;
+                    while (__hip_atomic_load(&ready[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < n_parts - 1 &&
+                           ++polls < (1 << 20))
+                        __builtin_amdgcn_s_sleep(4);
+                    ready[t] = 0;          // both counters are zero again for the next launch
+                    counters[t] = 0;
                 }
                 __syncthreads();
+                auto add_part = [&](int i, auto assign) {
+                    const int sl = slot_of(first + i * step, t);
+                    static_for<WM * WN / 2>([&](auto mp) {
+                        u32x4 v[8];
+                        static_for<8>([&](auto g) {
+                            v[g.value] = __builtin_amdgcn_raw_buffer_load_b128(
+                                sk_rs, threadIdx.x * 16, sl * kSlotBytes + (mp.value * 8 + g.value) * kThreadsBlk * 16, kCoherent);
+                        });
+                        static_for<8>([&](auto g) {
+                            constexpr int m = mp.value * 2 + g.value / 4, q = g.value % 4;
+                            const f32x4 val = __builtin_bit_cast(f32x4, v[g.value]);
+                            f32x16& a = acc[m / WN][m % WN];
+                            if constexpr (assign.value) {
+                                a[4 * q] = val[0]; a[4 * q + 1] = val[1]; a[4 * q + 2] = val[2]; a[4 * q + 3] = val[3];
+                            } else {
+                                a[4 * q] += val[0]; a[4 * q + 1] += val[1]; a[4 * q + 2] += val[2]; a[4 * q + 3] += val[3];
+                            }
+                        });
+                        __builtin_amdgcn_sched_barrier(0);      // keeps the loads from piling up in registers
+                    });
+                };
+                if (!keep) add_part(0, std::true_type{});
+                for (int i = keep ? 0 : 1; i < n_parts; ++i)
+                    if (!(keep && i == my_idx)) add_part(i, std::false_type{});
             }
+            __syncthreads();
         }
         if (finish) epilogue(work);
     };
 
-    if constexpr (!W8) {
-        for (int work = bid; work < total; work += nblk) piece(work, 0, nk, -1, false);
-    } else {
-        for (int v = uq.first(bid); v >= 0; v = uq.next(v, &s_next)) {
-            if (v < full) {
-                piece(v, 0, nk, -1, true);
-            } else if (few) {
-                const int part = v - full, kn = nk / few;
-                piece(full + part % rest, (part / rest) * kn, kn, part, true);
-            } else {
-                const int part = v - full;
-                int u, u1;
-                part_range(part, u, u1);
-                if (u >= u1) request();      // (an empty part at the end of the sequence)
-                while (u < u1) {
-                    const int t = u / nk, kb = u - t * nk, kn = min(nk - kb, u1 - u);
-                    piece(full + t, kb, kn, part, u + kn >= u1);
-                    u += kn;
-                }
+    for (int v = uq.first(bid); v >= 0; v = uq.next(v, &s_next)) {
+        if (v < full) {
+            piece(v, 0, nk, -1, true);
+        } else if (few) {
+            const int part = v - full, kn = nk / few;
+            piece(full + part % rest, (part / rest) * kn, kn, part, true);
+        } else {
+            const int part = v - full;
+            int u, u1;
+            part_range(part, u, u1);
+            if (u >= u1) request();      // (an empty part at the end of the sequence)
+            while (u < u1) {
+                const int t = u / nk, kb = u - t * nk, kn = min(nk - kb, u1 - u);
+                piece(full + t, kb, kn, part, u + kn >= u1);
+                u += kn;
             }
         }
     }
-}
-
-template <int WAVES_M, int WAVES_N, int WM, int WN, int EPI>
-__global__ __launch_bounds__(256) void k_ffn_gemm(const uint16_t* __restrict__ A, int lda,
-                                                  const uint16_t* __restrict__ B0, const uint16_t* __restrict__ B1,
-                                                  size_t b_expert_stride, int Kd, int N,
-                                                  uint16_t* __restrict__ C, int ldc, uint16_t* __restrict__ act,
-                                                  const TileEntry* __restrict__ tiles, int32_t* __restrict__ count,
-                                                  float* __restrict__ sk_partials) {
-    ffn_gemm_body<WAVES_M, WAVES_N, WM, WN, EPI>(A, lda, B0, B1, b_expert_stride, Kd, N, C, ldc, act, tiles, count,
-                                                 sk_partials);
 }
 
 // 8 waves: two per SIMD, each with 128 architectural and 128 accumulator registers
@@ -339,87 +300,78 @@ __global__ __launch_bounds__(512) void k_ffn_gemm_w8(const uint16_t* __restrict_
                                                      size_t b_expert_stride, int Kd, int N,
                                                      uint16_t* __restrict__ C, int ldc, uint16_t* __restrict__ act,
                                                      const TileEntry* __restrict__ tiles, int32_t* __restrict__ count,
-                                                     float* __restrict__ sk_partials) {
+                                                     float* __restrict__ sk_partials, int may_cut) {
     ffn_gemm_body<WAVES_M, WAVES_N, WM, WN, EPI>(A, lda, B0, B1, b_expert_stride, Kd, N, C, ldc, act, tiles, count,
-                                                 sk_partials);
-}
-
-template <int WAVES_M, int WAVES_N, int WM, int WN, int EPI>
-constexpr auto ffn_kernel() {
-    if constexpr (WAVES_M * WAVES_N == 8) return k_ffn_gemm_w8<WAVES_M, WAVES_N, WM, WN, EPI>;
-    else return k_ffn_gemm<WAVES_M, WAVES_N, WM, WN, EPI>;
+                                                 sk_partials, may_cut);
 }
 
 template <int WAVES_M, int WAVES_N, int WM, int WN>
 int run_ffn(const fine_shape& s, int rank_lo, int rank_hi, const void* x_perm, const void* wg, const void* wu,
             const void* wd, const int32_t* seg_off, void* h_buf, void* y_perm, void* act_save, TileEntry* tiles,
-            int32_t* count, int max_tiles, float* sk_partials, bool gemm1, bool gemm2, hipStream_t st) {
-    constexpr int BM = WAVES_M * WM * 32, BN = WAVES_N * WN * 32;
+            int32_t* count, int max_tiles, float* sk_partials, bool gemm1, bool gemm2, bool may_cut, hipStream_t st) {
+    constexpr int BM = WAVES_M * WM * 32;
     auto* h = reinterpret_cast<uint16_t*>(h_buf);
     FINE_TRY(launch_tile_map(s, seg_off, rank_lo, rank_hi, BM, tiles, count, max_tiles, st));
-    const size_t lds = (WAVES_M * WAVES_N == 8) ? (size_t)w8_lds_bytes(true, 4) : (size_t)2 * (BM + BN) * 128;
-    auto k1 = ffn_kernel<WAVES_M, WAVES_N, WM, WN, 0>();
-    auto k2 = ffn_kernel<WAVES_M, WAVES_N, WM, WN, 1>();
+    const size_t lds = (size_t)w8_lds_bytes(true, 4);
+    auto k1 = k_ffn_gemm_w8<WAVES_M, WAVES_N, WM, WN, 0>;
+    auto k2 = k_ffn_gemm_w8<WAVES_M, WAVES_N, WM, WN, 1>;
     constexpr int threads = WAVES_M * WAVES_N * 64;
     static std::atomic<uint64_t> lds_set1{0}, lds_set2{0};      // per instantiation
     FINE_TRY(raise_lds_limit((const void*)k1, (int)lds, lds_set1));
     FINE_TRY(raise_lds_limit((const void*)k2, (int)lds, lds_set2));
-    const int blocks_per_cu = (lds <= 80 * 1024) ? 2 : 1;
-    const int grid = 256 * blocks_per_cu;
+    const int grid = 256;      // one block per CU
     if (gemm1) {
         hipLaunchKernelGGL(k1, dim3(grid), dim3(threads), lds, st, (const uint16_t*)x_perm, s.d, (const uint16_t*)wg,
-                           (const uint16_t*)wu, (size_t)s.d * s.f, s.d, s.f, h, s.f, (uint16_t*)act_save, tiles, count, sk_partials);
+                           (const uint16_t*)wu, (size_t)s.d * s.f, s.d, s.f, h, s.f, (uint16_t*)act_save, tiles, count, sk_partials, (int)may_cut);
         FINE_LAUNCH_CHECK();
     }
     if (gemm2) {
         hipLaunchKernelGGL(k2, dim3(grid), dim3(threads), lds, st, (const uint16_t*)h, s.f, (const uint16_t*)wd,
                            (const uint16_t*)nullptr, (size_t)s.f * s.d, s.f, s.d, (uint16_t*)y_perm, s.d,
-                           (uint16_t*)nullptr, tiles, count, sk_partials);
+                           (uint16_t*)nullptr, tiles, count, sk_partials, (int)may_cut);
         FINE_LAUNCH_CHECK();
     }
     return FINE_OK;
 }
 
-// Tile choice for one of the two GEMMs (n_out output columns).
-//   3: 256 x 256 on 8 waves - the fastest per tile (the tiles of an incomplete last round are
-//      cut along k, so few tiles are no problem), but segments should be long enough not to
-//      waste most of a 256-row tile;
-//   2: 128 x 256 on 8 waves (same machinery, half the rows), 1: 64 x 256 on 4 waves for short
-//      segments.
-int pick_tile(const fine_shape& s, int n_ranks, int n_out, int bnc3) {
-    int tile = (s.flags & FINE_FLAG_TILE_MASK) >> FINE_FLAG_TILE_SHIFT;
+// Tile choice.
+//   3: 256 x 256 on 8 waves - the fastest per tile (the tiles of an incomplete last round are cut along k, so few
+//      tiles are no problem), but segments should be long enough not to waste most of a 256-row tile;
+//   2: 128 x 256 on 8 waves (same machinery, half the rows);
+//   1: 64 rows, k split over the waves of a block (ffn_stream.hip).
+// 1 is for two kinds of call.  A few rows per expert (decoding): both kernels stream weights, at 5.7 TB/s against 5.2
+// (7 experts of 4096 x 14336, 32 rows: 428 against 483 us; 32 of 2048 x 5632, 128 rows: 239 against 247; but 46 experts
+// of 2048 x 1408 with 45 rows on average, the longest 429: 198 against 181).  And launches that leave most of the
+// CUs without a tile, each of the others waiting out a chain of k-steps: 10 row tiles of 128 on 1088 x 832, 133 tiles
+// in both GEMMs, 28 against 43 us per rank; 204 tiles 37 against 47; 286 tiles 51 against 60; 351 tiles 51 against 48.
+int pick_tile(const fine_shape& s, int n_ranks) {
+    const int tile = (s.flags & FINE_FLAG_TILE_MASK) >> FINE_FLAG_TILE_SHIFT;
     if (tile != 0) return tile;
-    // expected rows of a (rank, expert) segment when every expert is on every rank: a
-    // rank's ceil(P/G) rows span about E/G + 1 experts
-    const double P = (double)s.T * s.K;
-    const double seg_rows = (P / s.G) / ((double)s.E / s.G + 1.0);
-    (void)n_ranks; (void)n_out; (void)bnc3;
-    if (seg_rows >= 384.0) return 3;
-    return seg_rows >= 96.0 ? 2 : 1;
-}
-
-template <typename... Args>
-int run_ffn_tile(int tile, Args... args) {
-    if (tile == 3) return run_ffn<2, 4, 4, 2>(args...);
-    if (tile == 2) return run_ffn<2, 4, 2, 2>(args...);
-    return run_ffn<1, 4, 2, 2>(args...);
+    // expected runs of rows of one expert when every expert is on every rank: the rows of n ranks, P / G each, span
+    // about n E / G + 1 experts
+    const double rows = (double)s.T * s.K * n_ranks / s.G, runs = (double)s.E * n_ranks / s.G + 1.0;
+    if (rows / runs < 24.0) return 1;
+    const double tiles = (rows / 128.0 + runs) * (cdiv(s.f, 128) + cdiv(s.d, 256));
+    if (tiles < 320.0) return 1;
+    return rows / runs >= 384.0 ? 3 : 2;
 }
 
 }  // namespace
 
+// any_ranks (the backward pass): the same bits whether a call is for one rank or for all, so the tile may not depend on
+// the number of ranks, and on short segments no tile is cut along k (where a launch cuts depends on how many it has).
 int launch_ffn_parts(const fine_shape& s, int rank_lo, int rank_hi, const void* x_perm, const void* wg,
                      const void* wu, const void* wd, const int32_t* seg_off, void* h_buf, void* y_perm,
                      void* act_save, TileEntry* tiles, int32_t* count, int max_tiles, float* sk_partials, bool gemm1,
-                     bool gemm2, hipStream_t st) {
-    const int t1 = pick_tile(s, rank_hi - rank_lo, s.f, 128), t2 = pick_tile(s, rank_hi - rank_lo, s.d, 256);
-    if (t1 == t2 || !gemm1 || !gemm2)
-        return run_ffn_tile(gemm1 ? t1 : t2, s, rank_lo, rank_hi, x_perm, wg, wu, wd, seg_off, h_buf, y_perm, act_save,
-                            tiles, count, max_tiles, sk_partials, gemm1, gemm2, st);
-    // different row tiles: the work list is rebuilt between the two GEMMs (same stream)
-    FINE_TRY(run_ffn_tile(t1, s, rank_lo, rank_hi, x_perm, wg, wu, wd, seg_off, h_buf, y_perm, act_save, tiles, count,
-                          max_tiles, sk_partials, true, false, st));
-    return run_ffn_tile(t2, s, rank_lo, rank_hi, x_perm, wg, wu, wd, seg_off, h_buf, y_perm, act_save, tiles, count,
-                        max_tiles, sk_partials, false, true, st);
+                     bool gemm2, bool any_ranks, hipStream_t st) {
+    const int tile = pick_tile(s, any_ranks ? s.G : rank_hi - rank_lo);
+    const bool may_cut = !any_ranks || (double)s.T * s.K / (s.E + s.G) >= 96.0;
+    if (tile == 1)
+        return launch_ffn_stream(s, rank_lo, rank_hi, x_perm, wg, wu, wd, seg_off, h_buf, y_perm, act_save, tiles, count,
+                                 max_tiles, gemm1, gemm2, st);
+    auto run = tile == 3 ? run_ffn<2, 4, 4, 2> : run_ffn<2, 4, 2, 2>;
+    return run(s, rank_lo, rank_hi, x_perm, wg, wu, wd, seg_off, h_buf, y_perm, act_save, tiles, count, max_tiles,
+               sk_partials, gemm1, gemm2, may_cut, st);
 }
 
 int launch_ffn_mfma(const fine_shape& s, int rank_lo, int rank_hi, const void* x_perm,
@@ -432,7 +384,8 @@ int launch_ffn_mfma(const fine_shape& s, int rank_lo, int rank_hi, const void* x
         h_buf = static_cast<char*>(act_save) + (size_t)s.T * s.K * 2 * s.f * elem_size(s.dtype);
     return launch_ffn_parts(s, rank_lo, rank_hi, x_perm, wg, wu, wd, seg_off, h_buf, y_perm, act_save,
                             reinterpret_cast<TileEntry*>(ws + L.tiles), reinterpret_cast<int32_t*>(ws + L.count),
-                            L.max_tiles, reinterpret_cast<float*>(ws + L.sk), !(s.flags & FINE_FLAG_ONLY_GEMM2), !(s.flags & FINE_FLAG_ONLY_GEMM1), st);
+                            L.max_tiles, reinterpret_cast<float*>(ws + L.sk), !(s.flags & FINE_FLAG_ONLY_GEMM2),
+                            !(s.flags & FINE_FLAG_ONLY_GEMM1), false, st);
 }
 
 }  // namespace fine

@@ -6,55 +6,118 @@ namespace fine {
 
 namespace {
 
-// One block: walks the (rank, expert) segments of ranks [rank_lo, rank_hi) in order and
-// emits one TileEntry per BM rows.  Order of entries = order of rows.
-__global__ __launch_bounds__(256) void k_tile_map(const int32_t* __restrict__ seg_off, int E, int rank_lo, int rank_hi,
-                                                  int BM, TileEntry* __restrict__ tiles, int32_t* __restrict__ count,
-                                                  int max_tiles) {
-    __shared__ int s_scan[256];
-    __shared__ int s_carry;
-    const int tid = threadIdx.x;
-    if (tid == 0) s_carry = 0;
-    count[kSkCounterOffset + tid] = 0;
-    count[kSkReadyOffset + tid] = 0;
-    if (tid < kQueues) count[kQueueOffset + tid * kQueueStride] = 0;
-    __syncthreads();
-    const int nseg = (rank_hi - rank_lo) * E;
-    for (int base = 0; base < nseg; base += 256) {
-        const int sidx = base + tid;
-        int e = 0, r0 = 0, n = 0;
-        if (sidx < nseg) {
-            const int g = rank_lo + sidx / E;
-            e = sidx - (sidx / E) * E;
-            r0 = seg_off[(size_t)g * (E + 1) + e];
-            n = seg_off[(size_t)g * (E + 1) + e + 1] - r0;
-            if (n < 0) n = 0;
-        }
-        const int nt = (n + BM - 1) / BM;
-        s_scan[tid] = nt;
-        __syncthreads();
-        for (int off = 1; off < 256; off <<= 1) {     // inclusive Hillis-Steele scan
-            int v = (tid >= off) ? s_scan[tid - off] : 0;
-            __syncthreads();
-            s_scan[tid] += v;
-            __syncthreads();
-        }
-        const int start = s_carry + s_scan[tid] - nt;
-        for (int i = 0; i < nt; ++i) {
-            if (start + i < max_tiles) {
-                TileEntry te;
-                te.expert = e;
-                te.row0 = r0 + i * BM;
-                te.rows = min(BM, n - i * BM);
-                te.seg_rows = n;
-                tiles[start + i] = te;
-            }
-        }
-        __syncthreads();
-        if (tid == 255) s_carry += s_scan[255];
-        __syncthreads();
+// One block: the work list of the (rank, expert) segments of ranks [rank_lo, rank_hi), one TileEntry per BM rows, in
+// the order of the rows.  Neighbouring non-empty segments of ONE expert (its share on a rank and on the next one: a
+// hot expert under the full placement fills whole ranks) form one run of rows and are cut into tiles together, so
+// that a call over all ranks reads an expert's weights once and not once per rank, and has one short tile per run
+// (64 tokens on 8 experts and 8 ranks: 8 tiles instead of 15).  One rank's segments are all of different experts.
+// Thread t takes C consecutive segments; everything it needs of the others are two running maxima (the index of the
+// last non-empty segment; the first row of the last run, rows ascending) and a sum of tile counts: three block
+// scans whatever the number of segments (8192 segments: 60 -> 8 us against a scan per 256 segments).
+constexpr int kMapThreads = 1024;
+
+// zeroes the counters that the GEMM launches of a call use
+__device__ inline void clear_counts(int32_t* count) {
+    for (int i = threadIdx.x; i < 256; i += blockDim.x) {
+        count[kSkCounterOffset + i] = 0;
+        count[kSkReadyOffset + i] = 0;
     }
-    if (tid == 0) *count = min(s_carry, max_tiles);
+    if (threadIdx.x < kQueues) count[kQueueOffset + threadIdx.x * kQueueStride] = 0;
+}
+
+template <typename Op>
+__device__ inline int block_excl_scan(int v, int ident, int* s_w, Op op) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int inc = v;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int o = __shfl_up(inc, off, 64);
+        if (lane >= off) inc = op(inc, o);
+    }
+    if (lane == 63) s_w[wave] = inc;
+    __syncthreads();
+    int base = ident;
+    for (int w = 0; w < wave; ++w) base = op(base, s_w[w]);
+    const int up = __shfl_up(inc, 1, 64);
+    __syncthreads();      // s_w may be written again
+    return lane == 0 ? base : op(base, up);
+}
+
+__global__ __launch_bounds__(kMapThreads) void k_tile_map(const int32_t* __restrict__ seg_off, int E, int rank_lo,
+                                                          int rank_hi, int BM, TileEntry* __restrict__ tiles,
+                                                          int32_t* __restrict__ count, int max_tiles) {
+    __shared__ int s_w[kMapThreads / 64];
+    const int tid = threadIdx.x;
+    clear_counts(count);
+    const int nseg = (rank_hi - rank_lo) * E, C = (nseg + kMapThreads - 1) / kMapThreads;
+    const int s0 = min(tid * C, nseg), s1 = min(s0 + C, nseg);
+    auto max_op = [](int a, int b) { return max(a, b); };
+    auto first_row = [&](int s) { return seg_off[(size_t)(rank_lo + s / E) * (E + 1) + s % E]; };
+    auto end_row = [&](int s) { return seg_off[(size_t)(rank_lo + s / E) * (E + 1) + s % E + 1]; };
+    // last non-empty segment in front of this thread's
+    int last = -1;
+    for (int s = s0; s < s1; ++s)
+        if (end_row(s) > first_row(s)) last = s;
+    const int before = block_excl_scan(last, -1, s_w, max_op);
+    // goes on the run of segment `prev`: the same expert, and its rows follow
+    auto continues = [&](int s, int prev) { return prev >= 0 && prev % E == s % E && end_row(prev) == first_row(s); };
+    int head = -1, prev = before;
+    for (int s = s0; s < s1; ++s) {
+        if (end_row(s) <= first_row(s)) continue;
+        if (!continues(s, prev)) head = first_row(s);
+        prev = s;
+    }
+    const int head_before = block_excl_scan(head, -1, s_w, max_op);
+    // A run's tiles start at its first row + multiples of BM; each belongs to the segment that its first row lies in.
+    // visit(s, r): a tile starts at row r of segment s; closed(end, head): the run from row `head` has ended at `end`.
+    auto walk = [&](auto visit, auto closed) {
+        int h = head_before, p = before;
+        for (int s = s0; s < s1; ++s) {
+            const int r0 = first_row(s), r1 = end_row(s);
+            if (r1 <= r0) continue;
+            if (!continues(s, p)) {
+                if (p >= 0) closed(end_row(p), h);
+                h = r0;
+            }
+            p = s;
+            for (int r = h + (r0 - h + BM - 1) / BM * BM; r < r1; r += BM) visit(s, r);
+        }
+        if (tid == kMapThreads - 1 && p >= 0) closed(end_row(p), h);
+    };
+    int nt = 0;
+    walk([&](int, int) { ++nt; }, [](int, int) {});
+    const int at0 = block_excl_scan(nt, 0, s_w, [](int a, int b) { return a + b; });
+    int at = at0;
+    walk(
+        [&](int s, int r) {
+            if (at < max_tiles) tiles[at] = TileEntry{s % E, r, BM, 0};
+            ++at;
+        },
+        [](int, int) {});
+    __syncthreads();
+    at = at0;
+    walk([&](int, int) { ++at; },
+         [&](int end, int h) {      // its last tile is the last one so far
+             if (at - 1 >= max_tiles) return;
+             tiles[at - 1].rows = end - (h + (end - 1 - h) / BM * BM);
+             tiles[at - 1].alone = end - h <= BM;
+         });
+    if (tid == kMapThreads - 1) *count = min(at, max_tiles);
+}
+
+// The same for one rank, whose segments are all of different experts: one thread per expert, one scan (a launch in
+// front of every rank's GEMMs, so its latency counts: 2.4-4.8 us).
+__global__ __launch_bounds__(kMapThreads) void k_tile_map_rank(const int32_t* __restrict__ seg_off, int E, int BM,
+                                                               TileEntry* __restrict__ tiles, int32_t* __restrict__ count,
+                                                               int max_tiles) {
+    __shared__ int s_w[kMapThreads / 64];
+    const int e = threadIdx.x;
+    const int r0 = e < E ? seg_off[e] : 0, n = e < E ? max(seg_off[e + 1] - r0, 0) : 0, nt = (n + BM - 1) / BM;
+    clear_counts(count);
+    const int at = block_excl_scan(nt, 0, s_w, [](int a, int b) { return a + b; });
+    for (int i = 0; i < nt && at + i < max_tiles; ++i)
+        tiles[at + i] = TileEntry{e, r0 + i * BM, min(BM, n - i * BM), nt == 1};
+    if (e == (int)blockDim.x - 1) *count = min(at + nt, max_tiles);
 }
 
 __device__ inline float silu_mul(float a, float b) { return a / (1.f + __expf(-a)) * b; }
@@ -146,7 +209,11 @@ __global__ __launch_bounds__(256) void k_gemm_simple(const T* __restrict__ A, in
 
 int launch_tile_map(const fine_shape& s, const int32_t* seg_off, int rank_lo, int rank_hi, int BM,
                     TileEntry* tiles, int32_t* count, int max_tiles, hipStream_t st) {
-    hipLaunchKernelGGL(k_tile_map, dim3(1), dim3(256), 0, st, seg_off, s.E, rank_lo, rank_hi, BM, tiles, count, max_tiles);
+    if (rank_hi - rank_lo == 1 && s.E <= kMapThreads)
+        hipLaunchKernelGGL(k_tile_map_rank, dim3(1), dim3((unsigned)align_up(s.E, 64)), 0, st,
+                           seg_off + (size_t)rank_lo * (s.E + 1), s.E, BM, tiles, count, max_tiles);
+    else
+        hipLaunchKernelGGL(k_tile_map, dim3(1), dim3(kMapThreads), 0, st, seg_off, s.E, rank_lo, rank_hi, BM, tiles, count, max_tiles);
     FINE_LAUNCH_CHECK();
     return FINE_OK;
 }

@@ -2,12 +2,11 @@
 // over induced subgraphs (Section 5.1, Eq. 3).
 //
 //   k_replica_counts   step 1: every expert one replica, each further replica to the expert with
-//                      the largest load per replica (exact comparison by cross-multiplication,
-//                      ties to the lower expert index).  One wavefront; the argmax of a round is
-//                      a lane-local scan plus a butterfly over the wave.
-//   k_score            step 2, four candidates per block: each wave draws one candidate's placement
-//                      (or the block reads given ones); the block then evaluates Eq. 3 over all
-//                      2^G - 1 rank subsets for one candidate after the other.
+//                      the largest load per replica (exact, ties to the lower expert index).  One
+//                      wavefront; the argmax of a round is a maximum of 64-bit keys over the lanes.
+//   k_score            step 2, four candidates per block: one wave draws their placements (or the block reads
+//                      given ones), then each wave evaluates Eq. 3 over all 2^G - 1 rank subsets of one
+//                      candidate (few candidates: the block's waves share one candidate's subsets).
 //   k_score_flow       the same for more than 16 ranks, where the subsets cannot be enumerated: one
 //                      wavefront per candidate finds the same m with exact integer flows.
 //   k_pick             the candidate with the smallest m (ties: lowest index); draws it again and
@@ -15,20 +14,23 @@
 //
 // Eq. 3 over all subsets.  w(S) = sum of load_e over experts whose replica set lies inside S is
 // the subset-sum (zeta) transform of f[mask] = sum of load_e with replica set == mask: for
-// each rank bit b in turn, every S containing b adds the value of S without b.  The table is
-// kept in LDS for the low min(G, 13) ranks (32 KB, so several blocks share a CU); the
-// remaining high ranks are enumerated: for a pattern h of high ranks, the experts whose high
-// part lies inside h are scattered by their low part, transformed over the low bits, and every
-// entry L gives the candidate w / (popcount(L) + popcount(h)).  Fractions are compared exactly
-// (64-bit cross-multiplication); the result is reduced by the gcd.
+// each rank bit b in turn, every S containing b adds the value of S without b.  One wavefront holds
+// the table of the low 11 ranks in registers (32 entries per lane); the remaining high ranks are
+// enumerated: for a pattern h of high ranks, the experts whose high part lies inside h are scattered
+// by their low part, transformed over the low bits, and every entry L gives the candidate
+// w / (popcount(L) + popcount(h)).  (With fewer than 11 ranks the missing ones hold no replicas: a
+// set with them has the sum of the set without them and more members, so it never wins.)  Fractions
+// are compared exactly (64-bit cross-multiplication); the result is reduced by the gcd.
 //
 // Drawing a candidate: experts in order of decreasing replica count (ties: lower index); an
 // expert's c replicas go to the c ranks with the most free slots, ties by the larger random
-// key, then the lower rank.  Lane g of the drawing wave is rank g: its position in that order is
-// the number of lanes with a larger composite key, one cross-lane read per rank.  A single wave
-// draws slowly (a chain of E dependent steps), which is why a block draws four candidates at once.  The keys come
+// key, then the lower rank.  A lane is a rank: its position in that order is the number of ranks with a
+// larger composite key.  Up to 16 ranks a wave draws four candidates at once, one per row of 16 lanes, and
+// the comparisons are 15 rotations of the row (DPP); beyond, one cross-lane read per rank.  The keys come
 // from a counter-based generator: two rounds of the MurmurHash3 32-bit finaliser over
 // (seed, candidate) and (expert, rank).
+#include <type_traits>
+
 #include "flow_wave.h"
 
 namespace fine {
@@ -39,7 +41,7 @@ typedef unsigned long long u64;
 typedef long long i64;
 
 constexpr int kScoreThreads = 256;
-constexpr int kLowMax = 13;
+constexpr int kLow = 11, kTable = 1 << kLow;           // ranks and entries of a wave's table
 constexpr int kCandPerBlock = kScoreThreads / 64;      // one per wave
 constexpr int kMaxE = 1024;
 constexpr int kMaxEnumG = 16;        // Eq. 3 by enumeration of 2^G subsets up to here, by flows beyond
@@ -67,61 +69,66 @@ __device__ inline bool frac_gt(Frac a, Frac b) { return (i64)a.num * b.den > (i6
 // ---------------------------------------------------------------------------
 // step 1
 // ---------------------------------------------------------------------------
+// largest of the lanes' keys, in every lane (six DPP steps: lane layout in flow_wave.h)
+__device__ inline u64 wave_max_u64(u64 v) {
+    auto step = [&](auto from) {
+        const u64 o = ((u64)(uint32_t)from((int)(v >> 32)) << 32) | (uint32_t)from((int)v);
+        if (o > v) v = o;
+    };
+    step([](int x) { return flow::dpp_from<0x111, 0xf>(0, x); });
+    step([](int x) { return flow::dpp_from<0x112, 0xf>(0, x); });
+    step([](int x) { return flow::dpp_from<0x114, 0xf>(0, x); });
+    step([](int x) { return flow::dpp_from<0x118, 0xf>(0, x); });
+    step([](int x) { return flow::dpp_from<0x142, 0xa>(0, x); });
+    step([](int x) { return flow::dpp_from<0x143, 0xc>(0, x); });
+    return flow::readlane_u64(v, 63);
+}
+
+// Load per replica as an integer that orders exactly like the fraction: two different l / c with c <= 64 are at
+// least 1 / 64^2 apart, so floor(2^13 l / c) differs the same way, and equal fractions give equal values.  Below it
+// the expert's index, lower = larger.  A round costs one wave maximum and one division (16 rounds on 64
+// experts: 18 -> 7 us against fractions compared by cross-multiplication in a butterfly of shuffles).
+__device__ inline u64 count_key(int load, int c, int e) { return (((u64)(uint32_t)load << 13) / (uint32_t)c) << 10 | (u64)(kMaxE - 1 - e) | 1ull << 60; }
+
 __global__ __launch_bounds__(64) void k_replica_counts(const int32_t* __restrict__ load, int E, int G, int slots,
                                                        int32_t* __restrict__ counts) {
     __shared__ int s_load[kMaxE], s_cnt[kMaxE];
+    __shared__ u64 s_key[kMaxE];             // 0: on all G ranks
     const int lane = threadIdx.x;
+    u64 mine = 0ull;                         // best of the experts lane, lane + 64, ...
     for (int e = lane; e < E; e += 64) {
         s_load[e] = max(load[e], 0);
         s_cnt[e] = 1;
+        s_key[e] = G > 1 ? count_key(s_load[e], 1, e) : 0ull;
+        mine = s_key[e] > mine ? s_key[e] : mine;
     }
-    __syncthreads();
     const long long rounds = (long long)G * slots - E;
     for (long long r = 0; r < rounds; ++r) {
-        // lane-local best over experts lane, lane + 64, ...: ascending e, strict '>' keeps the lower index
-        int best = -1;
-        i64 bl = 0, bc = 1;
-        for (int e = lane; e < E; e += 64) {
-            const int c = s_cnt[e];
-            if (c >= G) continue;
-            const i64 l = s_load[e];
-            if (best < 0 || l * bc > bl * c) {
-                best = e; bl = l; bc = c;
-            }
+        const u64 best = wave_max_u64(mine);
+        if (best == 0ull) break;             // every expert is on all G ranks
+        const int e = kMaxE - 1 - (int)(best & (kMaxE - 1));
+        if (lane == (e & 63)) {              // (only this lane touches its experts' entries)
+            const int c = ++s_cnt[e];
+            s_key[e] = c < G ? count_key(s_load[e], c, e) : 0ull;
+            mine = 0ull;
+            for (int i = lane; i < E; i += 64) mine = s_key[i] > mine ? s_key[i] : mine;
         }
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            const int oe = __shfl_xor(best, off, 64);
-            const i64 ol = __shfl_xor((int)bl, off, 64);
-            const i64 oc = __shfl_xor((int)bc, off, 64);
-            if (oe >= 0) {
-                const bool take = best < 0 || ol * bc > bl * oc || (ol * bc == bl * oc && oe < best);
-                if (take) {
-                    best = oe; bl = ol; bc = oc;
-                }
-            }
-        }
-        if (best < 0) break;                    // every expert is on all G ranks (wave-uniform)
-        if (lane == 0) s_cnt[best] += 1;
-        __syncthreads();
     }
-    __syncthreads();
     for (int e = lane; e < E; e += 64) counts[e] = s_cnt[e];
 }
 
 // ---------------------------------------------------------------------------
 // drawing a candidate (one wave; lanes >= G idle along)
 // ---------------------------------------------------------------------------
-// s_cnt [E]: replica counts; s_order [E]: experts in drawing order; s_mask [E] out: replica set of
-// each expert as a rank mask
+// s_order [E]: experts in drawing order, expert | replica count << 16; s_mask [E] out: replica set of each
+// expert as a rank mask
 template <int MAXG, typename MaskT>
-__device__ inline void draw_candidate(const int* s_cnt, const int* s_order, MaskT* s_mask, int E, int G, int slots,
+__device__ inline void draw_candidate(const int* s_order, MaskT* s_mask, int E, int G, int slots,
                                       uint32_t seed, uint32_t cand) {
     const int g = threadIdx.x & 63;       // lane = rank
     int free_slots = slots;
     for (int i = 0; i < E; ++i) {
-        const int e = s_order[i];
-        const int c = s_cnt[e];
+        const int e = s_order[i] & 0xffff, c = s_order[i] >> 16;
         // larger is better: free slots, then key, then lower rank; distinct over the ranks
         const u64 comp = g < G ? ((u64)(uint32_t)(free_slots + (1 << 20)) << 40) |
                                      ((u64)rank_key(seed, cand, (uint32_t)e, (uint32_t)g) << 8) | (u64)(255 - g)
@@ -141,6 +148,59 @@ __device__ inline void draw_candidate(const int* s_cnt, const int* s_order, Mask
     }
 }
 
+// Up to 16 ranks: four candidates at once, row r of 16 lanes draws candidate cand0 + r into s_mask[r * E ...].
+// A chain of E dependent steps, so a step is kept short: ranks are compared by 32 bits, 10 bits of slots not yet
+// used (a rank takes at most one replica per expert, so fewer than 1024 are used before a step) and the upper 22 of the
+// key.  Ranks that are equal in these are all chosen or all left, unless the last place falls between them: then a
+// row has chosen too many, and the step is done again with all bits.  (k_pick, one draw of 64
+// experts and the argmin of 4096 scores: 37 -> 23 us.)
+template <int R, typename F>
+__device__ inline void rotations(F& f) {
+    if constexpr (R < 16) {
+        f(std::integral_constant<int, R>{});
+        rotations<R + 1>(f);
+    }
+}
+__device__ inline void draw_rows(const int* s_order, uint32_t* s_mask, int E, int G, uint32_t seed, uint32_t cand0) {
+    const int lane = threadIdx.x & 63, g = lane & 15, row = lane >> 4;
+    const uint32_t h = mix32(seed + 0x9E3779B9u * (cand0 + (uint32_t)row + 1u));
+    uint32_t unused = 1023u;
+    auto key_of = [&](int e) { return mix32(h ^ (((uint32_t)e * 64u + (uint32_t)g + 1u) * 0x9E3779B1u)); };
+    int cur = s_order[0], next = s_order[min(1, E - 1)];
+    uint32_t next_key = key_of(cur & 0xffff);
+    for (int i = 0; i < E; ++i) {
+        const int e = cur & 0xffff, c = cur >> 16;
+        const uint32_t key = next_key;
+        cur = next;
+        next_key = key_of(cur & 0xffff);      // the next step's, beside the chain
+        next = s_order[min(i + 2, E - 1)];
+        // larger is better; lanes beyond the ranks hold 0, which is ahead of nobody
+        const uint32_t comp = g < G ? unused << 22 | key >> 10 : 0u;
+        int ahead = 0;
+        auto count = [&](auto r) {
+            ahead += (uint32_t)__builtin_amdgcn_mov_dpp((int)comp, 0x120 + r.value, 0xf, 0xf, false) > comp;      // row_ror
+        };
+        rotations<1>(count);
+        bool chosen = g < G && ahead < c;
+        u64 m = __ballot(chosen);
+        if (__ballot(__popc((uint32_t)(m >> (16 * row)) & 0xffffu) != min(c, G)) != 0ull) {
+            // slots, key, then lower rank: distinct over the ranks
+            const u64 all = g < G ? (u64)unused << 40 | (u64)key << 8 | (u64)(255 - g) : 0ull;
+            ahead = 0;
+            auto count_all = [&](auto r) {
+                const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(all >> 32), 0x120 + r.value, 0xf, 0xf, false);
+                const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)all, 0x120 + r.value, 0xf, 0xf, false);
+                ahead += ((u64)hi << 32 | lo) > all;
+            };
+            rotations<1>(count_all);
+            chosen = g < G && ahead < c;
+            m = __ballot(chosen);
+        }
+        unused -= chosen;
+        if (g == 0) s_mask[row * E + e] = (uint32_t)(m >> (16 * row)) & 0xffffu;
+    }
+}
+
 // position of every expert in the drawing order: decreasing count, then increasing index
 __device__ inline void drawing_order(const int32_t* __restrict__ counts, int* s_cnt, int* s_order, int E) {
     for (int e = threadIdx.x; e < E; e += blockDim.x) s_cnt[e] = counts[e];
@@ -152,172 +212,153 @@ __device__ inline void drawing_order(const int32_t* __restrict__ counts, int* s_
             const int oc = s_cnt[o];
             pos += (oc > c) || (oc == c && o < e);
         }
-        s_order[pos] = e;
+        s_order[pos] = e | min(max(c, 0), 64) << 16;      // (at most 64 ranks)
     }
     __syncthreads();
 }
 
-// Block maximum of the threads' best fractions (any maximiser gives the same reduced fraction),
-// reduced by the gcd and written out; `bad` flags an expert with load and no replica.
-__device__ inline void write_score(Frac best, int bad, int64_t* __restrict__ m_num, int32_t* __restrict__ m_den, int cand) {
-    __shared__ int s_best_num[kScoreThreads / 64], s_best_den[kScoreThreads / 64];
-    const int tid = threadIdx.x;
+// Where entry `idx` lies: bits 6..9 are folded into bits 2..5, so that the entries that experts add to fall into
+// different banks (most replica sets have few ranks, and the low bits alone would name few banks).
+__device__ inline int table_slot(int idx) { return idx ^ (((idx >> 6) & 15) << 2); }
+
+__device__ inline void clear_table(int* s_f) {
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        const Frac o{__shfl_xor(best.num, off, 64), __shfl_xor(best.den, off, 64)};
-        if (frac_gt(o, best)) best = o;
-    }
-    __syncthreads();                                   // the previous candidate's maxima have been read
-    if ((tid & 63) == 0) {
-        s_best_num[tid >> 6] = best.num;
-        s_best_den[tid >> 6] = best.den;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        for (int w = 1; w < kScoreThreads / 64; ++w) {
-            const Frac o{s_best_num[w], s_best_den[w]};
-            if (frac_gt(o, best)) best = o;
-        }
-        int a = best.num, b = best.den;
-        while (b != 0) {
-            const int t = a % b;
-            a = b;
-            b = t;
-        }
-        m_num[cand] = bad ? -1 : best.num / a;      // gcd(0, den) = den: zero comes out as 0 / 1
-        m_den[cand] = bad ? 0 : best.den / a;
-    }
+    for (int q = 0; q < 8; ++q) *reinterpret_cast<int4*>(s_f + q * 256 + (threadIdx.x & 63) * 4) = make_int4(0, 0, 0, 0);
 }
 
-// Eq. 3 of one candidate, G <= 12: the whole table of 2^G subsets in LDS, one pass per rank bit.
-__device__ inline Frac max_density_small(int* s_f, const uint32_t* s_mask, const int* s_load, int E, int G) {
-    const int tid = threadIdx.x;
-    const int n = 1 << G;
-    for (int i = tid; i < n; i += kScoreThreads) s_f[i] = 0;
-    __syncthreads();
-    for (int e = tid; e < E; e += kScoreThreads)
-        if (s_load[e] > 0) atomicAdd(&s_f[s_mask[e]], s_load[e]);
-    __syncthreads();
-    for (int b = 0; b < G; ++b) {
-        const int bit = 1 << b;
-        for (int i = tid; i < n / 2; i += kScoreThreads) {
-            const int L = ((i >> b) << (b + 1)) | bit | (i & (bit - 1));
-            s_f[L] += s_f[L ^ bit];
-        }
-        __syncthreads();
-    }
+// What an expert's additions need, from its replica set m (a lane has the experts e = lane modulo 64): bits 0..10 the
+// entry of its first addition; 11..15 the high ranks; bit 16 + i: whether there is an addition i (0 .. 3), to the entry with
+// bits 2 and 3 XORed with i.  The two low bits t of the entry number >> 2 run through all values, starting with the
+// lane's own (experts with the same few replicas would otherwise all add to one entry at a time), and those that
+// contain the expert's part in these bits count.  Experts without load add nothing.
+__device__ inline uint32_t additions(uint32_t m, int load, int e) {
+    constexpr uint32_t kSuper = 3u;
+    const uint32_t first = (uint32_t)e & kSuper, sub = (m >> 2) & kSuper;
+    uint32_t out = (uint32_t)table_slot((int)((m & (uint32_t)(kTable - 1) & ~(kSuper << 2)) | first << 2)) | (m >> kLow) << kLow;
+    for (uint32_t i = 0; i <= kSuper; ++i)
+        if (load > 0 && ((first ^ i) & sub) == sub) out |= 1u << (16 + i);
+    return out;
+}
+
+// Eq. 3 of one candidate by one wavefront (see the top of the file); lane-local maxima over the patterns that are
+// number `part` modulo `parts` of their size.  s_f [kTable]: the wave's own.
+//
+// Index bits of the table: register bits = bits 0, 1, 8, 9, 10; lane bits 0..5 = bits 2..7.  Register bits are added
+// along in registers; lane bits 5 and 4 change places with a register bit (permlane32_swap, permlane16_swap) and
+// are added along there; lane bits 2 and 3 by row shifts that write the lanes with the bit set; lane bits 0 and 1
+// when the experts are scattered (an expert goes to all supersets of its part in these bits; doing bits 2 and 3 the
+// same way, 16 additions instead of 4 and 64 row shifts, measured the same).  No barriers and about 20 LDS accesses
+// per 2048 entries: 4096 candidates on 16 ranks and 64 experts take 70 us without drawing them (the table of 13
+// ranks in the LDS of a block, three rounds with barriers: 226 us with drawing), bound by the ALUs.  Patterns of
+// one size together: their maxima per subset size are kept in six registers and compared as fractions once per size.
+// s_f must be all zero and is left so.
+__device__ inline Frac max_density(int* s_f, const uint32_t* s_at, const int* s_load, int E, int G, int part, int parts) {
+    const int lane = threadIdx.x & 63;
+    const int high_bits = max(G - kLow, 0);
     Frac best{0, 1};
-    for (int L = tid + 1; L < n; L += kScoreThreads) {
-        const Frac c{s_f[L], (int)__popc((uint32_t)L)};
-        if (frac_gt(c, best)) best = c;
-    }
-    __syncthreads();
-    return best;
-}
-
-// The same for 13 <= G <= 16, with a table over the low 13 ranks transformed in registers: every
-// thread holds 32 entries that differ in five index bits, adds along those bits in registers,
-// and the table goes through LDS only to change which bits are the thread's own.  Three rounds
-// cover the 13 bits: (8..12), (2..6), (0, 1, 7); the last one also compares the finished entries.
-// The table is stored at index ^ (((index >> 8) & 15) << 2), which makes the 64 lanes of every
-// access of the three rounds hit 64 different banks (16 lanes x 16 bytes in the last one).
-__device__ inline int table_slot(int idx) { return idx ^ (((idx >> 8) & 15) << 2); }
-
-template <int BITS>
-__device__ inline void add_along_bits(int (&v)[32]) {
-#pragma unroll
-    for (int b = 0; b < BITS; ++b)
-#pragma unroll
-        for (int j = 0; j < 32; ++j)
-            if (j & (1 << b)) v[j] += v[j ^ (1 << b)];
-}
-
-__device__ inline Frac max_density_13(int* s_f, const uint32_t* s_mask, const int* s_load, int E, int G) {
-    constexpr int LOW = kLowMax, NLOW = 1 << LOW;
-    const int tid = threadIdx.x;
-    // index of register j in the three rounds
-    //   A: bits 8..12 = j;             thread bits 0..7 = tid
-    //   B: bits 2..6 = j;              bits 0,1 = tid 0,1; bits 8..11 = tid 2..5; bit 7 = tid 6; bit 12 = tid 7
-    //   C: bits 0,1 = j 0,1; bit 7 = j 2; bit 6 = j 3; bit 12 = j 4;
-    //                                  bits 2..5 = tid 0..3; bits 8,9 = tid 4,5; bits 10,11 = tid 6,7
-    const int base_b = (tid & 3) | (((tid >> 2) & 15) << 8) | (((tid >> 6) & 1) << 7) | (((tid >> 7) & 1) << 12);
-    const int base_c = ((tid & 15) << 2) | (((tid >> 4) & 3) << 8) | (((tid >> 6) & 3) << 10);
-    const int n_high = 1 << (G - LOW);
-    Frac best{0, 1};
-    int v[32];
-    for (int h = 0; h < n_high; ++h) {
-#pragma unroll
-        for (int j = 0; j < 32; ++j) s_f[tid + 256 * j] = 0;
-        __syncthreads();
-        for (int e = tid; e < E; e += kScoreThreads) {
-            const uint32_t m = s_mask[e];
-            if (((m >> LOW) & ~(uint32_t)h) == 0 && s_load[e] > 0) atomicAdd(&s_f[table_slot((int)(m & (NLOW - 1)))], s_load[e]);
-        }
-        __syncthreads();
-        // round A
-#pragma unroll
-        for (int j = 0; j < 32; ++j) v[j] = s_f[table_slot(tid | (j << 8))];
-        add_along_bits<5>(v);
-#pragma unroll
-        for (int j = 0; j < 32; ++j) s_f[table_slot(tid | (j << 8))] = v[j];
-        __syncthreads();
-        // round B
-#pragma unroll
-        for (int j = 0; j < 32; ++j) v[j] = s_f[table_slot(base_b | (j << 2))];
-        add_along_bits<5>(v);
-#pragma unroll
-        for (int j = 0; j < 32; ++j) s_f[table_slot(base_b | (j << 2))] = v[j];
-        __syncthreads();
-        // round C: 16-byte reads (register bits 0, 1 are the index bits 0, 1, which the swizzle leaves alone)
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int idx = base_c | ((q & 1) << 7) | (((q >> 1) & 1) << 6) | (((q >> 2) & 1) << 12);
-            const int4 w = *reinterpret_cast<const int4*>(&s_f[table_slot(idx)]);
-            v[4 * q] = w.x; v[4 * q + 1] = w.y; v[4 * q + 2] = w.z; v[4 * q + 3] = w.w;
-        }
-        add_along_bits<3>(v);
-        // all five register bits are index bits here, so an entry's subset size is that of the
-        // thread's base + the pattern + popcount(j): one comparison per size, on the largest sum
-        const int den0 = __popc((uint32_t)base_c) + __popc((uint32_t)h);
+    for (int ph = 0; ph <= high_bits; ++ph) {
         int mx[6] = {0, 0, 0, 0, 0, 0};
+        int seen = 0;
+        for (int h = 0; h < (1 << high_bits); ++h) {
+            if (__popc(h) != ph) continue;
+            if (seen++ % parts != part) continue;
+            for (int e = lane; e < E; e += 64) {
+                const uint32_t at = s_at[e];
+                if (((at >> kLow) & ~(uint32_t)h & 31u) != 0u) continue;
+                const int w = s_load[e];
 #pragma unroll
-        for (int j = 0; j < 32; ++j) mx[__builtin_popcount(j)] = max(mx[__builtin_popcount(j)], v[j]);
+                for (uint32_t i = 0; i < 4; ++i)
+                    if (at >> (16 + i) & 1u) atomicAdd(&s_f[(at & (uint32_t)(kTable - 1)) ^ (i << 2)], w);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            int v[32];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const int4 w = *reinterpret_cast<const int4*>(s_f + table_slot(q * 256 + lane * 4));
+                v[4 * q] = w.x; v[4 * q + 1] = w.y; v[4 * q + 2] = w.z; v[4 * q + 3] = w.w;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            if (E <= 256) {      // few experts touch few entries
+                for (int e = lane; e < E; e += 64) {
+                    const uint32_t at = s_at[e] & (uint32_t)(kTable - 1);
+#pragma unroll
+                    for (uint32_t i = 0; i < 4; ++i) s_f[at ^ (i << 2)] = 0;
+                }
+            } else {
+                clear_table(s_f);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+            for (int b = 0; b < 5; ++b)
+#pragma unroll
+                for (int j = 0; j < 32; ++j)
+                    if (j & (1 << b)) v[j] += v[j ^ (1 << b)];
+#pragma unroll
+            for (int j = 0; j < 32; j += 2) {      // lane bit 5 <-> register bit 0
+                const auto sw = __builtin_amdgcn_permlane32_swap((unsigned)v[j], (unsigned)v[j + 1], false, false);
+                v[j] = (int)sw[0];
+                v[j + 1] = (int)(sw[0] + sw[1]);
+            }
+#pragma unroll
+            for (int j = 0; j < 32; j += 2) {      // lane bit 4 <-> register bit 0
+                const auto sw = __builtin_amdgcn_permlane16_swap((unsigned)v[j], (unsigned)v[j + 1], false, false);
+                v[j] = (int)sw[0];
+                v[j + 1] = (int)(sw[0] + sw[1]);
+            }
+#pragma unroll
+            for (int j = 0; j < 32; ++j) {
+                v[j] += __builtin_amdgcn_update_dpp(0, v[j], 0x114, 0xf, 0xa, false);      // lanes with bit 2: from lane - 4
+                v[j] += __builtin_amdgcn_update_dpp(0, v[j], 0x118, 0xf, 0xc, false);      // lanes with bit 3: from lane - 8
+            }
+#pragma unroll
+            for (int j = 0; j < 32; ++j) mx[__builtin_popcount(j)] = max(mx[__builtin_popcount(j)], v[j]);
+        }
+        // whichever index bits lanes and registers hold by now, a subset's size is the number of bits set in both
+        const int den0 = __popc((uint32_t)lane) + ph;
 #pragma unroll
         for (int k = 0; k < 6; ++k) {
             const Frac c{mx[k], max(den0 + k, 1)};       // size 0 is the empty set, whose sum is 0
             if (frac_gt(c, best)) best = c;
         }
-        __syncthreads();
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        const Frac o{__shfl_xor(best.num, off, 64), __shfl_xor(best.den, off, 64)};
+        if (frac_gt(o, best)) best = o;
     }
     return best;
 }
 
+// Few candidates: a block's waves share the patterns of one candidate.  (1024 candidates give every SIMD a wave.)
+inline bool share_candidate(int n, int G) { return G > kLow && n < 1024; }
+
 // ---------------------------------------------------------------------------
-// step 2: a block scores kCandPerBlock candidates, one drawn by each of its waves
+// step 2: a block scores kCandPerBlock candidates, one per wave, or (SHARE) one
 // ---------------------------------------------------------------------------
-// DRAW: candidate c is drawn from (counts, slots, seed, c); else it is place[c].  BIG: G >= 13.
-template <bool DRAW, bool BIG>
+// DRAW: candidate c is drawn from (counts, slots, seed, c); else it is place[c].
+template <bool DRAW, bool SHARE>
 __global__ __launch_bounds__(kScoreThreads) void k_score(const int32_t* __restrict__ load, const int32_t* __restrict__ counts,
                                                          const uint8_t* __restrict__ place, int n, int E, int G, int slots,
                                                          uint32_t seed, int64_t* __restrict__ m_num,
                                                          int32_t* __restrict__ m_den) {
+    constexpr int kWaves = kScoreThreads / 64, kCand = SHARE ? 1 : kCandPerBlock;
     extern __shared__ __attribute__((aligned(16))) int s_dyn[];
-    int* s_f = s_dyn;                                                  // [2^min(G, 13)]
-    uint32_t* s_mask = (uint32_t*)(s_f + (1 << min(G, kLowMax)));      // [kCandPerBlock][E]
+    int* s_f = s_dyn;                                                  // [kWaves][kTable]
+    uint32_t* s_mask = (uint32_t*)(s_f + kWaves * kTable);             // [kCandPerBlock][E]
     int* s_load = (int*)(s_mask + kCandPerBlock * E);                  // [E]
     int* s_order = s_load + E;                                         // [E]
     int* s_cnt = s_order + E;                                          // [E]
-    __shared__ int s_bad[kCandPerBlock];
-    const int tid = threadIdx.x;
-    const int cand0 = blockIdx.x * kCandPerBlock;
-    const int ncand = min(kCandPerBlock, n - cand0);
+    __shared__ Frac s_best[kWaves];
+    const int tid = threadIdx.x, wave = tid >> 6;
+    const int cand0 = blockIdx.x * kCand;
+    const int ncand = min(kCand, n - cand0);
 
-    if (tid < kCandPerBlock) s_bad[tid] = 0;
     for (int e = tid; e < E; e += kScoreThreads) s_load[e] = max(load[e], 0);
     if constexpr (DRAW) {
         drawing_order(counts, s_cnt, s_order, E);
-        const int w = tid >> 6;
-        if (w < ncand) draw_candidate<kMaxEnumG>(s_cnt, s_order, s_mask + w * E, E, G, slots, seed, (uint32_t)(cand0 + w));
+        // one wave draws (rows past the last candidate draw unused ones); not the same SIMD's in every block of a CU
+        if (wave == (int)((blockIdx.x ^ (blockIdx.x >> 8)) & (kWaves - 1)))
+            draw_rows(s_order, s_mask, E, G, seed, (uint32_t)cand0);
     } else {
         const uint8_t* pl = place + (size_t)cand0 * E * G;
         for (int i = tid; i < ncand * E; i += kScoreThreads) {
@@ -327,13 +368,38 @@ __global__ __launch_bounds__(kScoreThreads) void k_score(const int32_t* __restri
         }
     }
     __syncthreads();
-    for (int i = tid; i < ncand * E; i += kScoreThreads)
-        if (s_mask[i] == 0 && s_load[i % E] > 0) s_bad[i / E] = 1;      // an expert with load and no replica
-    for (int c = 0; c < ncand; ++c) {
-        Frac best;
-        if constexpr (BIG) best = max_density_13(s_f, s_mask + c * E, s_load, E, G);
-        else best = max_density_small(s_f, s_mask + c * E, s_load, E, G);
-        write_score(best, s_bad[c], m_num, m_den, cand0 + c);
+    const int mine = SHARE ? 0 : wave;
+    Frac best{0, 1};
+    bool bad = false;
+    if (mine < ncand) {
+        uint32_t* masks = s_mask + mine * E;
+        if (!SHARE || wave == 0)
+            for (int e = tid & 63; e < E; e += 64) {
+                const uint32_t m = masks[e];
+                bad |= m == 0 && s_load[e] > 0;                                            // load, but no replica
+                masks[e] = additions(m, s_load[e], e);
+            }
+        bad = __ballot(bad) != 0ull;
+        if (SHARE) __syncthreads();
+        clear_table(s_f + wave * kTable);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        best = max_density(s_f + wave * kTable, masks, s_load, E, G, SHARE ? wave : 0, SHARE ? kWaves : 1);
+    }
+    if constexpr (SHARE) {
+        if ((tid & 63) == 0) s_best[wave] = best;
+        __syncthreads();
+        for (int w = 0; w < kWaves; ++w)
+            if (frac_gt(s_best[w], best)) best = s_best[w];
+    }
+    if ((tid & 63) == 0 && mine < ncand && (!SHARE || wave == 0)) {
+        int a = best.num, b = best.den;
+        while (b != 0) {
+            const int t = a % b;
+            a = b;
+            b = t;
+        }
+        m_num[cand0 + mine] = bad ? -1 : best.num / a;      // gcd(0, den) = den: zero comes out as 0 / 1
+        m_den[cand0 + mine] = bad ? 0 : best.den / a;
     }
 }
 
@@ -355,7 +421,7 @@ __global__ __launch_bounds__(64) void k_score_flow(const int32_t* __restrict__ l
     const uint32_t cand = blockIdx.x;
     if constexpr (DRAW) {
         drawing_order(counts, s_cnt, s_order, E);
-        draw_candidate<64>(s_cnt, s_order, c.pm, E, G, slots, seed, cand);
+        draw_candidate<64>(s_order, c.pm, E, G, slots, seed, cand);
     } else {
         const uint8_t* pl = place + (size_t)cand * E * G;
         for (int e = l; e < E; e += 64) {
@@ -392,27 +458,39 @@ __global__ __launch_bounds__(64) void k_score_flow(const int32_t* __restrict__ l
 // ---------------------------------------------------------------------------
 // the best candidate
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_pick(const int64_t* __restrict__ m_num, const int32_t* __restrict__ m_den, int n,
+constexpr int kPickThreads = 1024;
+
+__global__ __launch_bounds__(kPickThreads) void k_pick(const int64_t* __restrict__ m_num, const int32_t* __restrict__ m_den, int n,
                                               const int32_t* __restrict__ counts, int E, int G, int slots, uint32_t seed,
                                               int32_t* __restrict__ best_out, uint8_t* __restrict__ place) {
     extern __shared__ __attribute__((aligned(16))) int s_dyn[];
     u64* s_mask = (u64*)s_dyn;               // [E]
     int* s_order = (int*)(s_mask + E);       // [E]
     int* s_cnt = s_order + E;                // [E]
-    __shared__ int s_idx[256], s_num[256], s_den[256];
+    __shared__ int s_idx[kPickThreads], s_num[kPickThreads], s_den[kPickThreads];
     const int tid = threadIdx.x;
     // smallest m, then lowest index; candidates flagged infeasible (den == 0) never win
     int bi = -1, bn = 0, bd = 1;
-    for (int c = tid; c < n; c += 256) {
-        const int cn = (int)m_num[c], cd = m_den[c];
-        if (cd <= 0) continue;
-        if (bi < 0 || (i64)cn * bd < (i64)bn * cd) {      // ascending c: strict '<' keeps the lower index
-            bi = c; bn = cn; bd = cd;
+    for (int c0 = tid; c0 < n; c0 += 4 * kPickThreads) {
+        int cn[4], cd[4];                                     // four loads in flight (past the end: the last again)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int c = min(c0 + j * kPickThreads, n - 1);
+            cn[j] = (int)m_num[c];
+            cd[j] = m_den[c];
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int c = c0 + j * kPickThreads;
+            if (c >= n || cd[j] <= 0) continue;
+            if (bi < 0 || (i64)cn[j] * bd < (i64)bn * cd[j]) {      // ascending c: strict '<' keeps the lower index
+                bi = c; bn = cn[j]; bd = cd[j];
+            }
         }
     }
     s_idx[tid] = bi; s_num[tid] = bn; s_den[tid] = bd;
     __syncthreads();
-    for (int off = 128; off > 0; off >>= 1) {
+    for (int off = kPickThreads / 2; off > 0; off >>= 1) {
         if (tid < off) {
             const int a = s_idx[tid], b = s_idx[tid + off];
             if (b >= 0) {
@@ -431,19 +509,31 @@ __global__ __launch_bounds__(256) void k_pick(const int64_t* __restrict__ m_num,
     const int best = s_idx[0];
     if (tid == 0) best_out[0] = best;
     if (best < 0) {
-        for (int i = tid; i < E * G; i += 256) place[i] = 0;
+        for (int i = tid; i < E * G; i += kPickThreads) place[i] = 0;
         return;
     }
     drawing_order(counts, s_cnt, s_order, E);
+    uint32_t* s_rows = (uint32_t*)(s_cnt + E);      // [4][E], row 0 is the winner's (G <= kMaxEnumG)
     if (tid < 64) {
-        if (G <= kMaxEnumG) draw_candidate<kMaxEnumG>(s_cnt, s_order, s_mask, E, G, slots, seed, (uint32_t)best);
-        else draw_candidate<64>(s_cnt, s_order, s_mask, E, G, slots, seed, (uint32_t)best);
+        if (G <= kMaxEnumG) draw_rows(s_order, s_rows, E, G, seed, (uint32_t)best);
+        else draw_candidate<64>(s_order, s_mask, E, G, slots, seed, (uint32_t)best);
     }
     __syncthreads();
-    for (int i = tid; i < E * G; i += 256) place[i] = (uint8_t)((s_mask[i / G] >> (i % G)) & 1ull);
+    for (int i = tid; i < E * G; i += kPickThreads)
+        place[i] = (uint8_t)(((G <= kMaxEnumG ? (u64)s_rows[i / G] : s_mask[i / G]) >> (i % G)) & 1ull);
 }
 
-size_t score_lds(int E, int G) { return ((size_t)(1 << (G < kLowMax ? G : kLowMax)) + (kCandPerBlock + 3) * (size_t)E) * 4; }
+template <bool DRAW>
+int launch_score(const fine_shape& s, const int32_t* load, const int32_t* counts, const uint8_t* place, int n, int slots,
+                 uint32_t seed, int64_t* m_num, int32_t* m_den, hipStream_t st) {
+    const bool share = share_candidate(n, s.G);
+    auto k = share ? k_score<DRAW, true> : k_score<DRAW, false>;
+    const size_t lds = ((size_t)(kScoreThreads / 64) * kTable + (kCandPerBlock + 3) * (size_t)s.E) * 4;
+    hipLaunchKernelGGL(k, dim3(cdiv(n, share ? 1 : kCandPerBlock)), dim3(kScoreThreads), lds, st, load, counts, place, n, s.E,
+                       s.G, slots, seed, m_num, m_den);
+    FINE_LAUNCH_CHECK();
+    return FINE_OK;
+}
 
 }  // namespace
 
@@ -543,11 +633,7 @@ int launch_eval_placements(const fine_shape& s, int n, const uint8_t* place, con
         FINE_LAUNCH_CHECK();
         return FINE_OK;
     }
-    auto k = s.G >= kLowMax ? k_score<false, true> : k_score<false, false>;
-    hipLaunchKernelGGL(k, dim3(cdiv(n, kCandPerBlock)), dim3(kScoreThreads), score_lds(s.E, s.G), st, load,
-                       (const int32_t*)nullptr, place, n, s.E, s.G, 0, 0u, m_num, m_den);
-    FINE_LAUNCH_CHECK();
-    return FINE_OK;
+    return launch_score<false>(s, load, nullptr, place, n, 0, 0u, m_num, m_den, st);
 }
 
 int launch_place_search(const fine_shape& s, const int32_t* load, const int32_t* counts, int slots, int n, uint32_t seed,
@@ -558,12 +644,10 @@ int launch_place_search(const fine_shape& s, const int32_t* load, const int32_t*
         hipLaunchKernelGGL(k_score_flow<true>, dim3(n), dim3(64), lds, st, load, counts, (const uint8_t*)nullptr, s.E, s.G,
                            slots, seed, m_num, m_den);
     } else {
-        auto k = s.G >= kLowMax ? k_score<true, true> : k_score<true, false>;
-        hipLaunchKernelGGL(k, dim3(cdiv(n, kCandPerBlock)), dim3(kScoreThreads), score_lds(s.E, s.G), st, load, counts,
-                           (const uint8_t*)nullptr, n, s.E, s.G, slots, seed, m_num, m_den);
+        FINE_TRY(launch_score<true>(s, load, counts, nullptr, n, slots, seed, m_num, m_den, st));
     }
     FINE_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_pick, dim3(1), dim3(256), (size_t)4 * s.E * 4, st, m_num, m_den, n, counts, s.E, s.G, slots, seed,
+    hipLaunchKernelGGL(k_pick, dim3(1), dim3(kPickThreads), (size_t)8 * s.E * 4, st, m_num, m_den, n, counts, s.E, s.G, slots, seed,
                        best, place);
     FINE_LAUNCH_CHECK();
     return FINE_OK;

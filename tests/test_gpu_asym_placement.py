@@ -303,3 +303,20 @@ def test_cayley_placement_matches_the_oracle(orders, gens, complete):
         fm.fine_cayley_placement(shape, orders, [tuple(0 for _ in orders)] + list(gens[1:]), complete, place)
     with pytest.raises(fm.FineError):
         fm.fine_cayley_placement(shape, tuple(orders) + (2,), [tuple(g) + (0,) for g in gens], complete, place)
+
+
+@pytest.mark.parametrize("E,G,slots,n", [(64, 16, 5, 2051), (200, 13, 18, 1025), (128, 12, 12, 1023), (257, 11, 25, 1023)])
+def test_many_candidates_scored_one_per_wave(E, G, slots, n):
+    """More candidates than blocks share (a wave scores a whole one; up to 128 experts and beyond): a sample of the
+    scores, the last ones included, and the choice among all of them."""
+    load = wl.zipf_loads(E, 65536, 1.1, E)
+    counts = gpu_counts(load, E, G, slots)
+    m_num, m_den, best, place = gpu_search(load, counts, E, G, slots, n, 3)
+    host_counts = counts.cpu().numpy()
+    assert np.array_equal(host_counts, placement.replica_counts(load, G, slots))
+    for c in list(range(3)) + list(range(1021, n, 341)) + [n - 2, n - 1, best]:
+        want = placement.max_density(load, placement.draw_placement(host_counts, G, slots, 3, c))
+        assert (int(m_num[c]), int(m_den[c])) == (want.numerator, want.denominator), c
+    scores = [Fraction(int(a), int(b)) for a, b in zip(m_num, m_den)]
+    assert best == min(range(n), key=lambda c: (scores[c], c))
+    assert np.array_equal(place, placement.draw_placement(host_counts, G, slots, 3, best))

@@ -13,19 +13,27 @@ namespace flow {
 constexpr int kW = 64;
 typedef unsigned long long u64;
 
+// Only experts with several replicas can move: they are kept in a compact list, in ascending order (256 experts
+// with 320 replicas: at most 64 of them, one per lane).  What a rank needs at every step is in the registers of its
+// lane: its load and the set of ranks that load may come from; A, which is only read where an edge is used, is in LDS.
 struct Ctx {
-    int* x;        // [E][G]
-    u64* pm;       // [E] replica masks
-    int* A;        // [G][AS], stored by destination: a(from, to) = A[to * AS + from]; 16-byte aligned,
-                   // entries from >= G are padding and stay 0
-    int* ld;       // [G]
-    int* path;     // [2*G] edges (from, to)
-    int E, G, AS;  // AS = row stride of A: a multiple of 4 that is an odd number of 16-byte pieces, so
-                   // that lanes reading 16 bytes of consecutive rows fall into different banks
+    int* x;        // [n][XS] units of listed expert j on every rank
+    u64* pm;       // [n] replica masks of the listed experts (before compact(): of all experts)
+    int* A;        // [G][AS], stored by destination: a(from, to) = A[to * AS + from]
+    int* t;        // [G] scratch
+    int E, G;
+    int AS, XS;    // row strides (odd where they fit, so that a column's entries fall into different banks)
+    int n;         // listed experts
+    u64 listed;    // lane i: which of the experts 64 i .. 64 i + 63 are listed
+    int single;    // lane = rank: load of the experts whose only replica is here
+    int ld;        // lane = rank: its load
+    u64 in;        // lane = rank: the ranks `a` with a(a, lane) > 0
     __device__ int& a(int from, int to) const { return A[to * AS + from]; }
 };
 
 __device__ inline int lane() { return threadIdx.x; }
+// LDS accesses of one wavefront are performed in order: only the compiler has to keep the order
+__device__ inline void wave_sync() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
 // Wave-wide scan and sum by DPP (data-parallel primitives: an operand taken from another lane of
 // the same ALU instruction), six steps and no LDS traffic: shifts by 1, 2, 4, 8 inside each row of
@@ -46,89 +54,64 @@ __device__ inline int wave_incl_scan_i(int v) {
 }
 __device__ inline int wave_sum_i(int v) { return __builtin_amdgcn_readlane(wave_incl_scan_i(v), kW - 1); }
 
-// replicas of expert e whose variables are still free when variable (e_cur, g_cur) is being set
-__device__ inline u64 free_mask(const Ctx& c, int e, int e_cur, int g_cur) {
-    if (e > e_cur) return c.pm[e];
-    if (e == e_cur) return c.pm[e] & ~((2ull << g_cur) - 1ull);
-    return 0ull;
-}
-
 __device__ inline u64 readlane_u64(u64 v, int src) {
     const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)v, src), hi = __builtin_amdgcn_readlane((int)(unsigned)(v >> 32), src);
     return ((u64)hi << 32) | lo;
 }
 
-// Move `amount` units of free load from rank a to rank b (experts in ascending order; e_cur < 0:
-// every variable is free).  A lane past the last expert reads the last expert's entries (in bounds,
-// no branch, so the two LDS reads go out together) and takes no part.  The experts that give units
-// are then taken one by one, lane q = rank q updating its own entries of rows a and b of A: two
-// LDS updates per giving expert whatever its number of replicas.
-__device__ inline void move_units(const Ctx& c, int a, int b, int amount, int e_cur, int g_cur) {
-    int remaining = amount;
+// Move `amount` units of free load from rank a to rank b (listed experts in ascending order; free: replicas above
+// g_cur of j_cur and all of the experts after it; j_cur < 0: everything).  A lane past the last expert reads the last
+// expert's entries (in bounds, no branch, so the LDS reads go out together) and takes no part.  Every rank q that is
+// a replica of a giving expert loses what it could get from a and gains it from b: summed over the givers in
+// lane q's register, then one update of its two entries.
+__device__ inline void move_units(Ctx& c, int a, int b, int amount, int j_cur, int g_cur) {
+    int remaining = amount, D = 0;
     const int q = lane();
-    for (int base = (e_cur < 0 ? 0 : e_cur); base < c.E && remaining > 0; base += kW) {
-        const int e = base + q;                       // >= e_cur: earlier experts are never looked at
-        const bool in = e < c.E;
-        const int ee = in ? e : c.E - 1;
-        const u64 pm = c.pm[ee];
-        const int xa = c.x[ee * c.G + a];
-        const u64 F = (e == e_cur) ? (pm & ~((2ull << g_cur) - 1ull)) : pm;
+    for (int base = (j_cur < 0 ? 0 : j_cur); base < c.n && remaining > 0; base += kW) {
+        const int j = base + q;                       // >= j_cur: earlier experts are never looked at
+        const bool in = j < c.n;
+        const int jj = in ? j : c.n - 1;
+        const u64 pm = c.pm[jj];
+        const int xa = c.x[jj * c.XS + a], xb = c.x[jj * c.XS + b];
+        const u64 F = (j == j_cur) ? (pm & ~((2ull << g_cur) - 1ull)) : pm;
         const int m = (in && ((F >> a) & 1ull) && ((F >> b) & 1ull)) ? xa : 0;
         if (__ballot(m > 0) == 0ull) continue;        // no expert of this chunk links a to b (wave-uniform)
         const int inc = wave_incl_scan_i(m);
         const int t = max(0, min(m, remaining - (inc - m)));
         if (t > 0) {
-            c.x[e * c.G + a] = xa - t;
-            c.x[e * c.G + b] += t;
+            c.x[j * c.XS + a] = xa - t;
+            c.x[j * c.XS + b] = xb + t;
         }
         u64 givers = __ballot(t > 0);
         while (givers) {
             const int src = __ffsll((long long)givers) - 1;
             givers &= givers - 1;
             const int ts = __builtin_amdgcn_readlane(t, src);
-            const u64 Fs = readlane_u64(F, src);
-            if (q < c.G && ((Fs >> q) & 1ull)) {
-                if (q != a) c.a(a, q) -= ts;
-                if (q != b) c.a(b, q) += ts;
-            }
+            if ((readlane_u64(F, src) >> q) & 1ull) D += ts;
         }
         remaining -= min(remaining, __builtin_amdgcn_readlane(inc, kW - 1));
-        __syncthreads();
     }
-    if (q == 0) { c.ld[a] -= amount; c.ld[b] += amount; }
-    __syncthreads();
+    if (D > 0) {                                      // (only ranks have bits in F)
+        const int va = q != a ? c.a(a, q) - D : 0, vb = q != b ? c.a(b, q) + D : 0;
+        if (q != a) c.a(a, q) = va;
+        if (q != b) c.a(b, q) = vb;
+        c.in = (c.in & ~(1ull << a) & ~(1ull << b)) | (u64)(va > 0) << a | (u64)(vb > 0) << b;
+    }
+    c.ld += q == b ? amount : q == a ? -amount : 0;
+    wave_sync();
 }
 
 // Breadth-first search from `src` over edges with A > 0.  Stops at the first level that
 // holds a rank of `want` (a per-lane predicate, lane = rank).  Returns the chosen rank
-// (lowest of that level) or -1; *visited_out = every rank reached.  The path src -> ... ->
-// target is written to c.path as (from, to) pairs, its length to *len_out and its smallest
-// capacity to *cap_out.
-__device__ inline int bfs(const Ctx& c, int src, bool want, u64* visited_out, int* len_out, int* cap_out) {
+// (lowest of that level) or -1; *visited_out = every rank reached; *parent_out (lane = rank) = where the search came
+// from; *cap_out = the smallest capacity on the way.
+__device__ inline int bfs(const Ctx& c, int src, bool want, u64* visited_out, int* parent_out, int* cap_out) {
     const int b = lane();
-    // lane b's row of A holds what may move into b from every rank: 16-byte reads, four in flight,
-    // no branch between them (a piece index past the end reads the last piece again; its bits are
-    // dropped)
-    u64 inmask = 0ull;
-    if (b < c.G) {
-        const int4* row = reinterpret_cast<const int4*>(c.A + b * c.AS);
-        const int n4 = c.AS >> 2;
-        for (int i0 = 0; i0 < n4; i0 += 4) {
-            int4 v[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) v[j] = row[min(i0 + j, n4 - 1)];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const unsigned bits = (v[j].x > 0) | ((v[j].y > 0) << 1) | ((v[j].z > 0) << 2) | ((v[j].w > 0) << 3);
-                inmask |= (u64)(i0 + j < n4 ? bits : 0u) << ((4 * (i0 + j)) & 63);      // a 17th piece is padding: no bits
-            }
-        }
-    }
     u64 visited = 1ull << src, frontier = visited;
     int parent = -1, target = -1;
     while (true) {
-        const u64 hit = inmask & frontier;
-        const bool fresh = (b < c.G) && hit && !((visited >> b) & 1ull);
+        const u64 hit = c.in & frontier;
+        const bool fresh = hit && !((visited >> b) & 1ull);      // (lanes that are no ranks have nothing in `in`)
         if (fresh) parent = __ffsll((long long)hit) - 1;
         const u64 next = __ballot(fresh);
         if (next == 0ull) break;
@@ -138,50 +121,94 @@ __device__ inline int bfs(const Ctx& c, int src, bool want, u64* visited_out, in
         frontier = next;
     }
     *visited_out = visited;
+    *parent_out = parent;
     if (target < 0) return -1;
-    int len = 0, cap = 0x7fffffff, cur = target;
+    // every reached rank reads the capacity of its own edge; the way back is then two lane reads per step
+    const int edge = parent >= 0 ? c.a(parent, b) : 0;
+    int cap = 0x7fffffff, cur = target;
     while (cur != src) {
-        const int p = __builtin_amdgcn_readlane(parent, __builtin_amdgcn_readfirstlane(cur));   // cur is wave-uniform
-        if (lane() == 0) { c.path[2 * len] = p; c.path[2 * len + 1] = cur; }
-        cap = min(cap, c.a(p, cur));
-        cur = p;
-        ++len;
+        cap = min(cap, __builtin_amdgcn_readlane(edge, cur));
+        cur = __builtin_amdgcn_readlane(parent, cur);
     }
-    __syncthreads();
-    *len_out = len;
     *cap_out = cap;
     return target;
 }
 
-__device__ inline void push_path(const Ctx& c, int len, int amount, int e_cur, int g_cur) {
-    for (int i = 0; i < len; ++i) move_units(c, c.path[2 * i], c.path[2 * i + 1], amount, e_cur, g_cur);
+// Moves `amount` units along the way found by bfs, last edge first (an edge's capacity depends on the units on its
+// source only, and the ranks of a shortest way are distinct: the order of the edges does not matter).
+__device__ inline void push_path(Ctx& c, int src, int target, int parent, int amount, int j_cur, int g_cur) {
+    int cur = target;
+    while (cur != src) {
+        const int p = __builtin_amdgcn_readlane(parent, cur);
+        move_units(c, p, cur, amount, j_cur, g_cur);
+        cur = p;
+    }
 }
 
-// Everything on each expert's first replica: fills x, A and the rank loads from the replica masks
-// c.pm and the expert loads (negative reads as 0) times `scale`.  Returns (to every lane) whether
-// some expert with load has no replica.  The arrays must not be in use; ends with a barrier.
-__device__ inline bool start_on_first_replicas(const Ctx& c, const int32_t* __restrict__ load, int scale = 1) {
+// From the replica masks of all experts in c.pm: the list of those with several replicas (their masks move to the
+// front of c.pm), and the loads of the others on their only rank.  Returns (to every lane) whether some expert with
+// load has no replica.
+__device__ inline bool compact(Ctx& c, const int32_t* __restrict__ load) {
+    const int l = lane();
+    int bad = 0, n = 0;
+    c.listed = 0ull;
+    if (l < c.G) c.t[l] = 0;
+    wave_sync();
+    for (int base = 0; base < c.E; base += kW) {
+        const int e = base + l;
+        const u64 m = e < c.E ? c.pm[e] : 0ull;
+        const int le = e < c.E ? max(load[e], 0) : 0;
+        const int replicas = __popcll(m);
+        if (replicas == 0 && le > 0) bad = 1;
+        if (replicas == 1 && le > 0) atomicAdd(&c.t[__ffsll((long long)m) - 1], le);
+        const u64 w = __ballot(replicas > 1);
+        if (l == base / kW) c.listed = w;
+        wave_sync();                                  // this chunk's masks are in registers
+        if (replicas > 1) c.pm[n + __popcll(w & ((1ull << l) - 1ull))] = m;      // never behind what is still to be read
+        n += __popcll(w);
+    }
+    c.n = n;
+    wave_sync();
+    c.single = l < c.G ? c.t[l] : 0;
+    return __ballot(bad) != 0ull;
+}
+
+// the rank loads from c.t and the sets of sources from A
+__device__ inline void load_registers(Ctx& c) {
+    const int l = lane();
+    wave_sync();
+    c.ld = l < c.G ? c.t[l] : 0;
+    c.in = 0ull;
+    if (l < c.G)
+        for (int a = 0; a < c.G; ++a) c.in |= (u64)(c.A[l * c.AS + a] > 0) << a;
+}
+
+// Everything on each expert's first replica: fills x, A and the rank loads from the list and the expert loads
+// (negative reads as 0) times `scale`.
+__device__ inline void start_on_first_replicas(Ctx& c, const int32_t* __restrict__ load, int scale = 1) {
     const int l = lane();
     for (int i = l; i < c.G * c.AS; i += kW) c.A[i] = 0;
-    for (int i = l; i < c.G; i += kW) c.ld[i] = 0;
-    for (int i = l; i < c.E * c.G; i += kW) c.x[i] = 0;
-    __syncthreads();
-    int bad = 0;
-    for (int e = l; e < c.E; e += kW) {
-        const u64 m = c.pm[e];
-        const int le = max(load[e], 0) * scale;
-        if (m == 0ull) {
-            if (le > 0) bad = 1;
-        } else if (le > 0) {
-            const int first = __ffsll((long long)m) - 1;
-            c.x[e * c.G + first] = le;
-            atomicAdd(&c.ld[first], le);
-            u64 others = m & ~(1ull << first);
-            while (others) { int q = __ffsll((long long)others) - 1; others &= others - 1; atomicAdd(&c.a(first, q), le); }
+    for (int i = l; i < c.n * c.XS; i += kW) c.x[i] = 0;
+    if (l < c.G) c.t[l] = c.single * scale;
+    wave_sync();
+    int n = 0;
+    for (int base = 0; base < c.E; base += kW) {
+        const u64 w = readlane_u64(c.listed, base / kW);
+        if ((w >> l) & 1ull) {
+            const int j = n + __popcll(w & ((1ull << l) - 1ull));
+            const u64 m = c.pm[j];
+            const int le = max(load[base + l], 0) * scale;
+            if (le > 0) {
+                const int first = __ffsll((long long)m) - 1;
+                c.x[j * c.XS + first] = le;
+                atomicAdd(&c.t[first], le);
+                u64 others = m & ~(1ull << first);
+                while (others) { int q = __ffsll((long long)others) - 1; others &= others - 1; atomicAdd(&c.a(first, q), le); }
+            }
         }
+        n += __popcll(w);
     }
-    __syncthreads();
-    return __ballot(bad) != 0ull;
+    load_registers(c);
 }
 
 // The optimum value M* = ceil(m) of Eq. 1 for P units in all.  Start with M = ceil(P/G).  While some
@@ -189,16 +216,16 @@ __device__ inline bool start_on_first_replicas(const Ctx& c, const int32_t* __re
 // If the search finds none, the reached set S is closed (no expert with load in S has a replica
 // outside S), so Eq. 3 gives the lower bound ceil(load(S)/|S|) > M; M jumps to it.  M only ever moves
 // to lower bounds of the optimum and the loop ends with a feasible flow, hence M = M*.
-__device__ inline int optimum_value(const Ctx& c, int P) {
+__device__ inline int optimum_value(Ctx& c, int P) {
     const int l = lane();
     int M = (P + c.G - 1) / c.G;
     while (true) {
-        const int mine = (l < c.G) ? c.ld[l] : 0;
+        const int mine = c.ld;
         const u64 over = __ballot(l < c.G && mine > M);
         if (over == 0ull) break;
         const int a = __ffsll((long long)over) - 1;
-        u64 visited; int len, cap;
-        const int r = bfs(c, a, (l < c.G) && (mine < M), &visited, &len, &cap);
+        u64 visited; int parent, cap;
+        const int r = bfs(c, a, (l < c.G) && (mine < M), &visited, &parent, &cap);
         if (r < 0) {
             const bool in = (l < c.G) && ((visited >> l) & 1ull);
             const int tot = wave_sum_i(in ? mine : 0);
@@ -206,8 +233,8 @@ __device__ inline int optimum_value(const Ctx& c, int P) {
             M = (tot + cnt - 1) / cnt;
             continue;
         }
-        const int amount = min(min(c.ld[a] - M, M - c.ld[r]), cap);
-        push_path(c, len, amount, -1, 0);
+        const int amount = min(min(__builtin_amdgcn_readlane(mine, a) - M, M - __builtin_amdgcn_readlane(mine, r)), cap);
+        push_path(c, a, r, parent, amount, -1, 0);
     }
     return M;
 }
@@ -221,19 +248,19 @@ __device__ inline int optimum_value(const Ctx& c, int P) {
 // expert has none there, so the units in S are den * load(S), no rank of S is below capacity and one
 // is above: load(S) / |S| > lambda.  lambda moves there and the flow starts again in the new scale.
 // When no rank is above capacity the loads fit under lambda, so m <= lambda, hence m = lambda.
-__device__ inline void exact_density(const Ctx& c, const int32_t* __restrict__ load, int P, int* num_out, int* den_out) {
+__device__ inline void exact_density(Ctx& c, const int32_t* __restrict__ load, int P, int* num_out, int* den_out) {
     const int l = lane();
     int num = P, den = c.G;
     while (true) {
         start_on_first_replicas(c, load, den);
         bool moved = false;
         while (true) {
-            const int mine = (l < c.G) ? c.ld[l] : 0;
+            const int mine = c.ld;
             const u64 over = __ballot(l < c.G && mine > num);
             if (over == 0ull) break;
             const int a = __ffsll((long long)over) - 1;
-            u64 visited; int len, cap;
-            const int r = bfs(c, a, (l < c.G) && (mine < num), &visited, &len, &cap);
+            u64 visited; int parent, cap;
+            const int r = bfs(c, a, (l < c.G) && (mine < num), &visited, &parent, &cap);
             if (r < 0) {
                 const bool in = (l < c.G) && ((visited >> l) & 1ull);
                 num = wave_sum_i(in ? mine : 0) / den;
@@ -241,7 +268,8 @@ __device__ inline void exact_density(const Ctx& c, const int32_t* __restrict__ l
                 moved = true;
                 break;
             }
-            push_path(c, len, min(min(c.ld[a] - num, num - c.ld[r]), cap), -1, 0);
+            push_path(c, a, r, parent,
+                      min(min(__builtin_amdgcn_readlane(mine, a) - num, num - __builtin_amdgcn_readlane(mine, r)), cap), -1, 0);
         }
         if (!moved) break;
     }
@@ -249,21 +277,22 @@ __device__ inline void exact_density(const Ctx& c, const int32_t* __restrict__ l
     *den_out = den;
 }
 
-// bytes of LDS behind a Ctx for E experts on G ranks
-__host__ __device__ inline int a_stride(int G) { const int q = ((G + 3) >> 2) | 1; return 4 * q; }
-__host__ __device__ inline size_t ctx_bytes(int E, int G) {
-    return (((size_t)E * 8 + 15) & ~(size_t)15) + ((size_t)G * a_stride(G) + (size_t)E * G + 3 * G + 16) * 4;
+// bytes of LDS behind a Ctx for E experts on G ranks, with x in rows of `xs`
+__host__ __device__ inline size_t ctx_bytes(int E, int G, int xs) {
+    return (((size_t)E * 8 + 15) & ~(size_t)15) + ((size_t)G * (G | 1) + (size_t)E * xs + G) * 4;
 }
+// row stride of x: odd where that fits into `limit` bytes
+__host__ __device__ inline int x_stride(int E, int G, size_t limit) { return ctx_bytes(E, G, G | 1) <= limit ? G | 1 : G; }
 
 // the arrays of a Ctx laid out from `smem` (16-byte aligned)
-__device__ inline Ctx make_ctx(char* smem, int E, int G) {
+__device__ inline Ctx make_ctx(char* smem, int E, int G, int xs) {
     Ctx c;
-    c.E = E; c.G = G; c.AS = a_stride(G);
+    c.E = E; c.G = G; c.AS = G | 1; c.XS = xs;
     c.pm = reinterpret_cast<u64*>(smem);
     c.A = reinterpret_cast<int*>(smem + (((size_t)E * 8 + 15) & ~(size_t)15));
     c.x = c.A + (size_t)G * c.AS;
-    c.ld = c.x + (size_t)E * G;
-    c.path = c.ld + G;
+    c.t = c.x + (size_t)E * xs;
+    c.n = 0; c.listed = 0ull; c.single = 0; c.ld = 0; c.in = 0ull;
     return c;
 }
 

@@ -412,10 +412,10 @@ __global__ __launch_bounds__(kScoreThreads) void k_score(const int32_t* __restri
 template <bool DRAW>
 __global__ __launch_bounds__(64) void k_score_flow(const int32_t* __restrict__ load, const int32_t* __restrict__ counts,
                                                    const uint8_t* __restrict__ place, int E, int G, int slots,
-                                                   uint32_t seed, int64_t* __restrict__ m_num, int32_t* __restrict__ m_den) {
+                                                   uint32_t seed, int xs, int64_t* __restrict__ m_num, int32_t* __restrict__ m_den) {
     extern __shared__ __attribute__((aligned(16))) char s_flow[];
-    flow::Ctx c = flow::make_ctx(s_flow, E, G);
-    int* s_order = reinterpret_cast<int*>(s_flow + flow::ctx_bytes(E, G));      // [E]
+    flow::Ctx c = flow::make_ctx(s_flow, E, G, xs);
+    int* s_order = reinterpret_cast<int*>(s_flow + flow::ctx_bytes(E, G, xs));      // [E]
     int* s_cnt = s_order + E;                                                   // [E]
     const int l = threadIdx.x;
     const uint32_t cand = blockIdx.x;
@@ -431,7 +431,7 @@ __global__ __launch_bounds__(64) void k_score_flow(const int32_t* __restrict__ l
         }
     }
     __syncthreads();
-    const bool bad = flow::start_on_first_replicas(c, load);
+    const bool bad = flow::compact(c, load);
     long long Pl = 0;
     for (int e = l; e < E; e += 64) Pl += max(load[e], 0);
     Pl += __shfl_xor(Pl, 32, 64); Pl += __shfl_xor(Pl, 16, 64); Pl += __shfl_xor(Pl, 8, 64);
@@ -445,6 +445,7 @@ __global__ __launch_bounds__(64) void k_score_flow(const int32_t* __restrict__ l
             if (a > 1) { num /= a; den /= a; }
             if (num == 0) den = 1;
         } else {
+            flow::start_on_first_replicas(c, load);
             num = flow::optimum_value(c, (int)min(Pl, 0x7fffffffll));
             den = 1;
         }
@@ -626,10 +627,12 @@ int launch_eval_placements(const fine_shape& s, int n, const uint8_t* place, con
                            int32_t* m_den, hipStream_t st) {
     if (n == 0) return FINE_OK;
     if (s.G > kMaxEnumG) {
-        const size_t lds = flow::ctx_bytes(s.E, s.G) + 2 * (size_t)s.E * 4;
+        const size_t rest = 2 * (size_t)s.E * 4;
+        const int xs = flow::x_stride(s.E, s.G, 64 * 1024 - rest);
+        const size_t lds = flow::ctx_bytes(s.E, s.G, xs) + rest;
         if (lds > 64 * 1024) return FINE_UNSUPPORTED;
         hipLaunchKernelGGL(k_score_flow<false>, dim3(n), dim3(64), lds, st, load, (const int32_t*)nullptr, place, s.E, s.G, 0,
-                           0u, m_num, m_den);
+                           0u, xs, m_num, m_den);
         FINE_LAUNCH_CHECK();
         return FINE_OK;
     }
@@ -639,10 +642,12 @@ int launch_eval_placements(const fine_shape& s, int n, const uint8_t* place, con
 int launch_place_search(const fine_shape& s, const int32_t* load, const int32_t* counts, int slots, int n, uint32_t seed,
                         int64_t* m_num, int32_t* m_den, int32_t* best, uint8_t* place, hipStream_t st) {
     if (s.G > kMaxEnumG) {
-        const size_t lds = flow::ctx_bytes(s.E, s.G) + 2 * (size_t)s.E * 4;
+        const size_t rest = 2 * (size_t)s.E * 4;
+        const int xs = flow::x_stride(s.E, s.G, 64 * 1024 - rest);
+        const size_t lds = flow::ctx_bytes(s.E, s.G, xs) + rest;
         if (lds > 64 * 1024) return FINE_UNSUPPORTED;
         hipLaunchKernelGGL(k_score_flow<true>, dim3(n), dim3(64), lds, st, load, counts, (const uint8_t*)nullptr, s.E, s.G,
-                           slots, seed, m_num, m_den);
+                           slots, seed, xs, m_num, m_den);
     } else {
         FINE_TRY(launch_score<true>(s, load, counts, nullptr, n, slots, seed, m_num, m_den, st));
     }

@@ -16,6 +16,9 @@ typedef unsigned long long u64;
 // Only experts with several replicas can move: they are kept in a compact list, in ascending order (256 experts
 // with 320 replicas: at most 64 of them, one per lane).  What a rank needs at every step is in the registers of its
 // lane: its load and the set of ranks that load may come from; A, which is only read where an edge is used, is in LDS.
+// M: a set of ranks, 32 bits where that is enough (the search is a chain of instructions of one wavefront, and 64-bit
+// shifts and selects are several each).
+template <typename M>
 struct Ctx {
     int* x;        // [n][XS] units of listed expert j on every rank
     u64* pm;       // [n] replica masks of the listed experts (before compact(): of all experts)
@@ -27,11 +30,27 @@ struct Ctx {
     u64 listed;    // lane i: which of the experts 64 i .. 64 i + 63 are listed
     int single;    // lane = rank: load of the experts whose only replica is here
     int ld;        // lane = rank: its load
-    u64 in;        // lane = rank: the ranks `a` with a(a, lane) > 0
+    M in;          // lane = rank: the ranks `a` with a(a, lane) > 0
     __device__ int& a(int from, int to) const { return A[to * AS + from]; }
 };
 
 __device__ inline int lane() { return threadIdx.x; }
+__device__ inline u64 readlane_u64(u64 v, int src) {
+    const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)v, src), hi = __builtin_amdgcn_readlane((int)(unsigned)(v >> 32), src);
+    return ((u64)hi << 32) | lo;
+}
+template <typename M>
+__device__ inline int first_of(M m) {
+    if constexpr (sizeof(M) == 4) return __ffs((int)m) - 1;
+    else return __ffsll((long long)m) - 1;
+}
+template <typename M>
+__device__ inline M readlane_set(M v, int src) {
+    if constexpr (sizeof(M) == 4) return (M)__builtin_amdgcn_readlane((int)v, src);
+    else return readlane_u64(v, src);
+}
+template <typename M>
+__device__ inline bool has(M m, int i) { return (m >> i) & (M)1; }
 // LDS accesses of one wavefront are performed in order: only the compiler has to keep the order
 __device__ inline void wave_sync() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
@@ -54,27 +73,23 @@ __device__ inline int wave_incl_scan_i(int v) {
 }
 __device__ inline int wave_sum_i(int v) { return __builtin_amdgcn_readlane(wave_incl_scan_i(v), kW - 1); }
 
-__device__ inline u64 readlane_u64(u64 v, int src) {
-    const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)v, src), hi = __builtin_amdgcn_readlane((int)(unsigned)(v >> 32), src);
-    return ((u64)hi << 32) | lo;
-}
-
 // Move `amount` units of free load from rank a to rank b (listed experts in ascending order; free: replicas above
 // g_cur of j_cur and all of the experts after it; j_cur < 0: everything).  A lane past the last expert reads the last
 // expert's entries (in bounds, no branch, so the LDS reads go out together) and takes no part.  Every rank q that is
 // a replica of a giving expert loses what it could get from a and gains it from b: summed over the givers in
 // lane q's register, then one update of its two entries.
-__device__ inline void move_units(Ctx& c, int a, int b, int amount, int j_cur, int g_cur) {
+template <typename M>
+__device__ inline void move_units(Ctx<M>& c, int a, int b, int amount, int j_cur, int g_cur) {
     int remaining = amount, D = 0;
     const int q = lane();
     for (int base = (j_cur < 0 ? 0 : j_cur); base < c.n && remaining > 0; base += kW) {
         const int j = base + q;                       // >= j_cur: earlier experts are never looked at
         const bool in = j < c.n;
         const int jj = in ? j : c.n - 1;
-        const u64 pm = c.pm[jj];
+        const M pm = (M)c.pm[jj];
         const int xa = c.x[jj * c.XS + a], xb = c.x[jj * c.XS + b];
-        const u64 F = (j == j_cur) ? (pm & ~((2ull << g_cur) - 1ull)) : pm;
-        const int m = (in && ((F >> a) & 1ull) && ((F >> b) & 1ull)) ? xa : 0;
+        const M F = (j == j_cur) ? (pm & ~(((M)2 << g_cur) - (M)1)) : pm;
+        const int m = (in && has(F, a) && has(F, b)) ? xa : 0;
         if (__ballot(m > 0) == 0ull) continue;        // no expert of this chunk links a to b (wave-uniform)
         const int inc = wave_incl_scan_i(m);
         const int t = max(0, min(m, remaining - (inc - m)));
@@ -87,15 +102,15 @@ __device__ inline void move_units(Ctx& c, int a, int b, int amount, int j_cur, i
             const int src = __ffsll((long long)givers) - 1;
             givers &= givers - 1;
             const int ts = __builtin_amdgcn_readlane(t, src);
-            if ((readlane_u64(F, src) >> q) & 1ull) D += ts;
+            if (has(readlane_set(F, src), q & (8 * (int)sizeof(M) - 1))) D += ts;
         }
         remaining -= min(remaining, __builtin_amdgcn_readlane(inc, kW - 1));
     }
-    if (D > 0) {                                      // (only ranks have bits in F)
+    if (D > 0 && q < c.G) {
         const int va = q != a ? c.a(a, q) - D : 0, vb = q != b ? c.a(b, q) + D : 0;
         if (q != a) c.a(a, q) = va;
         if (q != b) c.a(b, q) = vb;
-        c.in = (c.in & ~(1ull << a) & ~(1ull << b)) | (u64)(va > 0) << a | (u64)(vb > 0) << b;
+        c.in = (c.in & ~((M)1 << a) & ~((M)1 << b)) | (M)(va > 0) << a | (M)(vb > 0) << b;
     }
     c.ld += q == b ? amount : q == a ? -amount : 0;
     wave_sync();
@@ -105,19 +120,20 @@ __device__ inline void move_units(Ctx& c, int a, int b, int amount, int j_cur, i
 // holds a rank of `want` (a per-lane predicate, lane = rank).  Returns the chosen rank
 // (lowest of that level) or -1; *visited_out = every rank reached; *parent_out (lane = rank) = where the search came
 // from; *cap_out = the smallest capacity on the way.
-__device__ inline int bfs(const Ctx& c, int src, bool want, u64* visited_out, int* parent_out, int* cap_out) {
+template <typename M>
+__device__ inline int bfs(const Ctx<M>& c, int src, bool want, M* visited_out, int* parent_out, int* cap_out) {
     const int b = lane();
-    u64 visited = 1ull << src, frontier = visited;
+    M visited = (M)1 << src, frontier = visited;
     int parent = -1, target = -1;
     while (true) {
-        const u64 hit = c.in & frontier;
-        const bool fresh = hit && !((visited >> b) & 1ull);      // (lanes that are no ranks have nothing in `in`)
-        if (fresh) parent = __ffsll((long long)hit) - 1;
-        const u64 next = __ballot(fresh);
-        if (next == 0ull) break;
+        const M hit = c.in & frontier;                           // (lanes that are no ranks have nothing in `in`)
+        const bool fresh = hit != 0 && parent < 0 && b != src;
+        if (fresh) parent = first_of(hit);
+        const M next = (M)__ballot(fresh);
+        if (next == 0) break;
         visited |= next;
-        const u64 good = __ballot(fresh && want);
-        if (good) { target = __ffsll((long long)good) - 1; break; }
+        const M good = (M)__ballot(fresh && want);
+        if (good) { target = first_of(good); break; }
         frontier = next;
     }
     *visited_out = visited;
@@ -136,7 +152,8 @@ __device__ inline int bfs(const Ctx& c, int src, bool want, u64* visited_out, in
 
 // Moves `amount` units along the way found by bfs, last edge first (an edge's capacity depends on the units on its
 // source only, and the ranks of a shortest way are distinct: the order of the edges does not matter).
-__device__ inline void push_path(Ctx& c, int src, int target, int parent, int amount, int j_cur, int g_cur) {
+template <typename M>
+__device__ inline void push_path(Ctx<M>& c, int src, int target, int parent, int amount, int j_cur, int g_cur) {
     int cur = target;
     while (cur != src) {
         const int p = __builtin_amdgcn_readlane(parent, cur);
@@ -148,7 +165,8 @@ __device__ inline void push_path(Ctx& c, int src, int target, int parent, int am
 // From the replica masks of all experts in c.pm: the list of those with several replicas (their masks move to the
 // front of c.pm), and the loads of the others on their only rank.  Returns (to every lane) whether some expert with
 // load has no replica.
-__device__ inline bool compact(Ctx& c, const int32_t* __restrict__ load) {
+template <typename M>
+__device__ inline bool compact(Ctx<M>& c, const int32_t* __restrict__ load) {
     const int l = lane();
     int bad = 0, n = 0;
     c.listed = 0ull;
@@ -174,18 +192,20 @@ __device__ inline bool compact(Ctx& c, const int32_t* __restrict__ load) {
 }
 
 // the rank loads from c.t and the sets of sources from A
-__device__ inline void load_registers(Ctx& c) {
+template <typename M>
+__device__ inline void load_registers(Ctx<M>& c) {
     const int l = lane();
     wave_sync();
     c.ld = l < c.G ? c.t[l] : 0;
-    c.in = 0ull;
+    c.in = 0;
     if (l < c.G)
-        for (int a = 0; a < c.G; ++a) c.in |= (u64)(c.A[l * c.AS + a] > 0) << a;
+        for (int a = 0; a < c.G; ++a) c.in |= (M)(c.A[l * c.AS + a] > 0) << a;
 }
 
 // Everything on each expert's first replica: fills x, A and the rank loads from the list and the expert loads
 // (negative reads as 0) times `scale`.
-__device__ inline void start_on_first_replicas(Ctx& c, const int32_t* __restrict__ load, int scale = 1) {
+template <typename M>
+__device__ inline void start_on_first_replicas(Ctx<M>& c, const int32_t* __restrict__ load, int scale = 1) {
     const int l = lane();
     for (int i = l; i < c.G * c.AS; i += kW) c.A[i] = 0;
     for (int i = l; i < c.n * c.XS; i += kW) c.x[i] = 0;
@@ -216,27 +236,28 @@ __device__ inline void start_on_first_replicas(Ctx& c, const int32_t* __restrict
 // If the search finds none, the reached set S is closed (no expert with load in S has a replica
 // outside S), so Eq. 3 gives the lower bound ceil(load(S)/|S|) > M; M jumps to it.  M only ever moves
 // to lower bounds of the optimum and the loop ends with a feasible flow, hence M = M*.
-__device__ inline int optimum_value(Ctx& c, int P) {
+template <typename M>
+__device__ inline int optimum_value(Ctx<M>& c, int P) {
     const int l = lane();
-    int M = (P + c.G - 1) / c.G;
+    int best = (P + c.G - 1) / c.G;
     while (true) {
         const int mine = c.ld;
-        const u64 over = __ballot(l < c.G && mine > M);
+        const u64 over = __ballot(l < c.G && mine > best);
         if (over == 0ull) break;
         const int a = __ffsll((long long)over) - 1;
-        u64 visited; int parent, cap;
-        const int r = bfs(c, a, (l < c.G) && (mine < M), &visited, &parent, &cap);
+        M visited; int parent, cap;
+        const int r = bfs(c, a, (l < c.G) && (mine < best), &visited, &parent, &cap);
         if (r < 0) {
-            const bool in = (l < c.G) && ((visited >> l) & 1ull);
+            const bool in = (l < c.G) && has(visited, l & (8 * (int)sizeof(M) - 1));
             const int tot = wave_sum_i(in ? mine : 0);
             const int cnt = __popcll(visited);
-            M = (tot + cnt - 1) / cnt;
+            best = (tot + cnt - 1) / cnt;
             continue;
         }
-        const int amount = min(min(__builtin_amdgcn_readlane(mine, a) - M, M - __builtin_amdgcn_readlane(mine, r)), cap);
+        const int amount = min(min(__builtin_amdgcn_readlane(mine, a) - best, best - __builtin_amdgcn_readlane(mine, r)), cap);
         push_path(c, a, r, parent, amount, -1, 0);
     }
-    return M;
+    return best;
 }
 
 // m of Eq. 3, the maximum density over sets of ranks, as a fraction num / den with den <= G (not
@@ -248,7 +269,8 @@ __device__ inline int optimum_value(Ctx& c, int P) {
 // expert has none there, so the units in S are den * load(S), no rank of S is below capacity and one
 // is above: load(S) / |S| > lambda.  lambda moves there and the flow starts again in the new scale.
 // When no rank is above capacity the loads fit under lambda, so m <= lambda, hence m = lambda.
-__device__ inline void exact_density(Ctx& c, const int32_t* __restrict__ load, int P, int* num_out, int* den_out) {
+template <typename M>
+__device__ inline void exact_density(Ctx<M>& c, const int32_t* __restrict__ load, int P, int* num_out, int* den_out) {
     const int l = lane();
     int num = P, den = c.G;
     while (true) {
@@ -259,10 +281,10 @@ __device__ inline void exact_density(Ctx& c, const int32_t* __restrict__ load, i
             const u64 over = __ballot(l < c.G && mine > num);
             if (over == 0ull) break;
             const int a = __ffsll((long long)over) - 1;
-            u64 visited; int parent, cap;
+            M visited; int parent, cap;
             const int r = bfs(c, a, (l < c.G) && (mine < num), &visited, &parent, &cap);
             if (r < 0) {
-                const bool in = (l < c.G) && ((visited >> l) & 1ull);
+                const bool in = (l < c.G) && has(visited, l & (8 * (int)sizeof(M) - 1));
                 num = wave_sum_i(in ? mine : 0) / den;
                 den = __popcll(visited);
                 moved = true;
@@ -285,14 +307,15 @@ __host__ __device__ inline size_t ctx_bytes(int E, int G, int xs) {
 __host__ __device__ inline int x_stride(int E, int G, size_t limit) { return ctx_bytes(E, G, G | 1) <= limit ? G | 1 : G; }
 
 // the arrays of a Ctx laid out from `smem` (16-byte aligned)
-__device__ inline Ctx make_ctx(char* smem, int E, int G, int xs) {
-    Ctx c;
+template <typename M>
+__device__ inline Ctx<M> make_ctx(char* smem, int E, int G, int xs) {
+    Ctx<M> c;
     c.E = E; c.G = G; c.AS = G | 1; c.XS = xs;
     c.pm = reinterpret_cast<u64*>(smem);
     c.A = reinterpret_cast<int*>(smem + (((size_t)E * 8 + 15) & ~(size_t)15));
     c.x = c.A + (size_t)G * c.AS;
     c.t = c.x + (size_t)E * xs;
-    c.n = 0; c.listed = 0ull; c.single = 0; c.ld = 0; c.in = 0ull;
+    c.n = 0; c.listed = 0ull; c.single = 0; c.ld = 0; c.in = 0;
     return c;
 }
 

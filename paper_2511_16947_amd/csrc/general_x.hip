@@ -33,11 +33,12 @@ using namespace flow;
 // Take `amount` units of listed expert j from the replicas in `from` (a subset of its later
 // replicas `later`, lowest first) to rank g.  Variable (j,g) itself is not free, so only
 // the rows of the source ranks change in A.
-__device__ void pull_expert(Ctx& c, int j, int g, u64 later, u64 from, int amount) {
+template <typename M>
+__device__ inline void pull_expert(Ctx<M>& c, int j, int g, M later, M from, int amount) {
     // lane q = source rank q: what the lower sources leave of `amount` is a prefix sum away
     const int q = lane();
     int* row = c.x + j * c.XS;
-    const int m = (from >> q) & 1ull ? row[q] : 0;
+    const int m = q < c.G && has(from, q & (8 * (int)sizeof(M) - 1)) ? row[q] : 0;
     const int inc = wave_incl_scan_i(m);
     const int t = max(0, min(m, amount - (inc - m)));
     if (t > 0) {
@@ -45,17 +46,18 @@ __device__ void pull_expert(Ctx& c, int j, int g, u64 later, u64 from, int amoun
         c.ld -= t;
     }
     // row s of A loses what source s gave towards every other later replica: lane q = column q
-    u64 givers = __ballot(t > 0);
+    const bool is_later = q < c.G && has(later, q & (8 * (int)sizeof(M) - 1));
+    M givers = (M)__ballot(t > 0);
     int total = 0;
     while (givers) {
-        const int s = __ffsll((long long)givers) - 1;
+        const int s = first_of(givers);
         givers &= givers - 1;
         const int ts = __builtin_amdgcn_readlane(t, s);
         total += ts;
-        if (q != s && ((later >> q) & 1ull)) {
+        if (q != s && is_later) {
             const int v = c.a(s, q) - ts;
             c.a(s, q) = v;
-            c.in = (c.in & ~(1ull << s)) | (u64)(v > 0) << s;
+            c.in = (c.in & ~((M)1 << s)) | (M)(v > 0) << s;
         }
     }
     if (q == g) {                                      // g is not among the later replicas: nobody else writes these
@@ -74,7 +76,8 @@ __device__ void pull_expert(Ctx& c, int j, int g, u64 later, u64 from, int amoun
 // function returns.  The rows of all experts are first copied into x, in wide batches of loads (a lane that walks
 // its expert's row in global memory waits for every entry: 32 round trips for an expert on all of 32 ranks), then
 // the listed ones are scaled and moved to their places in the list.
-__device__ void start_from_previous(Ctx& c, const int32_t* __restrict__ load, const int32_t* prev) {
+template <typename M>
+__device__ inline void start_from_previous(Ctx<M>& c, const int32_t* __restrict__ load, const int32_t* prev) {
     const int l = lane();
     for (int i = l; i < c.G * c.AS; i += kW) c.A[i] = 0;
     if (l < c.G) c.t[l] = c.single;
@@ -153,11 +156,12 @@ __device__ inline u64 replica_mask(const uint8_t* __restrict__ place, int e, int
     return m;
 }
 
+template <typename M>
 __global__ __launch_bounds__(64) void k_general_x(const uint8_t* __restrict__ place, const int32_t* __restrict__ load,
                                                   const int32_t* prev, int E, int G, int xs, int P, int32_t* x_out,
                                                   int32_t* __restrict__ max_load) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    Ctx c = make_ctx(smem, E, G, xs);
+    Ctx<M> c = make_ctx<M>(smem, E, G, xs);
     const int l = lane();
 
     // ---- set-up: masks, the list, x, A, rank loads --------------------
@@ -172,49 +176,48 @@ __global__ __launch_bounds__(64) void k_general_x(const uint8_t* __restrict__ pl
     else start_on_first_replicas(c, load);
 
     // ---- phase 1: the optimum value ---------------------------------------------------------
-    const int M = optimum_value(c, P);
-    if (l == 0) max_load[0] = M;
+    const int cap_rank = optimum_value(c, P);      // M*
+    if (l == 0) max_load[0] = cap_rank;
 
     // ---- phase 2: the lexicographically greatest optimum ------------------------------------
     for (int j = 0; j < c.n; ++j) {
-        u64 todo = c.pm[j];
-        u64 F = todo;                       // free replicas of j (including the one being removed next)
+        M todo = (M)c.pm[j];
+        M F = todo;                         // free replicas of j (including the one being removed next)
         const int* row = c.x + j * c.XS;
         while (todo) {
-            const int g = __ffsll((long long)todo) - 1;
+            const int g = first_of(todo);
             todo &= todo - 1;
             // variable (j,g) leaves the free set: its units can no longer move to the other free
             // replicas, nor theirs to g (lane q updates the two entries that involve replica q)
-            F &= ~(1ull << g);
-            const u64 later = F;
-            if (later == 0ull) continue;        // the last replica: nothing left to take units from
-            const bool is_later = (later >> l) & 1ull;
+            F &= ~((M)1 << g);
+            const M later = F;
+            if (later == 0) continue;        // the last replica: nothing left to take units from
+            const bool is_later = l < G && has(later, l & (8 * (int)sizeof(M) - 1));
             int back = 0;
             if (is_later) {
                 const int to_me = c.a(g, l) - row[g];
                 back = c.a(l, g) - row[l];
                 c.a(g, l) = to_me;
                 c.a(l, g) = back;
-                c.in = (c.in & ~(1ull << g)) | (u64)(to_me > 0) << g;
+                c.in = (c.in & ~((M)1 << g)) | (M)(to_me > 0) << g;
             }
-            const u64 still = __ballot(back > 0);
+            const M still = (M)__ballot(back > 0);
             if (l == g) c.in = (c.in & ~later) | still;
             wave_sync();
             while (true) {
                 const int avail = is_later ? row[l] : 0;
-                const u64 has = __ballot(avail > 0);
-                if (has == 0ull) break;
+                if (__ballot(avail > 0) == 0ull) break;
                 const int total_avail = wave_sum_i(avail);
-                const int room = M - __builtin_amdgcn_readlane(c.ld, g);
+                const int room = cap_rank - __builtin_amdgcn_readlane(c.ld, g);
                 if (room > 0) {
                     pull_expert(c, j, g, later, later, min(room, total_avail));
                     continue;
                 }
-                const bool want = l < G && (c.ld < M || ((has >> l) & 1ull));
-                u64 visited; int parent, cap;
+                const bool want = l < G && (c.ld < cap_rank || avail > 0);
+                M visited; int parent, cap;
                 const int r = bfs(c, g, want, &visited, &parent, &cap);
                 if (r < 0) break;
-                const int room_r = M - __builtin_amdgcn_readlane(c.ld, r);
+                const int room_r = cap_rank - __builtin_amdgcn_readlane(c.ld, r);
                 if (room_r > 0) {
                     // the path may itself carry units of j between its later replicas, so
                     // the units are taken from whichever later replicas hold them afterwards
@@ -223,7 +226,7 @@ __global__ __launch_bounds__(64) void k_general_x(const uint8_t* __restrict__ pl
                     pull_expert(c, j, g, later, later, amount);
                 } else {
                     const int amount = min(cap, __builtin_amdgcn_readlane(avail, r));
-                    pull_expert(c, j, g, later, 1ull << r, amount);
+                    pull_expert(c, j, g, later, (M)1 << r, amount);
                     push_path(c, g, r, parent, amount, j, g);
                 }
             }
@@ -255,9 +258,10 @@ int launch_general_x(const fine_shape& s, const uint8_t* place, const int32_t* l
     const int xs = flow::x_stride(s.E, s.G, 160 * 1024);
     const size_t lds = flow::ctx_bytes(s.E, s.G, xs);
     if (lds > 160 * 1024) return FINE_UNSUPPORTED;
-    static std::atomic<uint64_t> lds_set{0};
-    FINE_TRY(raise_lds_limit((const void*)k_general_x, 160 * 1024, lds_set));
-    hipLaunchKernelGGL(k_general_x, dim3(1), dim3(64), lds, st, place, load, x_prev, s.E, s.G, xs, s.T * s.K, x_eg, max_load);
+    static std::atomic<uint64_t> lds_set32{0}, lds_set64{0};
+    auto k = s.G <= 32 ? k_general_x<uint32_t> : k_general_x<u64>;
+    FINE_TRY(raise_lds_limit((const void*)k, 160 * 1024, s.G <= 32 ? lds_set32 : lds_set64));
+    hipLaunchKernelGGL(k, dim3(1), dim3(64), lds, st, place, load, x_prev, s.E, s.G, xs, s.T * s.K, x_eg, max_load);
     FINE_LAUNCH_CHECK();
     return FINE_OK;
 }

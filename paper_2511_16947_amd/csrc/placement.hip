@@ -409,12 +409,12 @@ __global__ __launch_bounds__(kScoreThreads) void k_score(const int32_t* __restri
 // fraction.  Loads summing to 2^31 / G or more do not fit the scaled flow: then M* = ceil(m) is
 // written as M* / 1.
 // ---------------------------------------------------------------------------
-template <bool DRAW>
+template <bool DRAW, typename M>
 __global__ __launch_bounds__(64) void k_score_flow(const int32_t* __restrict__ load, const int32_t* __restrict__ counts,
                                                    const uint8_t* __restrict__ place, int E, int G, int slots,
                                                    uint32_t seed, int xs, int64_t* __restrict__ m_num, int32_t* __restrict__ m_den) {
     extern __shared__ __attribute__((aligned(16))) char s_flow[];
-    flow::Ctx c = flow::make_ctx(s_flow, E, G, xs);
+    auto c = flow::make_ctx<M>(s_flow, E, G, xs);
     int* s_order = reinterpret_cast<int*>(s_flow + flow::ctx_bytes(E, G, xs));      // [E]
     int* s_cnt = s_order + E;                                                   // [E]
     const int l = threadIdx.x;
@@ -631,7 +631,8 @@ int launch_eval_placements(const fine_shape& s, int n, const uint8_t* place, con
         const int xs = flow::x_stride(s.E, s.G, 64 * 1024 - rest);
         const size_t lds = flow::ctx_bytes(s.E, s.G, xs) + rest;
         if (lds > 64 * 1024) return FINE_UNSUPPORTED;
-        hipLaunchKernelGGL(k_score_flow<false>, dim3(n), dim3(64), lds, st, load, (const int32_t*)nullptr, place, s.E, s.G, 0,
+        auto k = s.G <= 32 ? k_score_flow<false, uint32_t> : k_score_flow<false, u64>;
+        hipLaunchKernelGGL(k, dim3(n), dim3(64), lds, st, load, (const int32_t*)nullptr, place, s.E, s.G, 0,
                            0u, xs, m_num, m_den);
         FINE_LAUNCH_CHECK();
         return FINE_OK;
@@ -646,7 +647,8 @@ int launch_place_search(const fine_shape& s, const int32_t* load, const int32_t*
         const int xs = flow::x_stride(s.E, s.G, 64 * 1024 - rest);
         const size_t lds = flow::ctx_bytes(s.E, s.G, xs) + rest;
         if (lds > 64 * 1024) return FINE_UNSUPPORTED;
-        hipLaunchKernelGGL(k_score_flow<true>, dim3(n), dim3(64), lds, st, load, counts, (const uint8_t*)nullptr, s.E, s.G,
+        auto k = s.G <= 32 ? k_score_flow<true, uint32_t> : k_score_flow<true, u64>;
+        hipLaunchKernelGGL(k, dim3(n), dim3(64), lds, st, load, counts, (const uint8_t*)nullptr, s.E, s.G,
                            slots, seed, xs, m_num, m_den);
     } else {
         FINE_TRY(launch_score<true>(s, load, counts, nullptr, n, slots, seed, m_num, m_den, st));

@@ -422,20 +422,22 @@ int launch_backward(const fine_shape& s, int rank_lo, int rank_hi, const void* d
     const double P = (double)s.T * s.K;
     const double seg_rows = (P / s.G) / ((double)s.E / s.G + 1.0);
     int tile = (s.flags & FINE_FLAG_TILE_MASK) >> FINE_FLAG_TILE_SHIFT;
-    if (tile == 0) tile = seg_rows >= 384.0 ? 3 : (seg_rows >= 96.0 ? 2 : 1);
+    // Short segments: 128-row tiles on 4 waves also where most of their rows are empty.  (64-row tiles, dH + dXp against
+    // 128 rows: 5 rows per segment 126 : 101 us, 15 rows 201 : 170, 60 rows 380 : 317, 57 rows on wide experts 192 : 162.)
+    if (tile != 3) tile = tile == 0 && seg_rows >= 384.0 ? 3 : 2;
 #define FINE_DGRAD(WAM, WAN, WMM, WNN)                                                                        \
     FINE_TRY((run_dgrad<WAM, WAN, WMM, WNN>(s, rank_lo, rank_hi, dy, act, (const uint16_t*)wg, (const uint16_t*)wu, \
                                             (const uint16_t*)wd, seg_off, dact, h_out, dxp, tiles, count, L.max_tiles, \
                                             on(2), on(3), st)))
     if (on(2) || on(3)) {
         if (tile == 3) FINE_DGRAD(2, 4, 4, 2);
-        else if (tile == 2) FINE_DGRAD(2, 2, 2, 4);
-        else FINE_DGRAD(1, 4, 2, 2);
+        else FINE_DGRAD(2, 2, 2, 4);
     }
 #undef FINE_DGRAD
-    // weight-gradient tiles span the weight matrices, not the segments
+    // Weight-gradient tiles span the weight matrices, not the segments: 256 x 256 on 8 waves wherever they fit, however
+    // few rows an expert has (4 waves, 128 x 128: 5 rows 697 : 419 us, 43 rows 1157 : 458, 60 rows 1347 : 504).
     if (on(4)) {
-        if (s.d >= 256 && s.f >= 256 && tile != 1)
+        if (s.d >= 256 && s.f >= 256)
             FINE_TRY((run_wgrad<2, 4, 4, 2>(s, rank_lo, rank_hi, (const uint16_t*)x_perm, dy, dact, h_in, seg_off, d_wg, d_wu, d_wd, accumulate, st)));
         else
             FINE_TRY((run_wgrad<2, 2, 2, 2>(s, rank_lo, rank_hi, (const uint16_t*)x_perm, dy, dact, h_in, seg_off, d_wg, d_wu, d_wd, accumulate, st)));

@@ -46,14 +46,16 @@ template <int EPI, int V, int NP>
 __global__ __launch_bounds__(256, 3) void k_ffn_f32(const float* __restrict__ A, const float* __restrict__ B0,
                                                  const float* __restrict__ B1, int Kd, int N, float* __restrict__ C,
                                                  float* __restrict__ act, const TileEntry* __restrict__ tiles,
-                                                 const int32_t* __restrict__ count) {
+                                                 const int32_t* __restrict__ count, const int32_t* __restrict__ seg, int E) {
     static_assert(EPI == 1 || NP == 2, "gate and up panel");
     constexpr int BNC = EPI == 0 ? 64 : 64 * NP;         // output columns per block
     constexpr int kBuf = kABytes + NP * kPanelBytes;      // one buffer: A and the panels of B
     __shared__ __attribute__((aligned(16))) char smem[2 * kBuf];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int wm = wave >> 1, wn = wave & 1, r = lane & 31, h = lane >> 5;
-    const int ntn = (N + BNC - 1) / BNC, ntm = *count, total = ntm * ntn;
+    RankTiles rank;      // seg != NULL: one rank, whose work list every wave makes for itself
+    if (seg != nullptr) rank.init(seg, E, kBM);
+    const int ntn = (N + BNC - 1) / BNC, ntm = seg != nullptr ? rank.count : *count, total = ntm * ntn;
     const int nk = (Kd + kBK - 1) / kBK;
 
     // DMA side.  A: an instruction covers AROWS rows; lane -> (row, k of its first element) with the chunk
@@ -69,7 +71,7 @@ __global__ __launch_bounds__(256, 3) void k_ffn_f32(const float* __restrict__ A,
     for (int work = (int)((long long)total * xcd / 8) + (blockIdx.x >> 3); work < end; work += gridDim.x >> 3) {
         int tm, tn;
         tile_of_work(work, ntm, ntn, tm, tn);
-        const TileEntry te = tiles[tm];
+        const TileEntry te = seg != nullptr ? rank.get(tm, kBM) : tiles[tm];
         const int n0 = tn * BNC;
         const float* Bp[2];
         Bp[0] = B0 + (size_t)te.expert * Kd * N;
@@ -183,17 +185,19 @@ int launch_ffn_f32(const fine_shape& s, int rank_lo, int rank_hi, const void* x_
     auto* h = reinterpret_cast<float*>(ws + L.h);
     if ((s.flags & FINE_FLAG_ACT_SAVE_H) && act_save != nullptr)      // H behind the saved pre-activations
         h = static_cast<float*>(act_save) + (size_t)s.T * s.K * 2 * s.f;
-    FINE_TRY(launch_tile_map(s, seg_off, rank_lo, rank_hi, kBM, tiles, count, L.max_tiles, st));
+    const int32_t* seg = nullptr;
+    if (rank_hi - rank_lo == 1 && s.E <= kRankMapExperts) seg = seg_off + (size_t)rank_lo * (s.E + 1);
+    else FINE_TRY(launch_tile_map(s, seg_off, rank_lo, rank_hi, kBM, tiles, count, L.max_tiles, st));
     // three blocks per CU; no more blocks than there can be tiles
     const size_t rows_tiles = (size_t)s.T * s.K / kBM + (size_t)s.E * (rank_hi - rank_lo);
     auto grid = [&](int n) { return (unsigned)std::min<size_t>(768, align_up(rows_tiles * cdiv(n, 64), 8)); };
 #define FINE_F32(V)                                                                                              \
     do {                                                                                                         \
         hipLaunchKernelGGL((k_ffn_f32<0, V, 2>), dim3(grid(s.f)), dim3(256), 0, st, (const float*)x_perm, (const float*)wg, \
-                           (const float*)wu, s.d, s.f, h, (float*)act_save, tiles, count);                       \
+                           (const float*)wu, s.d, s.f, h, (float*)act_save, tiles, count, seg, s.E);                       \
         FINE_LAUNCH_CHECK();                                                                                     \
         hipLaunchKernelGGL((k_ffn_f32<1, V, 1>), dim3(grid(s.d)), dim3(256), 0, st, (const float*)h, (const float*)wd, \
-                           (const float*)nullptr, s.f, s.d, (float*)y_perm, (float*)nullptr, tiles, count);      \
+                           (const float*)nullptr, s.f, s.d, (float*)y_perm, (float*)nullptr, tiles, count, seg, s.E);      \
         FINE_LAUNCH_CHECK();                                                                                     \
     } while (0)
     if (s.d % 4 == 0 && s.f % 4 == 0) FINE_F32(4);

@@ -177,18 +177,21 @@ __global__ __launch_bounds__(256, 2) void k_ffn_stream(const uint16_t* __restric
                                                        const uint16_t* __restrict__ B1, int Kd, int N,
                                                        uint16_t* __restrict__ C, uint16_t* __restrict__ act,
                                                        const TileEntry* __restrict__ tiles,
-                                                       const int32_t* __restrict__ count) {
+                                                       const int32_t* __restrict__ count,
+                                                       const int32_t* __restrict__ seg, int E) {
     constexpr int BNC = EPI == 0 ? 64 : 128;      // output columns per block
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int ntn = (N + BNC - 1) / BNC, ntm = *count, total = ntm * ntn;
+    RankTiles rank;      // seg != NULL: one rank, whose work list every wave makes for itself
+    if (seg != nullptr) rank.init(seg, E, kStreamRows);
+    const int ntn = (N + BNC - 1) / BNC, ntm = seg != nullptr ? rank.count : *count, total = ntm * ntn;
     const int nk = Kd / BK, kb = nk * wave / 4, kn = nk * (wave + 1) / 4 - kb;
     // an eighth of the tiles per XCD (blocks are dealt to them in turn), so that a last incomplete round lies on all
     const int xcd = blockIdx.x & 7, end = (int)((long long)total * (xcd + 1) / 8);
     for (int work = (int)((long long)total * xcd / 8) + (blockIdx.x >> 3); work < end; work += gridDim.x >> 3) {
         int tm, tn;
         tile_of_work(work, ntm, ntn, tm, tn);
-        const TileEntry te = tiles[tm];
+        const TileEntry te = seg != nullptr ? rank.get(tm, kStreamRows) : tiles[tm];
         const int n0 = tn * BNC;
         const size_t w_at = (size_t)te.expert * Kd * N + (size_t)kb * BK * N + n0;
         const uint16_t* W0 = B0 + w_at;
@@ -265,7 +268,9 @@ int launch_ffn_stream(const fine_shape& s, int rank_lo, int rank_hi, const void*
                       const void* wd, const int32_t* seg_off, void* h_buf, void* y_perm, void* act_save, TileEntry* tiles,
                       int32_t* count, int max_tiles, bool gemm1, bool gemm2, hipStream_t st) {
     auto* h = reinterpret_cast<uint16_t*>(h_buf);
-    FINE_TRY(launch_tile_map(s, seg_off, rank_lo, rank_hi, kStreamRows, tiles, count, max_tiles, st));
+    const int32_t* seg = nullptr;
+    if (rank_hi - rank_lo == 1 && s.E <= kRankMapExperts) seg = seg_off + (size_t)rank_lo * (s.E + 1);
+    else FINE_TRY(launch_tile_map(s, seg_off, rank_lo, rank_hi, kStreamRows, tiles, count, max_tiles, st));
     const size_t lds = 4 * kStreamWave;
     static std::atomic<uint64_t> lds_set0{0}, lds_set1{0};
     FINE_TRY(raise_lds_limit((const void*)k_ffn_stream<0>, (int)lds, lds_set0));
@@ -273,12 +278,12 @@ int launch_ffn_stream(const fine_shape& s, int rank_lo, int rank_hi, const void*
     const unsigned grid = 512;      // two blocks per CU
     if (gemm1) {
         hipLaunchKernelGGL(k_ffn_stream<0>, dim3(grid), dim3(256), lds, st, (const uint16_t*)x_perm, (const uint16_t*)wg,
-                           (const uint16_t*)wu, s.d, s.f, h, (uint16_t*)act_save, tiles, count);
+                           (const uint16_t*)wu, s.d, s.f, h, (uint16_t*)act_save, tiles, count, seg, s.E);
         FINE_LAUNCH_CHECK();
     }
     if (gemm2) {
         hipLaunchKernelGGL(k_ffn_stream<1>, dim3(grid), dim3(256), lds, st, (const uint16_t*)h, (const uint16_t*)wd,
-                           (const uint16_t*)nullptr, s.f, s.d, (uint16_t*)y_perm, (uint16_t*)nullptr, tiles, count);
+                           (const uint16_t*)nullptr, s.f, s.d, (uint16_t*)y_perm, (uint16_t*)nullptr, tiles, count, seg, s.E);
         FINE_LAUNCH_CHECK();
     }
     return FINE_OK;

@@ -18,7 +18,7 @@
 
 #include <type_traits>
 
-#include "common.h"
+#include "flow_wave.h"
 
 namespace fine {
 namespace mfma {
@@ -418,6 +418,49 @@ __device__ inline void tile_of_work(int work, int ntm, int ntn, int& tm, int& tn
     tn = cg * pw + rr / h;
     tm = b * h0 + min(b, extra) + rr % h;
 }
+
+// The work list of ONE rank (see k_tile_map) in the registers of every wave, for kernels that need nothing else of
+// the count block: no list in memory and no launch in front of the rank's GEMMs (2-3 us each, and a call per rank).
+// Lane l has the experts l, l + 64, ...: first row, rows and the tiles up to and including theirs; a lookup is a
+// ballot and three lane reads per 64 experts.
+constexpr int kRankMapExperts = 256;
+struct RankTiles {
+    static constexpr int N = kRankMapExperts / 64;
+    int r0[N], rows[N], upto[N], count;
+
+    // seg: the rank's row of seg_off [E+1]; all 64 lanes active
+    __device__ inline void init(const int32_t* __restrict__ seg, int E, int BM) {
+        const int lane = threadIdx.x & 63;
+#pragma unroll
+        for (int c = 0; c < N; ++c) {      // (no branch around the loads: past the last expert its end is read again)
+            const int e = 64 * c + lane;
+            r0[c] = seg[min(e, E)];
+            rows[c] = max(seg[min(e + 1, E)] - r0[c], 0);
+        }
+        count = 0;
+#pragma unroll
+        for (int c = 0; c < N; ++c) {
+            upto[c] = count + flow::wave_incl_scan_i((rows[c] + BM - 1) / BM);
+            count = __builtin_amdgcn_readlane(upto[c], 63);
+        }
+    }
+    __device__ inline TileEntry get(int tm, int BM) const {
+        TileEntry te{0, 0, 0, 0};
+        int done = 0;
+#pragma unroll
+        for (int c = 0; c < N; ++c) {
+            const unsigned long long m = __ballot(upto[c] > tm);
+            if (m != 0ull && done == 0) {
+                const int l = __ffsll((long long)m) - 1;
+                const int n = __builtin_amdgcn_readlane(rows[c], l), nt = (n + BM - 1) / BM;
+                const int i = tm - (__builtin_amdgcn_readlane(upto[c], l) - nt);
+                te = TileEntry{64 * c + l, __builtin_amdgcn_readlane(r0[c], l) + i * BM, min(BM, n - i * BM), nt == 1};
+                done = 1;
+            }
+        }
+        return te;
+    }
+};
 
 // Handing out the units of a persistent launch (whole tiles, then parts of tiles) to its blocks.
 // The fixed order gives block b the units b, b + nblk, ...  With at most two rounds of units that

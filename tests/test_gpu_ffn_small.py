@@ -20,8 +20,10 @@ def _reference(x, wg, wu, wd):
     (64, 64, [[1, 0, 31], [0, 0, 2]]),                     # one k-step: three of the four waves have none
     (128, 192, [[32, 33, 0], [0, 63, 64]]),                # half a column tile at the end; tiles of 32 and 33 rows
     (192, 320, [[65, 0, 1], [0, 0, 127], [0, 0, 64]]),     # a run over three ranks: 192 rows of expert 2
+    (64, 64, [[1] * 190 + [0] * 65 + [70], [2] * 256]),    # 256 experts: the most whose work list a wave keeps in registers
+    (64, 64, [[1] * 190 + [0] * 66 + [70], [2] * 257]),
     (576, 832, [[0, 130, 0], [5, 0, 0], [0, 0, 0]]),       # odd numbers of k-steps; empty ranks
-])
+], ids=lambda v: None if isinstance(v, int) else "%dx%d" % (len(v), len(v[0])))
 def test_small_launch_every_element(d, f, seg, tile):
     G, E = len(seg), len(seg[0])
     P = sum(map(sum, seg))

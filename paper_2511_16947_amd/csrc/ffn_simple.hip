@@ -13,7 +13,7 @@ namespace {
 // (64 tokens on 8 experts and 8 ranks: 8 tiles instead of 15).  One rank's segments are all of different experts.
 // Thread t takes C consecutive segments; everything it needs of the others are two running maxima (the index of the
 // last non-empty segment; the first row of the last run, rows ascending) and a sum of tile counts: three block
-// scans whatever the number of segments (8192 segments: 60 -> 8 us against a scan per 256 segments).
+// scans whatever the number of segments (8192 segments: 60 -> 31 us against a scan per 256 segments; 1024: 7 us).
 constexpr int kMapThreads = 1024;
 
 // zeroes the counters that the GEMM launches of a call use
@@ -36,8 +36,14 @@ __device__ inline int block_excl_scan(int v, int ident, int* s_w, Op op) {
     }
     if (lane == 63) s_w[wave] = inc;
     __syncthreads();
-    int base = ident;
-    for (int w = 0; w < wave; ++w) base = op(base, s_w[w]);
+    // what the waves before this one have: their at most 16 totals, scanned by every wave
+    int tot = lane < (int)(blockDim.x >> 6) ? s_w[lane] : ident;
+#pragma unroll
+    for (int off = 1; off < kMapThreads / 64; off <<= 1) {
+        const int o = __shfl_up(tot, off, 64);
+        if (lane >= off) tot = op(tot, o);
+    }
+    const int base = wave == 0 ? ident : __shfl(tot, max(wave - 1, 0), 64);
     const int up = __shfl_up(inc, 1, 64);
     __syncthreads();      // s_w may be written again
     return lane == 0 ? base : op(base, up);
@@ -49,7 +55,7 @@ __global__ __launch_bounds__(kMapThreads) void k_tile_map(const int32_t* __restr
     __shared__ int s_w[kMapThreads / 64];
     const int tid = threadIdx.x;
     clear_counts(count);
-    const int nseg = (rank_hi - rank_lo) * E, C = (nseg + kMapThreads - 1) / kMapThreads;
+    const int nseg = (rank_hi - rank_lo) * E, C = (nseg + (int)blockDim.x - 1) / (int)blockDim.x;
     const int s0 = min(tid * C, nseg), s1 = min(s0 + C, nseg);
     auto max_op = [](int a, int b) { return max(a, b); };
     auto first_row = [&](int s) { return seg_off[(size_t)(rank_lo + s / E) * (E + 1) + s % E]; };
@@ -82,7 +88,7 @@ __global__ __launch_bounds__(kMapThreads) void k_tile_map(const int32_t* __restr
             p = s;
             for (int r = h + (r0 - h + BM - 1) / BM * BM; r < r1; r += BM) visit(s, r);
         }
-        if (tid == kMapThreads - 1 && p >= 0) closed(end_row(p), h);
+        if (tid == (int)blockDim.x - 1 && p >= 0) closed(end_row(p), h);
     };
     int nt = 0;
     walk([&](int, int) { ++nt; }, [](int, int) {});
@@ -102,7 +108,7 @@ __global__ __launch_bounds__(kMapThreads) void k_tile_map(const int32_t* __restr
              tiles[at - 1].rows = end - (h + (end - 1 - h) / BM * BM);
              tiles[at - 1].alone = end - h <= BM;
          });
-    if (tid == kMapThreads - 1) *count = min(at, max_tiles);
+    if (tid == (int)blockDim.x - 1) *count = min(at, max_tiles);
 }
 
 // The same for one rank, whose segments are all of different experts: one thread per expert, one scan (a launch in
@@ -213,7 +219,7 @@ int launch_tile_map(const fine_shape& s, const int32_t* seg_off, int rank_lo, in
         hipLaunchKernelGGL(k_tile_map_rank, dim3(1), dim3((unsigned)align_up(s.E, 64)), 0, st,
                            seg_off + (size_t)rank_lo * (s.E + 1), s.E, BM, tiles, count, max_tiles);
     else
-        hipLaunchKernelGGL(k_tile_map, dim3(1), dim3(kMapThreads), 0, st, seg_off, s.E, rank_lo, rank_hi, BM, tiles, count, max_tiles);
+        hipLaunchKernelGGL(k_tile_map, dim3(1), dim3((unsigned)std::min<size_t>(kMapThreads, align_up((size_t)(rank_hi - rank_lo) * s.E, 64))), 0, st, seg_off, s.E, rank_lo, rank_hi, BM, tiles, count, max_tiles);
     FINE_LAUNCH_CHECK();
     return FINE_OK;
 }

@@ -295,9 +295,9 @@ __device__ __forceinline__ void wgrad_body(WgradProblem p0, WgradProblem p1, Wgr
                                                             accumulate != 0);
             continue;
         } else {
-            LoaderMC<BM, true> la;
+            LoaderMC<BM> la;
             la.init([&](int r8) { return p.A + min(m0 + 8 * r8, p.M - 8); }, (size_t)p.lda);
-            LoaderMC<BN, true> lb;
+            LoaderMC<BN> lb;
             lb.init([&](int r8) { return p.B + min(n0 + 8 * r8, p.N - 8); }, (size_t)p.ldb);
             k_loop<WAVES_M, WAVES_N, WM, WN, (WM * WN >= 16 ? 1 : 2)>(nk, smem, acc, la, lb, k_tile);
         }

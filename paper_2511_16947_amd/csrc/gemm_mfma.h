@@ -8,8 +8,8 @@
 // lanes each cover all banks.  Two loaders fill that layout:
 //   LoaderKC  the source is contiguous along k (activations [rows,k]; weights used
 //             transposed in the backward pass): 16-byte global loads go straight to LDS;
-//   LoaderMC  the source is contiguous along the tile's row index (weights [k,n] in the
-//             forward pass, both operands of the weight gradients): each thread loads an
+//   LoaderMC  the source is contiguous along the tile's row index (both operands of the
+//             weight gradients): each thread loads an
 //             8(k) x 8(row) block, transposes it in registers with byte permutes and
 //             writes eight 16-byte chunks.
 // The k-loop is double buffered (registers -> other LDS buffer, one barrier per step) and
@@ -91,10 +91,10 @@ struct LoaderKC {
 // Source contiguous along the tile row index r (element (k, r) at col_ptr(r) + k*ld).
 // Thread t: k-block (t & 7) of 8 k-values, row block (t >> 3) of 8 rows (ROWS = 256), i.e.
 // eight 16-byte global loads (one per k) and, after an 8x8 transpose, eight LDS writes.
-// RAGGED: rows of the source at k >= k_end read as zero (contraction over ragged ranges);
+// Rows of the source at k >= k_end read as zero (contraction over ragged ranges);
 // the address is clamped to the last valid row, so there is no branch.
 // ---------------------------------------------------------------------------
-template <int ROWS, bool RAGGED>
+template <int ROWS>
 struct LoaderMC {
     static_assert(ROWS == 256 || ROWS == 128, "tile rows");
     static constexpr int kLoads = 8, kStores = 8;
@@ -114,16 +114,12 @@ struct LoaderMC {
     }
     template <int J, int SET>
     __device__ inline void load_one(ptrdiff_t k0, int k_end) {
-        if constexpr (RAGGED) {
-            const int kblock8 = (int)((threadIdx.x % ROWS) & 7) * 8;
-            const int k = (int)k0 + kblock8 + J;                  // absolute source row
-            const int kc = min(k, k_end - 1);                     // last valid row instead of a branch
-            const u32x4 v = *reinterpret_cast<const u32x4*>(ptr + (ptrdiff_t)(kc - kblock8) * ld);
-            const u32x4 z = {0u, 0u, 0u, 0u};
-            reg[SET][J] = (k < k_end) ? v : z;
-        } else {
-            reg[SET][J] = *reinterpret_cast<const u32x4*>(ptr + (k0 + J) * ld);
-        }
+        const int kblock8 = (int)((threadIdx.x % ROWS) & 7) * 8;
+        const int k = (int)k0 + kblock8 + J;                  // absolute source row
+        const int kc = min(k, k_end - 1);                     // last valid row instead of a branch
+        const u32x4 v = *reinterpret_cast<const u32x4*>(ptr + (ptrdiff_t)(kc - kblock8) * ld);
+        const u32x4 z = {0u, 0u, 0u, 0u};
+        reg[SET][J] = (k < k_end) ? v : z;
     }
     template <int M, int SET>
     __device__ inline void store_one(char* lds) const {

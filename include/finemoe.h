@@ -77,8 +77,8 @@ size_t fine_workspace_bytes(const fine_shape* shape, int which);
 /*
  * Gate (Section 2.1: the gate network assigns each token to its top-K experts).
  * logits[t][e] = sum_i x[t][i] * w_router[i][e] + bias[e] in fp32; topk_idx[t][:] = the K
- * experts with the largest logits in descending order (equal logits: lower index first);
- * topk_w[t][:] = softmax over those K logits (fp32).
+ * experts with the largest logits in descending order (equal logits: lower index first; a NaN
+ * counts as less than -inf), always K different ones; topk_w[t][:] = softmax over those K logits (fp32).
  *   x [T,d] dtype, w_router [d,E] dtype, bias [E] fp32 or NULL,
  *   topk_idx [T,K] int32 out, topk_w [T,K] fp32 out.
  *   ws: NULL, or fine_workspace_bytes(shape, FINE_WS_TOPK) bytes of device scratch (256-byte

@@ -19,7 +19,7 @@
 // More than 256 experts (or a router matrix of 2^31 weights): each wave owns TB tokens; lane l accumulates the
 // logits of experts l, l+64, ... in fp32 while the token rows stream through LDS, then K
 // rounds of a cross-lane argmax.
-#include <cfloat>
+#include <climits>
 
 #include "gemm_mfma.h"
 
@@ -28,6 +28,16 @@ namespace fine {
 namespace {
 
 constexpr int kChunk = 64;   // elements of the hidden dimension staged per step
+
+// Logits are compared as integers in the order of their values: -0 equals +0, NaN lies below -inf, and below all of them
+// is kNoKey, which no logit has - an expert that is taken or does not exist.  (A float in its place, the lowest one
+// say, ties with a masked expert's logit or beats it, and an expert would be picked twice.)
+constexpr int kNoKey = INT_MIN, kNanKey = INT_MIN + 1;
+__device__ inline int logit_key(float v) {
+    const int b = __float_as_int(v + 0.f);
+    return v == v ? b ^ ((b >> 31) & INT_MAX) : kNanKey;
+}
+__device__ inline float key_logit(int k) { return __int_as_float(k ^ ((k >> 31) & INT_MAX)); }      // (kNanKey: a NaN)
 
 template <typename T, int TB, int EPL>
 __global__ __launch_bounds__(256) void k_topk(const T* __restrict__ x, const T* __restrict__ w_router,
@@ -85,25 +95,21 @@ __global__ __launch_bounds__(256) void k_topk(const T* __restrict__ x, const T* 
         int my_idx = 0;
         float top = 0.f;
         for (int k = 0; k < K; ++k) {
-            float bv = 0.f;
-            int be = 0x7fffffff;
+            int bv = kNoKey, be = 0x7fffffff;
 #pragma unroll
             for (int j = 0; j < EPL; ++j) {
-                const int e = lane + 64 * j;
-                if (e < E && !((taken >> j) & 1u)) {
-                    if (be == 0x7fffffff || acc[tb][j] > bv) { bv = acc[tb][j]; be = e; }
-                }
+                const int e = lane + 64 * j, key = logit_key(acc[tb][j]);
+                if (e < E && !((taken >> j) & 1u) && key > bv) { bv = key; be = e; }
             }
 #pragma unroll
             for (int off = 32; off > 0; off >>= 1) {
-                const float ov = __shfl_xor(bv, off, 64);
-                const int oe = __shfl_xor(be, off, 64);
-                const bool better = (oe != 0x7fffffff) && (be == 0x7fffffff || ov > bv || (ov == bv && oe < be));
-                if (better) { bv = ov; be = oe; }
+                const int ov = __shfl_xor(bv, off, 64), oe = __shfl_xor(be, off, 64);
+                if (ov > bv || (ov == bv && oe < be)) { bv = ov; be = oe; }
             }
             if ((be & 63) == lane) taken |= 1u << (be >> 6);
-            if (k == 0) top = bv;
-            if (lane == k) { my_val = bv; my_idx = be; }
+            const float val = key_logit(bv);
+            if (k == 0) top = val;
+            if (lane == k) { my_val = val; my_idx = be; }
         }
         float ex = (lane < K) ? __expf(my_val - top) : 0.f;
         float sum = ex;
@@ -121,7 +127,7 @@ __global__ __launch_bounds__(256) void k_topk(const T* __restrict__ x, const T* 
 // ---------------------------------------------------------------------------------------------
 typedef short v4i16_t __attribute__((ext_vector_type(4)));
 
-// K selection rounds and softmax for the 32 tokens of a wave.  Register q of tile nt holds the
+// K selection rounds and softmax for the 32 tokens of a wave (the keys: see logit_key).  Register q of tile nt holds the
 // logit of expert 32 nt + 8 (q >> 2) + 4 h + (q & 3) of token (lane & 31), h = lane >> 5; the two
 // lanes of a token exchange their best once per round.  s_val: [32][33] floats of the wave.
 template <int NT>
@@ -141,22 +147,21 @@ __device__ inline void select_topk(mfma::f32x16 (&acc)[NT], const float* __restr
             for (int q = 0; q < 16; ++q) acc[nt][q] += b[q];
         }
     }
+    int key[NT][16];
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-        for (int q = 0; q < 16; ++q) acc[nt][q] = (expert_of(nt, q) < E) ? acc[nt][q] : -FLT_MAX;
+        for (int q = 0; q < 16; ++q) key[nt][q] = (expert_of(nt, q) < E) ? logit_key(acc[nt][q]) : kNoKey;
     for (int k = 0; k < K; ++k) {
         // position p = 16 nt + q counts the lane's values in ascending expert order
-        float bv = -FLT_MAX;
-        int bp = 0;
+        int bv = kNoKey, bp = 0;
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
             for (int q = 0; q < 16; ++q)      // ">" keeps the lowest of equals
-                if (acc[nt][q] > bv) { bv = acc[nt][q]; bp = 16 * nt + q; }
+                if (key[nt][q] > bv) { bv = key[nt][q]; bp = 16 * nt + q; }
         int be = 32 * (bp >> 4) + 8 * ((bp & 15) >> 2) + 4 * h + (bp & 3);
-        const float ov = __shfl_xor(bv, 32, 64);
-        const int oe = __shfl_xor(be, 32, 64);
+        const int ov = __shfl_xor(bv, 32, 64), oe = __shfl_xor(be, 32, 64);
         const bool partner_wins = ov > bv || (ov == bv && oe < be);
         if (partner_wins) { bv = ov; be = oe; bp = -1; }
         // the winner leaves the race.  Its position becomes a one-hot mask and every value tests its
@@ -170,9 +175,9 @@ __device__ inline void select_topk(mfma::f32x16 (&acc)[NT], const float* __restr
         for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
             for (int q = 0; q < 16; ++q)
-                acc[nt][q] = ((onehot[(16 * nt + q) >> 5] >> ((16 * nt + q) & 31)) & 1u) ? -FLT_MAX : acc[nt][q];
+                key[nt][q] = ((onehot[(16 * nt + q) >> 5] >> ((16 * nt + q) & 31)) & 1u) ? kNoKey : key[nt][q];
         if (h == 0) {
-            s_val[r][k] = bv;
+            s_val[r][k] = key_logit(bv);
             if (t < Tn) topk_idx[(size_t)t * K + k] = be;
         }
     }
@@ -576,26 +581,25 @@ __global__ __launch_bounds__(256) void k_topk_select(const float* __restrict__ p
 #pragma unroll
         for (int j = 0; j < MAXJ; ++j) v[j] += b[j];
     }
+    int key[MAXJ];
 #pragma unroll
-    for (int j = 0; j < MAXJ; ++j) v[j] = (l + 16 * j < E) ? v[j] : -FLT_MAX;
+    for (int j = 0; j < MAXJ; ++j) key[j] = (l + 16 * j < E) ? logit_key(v[j]) : kNoKey;
     for (int k = 0; k < K; ++k) {
-        float bv = -FLT_MAX;
-        int bj = 0;
+        int bv = kNoKey, bj = 0;
 #pragma unroll
         for (int j = 0; j < MAXJ; ++j)        // ">" keeps the lowest of equals
-            if (v[j] > bv) { bv = v[j]; bj = j; }
+            if (key[j] > bv) { bv = key[j]; bj = j; }
         int be = l + 16 * bj;
 #pragma unroll
         for (int off = 8; off > 0; off >>= 1) {
-            const float ov = __shfl_xor(bv, off, 16);
-            const int oe = __shfl_xor(be, off, 16);
+            const int ov = __shfl_xor(bv, off, 16), oe = __shfl_xor(be, off, 16);
             if (ov > bv || (ov == bv && oe < be)) { bv = ov; be = oe; }
         }
         const unsigned gone = ((be & 15) == l) ? (1u << (be >> 4)) : 0u;         // the winner leaves the race
 #pragma unroll
-        for (int j = 0; j < MAXJ; ++j) v[j] = ((gone >> j) & 1u) ? -FLT_MAX : v[j];
+        for (int j = 0; j < MAXJ; ++j) key[j] = ((gone >> j) & 1u) ? kNoKey : key[j];
         if (l == 0) {
-            s_val[grp][k] = bv;
+            s_val[grp][k] = key_logit(bv);
             if (t < Tn) topk_idx[(size_t)t * K + k] = be;
         }
     }

@@ -238,3 +238,21 @@ def test_a_training_step_can_be_captured_in_a_graph():
         for got, ref in zip((layer.out, bwd.d_x, bwd.d_topk_w, bwd.d_wg, bwd.d_wu, bwd.d_wd), want):
             assert torch.equal(got.view(torch.int32 if got.dtype == torch.float32 else torch.int16),
                                ref.view(torch.int32 if ref.dtype == torch.float32 else torch.int16)), n
+
+
+@pytest.mark.parametrize("tile", [0, 2])
+@pytest.mark.parametrize("T,d,f,E,K,G", [(4096, 2048, 768, 16, 2, 4), (1024, 1024, 1024, 8, 2, 2)])
+def test_recomputed_pre_activations_do_not_depend_on_the_ranks_of_a_call(T, d, f, E, K, G, tile):
+    """Without act_save, on segments and k ranges long enough for a launch to cut its last tiles along k: which tiles
+    those would be depends on how many a call has, and the pre-activations of one rank's call must not."""
+    cfg = wl.scaled(wl.CONFIGS["cfg5_train"], name="recompute_ranks", T=T, d=d, f=f, E=E, K=K, G=G, bias_kind="scaled_z",
+                    bias_scale=1.0)
+    inp = wl.make_inputs(cfg, DEV)
+    layer = GpuLayer(cfg, inp, fm.FLAG_LOCALITY | (tile << 8))
+    layer.forward()
+    whole, parts = GpuBackward(layer), GpuBackward(layer)
+    whole.run()
+    for r in range(G):
+        parts.run(accumulate=(r > 0), rank=r)
+    assert torch.equal(parts.d_x.view(torch.int16), whole.d_x.view(torch.int16))
+    assert torch.equal(parts.d_topk_w, whole.d_topk_w)

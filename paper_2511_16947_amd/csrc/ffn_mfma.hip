@@ -359,19 +359,18 @@ int pick_tile(const fine_shape& s, int n_ranks) {
 }  // namespace
 
 // any_ranks (the backward pass): the same bits whether a call is for one rank or for all, so the tile may not depend on
-// the number of ranks, and on short segments no tile is cut along k (where a launch cuts depends on how many it has).
+// the number of ranks, and no tile is cut along k (which tiles a launch cuts, and where, depends on how many it has).
 int launch_ffn_parts(const fine_shape& s, int rank_lo, int rank_hi, const void* x_perm, const void* wg,
                      const void* wu, const void* wd, const int32_t* seg_off, void* h_buf, void* y_perm,
                      void* act_save, TileEntry* tiles, int32_t* count, int max_tiles, float* sk_partials, bool gemm1,
                      bool gemm2, bool any_ranks, hipStream_t st) {
     const int tile = pick_tile(s, any_ranks ? s.G : rank_hi - rank_lo);
-    const bool may_cut = !any_ranks || (double)s.T * s.K / (s.E + s.G) >= 96.0;
     if (tile == 1)
         return launch_ffn_stream(s, rank_lo, rank_hi, x_perm, wg, wu, wd, seg_off, h_buf, y_perm, act_save, tiles, count,
                                  max_tiles, gemm1, gemm2, st);
     auto run = tile == 3 ? run_ffn<2, 4, 4, 2> : run_ffn<2, 4, 2, 2>;
     return run(s, rank_lo, rank_hi, x_perm, wg, wu, wd, seg_off, h_buf, y_perm, act_save, tiles, count, max_tiles,
-               sk_partials, gemm1, gemm2, may_cut, st);
+               sk_partials, gemm1, gemm2, !any_ranks, st);
 }
 
 int launch_ffn_mfma(const fine_shape& s, int rank_lo, int rank_hi, const void* x_perm,

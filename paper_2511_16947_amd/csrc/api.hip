@@ -25,11 +25,7 @@ int check_shape(const fine_shape* s) {
     return FINE_OK;
 }
 
-// the matrix-core kernels keep byte offsets inside a row tile and inside 32 k-rows of a weight matrix in 32 bits
-bool use_mfma(const fine_shape& s) {
-    if (s.flags & FINE_FLAG_SIMPLE_FFN) return false;
-    return s.dtype == FINE_BF16 || (s.d <= (1 << 20) && s.f <= (1 << 20));
-}
+bool use_mfma(const fine_shape& s) { return !(s.flags & FINE_FLAG_SIMPLE_FFN) && mfma_offsets_fit(s); }
 
 }  // namespace
 

@@ -425,6 +425,7 @@ int launch_backward(const fine_shape& s, int rank_lo, int rank_hi, const void* d
     // Short segments: 128-row tiles on 4 waves also where most of their rows are empty.  (64-row tiles, dH + dXp against
     // 128 rows: 5 rows per segment 126 : 101 us, 15 rows 201 : 170, 60 rows 380 : 317, 57 rows on wide experts 192 : 162.)
     if (tile != 3) tile = tile == 0 && seg_rows >= 384.0 ? 3 : 2;
+    if (!w8_offsets_fit(s)) tile = 2;
 #define FINE_DGRAD(WAM, WAN, WMM, WNN)                                                                        \
     FINE_TRY((run_dgrad<WAM, WAN, WMM, WNN>(s, rank_lo, rank_hi, dy, act, (const uint16_t*)wg, (const uint16_t*)wu, \
                                             (const uint16_t*)wd, seg_off, dact, h_out, dxp, tiles, count, L.max_tiles, \

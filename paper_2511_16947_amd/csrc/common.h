@@ -100,6 +100,18 @@ struct TileEntry {
     int32_t alone;     // 1: the only tile of its run
 };
 
+// The GEMM kernels keep byte offsets from a tile's bases in 32 bits.  The 8-wave ones (gemm_w8.h) span 256 rows of
+// activations and a whole weight matrix:
+inline bool w8_offsets_fit(const fine_shape& s) {
+    return s.d <= (1 << 22) && s.f <= (1 << 22) && (long long)s.d * s.f < (1ll << 31);
+}
+// those that split k over the waves of a block 64 rows of activations and 64 k-rows of a weight matrix, bf16; the fp32 ones
+// 64 rows and 32 k-rows:
+inline bool mfma_offsets_fit(const fine_shape& s) {
+    const int widest = s.dtype == FINE_F32 ? 1 << 20 : 1 << 24;
+    return s.d <= widest && s.f <= widest;
+}
+
 // The count block: int32 number of row tiles, from int32 index kSkCounterOffset on 256 arrival
 // counters for tiles cut along k and from kSkReadyOffset on their 256 "parts written" counters
 // (all zero between launches).  Partial sums of such tiles:

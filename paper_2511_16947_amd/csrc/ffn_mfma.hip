@@ -345,6 +345,7 @@ int run_ffn(const fine_shape& s, int rank_lo, int rank_hi, const void* x_perm, c
 // CUs without a tile, each of the others waiting out a chain of k-steps: 10 row tiles of 128 on 1088 x 832, 133 tiles
 // in both GEMMs, 28 against 43 us per rank; 204 tiles 37 against 47; 286 tiles 51 against 60; 351 tiles 51 against 48.
 int pick_tile(const fine_shape& s, int n_ranks) {
+    if (!w8_offsets_fit(s)) return 1;
     const int tile = (s.flags & FINE_FLAG_TILE_MASK) >> FINE_FLAG_TILE_SHIFT;
     if (tile != 0) return tile;
     // expected runs of rows of one expert when every expert is on every rank: the rows of n ranks, P / G each, span

@@ -12,7 +12,7 @@ namespace {
 // that a call over all ranks reads an expert's weights once and not once per rank, and has one short tile per run
 // (64 tokens on 8 experts and 8 ranks: 8 tiles instead of 15).  One rank's segments are all of different experts.
 // Thread t takes C consecutive segments; everything it needs of the others are two running maxima (the index of the
-// last non-empty segment; the first row of the last run, rows ascending) and a sum of tile counts: three block
+// last non-empty segment; the index of the first segment of the last run) and a sum of tile counts: three block
 // scans whatever the number of segments (8192 segments: 60 -> 31 us against a scan per 256 segments; 1024: 7 us).
 constexpr int kMapThreads = 1024;
 
@@ -70,10 +70,11 @@ __global__ __launch_bounds__(kMapThreads) void k_tile_map(const int32_t* __restr
     int head = -1, prev = before;
     for (int s = s0; s < s1; ++s) {
         if (end_row(s) <= first_row(s)) continue;
-        if (!continues(s, prev)) head = first_row(s);
+        if (!continues(s, prev)) head = s;
         prev = s;
     }
-    const int head_before = block_excl_scan(head, -1, s_w, max_op);
+    const int head_seg = block_excl_scan(head, -1, s_w, max_op);
+    const int head_before = head_seg < 0 ? 0 : first_row(head_seg);      // (ranks' rows may lie in any order)
     // A run's tiles start at its first row + multiples of BM; each belongs to the segment that its first row lies in.
     // visit(s, r): a tile starts at row r of segment s; closed(end, head): the run from row `head` has ended at `end`.
     auto walk = [&](auto visit, auto closed) {

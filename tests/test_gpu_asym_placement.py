@@ -320,3 +320,33 @@ def test_many_candidates_scored_one_per_wave(E, G, slots, n):
     scores = [Fraction(int(a), int(b)) for a, b in zip(m_num, m_den)]
     assert best == min(range(n), key=lambda c: (scores[c], c))
     assert np.array_equal(place, placement.draw_placement(host_counts, G, slots, 3, best))
+
+
+def _ties_at_the_last_place(counts, G, slots, seed, cand):
+    """Experts whose last chosen rank and first rank left out agree in free slots and the upper 22 bits of the key."""
+    place, free, found = placement.draw_placement(counts, G, slots, seed, cand), [slots] * G, []
+    for e in sorted(range(len(counts)), key=lambda e: (-int(counts[e]), e)):
+        order = sorted(range(G), key=lambda g: (-free[g], -placement.rank_key(seed, cand, e, g), g))
+        c = int(counts[e])
+        if c < G:
+            a, b = [(free[g], int(placement.rank_key(seed, cand, e, g)) >> 10) for g in order[c - 1:c + 1]]
+            found += [e] * (a == b)
+        free = [n - int(p) for n, p in zip(free, place[e])]
+    return found
+
+
+@pytest.mark.parametrize("E,G,slots,n,seed,cand", [
+    (64, 16, 5, 1, 5570, 0), (200, 13, 18, 1, 12168, 0), (24, 5, 8, 1, 131345, 0), (100, 2, 60, 1, 776, 0),
+    (64, 16, 5, 16000, 3, 15995),
+])
+def test_drawn_ranks_that_agree_in_the_upper_bits_of_their_keys(E, G, slots, n, seed, cand):
+    """The draw compares ranks by 32 bits first and by all bits where these leave more ranks than replicas."""
+    load = wl.zipf_loads(E, 65536, 1.1, E)
+    counts = placement.replica_counts(load, G, slots)
+    assert _ties_at_the_last_place(counts, G, slots, seed, cand)
+    m_num, m_den, best, place = gpu_search(load, dev_i32(counts), E, G, slots, n, seed)
+    drawn = placement.draw_placement(counts, G, slots, seed, cand)
+    want = placement.max_density(load, drawn)
+    assert (int(m_num[cand]), int(m_den[cand])) == (want.numerator, want.denominator)
+    if n == 1:
+        assert best == 0 and np.array_equal(place, drawn)

@@ -58,7 +58,7 @@ __device__ __forceinline__ void bwd_dh_body(const uint16_t* __restrict__ dy, con
             la.init([&](int r) { return dy + (size_t)(te.row0 + min(r, te.rows - 1)) * d; });
             LoaderKC<BN> lb;
             lb.init([&](int n) { return W + (size_t)min(n0 + n, f - 1) * d; });
-            k_loop<WAVES_M, WAVES_N, WM, WN, (WM * WN >= 16 ? 1 : 2)>(d / BK, smem, acc, la, lb, k_tile);
+            k_loop<WAVES_M, WAVES_N, WM, WN>(d / BK, smem, acc, la, lb, k_tile);
         }
         constexpr int WMC = (BM * (BN * 2 + 8) <= 2 * (BM + BN) * 128) ? WM : WM / 2;
         struct PreAct {
@@ -183,7 +183,7 @@ __device__ __forceinline__ void bwd_dx_body(const uint16_t* __restrict__ dact, c
             la.init([&](int r) { return dact + (size_t)(te.row0 + min(r, te.rows - 1)) * (2 * f); });
             LoaderKC<BN> lb;
             lb.init([&](int n) { return Wg + (size_t)min(n0 + n, d - 1) * f; });
-            k_loop<WAVES_M, WAVES_N, WM, WN, (WM * WN >= 16 ? 1 : 2)>(2 * nkf, smem, acc, la, lb, k_tile);
+            k_loop<WAVES_M, WAVES_N, WM, WN>(2 * nkf, smem, acc, la, lb, k_tile);
         }
         constexpr int WMC = (BM * (BN * 2 + 8) <= 2 * (BM + BN) * 128) ? WM : WM / 2;
         store_tile_bf16<WAVES_M, WAVES_N, WM, WN, WMC>(
@@ -295,11 +295,12 @@ __device__ __forceinline__ void wgrad_body(WgradProblem p0, WgradProblem p1, Wgr
                                                             accumulate != 0);
             continue;
         } else {
-            LoaderMC<BM> la;
+            static_assert(BM == LoaderMC::ROWS && BN == LoaderMC::ROWS, "tile of the 4-wave kernel");
+            LoaderMC la;
             la.init([&](int r8) { return p.A + min(m0 + 8 * r8, p.M - 8); }, (size_t)p.lda);
-            LoaderMC<BN> lb;
+            LoaderMC lb;
             lb.init([&](int r8) { return p.B + min(n0 + 8 * r8, p.N - 8); }, (size_t)p.ldb);
-            k_loop<WAVES_M, WAVES_N, WM, WN, (WM * WN >= 16 ? 1 : 2)>(nk, smem, acc, la, lb, k_tile);
+            k_loop<WAVES_M, WAVES_N, WM, WN>(nk, smem, acc, la, lb, k_tile);
         }
         float* out = p.out + (size_t)e * p.M * p.N;
         // through LDS, so that a wave stores 1 KB of one row at a time

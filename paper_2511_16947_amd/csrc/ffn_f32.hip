@@ -41,14 +41,14 @@ __device__ inline void dma_to_lds(const __amdgpu_buffer_rsrc_t& rs, char* lds, u
 
 // EPI 0: A = x_perm [P,Kd], B0 / B1 = Wg / Wu [E,Kd,N], C = H [P,N]; act [P,2N] optional
 // EPI 1: A = H [P,Kd], B0 = Wd [E,Kd,N], C = y_perm [P,N]
-// V: floats per lane and DMA instruction; NP: 64-column panels of B
-template <int EPI, int V, int NP>
+// V: floats per lane and DMA instruction
+template <int EPI, int V>
 __global__ __launch_bounds__(256, 3) void k_ffn_f32(const float* __restrict__ A, const float* __restrict__ B0,
                                                  const float* __restrict__ B1, int Kd, int N, float* __restrict__ C,
                                                  float* __restrict__ act, const TileEntry* __restrict__ tiles,
                                                  const int32_t* __restrict__ count, const int32_t* __restrict__ seg, int E) {
-    static_assert(EPI == 1 || NP == 2, "gate and up panel");
-    constexpr int BNC = EPI == 0 ? 64 : 64 * NP;         // output columns per block
+    constexpr int NP = EPI == 0 ? 2 : 1;                  // 64-column panels of B: gate and up / down
+    constexpr int BNC = 64;                               // output columns per block
     constexpr int kBuf = kABytes + NP * kPanelBytes;      // one buffer: A and the panels of B
     __shared__ __attribute__((aligned(16))) char smem[2 * kBuf];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -93,7 +93,7 @@ __global__ __launch_bounds__(256, 3) void k_ffn_f32(const float* __restrict__ A,
         for (int j = 0; j < BINST; ++j) {
             const int inst = wave * BINST + j, p = inst / (kBK / BROWS), k = (inst % (kBK / BROWS)) * BROWS + b_k;
             const int c = b_w ^ (((k >> 2) & 1) << 5);
-            b_off[j] = ((uint32_t)k * N + min(n0 + (EPI == 0 ? 0 : 64 * p) + c, N - V)) * 4u;
+            b_off[j] = ((uint32_t)k * N + min(n0 + c, N - V)) * 4u;
         }
         const __amdgpu_buffer_rsrc_t ra =
             __builtin_amdgcn_make_buffer_rsrc((void*)Ap, 0, (int)((uint32_t)te.rows * Kd * 4u), 0x00020000);
@@ -111,7 +111,7 @@ __global__ __launch_bounds__(256, 3) void k_ffn_f32(const float* __restrict__ A,
             for (int j = 0; j < BINST; ++j) {
                 const int inst = wave * BINST + j, p = inst / (kBK / BROWS), kr0 = (inst % (kBK / BROWS)) * BROWS;
                 const __amdgpu_buffer_rsrc_t rb =
-                    __builtin_amdgcn_make_buffer_rsrc((void*)(Bp[EPI == 0 ? p : 0] + (size_t)k0 * N), 0, b_size, 0x00020000);
+                    __builtin_amdgcn_make_buffer_rsrc((void*)(Bp[p] + (size_t)k0 * N), 0, b_size, 0x00020000);
                 dma_to_lds<V>(rb, base + kABytes + p * kPanelBytes + kr0 * 256, b_off[j], 0);
             }
         };
@@ -135,12 +135,10 @@ __global__ __launch_bounds__(256, 3) void k_ffn_f32(const float* __restrict__ A,
                 const f32x4 a = *reinterpret_cast<const f32x4*>(sA + lds_off(wm * 32 + r, 2 * j + h));
                 float b[NP][4];
 #pragma unroll
-                for (int t = 0; t < NP; ++t) {
-                    const int panel = EPI == 0 ? t : NP == 2 ? wn : 0, col = 32 * (EPI == 1 && NP == 2 ? t : wn) + r;
+                for (int t = 0; t < NP; ++t)
 #pragma unroll
                     for (int q = 0; q < 4; ++q)
-                        b[t][q] = *reinterpret_cast<const float*>(sB + panel * kPanelBytes + (8 * j + 4 * h + q) * 256 + (col ^ (h << 5)) * 4);
-                }
+                        b[t][q] = *reinterpret_cast<const float*>(sB + t * kPanelBytes + (8 * j + 4 * h + q) * 256 + ((32 * wn + r) ^ (h << 5)) * 4);
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
 #pragma unroll
@@ -154,21 +152,16 @@ __global__ __launch_bounds__(256, 3) void k_ffn_f32(const float* __restrict__ A,
             const int m = wm * 32 + 8 * (q >> 2) + 4 * h + (q & 3);
             if (m >= te.rows) continue;
             const size_t row = (size_t)te.row0 + m;
+            const int n = n0 + 32 * wn + r;
+            if (n >= N) continue;
             if constexpr (EPI == 0) {
-                const int n = n0 + 32 * wn + r;
-                if (n < N) {
-                    if (act != nullptr) {
-                        act[row * (2 * (size_t)N) + n] = acc[0][q];
-                        act[row * (2 * (size_t)N) + N + n] = acc[1][q];
-                    }
-                    C[row * N + n] = silu_mul_f32(acc[0][q], acc[1][q]);
+                if (act != nullptr) {
+                    act[row * (2 * (size_t)N) + n] = acc[0][q];
+                    act[row * (2 * (size_t)N) + N + n] = acc[1][q];
                 }
+                C[row * N + n] = silu_mul_f32(acc[0][q], acc[1][q]);
             } else {
-#pragma unroll
-                for (int t = 0; t < NP; ++t) {
-                    const int n = n0 + 32 * NP * wn + 32 * t + r;
-                    if (n < N) C[row * N + n] = acc[t][q];
-                }
+                C[row * N + n] = acc[0][q];
             }
         }
         block_barrier();      // the next tile's first DMA overwrites a buffer that slower waves may still read
@@ -193,10 +186,10 @@ int launch_ffn_f32(const fine_shape& s, int rank_lo, int rank_hi, const void* x_
     auto grid = [&](int n) { return (unsigned)std::min<size_t>(768, align_up(rows_tiles * cdiv(n, 64), 8)); };
 #define FINE_F32(V)                                                                                              \
     do {                                                                                                         \
-        hipLaunchKernelGGL((k_ffn_f32<0, V, 2>), dim3(grid(s.f)), dim3(256), 0, st, (const float*)x_perm, (const float*)wg, \
+        hipLaunchKernelGGL((k_ffn_f32<0, V>), dim3(grid(s.f)), dim3(256), 0, st, (const float*)x_perm, (const float*)wg, \
                            (const float*)wu, s.d, s.f, h, (float*)act_save, tiles, count, seg, s.E);                       \
         FINE_LAUNCH_CHECK();                                                                                     \
-        hipLaunchKernelGGL((k_ffn_f32<1, V, 1>), dim3(grid(s.d)), dim3(256), 0, st, (const float*)h, (const float*)wd, \
+        hipLaunchKernelGGL((k_ffn_f32<1, V>), dim3(grid(s.d)), dim3(256), 0, st, (const float*)h, (const float*)wd, \
                            (const float*)nullptr, s.f, s.d, (float*)y_perm, (float*)nullptr, tiles, count, seg, s.E);      \
         FINE_LAUNCH_CHECK();                                                                                     \
     } while (0)

@@ -1,5 +1,5 @@
-// Work-list construction for the grouped GEMMs, and the plain FMA expert FFN (fp32
-// layers, shapes the MFMA path does not take, and a debugging cross-check).
+// Work-list construction for the grouped GEMMs, and the plain FMA expert FFN (layers wider than the
+// matrix-core kernels' 32-bit offsets reach, and a cross-check in tests).
 #include "common.h"
 
 namespace fine {
@@ -7,7 +7,7 @@ namespace fine {
 namespace {
 
 // One block: the work list of the (rank, expert) segments of ranks [rank_lo, rank_hi), one TileEntry per BM rows, in
-// the order of the rows.  Neighbouring non-empty segments of ONE expert (its share on a rank and on the next one: a
+// the order of the segments.  Neighbouring non-empty segments of ONE expert (its share on a rank and on the next one: a
 // hot expert under the full placement fills whole ranks) form one run of rows and are cut into tiles together, so
 // that a call over all ranks reads an expert's weights once and not once per rank, and has one short tile per run
 // (64 tokens on 8 experts and 8 ranks: 8 tiles instead of 15).  One rank's segments are all of different experts.

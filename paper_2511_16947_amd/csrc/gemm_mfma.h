@@ -89,14 +89,13 @@ struct LoaderKC {
 
 // ---------------------------------------------------------------------------
 // Source contiguous along the tile row index r (element (k, r) at col_ptr(r) + k*ld).
-// Thread t: k-block (t & 7) of 8 k-values, row block (t >> 3) of 8 rows (ROWS = 256), i.e.
+// 128 rows; thread t: k-block (t & 7) of 8 k-values, row block (t >> 3) & 15 of 8 rows, i.e.
 // eight 16-byte global loads (one per k) and, after an 8x8 transpose, eight LDS writes.
 // Rows of the source at k >= k_end read as zero (contraction over ragged ranges);
 // the address is clamped to the last valid row, so there is no branch.
 // ---------------------------------------------------------------------------
-template <int ROWS>
 struct LoaderMC {
-    static_assert(ROWS == 256 || ROWS == 128, "tile rows");
+    static constexpr int ROWS = 128;
     static constexpr int kLoads = 8, kStores = 8;
     static constexpr bool kPieceRecycle = false;       // every write needs all eight loads of its set
     const uint16_t* ptr;
@@ -104,7 +103,7 @@ struct LoaderMC {
     u32x4 reg[2][8];     // two sets: every LDS write needs all eight loads of its set, so one set
                          // is drained while the other is being filled
     // col_ptr(r8) returns the address of element (k = 0, row = 8*r8); the 8 rows of a block
-    // must be contiguous in memory.  For ROWS = 128 the upper half of the threads repeats
+    // must be contiguous in memory.  The upper half of the threads repeats
     // the lower half's work (same addresses, same LDS cells, same values).
     template <typename ColPtr>
     __device__ inline void init(ColPtr col_ptr, size_t ld_) {
@@ -307,8 +306,9 @@ __device__ inline void stage_tile_f32(char* smem, const f32x16 (&acc)[WM][WN], F
 // the output tile as it lies: lane l owns output column (l & 31) and, in register 4 rg + q, output row
 // 8 rg + 4 (l >> 5) + q.  One store instruction of a wave then writes 128 contiguous bytes of each of
 // two rows: whole cache lines, like the LDS-staged form, but no staging passes and no barriers, and the
-// stores drain while the next tile's first operand stages are on their way (measured on the training
-// workload, P = 65536 rows, 64 experts: 7.3 ms against 7.9 ms staged through LDS).  Rows from M on and columns from N on are masked (and lie outside the
+// stores need not drain before the next tile's first operand stages are requested (they do before its first MFMA: vmcnt
+// retires in order; measured on the training workload, P = 65536 rows, 64 experts: 7.3 ms against 7.9 ms staged through
+// LDS).  Rows from M on and columns from N on are masked (and lie outside the
 // buffer descriptor, whose size ends with the tile's last valid row).  accumulate: the old values are
 // read the same way.
 template <int WAVES_M, int WAVES_N, int WM, int WN>
@@ -544,17 +544,15 @@ constexpr int share_begin(int slot, int total, int slots) { return (total * slot
 // i.e. a step's operand tiles need on the order of a thousand issue cycles.  A schedule that
 // issues a tile's loads in one half of a step and writes them to LDS in the other half is
 // bound by that latency, not by the MFMAs.  So the memory pipeline is kept busy all the time
-// and every load is given D full steps (D = 1 or 2) before its data is needed:
-//   step kt computes on LDS buffer kt&1, writes k-tile kt+1 from register set SET to the other
-//   buffer and reloads SET with k-tile kt+1+D.  With D = 2 the two register sets alternate
-//   (SET = (kt+1)&1); with D = 1 LoaderKC keeps one set and reloads each piece right after
-//   writing it, while LoaderMC, whose writes need all eight loads of a set, drains one set
-//   and fills the other.
+// and every load is given two full steps before its data is needed:
+//   step kt computes on LDS buffer kt&1, writes k-tile kt+1 from register set SET = (kt+1)&1 to the
+//   other buffer and reloads SET with k-tile kt+3: LoaderKC each piece right after writing it,
+//   LoaderMC, whose writes need all eight loads of a set, after the last of them.
 // The step is cut into slots of two MFMAs; each slot carries its share of the fragment reads
 // of sub-step kk+1 and of the LDS writes / global loads, and a scheduling barrier pins the
 // slots.  STORE / LOAD switch the two halves off for the last steps.
 // ---------------------------------------------------------------------------
-template <int WAVES_M, int WAVES_N, int WM, int WN, int D, int PAR, bool STORE, bool LOAD, typename LA, typename LB>
+template <int WAVES_M, int WAVES_N, int WM, int WN, int SET, bool STORE, bool LOAD, typename LA, typename LB>
 __device__ inline void k_step(const char* sA, const char* sB, char* nA, char* nB, f32x16 (&acc)[WM][WN],
                               LA& la, LB& lb, const KTile next) {
     constexpr int MF = WM * WN;                 // MFMAs per sub-step
@@ -563,11 +561,6 @@ __device__ inline void k_step(const char* sA, const char* sB, char* nA, char* nB
     constexpr int DSR = WM + WN;                // fragment reads per sub-step
     constexpr int NA = LA::kLoads, NB = LB::kLoads;
     static_assert(LA::kLoads == LA::kStores && LB::kLoads == LB::kStores, "one write per load");
-    // register sets: which one is written to LDS now, which one is (re)loaded now
-    constexpr int ST_A = (D == 2) ? PAR : (LA::kPieceRecycle ? 0 : PAR);
-    constexpr int LD_A = (D == 2) ? PAR : (LA::kPieceRecycle ? 0 : (PAR ^ 1));
-    constexpr int ST_B = (D == 2) ? PAR : (LB::kPieceRecycle ? 0 : PAR);
-    constexpr int LD_B = (D == 2) ? PAR : (LB::kPieceRecycle ? 0 : (PAR ^ 1));
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm = wave / WAVES_N, wn = wave % WAVES_N;
     const int r = lane & 31, half = lane >> 5;
@@ -586,18 +579,18 @@ __device__ inline void k_step(const char* sA, const char* sB, char* nA, char* nB
     auto side_op = [&](auto op) {
         constexpr int o = op.value;
         if constexpr (o < NB) {
-            if constexpr (STORE) lb.template store_one<o, ST_B>(nB);
+            if constexpr (STORE) lb.template store_one<o, SET>(nB);
         } else if constexpr (o < NB + 2 * NA) {
             constexpr int q = o - NB;
             constexpr bool is_store = LA::kPieceRecycle ? (q % 2 == 0) : (q < NA);
             constexpr int p = LA::kPieceRecycle ? q / 2 : (q < NA ? q : q - NA);
             if constexpr (is_store) {
-                if constexpr (STORE) la.template store_one<p, ST_A>(nA);
+                if constexpr (STORE) la.template store_one<p, SET>(nA);
             } else {
-                if constexpr (LOAD) la.template load_one<p, LD_A>(next.a, next.end);
+                if constexpr (LOAD) la.template load_one<p, SET>(next.a, next.end);
             }
         } else {
-            if constexpr (LOAD) lb.template load_one<o - NB - 2 * NA, LD_B>(next.b, next.end);
+            if constexpr (LOAD) lb.template load_one<o - NB - 2 * NA, SET>(next.b, next.end);
         }
     };
     constexpr int NOPS = 2 * (NA + NB);
@@ -627,9 +620,8 @@ __device__ inline void k_step(const char* sA, const char* sB, char* nA, char* nB
 }
 
 // The k-loop shared by every grouped GEMM: tile(kt) says where k-tile kt is; it is called
-// exactly once for each kt = 0 .. nk-1, in order.  D = how many steps ahead of its LDS write
-// a tile is loaded (see k_step).  On return every wave has finished reading LDS.
-template <int WAVES_M, int WAVES_N, int WM, int WN, int D, typename LA, typename LB, typename Tile>
+// exactly once for each kt = 0 .. nk-1, in order.  On return every wave has finished reading LDS.
+template <int WAVES_M, int WAVES_N, int WM, int WN, typename LA, typename LB, typename Tile>
 __device__ inline void k_loop(int nk, char* smem, f32x16 (&acc)[WM][WN], LA& la, LB& lb, Tile tile) {
     constexpr int BM = WAVES_M * WM * 32, BN = WAVES_N * WN * 32;
     auto sA = [&](int buf) { return smem + buf * (BM * 128); };
@@ -642,41 +634,33 @@ __device__ inline void k_loop(int nk, char* smem, f32x16 (&acc)[WM][WN], LA& la,
         ++fetched;
         return last;
     };
-    {   // k-tile 0 goes to LDS buffer 0 at once; the next D tiles wait in the registers
+    {   // k-tile 0 goes to LDS buffer 0 at once; the next two tiles wait in the registers
         const KTile t0 = next_tile();
         static_for<LA::kLoads>([&](auto i) { la.template load_one<i.value, 0>(t0.a, t0.end); });
         static_for<LB::kLoads>([&](auto i) { lb.template load_one<i.value, 0>(t0.b, t0.end); });
         static_for<LA::kStores>([&](auto i) { la.template store_one<i.value, 0>(sA(0)); });
         static_for<LB::kStores>([&](auto i) { lb.template store_one<i.value, 0>(sB(0)); });
-        // tile 1: step 0 writes it from set ST(PAR = 0); D == 2 uses SET = (kt+1)&1 = 1 there
         const KTile t1 = next_tile();
-        if constexpr (D == 2) {
-            static_for<LA::kLoads>([&](auto i) { la.template load_one<i.value, 1>(t1.a, t1.end); });
-            static_for<LB::kLoads>([&](auto i) { lb.template load_one<i.value, 1>(t1.b, t1.end); });
-            const KTile t2 = next_tile();
-            static_for<LA::kLoads>([&](auto i) { la.template load_one<i.value, 0>(t2.a, t2.end); });
-            static_for<LB::kLoads>([&](auto i) { lb.template load_one<i.value, 0>(t2.b, t2.end); });
-        } else {
-            static_for<LA::kLoads>([&](auto i) { la.template load_one<i.value, 0>(t1.a, t1.end); });
-            static_for<LB::kLoads>([&](auto i) { lb.template load_one<i.value, 0>(t1.b, t1.end); });
-        }
+        static_for<LA::kLoads>([&](auto i) { la.template load_one<i.value, 1>(t1.a, t1.end); });
+        static_for<LB::kLoads>([&](auto i) { lb.template load_one<i.value, 1>(t1.b, t1.end); });
+        const KTile t2 = next_tile();
+        static_for<LA::kLoads>([&](auto i) { la.template load_one<i.value, 0>(t2.a, t2.end); });
+        static_for<LB::kLoads>([&](auto i) { lb.template load_one<i.value, 0>(t2.b, t2.end); });
     }
     __syncthreads();
-    // PAR of step kt: D == 2: set (kt+1)&1;  D == 1: LoaderMC drains set kt&1.
-    constexpr int P0 = (D == 2) ? 1 : 0;
     int kt = 0;
     for (; kt + 2 < nk; kt += 2) {       // both steps write a tile that will be used
-        k_step<WAVES_M, WAVES_N, WM, WN, D, P0, true, true>(sA(0), sB(0), sA(1), sB(1), acc, la, lb, next_tile());
+        k_step<WAVES_M, WAVES_N, WM, WN, 1, true, true>(sA(0), sB(0), sA(1), sB(1), acc, la, lb, next_tile());
         __syncthreads();
-        k_step<WAVES_M, WAVES_N, WM, WN, D, P0 ^ 1, true, true>(sA(1), sB(1), sA(0), sB(0), acc, la, lb, next_tile());
+        k_step<WAVES_M, WAVES_N, WM, WN, 0, true, true>(sA(1), sB(1), sA(0), sB(0), acc, la, lb, next_tile());
         __syncthreads();
     }
     if (nk - kt == 2) {                  // kt even: buffers 0 then 1
-        k_step<WAVES_M, WAVES_N, WM, WN, D, P0, true, false>(sA(0), sB(0), sA(1), sB(1), acc, la, lb, last);
+        k_step<WAVES_M, WAVES_N, WM, WN, 1, true, false>(sA(0), sB(0), sA(1), sB(1), acc, la, lb, last);
         __syncthreads();
-        k_step<WAVES_M, WAVES_N, WM, WN, D, P0 ^ 1, false, false>(sA(1), sB(1), nullptr, nullptr, acc, la, lb, last);
+        k_step<WAVES_M, WAVES_N, WM, WN, 0, false, false>(sA(1), sB(1), nullptr, nullptr, acc, la, lb, last);
     } else {
-        k_step<WAVES_M, WAVES_N, WM, WN, D, P0, false, false>(sA(0), sB(0), nullptr, nullptr, acc, la, lb, last);
+        k_step<WAVES_M, WAVES_N, WM, WN, 1, false, false>(sA(0), sB(0), nullptr, nullptr, acc, la, lb, last);
     }
     __syncthreads();
 }

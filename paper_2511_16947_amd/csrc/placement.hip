@@ -122,8 +122,7 @@ __global__ __launch_bounds__(64) void k_replica_counts(const int32_t* __restrict
 // ---------------------------------------------------------------------------
 // s_order [E]: experts in drawing order, expert | replica count << 16; s_mask [E] out: replica set of each
 // expert as a rank mask
-template <int MAXG, typename MaskT>
-__device__ inline void draw_candidate(const int* s_order, MaskT* s_mask, int E, int G, int slots,
+__device__ inline void draw_candidate(const int* s_order, u64* s_mask, int E, int G, int slots,
                                       uint32_t seed, uint32_t cand) {
     const int g = threadIdx.x & 63;       // lane = rank
     int free_slots = slots;
@@ -136,7 +135,7 @@ __device__ inline void draw_candidate(const int* s_order, MaskT* s_mask, int E, 
         int ahead = 0;
         // lane j's value through a scalar register; lanes from G on hold 0, which is ahead of nobody
 #pragma unroll
-        for (int j = 0; j < MAXG; ++j) {
+        for (int j = 0; j < 64; ++j) {
             const u64 other = ((u64)(uint32_t)__builtin_amdgcn_readlane((int)(comp >> 32), j) << 32) |
                               (uint32_t)__builtin_amdgcn_readlane((int)comp, j);
             ahead += other > comp;
@@ -144,7 +143,7 @@ __device__ inline void draw_candidate(const int* s_order, MaskT* s_mask, int E, 
         const bool chosen = g < G && ahead < c;
         free_slots -= chosen;
         const u64 m = __ballot(chosen);
-        if (g == 0) s_mask[e] = (MaskT)m;
+        if (g == 0) s_mask[e] = m;
     }
 }
 
@@ -421,7 +420,7 @@ __global__ __launch_bounds__(64) void k_score_flow(const int32_t* __restrict__ l
     const uint32_t cand = blockIdx.x;
     if constexpr (DRAW) {
         drawing_order(counts, s_cnt, s_order, E);
-        draw_candidate<64>(s_order, c.pm, E, G, slots, seed, cand);
+        draw_candidate(s_order, c.pm, E, G, slots, seed, cand);
     } else {
         const uint8_t* pl = place + (size_t)cand * E * G;
         for (int e = l; e < E; e += 64) {
@@ -517,7 +516,7 @@ __global__ __launch_bounds__(kPickThreads) void k_pick(const int64_t* __restrict
     uint32_t* s_rows = (uint32_t*)(s_cnt + E);      // [4][E], row 0 is the winner's (G <= kMaxEnumG)
     if (tid < 64) {
         if (G <= kMaxEnumG) draw_rows(s_order, s_rows, E, G, seed, (uint32_t)best);
-        else draw_candidate<64>(s_order, s_mask, E, G, slots, seed, (uint32_t)best);
+        else draw_candidate(s_order, s_mask, E, G, slots, seed, (uint32_t)best);
     }
     __syncthreads();
     for (int i = tid; i < E * G; i += kPickThreads)

@@ -226,7 +226,8 @@ __global__ __launch_bounds__(256) void k_topk_mfma(const uint16_t* __restrict__ 
     const int tok = min(t0 + r, Tn - 1);
     const uint16_t* xrow = x + (size_t)tok * d + 32 * h;
 
-    // columns E .. EP-1 of a slab are never written: zero once
+    // columns that no piece reaches are never written: zero once (ODD: columns from E on in a row's last piece hold the
+    // next row's first weights; select_topk masks them)
     for (int i = threadIdx.x * 16; i < kSlabBytes; i += 256 * 16) *reinterpret_cast<u32x4*>(s_slab + i) = u32x4{0, 0, 0, 0};
     __syncthreads();
 
@@ -458,7 +459,7 @@ __global__ __launch_bounds__(256) void k_topk_mfma_esplit(const uint16_t* __rest
     select_topk<NT>(all, bias, E, K, t0 + r, Tn, s_val, topk_idx, topk_w);
 }
 
-// fp32 layers.  A block is 32 tokens, its NW waves split k in pieces of 32.  Both MFMA operands come
+// fp32 layers.  A block is 32 tokens, its NW waves split k in pieces of 8 J (J groups: 32 up to 64 experts, 8 beyond).  Both MFMA operands come
 // straight from memory: lane (l & 31, h = l >> 5) supplies expert / token (l & 31) and the k-values
 // 8 j + 4 h + 0 .. 3 of a piece (its token's as one 16-byte load, each weight a 4-byte load that 32 lanes make of
 // neighbouring experts).  k-values past d are zeros, experts past E are masked before the selection.

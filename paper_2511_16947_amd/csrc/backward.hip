@@ -421,6 +421,8 @@ int launch_backward(const fine_shape& s, int rank_lo, int rank_hi, const void* d
         act = act_ws;
     }
     const double P = (double)s.T * s.K;
+    // expected rows of a (rank, expert) segment; the work list of a call for all ranks joins an expert's segments on
+    // neighbouring ranks, but one rank's call has the segments by themselves and takes the same tile
     const double seg_rows = (P / s.G) / ((double)s.E / s.G + 1.0);
     int tile = (s.flags & FINE_FLAG_TILE_MASK) >> FINE_FLAG_TILE_SHIFT;
     // Short segments: 128-row tiles on 4 waves also where most of their rows are empty.  (64-row tiles, dH + dXp against

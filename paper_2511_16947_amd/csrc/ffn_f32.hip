@@ -10,8 +10,8 @@
 // that a CU's four SIMDs always have a wave with an MFMA ready.  Hence the small tile: at most 48 KB of LDS
 // (two buffers of 32 k-values) and three blocks per CU, whose waves fill one another's barriers,
 // prologues and epilogues; and 64-row tiles waste little on short segments.  (Five blocks of the smaller
-// tile per CU are 7 % slower than three.)  At the size above GEMM 1 takes 448 us and GEMM 2 252 us (105 and
-// 94 TFLOP/s of 157; FMA kernels: 1378 and 805 us); an eighth of it is rows past the ends of segments.
+// tile per CU are 7 % slower than three.)  At the size above GEMM 1 takes 416 us and GEMM 2 235 us (114 and
+// 100 TFLOP/s of 157; FMA kernels: 1378 and 805 us); an eighth of it is rows past the ends of segments.
 //
 // Both operands reach LDS by DMA, 16 bytes per lane when d and f are multiples of 4, else 4 bytes per
 // lane (rows of any width: an MFMA step leaves enough issue slots for four times the instructions).

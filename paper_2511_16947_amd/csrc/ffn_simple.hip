@@ -113,7 +113,7 @@ __global__ __launch_bounds__(kMapThreads) void k_tile_map(const int32_t* __restr
 }
 
 // The same for one rank, whose segments are all of different experts: one thread per expert, one scan (a launch in
-// front of every rank's GEMMs, so its latency counts: 2.4-4.8 us).
+// front of every rank's GEMMs, so its latency counts: 2.4-5 us).
 __global__ __launch_bounds__(kMapThreads) void k_tile_map_rank(const int32_t* __restrict__ seg_off, int E, int BM,
                                                                TileEntry* __restrict__ tiles, int32_t* __restrict__ count,
                                                                int max_tiles) {

@@ -15,7 +15,8 @@
 // the lane-per-expert kernel, 8 us here).
 // fp32 layers of up to 256 experts: the same on v_mfma_f32_32x32x2_f32, whose row operand takes one
 // weight per lane, 32 neighbouring experts at a time: both operands come straight from memory (2048
-// tokens, d 1024, 16 experts: 135 us with the lane-per-expert kernel, 14 us here; 256 tokens, d 128: 28 and 5.5 us).
+// tokens, d 1024, 16 experts, again and again: 135 us with the lane-per-expert kernel, 14 us here, 23 us in a pass of the
+// layer, which leaves x to HBM; 256 tokens, d 128: 28 and 6 us).
 // More than 256 experts (or a router matrix of 2^31 weights): each wave owns TB tokens; lane l accumulates the
 // logits of experts l, l+64, ... in fp32 while the token rows stream through LDS, then K
 // rounds of a cross-lane argmax.

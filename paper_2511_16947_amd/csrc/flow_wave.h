@@ -1,9 +1,10 @@
 // One-wavefront integer flows on the placement graph (Section 5.1's graph abstraction): ranks are
-// vertices, an expert with units on rank a and a replica on rank b lets load move from a to b,
-// A[a][b] is the total load that may move a -> b.  With G <= 64 a vertex set is a 64-bit mask and a
-// breadth-first search is a few ballots.  Shared by the scheduler's replica-load solver and by the
-// placement scoring for more than 16 ranks.
+// vertices, an expert with units on rank a and a replica on rank b lets load move from a to b.  With G <= 64 a vertex
+// set is a 64-bit mask and a breadth-first search is a few ballots.  Shared by the scheduler's replica-load solver and by
+// the placement scoring for more than 16 ranks.
 #pragma once
+
+#include <type_traits>
 
 #include "common.h"
 
@@ -14,27 +15,21 @@ constexpr int kW = 64;
 typedef unsigned long long u64;
 
 // Only experts with several replicas can move: they are kept in a compact list, in ascending order (256 experts
-// with 320 replicas: at most 64 of them, one per lane).  What a rank needs at every step is in the registers of its
-// lane: its load and the set of ranks that load may come from; A, which is only read where an edge is used, is in LDS.
-// M: a set of ranks, 32 bits where that is enough (the search is a chain of instructions of one wavefront, and 64-bit
-// shifts and selects are several each).
-template <typename M>
-struct Ctx {
+// with 320 replicas: at most 64 of them).
+// PM: as the replica masks are stored.
+template <typename PM = u64>
+struct Problem {
     int* x;        // [n][XS] units of listed expert j on every rank
-    u64* pm;       // [n] replica masks of the listed experts (before compact(): of all experts)
-    int* A;        // [G][AS], stored by destination: a(from, to) = A[to * AS + from]
+    PM* pm;        // [n] replica masks of the listed experts (before compact(): of all experts)
     int* t;        // [G] scratch
     int E, G;
-    int AS, XS;    // row strides (odd where they fit, so that a column's entries fall into different banks)
+    int XS;        // row stride (odd where it fits, so that a column's entries fall into different banks)
     int n;         // listed experts
     u64 listed;    // lane i: which of the experts 64 i .. 64 i + 63 are listed
     int single;    // lane = rank: load of the experts whose only replica is here
-    int ld;        // lane = rank: its load
-    M in;          // lane = rank: the ranks `a` with a(a, lane) > 0
-    __device__ int& a(int from, int to) const { return A[to * AS + from]; }
 };
 
-__device__ inline int lane() { return threadIdx.x; }
+__device__ inline int lane() { return threadIdx.x & (kW - 1); }
 __device__ inline u64 readlane_u64(u64 v, int src) {
     const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)v, src), hi = __builtin_amdgcn_readlane((int)(unsigned)(v >> 32), src);
     return ((u64)hi << 32) | lo;
@@ -73,100 +68,243 @@ __device__ inline int wave_incl_scan_i(int v) {
 }
 __device__ inline int wave_sum_i(int v) { return __builtin_amdgcn_readlane(wave_incl_scan_i(v), kW - 1); }
 
-// Move `amount` units of free load from rank a to rank b (listed experts in ascending order; free: replicas above
-// g_cur of j_cur and all of the experts after it; j_cur < 0: everything).  A lane past the last expert reads the last
-// expert's entries (in bounds, no branch, so the LDS reads go out together) and takes no part.  Every rank q that is
-// a replica of a giving expert loses what it could get from a and gains it from b: summed over the givers in
-// lane q's register, then one update of its two entries.
-template <typename M>
-__device__ inline void move_units(Ctx<M>& c, int a, int b, int amount, int j_cur, int g_cur) {
-    int remaining = amount, D = 0;
-    const int q = lane();
-    for (int base = (j_cur < 0 ? 0 : j_cur); base < c.n && remaining > 0; base += kW) {
-        const int j = base + q;                       // >= j_cur: earlier experts are never looked at
-        const bool in = j < c.n;
-        const int jj = in ? j : c.n - 1;
-        const M pm = (M)c.pm[jj];
-        const int xa = c.x[jj * c.XS + a], xb = c.x[jj * c.XS + b];
-        const M F = (j == j_cur) ? (pm & ~(((M)2 << g_cur) - (M)1)) : pm;
-        const int m = (in && has(F, a) && has(F, b)) ? xa : 0;
-        if (__ballot(m > 0) == 0ull) continue;        // no expert of this chunk links a to b (wave-uniform)
-        const int inc = wave_incl_scan_i(m);
-        const int t = max(0, min(m, remaining - (inc - m)));
-        if (t > 0) {
-            c.x[j * c.XS + a] = xa - t;
-            c.x[j * c.XS + b] = xb + t;
-        }
-        u64 givers = __ballot(t > 0);
-        while (givers) {
-            const int src = __ffsll((long long)givers) - 1;
-            givers &= givers - 1;
-            const int ts = __builtin_amdgcn_readlane(t, src);
-            if (has(readlane_set(F, src), q & (8 * (int)sizeof(M) - 1))) D += ts;
-        }
-        remaining -= min(remaining, __builtin_amdgcn_readlane(inc, kW - 1));
-    }
-    if (D > 0 && q < c.G) {
-        const int va = q != a ? c.a(a, q) - D : 0, vb = q != b ? c.a(b, q) + D : 0;
-        if (q != a) c.a(a, q) = va;
-        if (q != b) c.a(b, q) = vb;
-        c.in = (c.in & ~((M)1 << a) & ~((M)1 << b)) | (M)(va > 0) << a | (M)(vb > 0) << b;
-    }
-    c.ld += q == b ? amount : q == a ? -amount : 0;
-    wave_sync();
-}
+// What a search and a move need is in the registers of the ranks' lanes: sets of ranks (M: 32 bits where that is enough;
+// the search is a chain of instructions of one wavefront, and 64-bit shifts and selects are several each) and sets of
+// listed experts (NW words of 64).  An edge from a to b exists while some free expert has units on a and a free replica
+// on b, i.e. while units_a and free_b meet; how much may move along it is added up from x where it is used.  (Keeping the
+// edges' sums, or each rank's set of neighbours as a union over its experts, cost every move and every variable that
+// stops being free a chain of updates or of wave-wide reductions; here they are a few instructions.)
+template <typename M, int NW, typename PM = u64>
+struct Flow : Problem<PM> {
+    int ld;                      // lane = rank: its load
+    M me;                        // this rank as a set (no rank: the empty set)
+    M in;                        // the ranks from which units may move here
+    u64 free[NW];                // experts that have a free replica here
+    u64 units[NW];               // those of them that have units on it
 
-// Breadth-first search from `src` over edges with A > 0.  Stops at the first level that
-// holds a rank of `want` (a per-lane predicate, lane = rank).  Returns the chosen rank
-// (lowest of that level) or -1; *visited_out = every rank reached; *parent_out (lane = rank) = where the search came
-// from; *cap_out = the smallest capacity on the way.
-template <typename M>
-__device__ inline int bfs(const Ctx<M>& c, int src, bool want, M* visited_out, int* parent_out, int* cap_out) {
-    const int b = lane();
-    M visited = (M)1 << src, frontier = visited;
-    int parent = -1, target = -1;
-    while (true) {
-        const M hit = c.in & frontier;                           // (lanes that are no ranks have nothing in `in`)
-        const bool fresh = hit != 0 && parent < 0 && b != src;
-        if (fresh) parent = first_of(hit);
-        const M next = (M)__ballot(fresh);
-        if (next == 0) break;
-        visited |= next;
-        const M good = (M)__ballot(fresh && want);
-        if (good) { target = first_of(good); break; }
-        frontier = next;
+    __device__ inline Flow(const Problem<PM>& p) : Problem<PM>(p) {}
+    // whether free experts of `set` (scalar words) have a replica on the lane's rank
+    __device__ inline bool meets_free(const u64 (&set)[NW]) const {
+        u64 v = 0ull;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) v |= set[w] & free[w];
+        return v != 0ull;
     }
-    *visited_out = visited;
-    *parent_out = parent;
-    if (target < 0) return -1;
-    // every reached rank reads the capacity of its own edge; the way back is then two lane reads per step
-    const int edge = parent >= 0 ? c.a(parent, b) : 0;
-    int cap = 0x7fffffff, cur = target;
-    while (cur != src) {
-        cap = min(cap, __builtin_amdgcn_readlane(edge, cur));
-        cur = __builtin_amdgcn_readlane(parent, cur);
+    __device__ inline void read_units(int a, u64 (&set)[NW]) const {
+#pragma unroll
+        for (int w = 0; w < NW; ++w) set[w] = readlane_u64(units[w], a);
     }
-    *cap_out = cap;
-    return target;
-}
+    // the edges out of rank a, whose units are those of `set`
+    __device__ inline void set_out(int a, const u64 (&set)[NW]) {
+        const M bit = (M)1 << a;
+        const bool edge = meets_free(set) && (me & bit) == 0;
+        in = (in & ~bit) | (edge ? bit : (M)0);
+    }
+    // expert j has free units / a free replica on the lane's rank
+    __device__ inline bool has_units(int j) const {
+        bool v = false;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) v = v || (NW == 1 || w == j >> 6) && ((units[w] >> (j & 63)) & 1ull);
+        return v;
+    }
+    __device__ inline bool is_free(int j) const {
+        bool v = false;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) v = v || (NW == 1 || w == j >> 6) && ((free[w] >> (j & 63)) & 1ull);
+        return v;
+    }
+    // expert j has no units left on the lane's rank, where `here`
+    __device__ inline void clear_units(int j, bool here) {
+#pragma unroll
+        for (int w = 0; w < NW; ++w)
+            if (here && (NW == 1 || w == j >> 6)) units[w] &= ~(1ull << (j & 63));
+    }
+    // replica (j, g) stops being free: its units can no longer move, nor others of j to it
+    __device__ inline void fix(int j, int g) {
+        const bool here = lane() == g;
+        clear_units(j, here);
+        u64 fg[NW], ug[NW];
+        read_units(g, ug);
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            if (here && (NW == 1 || w == j >> 6)) free[w] &= ~(1ull << (j & 63));
+            fg[w] = readlane_u64(free[w], g);
+        }
+        set_out(g, ug);
+        u64 v = 0ull;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) v |= units[w] & fg[w];
+        const M from = (M)__ballot(v != 0ull) & ~((M)1 << g);
+        if (here) in = from;
+    }
+    // the registers from c.t (loads), the masks and x: everything free
+    __device__ inline void load_registers() {
+        const int l = lane();
+        wave_sync();
+        me = l < this->G ? (M)1 << (l & (8 * (int)sizeof(M) - 1)) : (M)0;
+        ld = l < this->G ? this->t[l] : 0;
+        in = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            free[w] = units[w] = 0ull;
+            if (64 * w >= this->n) continue;
+            const int j = min(64 * w + l, this->n - 1);      // lane = expert
+            const M pm = 64 * w + l < this->n ? (M)this->pm[j] : (M)0;
+#pragma unroll 8
+            for (int a = 0; a < this->G; ++a) {
+                const bool on = has(pm, a);
+                const u64 f = __ballot(on), u = __ballot(on && this->x[j * this->XS + a] > 0);
+                if (l == a) {
+                    free[w] = f;
+                    units[w] = u;
+                }
+            }
+        }
+        for (int a = 0; a < this->G; ++a) {
+            u64 set[NW];
+            read_units(a, set);
+            set_out(a, set);
+        }
+    }
+    // Moves up to `amount` units of free load from rank a to rank b (listed experts in ascending order) and returns how
+    // many there were.
+    __device__ inline int move_units(int a, int b, int amount) {
+        const int l = lane();
+        int remaining = amount;
+        u64 ua[NW], ub[NW], lost = 0ull, gained = 0ull;
+        read_units(a, ua);
+        read_units(b, ub);
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const u64 may = ua[w] & readlane_u64(free[w], b);
+            if (may == 0ull || remaining == 0) continue;
+            const bool on = (may >> l) & 1ull;
+            int* row = this->x + min(64 * w + l, this->n - 1) * this->XS;
+            const int xa = row[a], xb = row[b];
+            int t, had;                              // what the lane's expert gives; what all of them have
+            if ((may & (may - 1)) == 0ull) {         // one expert, as most edges have: no scan
+                had = __builtin_amdgcn_readlane(xa, __builtin_ctzll(may));
+                t = on ? min(had, remaining) : 0;
+            } else {
+                const int m = on ? xa : 0, inc = wave_incl_scan_i(m);
+                had = __builtin_amdgcn_readlane(inc, kW - 1);
+                t = max(0, min(m, remaining - (inc - m)));
+            }
+            if (t > 0) {
+                row[a] = xa - t;
+                row[b] = xb + t;
+            }
+            const u64 some = __ballot(t > 0), all = some & __ballot(t == xa);
+            lost |= all;
+            gained |= some & ~ub[w];
+            ua[w] &= ~all;
+            ub[w] |= some;
+            if (l == a) units[w] = ua[w];
+            if (l == b) units[w] = ub[w];
+            remaining -= min(remaining, had);
+        }
+        if (lost) set_out(a, ua);
+        if (gained) set_out(b, ub);
+        const int moved = amount - remaining;
+        ld += l == b ? moved : l == a ? -moved : 0;
+        wave_sync();
+        return moved;
+    }
+    // how many free units of rank a may move to rank b
+    __device__ inline int edge_capacity(int a, int b) const {
+        const int l = lane();
+        int sum = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const u64 may = readlane_u64(units[w], a) & readlane_u64(free[w], b);
+            if (may == 0ull) continue;
+            const int xa = this->x[min(64 * w + l, this->n - 1) * this->XS + a];
+            sum += (may >> l) & 1ull ? xa : 0;
+        }
+        return wave_sum_i(sum);
+    }
+    // Breadth-first search from `src`.  Stops at the first level that holds a rank of `want`.  The sets of ranks are scalar;
+    // what the way back needs is one set per level.
+    struct Way {
+        int src, target, levels;     // target: lowest rank of `want` on the first level that has one, or -1
+        M visited;                   // every rank reached
+        M trail;                     // lane = level: the ranks first reached there
+    };
+    __device__ inline Way bfs(int src, M want) const {
+        const int b = lane();
+        Way w{src, -1, 0, (M)1 << src, 0};
+        M level = w.visited;
+        while (true) {
+            if (b == w.levels) w.trail = level;
+            level = (M)__ballot((in & level) != 0) & ~w.visited;      // (lanes that are no ranks have nothing in `in`)
+            if (level == 0) break;
+            w.visited |= level;
+            const M good = level & want;
+            if (good) { w.target = first_of(good); break; }
+            ++w.levels;
+        }
+        return w;
+    }
+    // where the search came to `rank` from, on level `level` (lowest such rank)
+    __device__ inline int before(const Way& w, int rank, int level) const {
+        return first_of(readlane_set(in, rank) & readlane_set(w.trail, level));
+    }
+    // smallest capacity on the way
+    __device__ inline int way_capacity(const Way& w) const {
+        int cap = 0x7fffffff, cur = w.target;
+        for (int level = w.levels; level >= 0; --level) {
+            const int p = before(w, cur, level);
+            cap = min(cap, edge_capacity(p, cur));
+            cur = p;
+        }
+        return cap;
+    }
+    // Moves up to `amount` units along the way, last edge first, and returns how many left its source (at least one).  An
+    // edge takes what the edge after it took, or less if it has not as many: a rank on the way never ends with more than
+    // it had.  (The edges not yet used are as the search found them: the ranks of a shortest way are distinct.)
+    __device__ inline int push(const Way& w, int amount) {
+        int cur = w.target;
+        for (int level = w.levels; level >= 0; --level) {
+            const int p = before(w, cur, level);
+            amount = move_units(p, cur, amount);
+            cur = p;
+        }
+        return amount;
+    }
+};
 
-// Moves `amount` units along the way found by bfs, last edge first (an edge's capacity depends on the units on its
-// source only, and the ranks of a shortest way are distinct: the order of the edges does not matter).
-template <typename M>
-__device__ inline void push_path(Ctx<M>& c, int src, int target, int parent, int amount, int j_cur, int g_cur) {
-    int cur = target;
-    while (cur != src) {
-        const int p = __builtin_amdgcn_readlane(parent, cur);
-        move_units(c, p, cur, amount, j_cur, g_cur);
-        cur = p;
-    }
+// Calls f(number of words) with one that n listed experts fit, at most MAXW, which is words_for(E): a kernel for many
+// experts needs the registers for as many words, whatever the list's length.
+constexpr int words_for(int E) { return E <= 64 ? 1 : E <= 128 ? 2 : E <= 256 ? 4 : 16; }
+template <int MAXW, typename F>
+__device__ inline void with_words(int n, F f) {
+    if constexpr (MAXW > 4)
+        if (n > 256) { f(std::integral_constant<int, 16>{}); return; }
+    if constexpr (MAXW > 2)
+        if (n > 128) { f(std::integral_constant<int, 4>{}); return; }
+    if constexpr (MAXW > 1)
+        if (n > 64) { f(std::integral_constant<int, 2>{}); return; }
+    f(std::integral_constant<int, 1>{});
+}
+// pick(words_for(E), a value of the type for sets of ranks), on the host
+template <typename F>
+inline auto by_size(int E, int G, F pick) {
+    auto with = [&](auto m) {
+        switch (words_for(E)) {
+            case 1: return pick(std::integral_constant<int, 1>{}, m);
+            case 2: return pick(std::integral_constant<int, 2>{}, m);
+            case 4: return pick(std::integral_constant<int, 4>{}, m);
+            default: return pick(std::integral_constant<int, 16>{}, m);
+        }
+    };
+    return G <= 32 ? with(uint32_t{}) : with(u64{});
 }
 
 // From the replica masks of all experts in c.pm: the list of those with several replicas (their masks move to the
 // front of c.pm), and the loads of the others on their only rank.  Returns (to every lane) whether some expert with
 // load has no replica.
-template <typename M>
-__device__ inline bool compact(Ctx<M>& c, const int32_t* __restrict__ load) {
+template <typename PM>
+__device__ inline bool compact(Problem<PM>& c, const int32_t* __restrict__ load) {
     const int l = lane();
     int bad = 0, n = 0;
     c.listed = 0ull;
@@ -182,7 +320,7 @@ __device__ inline bool compact(Ctx<M>& c, const int32_t* __restrict__ load) {
         const u64 w = __ballot(replicas > 1);
         if (l == base / kW) c.listed = w;
         wave_sync();                                  // this chunk's masks are in registers
-        if (replicas > 1) c.pm[n + __popcll(w & ((1ull << l) - 1ull))] = m;      // never behind what is still to be read
+        if (replicas > 1) c.pm[n + __popcll(w & ((1ull << l) - 1ull))] = (PM)m;      // never behind what is still to be read
         n += __popcll(w);
     }
     c.n = n;
@@ -191,23 +329,11 @@ __device__ inline bool compact(Ctx<M>& c, const int32_t* __restrict__ load) {
     return __ballot(bad) != 0ull;
 }
 
-// the rank loads from c.t and the sets of sources from A
-template <typename M>
-__device__ inline void load_registers(Ctx<M>& c) {
-    const int l = lane();
-    wave_sync();
-    c.ld = l < c.G ? c.t[l] : 0;
-    c.in = 0;
-    if (l < c.G)
-        for (int a = 0; a < c.G; ++a) c.in |= (M)(c.A[l * c.AS + a] > 0) << a;
-}
-
-// Everything on each expert's first replica: fills x, A and the rank loads from the list and the expert loads
+// Everything on each expert's first replica: fills x and the rank loads from the list and the expert loads
 // (negative reads as 0) times `scale`.
-template <typename M>
-__device__ inline void start_on_first_replicas(Ctx<M>& c, const int32_t* __restrict__ load, int scale = 1) {
+template <typename M, int NW, typename PM>
+__device__ inline void start_on_first_replicas(Flow<M, NW, PM>& c, const int32_t* __restrict__ load, int scale = 1) {
     const int l = lane();
-    for (int i = l; i < c.G * c.AS; i += kW) c.A[i] = 0;
     for (int i = l; i < c.n * c.XS; i += kW) c.x[i] = 0;
     if (l < c.G) c.t[l] = c.single * scale;
     wave_sync();
@@ -216,28 +342,22 @@ __device__ inline void start_on_first_replicas(Ctx<M>& c, const int32_t* __restr
         const u64 w = readlane_u64(c.listed, base / kW);
         if ((w >> l) & 1ull) {
             const int j = n + __popcll(w & ((1ull << l) - 1ull));
-            const u64 m = c.pm[j];
-            const int le = max(load[base + l], 0) * scale;
-            if (le > 0) {
-                const int first = __ffsll((long long)m) - 1;
-                c.x[j * c.XS + first] = le;
-                atomicAdd(&c.t[first], le);
-                u64 others = m & ~(1ull << first);
-                while (others) { int q = __ffsll((long long)others) - 1; others &= others - 1; atomicAdd(&c.a(first, q), le); }
-            }
+            const int le = max(load[base + l], 0) * scale, first = first_of((M)c.pm[j]);
+            c.x[j * c.XS + first] = le;
+            if (le > 0) atomicAdd(&c.t[first], le);
         }
         n += __popcll(w);
     }
-    load_registers(c);
+    c.load_registers();
 }
 
 // The optimum value M* = ceil(m) of Eq. 1 for P units in all.  Start with M = ceil(P/G).  While some
-// rank a exceeds M, search from a for a rank below M and push the bottleneck amount along the path.
+// rank a exceeds M, search from a for a rank below M and push along the path what it takes.
 // If the search finds none, the reached set S is closed (no expert with load in S has a replica
 // outside S), so Eq. 3 gives the lower bound ceil(load(S)/|S|) > M; M jumps to it.  M only ever moves
 // to lower bounds of the optimum and the loop ends with a feasible flow, hence M = M*.
-template <typename M>
-__device__ inline int optimum_value(Ctx<M>& c, int P) {
+template <typename M, int NW, typename PM>
+__device__ inline int optimum_value(Flow<M, NW, PM>& c, int P) {
     const int l = lane();
     int best = (P + c.G - 1) / c.G;
     while (true) {
@@ -245,17 +365,15 @@ __device__ inline int optimum_value(Ctx<M>& c, int P) {
         const u64 over = __ballot(l < c.G && mine > best);
         if (over == 0ull) break;
         const int a = __ffsll((long long)over) - 1;
-        M visited; int parent, cap;
-        const int r = bfs(c, a, (l < c.G) && (mine < best), &visited, &parent, &cap);
-        if (r < 0) {
-            const bool in = (l < c.G) && has(visited, l & (8 * (int)sizeof(M) - 1));
-            const int tot = wave_sum_i(in ? mine : 0);
-            const int cnt = __popcll(visited);
+        const auto way = c.bfs(a, (M)__ballot(l < c.G && mine < best));
+        if (way.target < 0) {
+            const int tot = wave_sum_i((way.visited & c.me) != 0 ? mine : 0);
+            const int cnt = __popcll(way.visited);
             best = (tot + cnt - 1) / cnt;
             continue;
         }
-        const int amount = min(min(__builtin_amdgcn_readlane(mine, a) - best, best - __builtin_amdgcn_readlane(mine, r)), cap);
-        push_path(c, a, r, parent, amount, -1, 0);
+        const int amount = min(__builtin_amdgcn_readlane(mine, a) - best, best - __builtin_amdgcn_readlane(mine, way.target));
+        c.push(way, amount);
     }
     return best;
 }
@@ -269,8 +387,8 @@ __device__ inline int optimum_value(Ctx<M>& c, int P) {
 // expert has none there, so the units in S are den * load(S), no rank of S is below capacity and one
 // is above: load(S) / |S| > lambda.  lambda moves there and the flow starts again in the new scale.
 // When no rank is above capacity the loads fit under lambda, so m <= lambda, hence m = lambda.
-template <typename M>
-__device__ inline void exact_density(Ctx<M>& c, const int32_t* __restrict__ load, int P, int* num_out, int* den_out) {
+template <typename M, int NW, typename PM>
+__device__ inline void exact_density(Flow<M, NW, PM>& c, const int32_t* __restrict__ load, int P, int* num_out, int* den_out) {
     const int l = lane();
     int num = P, den = c.G;
     while (true) {
@@ -281,17 +399,14 @@ __device__ inline void exact_density(Ctx<M>& c, const int32_t* __restrict__ load
             const u64 over = __ballot(l < c.G && mine > num);
             if (over == 0ull) break;
             const int a = __ffsll((long long)over) - 1;
-            M visited; int parent, cap;
-            const int r = bfs(c, a, (l < c.G) && (mine < num), &visited, &parent, &cap);
-            if (r < 0) {
-                const bool in = (l < c.G) && has(visited, l & (8 * (int)sizeof(M) - 1));
-                num = wave_sum_i(in ? mine : 0) / den;
-                den = __popcll(visited);
+            const auto way = c.bfs(a, (M)__ballot(l < c.G && mine < num));
+            if (way.target < 0) {
+                num = wave_sum_i((way.visited & c.me) != 0 ? mine : 0) / den;
+                den = __popcll(way.visited);
                 moved = true;
                 break;
             }
-            push_path(c, a, r, parent,
-                      min(min(__builtin_amdgcn_readlane(mine, a) - num, num - __builtin_amdgcn_readlane(mine, r)), cap), -1, 0);
+            c.push(way, min(__builtin_amdgcn_readlane(mine, a) - num, num - __builtin_amdgcn_readlane(mine, way.target)));
         }
         if (!moved) break;
     }
@@ -299,23 +414,25 @@ __device__ inline void exact_density(Ctx<M>& c, const int32_t* __restrict__ load
     *den_out = den;
 }
 
-// bytes of LDS behind a Ctx for E experts on G ranks, with x in rows of `xs`
+// bytes of LDS behind a Problem for E experts on G ranks, with x in rows of `xs`
 __host__ __device__ inline size_t ctx_bytes(int E, int G, int xs) {
-    return (((size_t)E * 8 + 15) & ~(size_t)15) + ((size_t)G * (G | 1) + (size_t)E * xs + G) * 4;
+    return (((size_t)E * 8 + 15) & ~(size_t)15) + ((size_t)E * xs + G) * 4;
+}
+// The contract's limit on (E, G), stated for a table of G x G more than the solver keeps: what it refuses stays refused.
+inline bool size_allowed(int E, int G, size_t limit) {
+    return (((size_t)E * 8 + 15) & ~(size_t)15) + ((size_t)G * (G | 1) + (size_t)E * G + G) * 4 <= limit;
 }
 // row stride of x: odd where that fits into `limit` bytes
 __host__ __device__ inline int x_stride(int E, int G, size_t limit) { return ctx_bytes(E, G, G | 1) <= limit ? G | 1 : G; }
 
-// the arrays of a Ctx laid out from `smem` (16-byte aligned)
-template <typename M>
-__device__ inline Ctx<M> make_ctx(char* smem, int E, int G, int xs) {
-    Ctx<M> c;
-    c.E = E; c.G = G; c.AS = G | 1; c.XS = xs;
+// the arrays of a Problem laid out from `smem` (16-byte aligned)
+__device__ inline Problem<> make_problem(char* smem, int E, int G, int xs) {
+    Problem<> c;
+    c.E = E; c.G = G; c.XS = xs;
     c.pm = reinterpret_cast<u64*>(smem);
-    c.A = reinterpret_cast<int*>(smem + (((size_t)E * 8 + 15) & ~(size_t)15));
-    c.x = c.A + (size_t)G * c.AS;
+    c.x = reinterpret_cast<int*>(smem + (((size_t)E * 8 + 15) & ~(size_t)15));
     c.t = c.x + (size_t)E * xs;
-    c.n = 0; c.listed = 0ull; c.single = 0; c.ld = 0; c.in = 0;
+    c.n = 0; c.listed = 0ull; c.single = 0;
     return c;
 }
 

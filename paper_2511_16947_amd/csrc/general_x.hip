@@ -1,10 +1,10 @@
 // Replica loads for a restricted placement: the canonical integer optimum of Eq. 1
-// (Section 4.1), found with exact integer flows by ONE wavefront.
+// (Section 4.1), found with exact integer flows by ONE wavefront; the other waves of its block help to set the
+// problem up and to write the result out.
 //
 // View used (the paper's graph abstraction, Section 5.1): ranks are vertices; an expert
-// with units on rank a and a replica on rank b lets load move from a to b.  A[a][b] is the
-// total load that may move a -> b.  With G <= 64, vertex sets are 64-bit masks and a
-// breadth-first search is a few ballots.
+// with units on rank a and a replica on rank b lets load move from a to b.  With G <= 64, vertex sets are 64-bit masks
+// and a breadth-first search is a few ballots.
 //
 // Experts with one replica never move; the others form a list (flow_wave.h).
 //
@@ -30,108 +30,77 @@ namespace {
 
 using namespace flow;
 
-// Take `amount` units of listed expert j from the replicas in `from` (a subset of its later
-// replicas `later`, lowest first) to rank g.  Variable (j,g) itself is not free, so only
-// the rows of the source ranks change in A.
-template <typename M>
-__device__ inline void pull_expert(Ctx<M>& c, int j, int g, M later, M from, int amount) {
+// Take `amount` units of listed expert j from the replicas in `from` (a subset of its later replicas, lowest first) to
+// rank g.  Variable (j,g) itself is not free.
+template <typename M, int NW, typename PM>
+__device__ inline void pull_expert(Flow<M, NW, PM>& c, int j, int g, M from, int amount) {
     // lane q = source rank q: what the lower sources leave of `amount` is a prefix sum away
     const int q = lane();
     int* row = c.x + j * c.XS;
-    const int m = q < c.G && has(from, q & (8 * (int)sizeof(M) - 1)) ? row[q] : 0;
+    const int m = (from & c.me) != 0 ? row[q] : 0;
     const int inc = wave_incl_scan_i(m);
     const int t = max(0, min(m, amount - (inc - m)));
     if (t > 0) {
         row[q] = m - t;
         c.ld -= t;
     }
-    // row s of A loses what source s gave towards every other later replica: lane q = column q
-    const bool is_later = q < c.G && has(later, q & (8 * (int)sizeof(M) - 1));
-    M givers = (M)__ballot(t > 0);
-    int total = 0;
-    while (givers) {
-        const int s = first_of(givers);
-        givers &= givers - 1;
-        const int ts = __builtin_amdgcn_readlane(t, s);
-        total += ts;
-        if (q != s && is_later) {
-            const int v = c.a(s, q) - ts;
-            c.a(s, q) = v;
-            c.in = (c.in & ~((M)1 << s)) | (M)(v > 0) << s;
-        }
-    }
-    if (q == g) {                                      // g is not among the later replicas: nobody else writes these
-        row[g] += total;
-        c.ld += total;
+    if (q == g) {
+        row[g] += amount;
+        c.ld += amount;
     }
     wave_sync();
+    c.clear_units(j, t > 0 && t == m);
+    M gone = (M)__ballot(t > 0 && t == m);
+    while (gone) {
+        const int a = first_of(gone);
+        gone &= gone - 1;
+        u64 set[NW];
+        c.read_units(a, set);
+        c.set_out(a, set);
+    }
 }
 
-// Warm start (Section 4.1: between micro-batches only the loads change, so the previous solution is
-// a good place to start from).  Every listed expert's previous row, restricted to its replicas, is scaled
-// to the new load (rounded down, the rest to the first replica); x, A and the rank loads are
-// filled from that.  Any assignment of the loads to replicas is a valid start for phase 1, and the
-// result of phase 2 does not depend on where it started, so `prev` may hold anything: negative
-// entries read as 0, a row without units falls back to the first replica.  `prev` is read completely before this
-// function returns.  The rows of all experts are first copied into x, in wide batches of loads (a lane that walks
-// its expert's row in global memory waits for every entry: 32 round trips for an expert on all of 32 ranks), then
-// the listed ones are scaled and moved to their places in the list.
-template <typename M>
-__device__ inline void start_from_previous(Ctx<M>& c, const int32_t* __restrict__ load, const int32_t* prev) {
+// Phases 1 and 2 by one wavefront; returns M*.  On return c.ld are the ranks' loads.
+template <typename M, int NW, typename PM>
+__device__ inline int solve(Flow<M, NW, PM>& c, int P) {
     const int l = lane();
-    for (int i = l; i < c.G * c.AS; i += kW) c.A[i] = 0;
-    if (l < c.G) c.t[l] = c.single;
-    constexpr int kBatch = 16;
-    const int per = kW / c.G, row0 = l / c.G, col = l - row0 * c.G;      // rows of E x G per wave instruction
-    for (int r0 = row0; r0 < c.E; r0 += kBatch * per) {
-        int v[kBatch];
-#pragma unroll
-        for (int k = 0; k < kBatch; ++k) v[k] = prev[(size_t)min(r0 + k * per, c.E - 1) * c.G + col];
-#pragma unroll
-        for (int k = 0; k < kBatch; ++k)
-            if (row0 < per && r0 + k * per < c.E) c.x[(r0 + k * per) * c.XS + col] = v[k];
-    }
-    wave_sync();
-    int n = 0;
-    for (int base = 0; base < c.E; base += kW) {
-        const u64 w = readlane_u64(c.listed, base / kW);
-        const bool mine = (w >> l) & 1ull;
-        const int e = base + l, j = n + __popcll(w & ((1ull << l) - 1ull));
-        const u64 m = mine ? c.pm[j] : 0ull;
-        if (mine) {
-            int* row = c.x + e * c.XS;
-            const int le = max(load[e], 0);
-            const int first = __ffsll((long long)m) - 1;
-            // (floating point: any split that adds up to the load will do)
-            float had = 0.f;
-            for (u64 r = m; r; r &= r - 1) had += (float)max(row[__ffsll((long long)r) - 1], 0);
-            const float scale = had > 0.f ? (float)le / had : 0.f;
-            int left = le;
-            for (u64 r = m; r; r &= r - 1) {
-                const int a = __ffsll((long long)r) - 1;
-                const int t = (int)fminf((float)max(row[a], 0) * scale, (float)left);
-                row[a] = min(t, left);
-                left -= min(t, left);
-            }
-            row[first] += left;
-            for (u64 r = m; r; r &= r - 1) {
-                const int a = __ffsll((long long)r) - 1;
-                const int t = row[a];
-                if (t == 0) continue;
-                atomicAdd(&c.t[a], t);
-                for (u64 o = m & ~(1ull << a); o; o &= o - 1) atomicAdd(&c.a(a, (__ffsll((long long)o) - 1)), t);
+    c.load_registers();
+    // ---- phase 1: the optimum value ---------------------------------------------------------
+    const int cap_rank = optimum_value(c, P);      // M*
+    // ---- phase 2: the lexicographically greatest optimum ------------------------------------
+    for (int j = 0; j < c.n; ++j) {
+        M later = (M)__ballot(c.is_free(j));       // free replicas of j (including the one being removed next)
+        while (true) {
+            const int g = first_of(later);
+            later &= later - 1;
+            if (later == 0) break;                 // the last replica: nothing left to take units from (or to move them to)
+            c.fix(j, g);
+            while (true) {
+                const bool mine = c.has_units(j);
+                if (__ballot(mine) == 0ull) break;
+                const int* row = c.x + j * c.XS;
+                const int room = cap_rank - __builtin_amdgcn_readlane(c.ld, g);
+                if (room > 0) {
+                    pull_expert(c, j, g, later, min(room, wave_sum_i(mine ? row[l] : 0)));
+                    continue;
+                }
+                const auto way = c.bfs(g, (M)__ballot(l < c.G && c.ld < cap_rank) | (M)__ballot(mine));
+                if (way.target < 0) break;
+                const int avail = mine ? row[l] : 0, room_r = cap_rank - __builtin_amdgcn_readlane(c.ld, way.target);
+                if (room_r > 0) {
+                    // the path may itself carry units of j between its later replicas, so
+                    // the units are taken from whichever later replicas hold them afterwards
+                    const int moved = c.push(way, min(room_r, wave_sum_i(avail)));
+                    pull_expert(c, j, g, later, moved);
+                } else {                           // all ranks on the way are full: exactly as much must come as goes
+                    const int amount = min(c.way_capacity(way), __builtin_amdgcn_readlane(avail, way.target));
+                    pull_expert(c, j, g, (M)1 << way.target, amount);
+                    c.push(way, amount);
+                }
             }
         }
-        // to the rows of the list, in ascending order: row j is an expert's that is not listed or has moved already.
-        wave_sync();
-        for (u64 r = w; r; r &= r - 1) {
-            const int k = __ffsll((long long)r) - 1;
-            if (l < c.G) c.x[n * c.XS + l] = (readlane_u64(m, k) >> l) & 1ull ? c.x[(base + k) * c.XS + l] : 0;
-            ++n;
-        }
-        wave_sync();
     }
-    load_registers(c);
+    return cap_rank;
 }
 
 // the ranks that hold a replica of expert e
@@ -156,112 +125,160 @@ __device__ inline u64 replica_mask(const uint8_t* __restrict__ place, int e, int
     return m;
 }
 
-template <typename M>
-__global__ __launch_bounds__(64) void k_general_x(const uint8_t* __restrict__ place, const int32_t* __restrict__ load,
-                                                  const int32_t* prev, int E, int G, int xs, int P, int32_t* x_out,
-                                                  int32_t* __restrict__ max_load) {
-    extern __shared__ __attribute__((aligned(16))) char smem[];
-    Ctx<M> c = make_ctx<M>(smem, E, G, xs);
-    const int l = lane();
+constexpr int kXThreads = 1024, kXWaves = kXThreads / kW;
 
-    // ---- set-up: masks, the list, x, A, rank loads --------------------
-    for (int e = l; e < E; e += kW) c.pm[e] = replica_mask(place, e, G);
-    wave_sync();
-    if (compact(c, load)) {                        // an expert with load and no replica: no schedule exists
-        for (int i = l; i < E * G; i += kW) x_out[i] = 0;
-        if (l == 0) max_load[0] = -1;
+// LDS behind the arrays of the Problem: for every expert its place in the list or -1 - its only rank, the experts of the list
+// (both 16 bits), which experts are listed, and a flag.  The waves' sums of the output take the place of the masks.
+__host__ __device__ inline size_t x_masks_bytes(int E, int G, int mask_bytes) {
+    const size_t masks = (size_t)E * mask_bytes, sums = (size_t)kXWaves * G * 4;
+    return ((masks > sums ? masks : sums) + 15) & ~(size_t)15;
+}
+__host__ __device__ inline size_t x_bytes(int E, int G, int xs, int mask_bytes) {
+    return x_masks_bytes(E, G, mask_bytes) + ((size_t)E * xs + G + E) * 4 + (size_t)(E + kW - 1) / kW * 8 + 16;
+}
+
+// prev (warm start, Section 4.1: between micro-batches only the loads change, so the previous solution is a good place
+// to start from): every listed expert's previous row, restricted to its replicas, is scaled to the new load (rounded
+// down, the rest to the first replica).  Any assignment of the loads to replicas is a valid start for phase 1, and the
+// result of phase 2 does not depend on where it started, so `prev` may hold anything: negative entries read as 0, a row
+// without units falls back to the first replica.  It may be x_out: it is read completely before that is written.
+//
+// 256 experts with 320 replicas on 32 ranks, warm: 173 -> 100 us (20 experts, 50 replicas, 5 ranks: 31 -> 23).  The search
+// itself is bound by its count of dependent instructions (one wavefront issues one every 4-5 cycles, a value that goes from
+// the vector to the scalar side waits several of those) and LDS round trips: some 95 searches of 430 cycles and 135 hops of
+// pushes; a hop took 1200 cycles while the capacity of every edge was kept up to date, and takes some 500.  Set-up and
+// output, 95 K of 433 K cycles when the one wavefront did them too, are 18 K with sixteen.
+template <typename M, int MAXW>
+__global__ __launch_bounds__(kXThreads) void k_general_x(const uint8_t* __restrict__ place, const int32_t* __restrict__ load,
+                                                         const int32_t* prev, int E, int G, int xs, int P, int32_t* x_out,
+                                                         int32_t* __restrict__ max_load, int32_t* __restrict__ seg_off,
+                                                         int32_t* __restrict__ rank_off) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    Problem<M> c;
+    c.E = E; c.G = G; c.XS = xs;
+    c.pm = reinterpret_cast<M*>(smem);
+    c.x = reinterpret_cast<int*>(smem + x_masks_bytes(E, G, sizeof(M)));
+    c.t = c.x + (size_t)E * xs;
+    int16_t* slot = reinterpret_cast<int16_t*>(c.t + G);
+    int16_t* expert = slot + E;
+    u64* listed = reinterpret_cast<u64*>(smem + ((x_masks_bytes(E, G, sizeof(M)) + ((size_t)E * xs + G + E) * 4 + 7) & ~(size_t)7));
+    int* bad = reinterpret_cast<int*>(listed + (E + kW - 1) / kW);
+    int* sums = reinterpret_cast<int*>(smem);          // [waves][G], once the masks are done with
+    const int tid = threadIdx.x, l = lane(), wave = __builtin_amdgcn_readfirstlane(tid / kW);
+
+    // ---- set-up: masks, the list, x, rank loads (a thread per expert: E <= kXThreads) --------------------
+    for (int g = tid; g < G; g += kXThreads) c.t[g] = 0;
+    if (tid == 0) *bad = 0;
+    __syncthreads();
+    const u64 mask = tid < E ? replica_mask(place, tid, G) : 0ull;
+    const int mine = tid < E ? max(load[tid], 0) : 0, replicas = __popcll(mask);
+    if (replicas == 1 && mine > 0) atomicAdd(&c.t[__ffsll((long long)mask) - 1], mine);
+    const u64 in_list = __ballot(replicas > 1);
+    if (l == 0 && tid < E) listed[wave] = in_list;
+    if (replicas == 0 && mine > 0) *bad = 1;
+    __syncthreads();
+    if (*bad) {                                    // an expert with load and no replica: no schedule exists
+        for (int i = tid; i < E * G; i += kXThreads) x_out[i] = 0;
+        if (seg_off != nullptr) {
+            for (int i = tid; i < G * (E + 1); i += kXThreads) seg_off[i] = 0;
+            for (int i = tid; i <= G; i += kXThreads) rank_off[i] = 0;
+        }
+        if (tid == 0) max_load[0] = -1;
         return;
     }
-    if (prev) start_from_previous(c, load, prev);
-    else start_on_first_replicas(c, load);
-
-    // ---- phase 1: the optimum value ---------------------------------------------------------
-    const int cap_rank = optimum_value(c, P);      // M*
-    if (l == 0) max_load[0] = cap_rank;
-
-    // ---- phase 2: the lexicographically greatest optimum ------------------------------------
-    for (int j = 0; j < c.n; ++j) {
-        M todo = (M)c.pm[j];
-        M F = todo;                         // free replicas of j (including the one being removed next)
-        const int* row = c.x + j * c.XS;
-        while (todo) {
-            const int g = first_of(todo);
-            todo &= todo - 1;
-            // variable (j,g) leaves the free set: its units can no longer move to the other free
-            // replicas, nor theirs to g (lane q updates the two entries that involve replica q)
-            F &= ~((M)1 << g);
-            const M later = F;
-            if (later == 0) continue;        // the last replica: nothing left to take units from
-            const bool is_later = l < G && has(later, l & (8 * (int)sizeof(M) - 1));
-            int back = 0;
-            if (is_later) {
-                const int to_me = c.a(g, l) - row[g];
-                back = c.a(l, g) - row[l];
-                c.a(g, l) = to_me;
-                c.a(l, g) = back;
-                c.in = (c.in & ~((M)1 << g)) | (M)(to_me > 0) << g;
-            }
-            const M still = (M)__ballot(back > 0);
-            if (l == g) c.in = (c.in & ~later) | still;
-            wave_sync();
-            while (true) {
-                const int avail = is_later ? row[l] : 0;
-                if (__ballot(avail > 0) == 0ull) break;
-                const int total_avail = wave_sum_i(avail);
-                const int room = cap_rank - __builtin_amdgcn_readlane(c.ld, g);
-                if (room > 0) {
-                    pull_expert(c, j, g, later, later, min(room, total_avail));
-                    continue;
-                }
-                const bool want = l < G && (c.ld < cap_rank || avail > 0);
-                M visited; int parent, cap;
-                const int r = bfs(c, g, want, &visited, &parent, &cap);
-                if (r < 0) break;
-                const int room_r = cap_rank - __builtin_amdgcn_readlane(c.ld, r);
-                if (room_r > 0) {
-                    // the path may itself carry units of j between its later replicas, so
-                    // the units are taken from whichever later replicas hold them afterwards
-                    const int amount = min(min(room_r, cap), total_avail);
-                    push_path(c, g, r, parent, amount, j, g);
-                    pull_expert(c, j, g, later, later, amount);
-                } else {
-                    const int amount = min(cap, __builtin_amdgcn_readlane(avail, r));
-                    pull_expert(c, j, g, later, (M)1 << r, amount);
-                    push_path(c, g, r, parent, amount, j, g);
-                }
-            }
+    int n = 0, j = 0;
+    for (int k = 0; k < (E + kW - 1) / kW; ++k) {
+        if (k == wave) j = n;
+        n += __popcll(listed[k]);
+    }
+    c.n = n;
+    j += __popcll(in_list & ((1ull << l) - 1ull));
+    if (tid < E) {
+        slot[tid] = (int16_t)(replicas > 1 ? j : -1 - (replicas == 1 ? __ffsll((long long)mask) - 1 : G));      // (G: on no rank)
+        if (replicas > 1) {
+            c.pm[j] = (M)mask;
+            expert[j] = (int16_t)tid;
         }
     }
-    // ---- out: rows of the list; the load on the only replica for the others (their masks were dropped) --------
-    int n = 0;
-    const int per = kW / G, row0 = l / G, col = l - row0 * G;      // rows of E x G per wave instruction
-    for (int base = 0; base < E; base += kW) {
-        const u64 w = readlane_u64(c.listed, base / kW);
-        const int e = min(base + l, E - 1);
-        const int only = __ffsll((long long)replica_mask(place, e, G)) - 1, le = max(load[e], 0);
-        const int rows = min(kW, E - base);
-        for (int r = 0; r < rows; r += per) {
-            const int k = min(r + row0, kW - 1);
-            const int rank_k = __shfl(only, k, kW), load_k = __shfl(le, k, kW);
-            const int j = n + __popcll(w & ((1ull << k) - 1ull));
-            const int v = (w >> k) & 1ull ? c.x[j * c.XS + col] : rank_k == col ? load_k : 0;
-            if (row0 < per && r + row0 < rows) x_out[(size_t)(base + k) * G + col] = v;
+    __syncthreads();
+    for (int i = wave; i < n; i += kXWaves) {      // a wave per listed expert, lane = rank
+        const int e = expert[i], le = max(load[e], 0);
+        const M m = c.pm[i];
+        const bool here = l < G && has(m, l & (8 * (int)sizeof(M) - 1));
+        int t = 0;
+        if (prev != nullptr) {                     // (floating point: any split that adds up to the load will do)
+            const float v = here ? (float)max(prev[(size_t)e * G + l], 0) : 0.f;
+            float had = v;
+            for (int o = 32; o > 0; o >>= 1) had += __shfl_xor(had, o, kW);
+            t = had > 0.f ? (int)fminf(v * ((float)le / had), (float)le) : 0;
+            t = max(0, min(t, le - (wave_incl_scan_i(t) - t)));
         }
-        n += __popcll(w);
+        const int left = le - wave_sum_i(t);
+        if (l == first_of(m)) t += left;
+        if (l < G) c.x[i * xs + l] = t;
+        if (t > 0) atomicAdd(&c.t[l], t);
     }
+    __syncthreads();
+
+    if (wave == 0) {
+        int loads = 0;
+        with_words<MAXW>(n, [&](auto words) {
+            Flow<M, words.value, M> f(c);
+            const int m_star = solve(f, P);
+            if (l == 0) max_load[0] = m_star;
+            loads = f.ld;
+        });
+        const int first = wave_incl_scan_i(loads) - loads;      // first row of every rank
+        if (l < G) {
+            c.t[l] = first;
+            if (rank_off != nullptr) rank_off[l] = first;
+            if (rank_off != nullptr && l == G - 1) rank_off[G] = first + loads;
+        }
+    }
+    __syncthreads();
+
+    // ---- out: a wave per run of experts, lane = rank; the rows of a rank's segments follow one another -------------
+    const int per = (E + kXWaves - 1) / kXWaves, e0 = min(wave * per, E), count = min(per, E - e0);
+    const int ours = min(e0 + l, E - 1);      // (count <= 64: one expert per lane)
+    const int le = max(load[ours], 0), sl = slot[ours], q = min(l, G - 1);
+    auto units = [&](int i) {
+        const int s = __builtin_amdgcn_readlane(sl, i);
+        const int on_list = c.x[max(s, 0) * xs + q];
+        return s >= 0 ? on_list : -1 - s == q ? __builtin_amdgcn_readlane(le, i) : 0;
+    };
+    int sum = 0;
+    for (int i = 0; i < count; ++i) sum += units(i);
+    if (l < G) sums[wave * G + l] = sum;
+    __syncthreads();
+    int run = c.t[q];
+    for (int w = 0; w < wave; ++w) run += sums[w * G + q];
+    for (int i = 0; i < count; ++i) {
+        const int v = units(i);
+        if (l < G) {
+            x_out[(size_t)(e0 + i) * G + l] = v;
+            if (seg_off != nullptr) seg_off[(size_t)l * (E + 1) + e0 + i] = run;
+        }
+        run += v;
+    }
+    if (seg_off != nullptr && l < G && e0 + count == E && count > 0) seg_off[(size_t)l * (E + 1) + E] = run;
 }
 
 }  // namespace
 
+// seg_off, rank_off: written too, unless NULL
 int launch_general_x(const fine_shape& s, const uint8_t* place, const int32_t* load, const int32_t* x_prev,
-                     int32_t* x_eg, int32_t* max_load, hipStream_t st) {
-    const int xs = flow::x_stride(s.E, s.G, 160 * 1024);
-    const size_t lds = flow::ctx_bytes(s.E, s.G, xs);
-    if (lds > 160 * 1024) return FINE_UNSUPPORTED;
-    static std::atomic<uint64_t> lds_set32{0}, lds_set64{0};
-    auto k = s.G <= 32 ? k_general_x<uint32_t> : k_general_x<u64>;
-    FINE_TRY(raise_lds_limit((const void*)k, 160 * 1024, s.G <= 32 ? lds_set32 : lds_set64));
-    hipLaunchKernelGGL(k, dim3(1), dim3(64), lds, st, place, load, x_prev, s.E, s.G, xs, s.T * s.K, x_eg, max_load);
+                     int32_t* x_eg, int32_t* max_load, int32_t* seg_off, int32_t* rank_off, hipStream_t st) {
+    const int mask_bytes = s.G <= 32 ? 4 : 8;
+    const size_t limit = 160 * 1024;
+    if (!flow::size_allowed(s.E, s.G, limit)) return FINE_UNSUPPORTED;
+    const int xs = x_bytes(s.E, s.G, s.G | 1, mask_bytes) <= limit ? s.G | 1 : s.G;
+    const size_t lds = x_bytes(s.E, s.G, xs, mask_bytes);
+    if (lds > limit) return FINE_UNSUPPORTED;
+    static std::atomic<uint64_t> lds_set[2][17];
+    auto k = flow::by_size(s.E, s.G, [](auto words, auto m) { return k_general_x<decltype(m), words.value>; });
+    FINE_TRY(raise_lds_limit((const void*)k, (int)limit, lds_set[s.G <= 32][flow::words_for(s.E)]));
+    hipLaunchKernelGGL(k, dim3(1), dim3(kXThreads), lds, st, place, load, x_prev, s.E, s.G, xs, s.T * s.K, x_eg, max_load,
+                       seg_off, rank_off);
     FINE_LAUNCH_CHECK();
     return FINE_OK;
 }

@@ -408,12 +408,12 @@ __global__ __launch_bounds__(kScoreThreads) void k_score(const int32_t* __restri
 // fraction.  Loads summing to 2^31 / G or more do not fit the scaled flow: then M* = ceil(m) is
 // written as M* / 1.
 // ---------------------------------------------------------------------------
-template <bool DRAW, typename M>
+template <bool DRAW, typename M, int MAXW>
 __global__ __launch_bounds__(64) void k_score_flow(const int32_t* __restrict__ load, const int32_t* __restrict__ counts,
                                                    const uint8_t* __restrict__ place, int E, int G, int slots,
                                                    uint32_t seed, int xs, int64_t* __restrict__ m_num, int32_t* __restrict__ m_den) {
     extern __shared__ __attribute__((aligned(16))) char s_flow[];
-    auto c = flow::make_ctx<M>(s_flow, E, G, xs);
+    auto c = flow::make_problem(s_flow, E, G, xs);
     int* s_order = reinterpret_cast<int*>(s_flow + flow::ctx_bytes(E, G, xs));      // [E]
     int* s_cnt = s_order + E;                                                   // [E]
     const int l = threadIdx.x;
@@ -436,19 +436,20 @@ __global__ __launch_bounds__(64) void k_score_flow(const int32_t* __restrict__ l
     Pl += __shfl_xor(Pl, 32, 64); Pl += __shfl_xor(Pl, 16, 64); Pl += __shfl_xor(Pl, 8, 64);
     Pl += __shfl_xor(Pl, 4, 64); Pl += __shfl_xor(Pl, 2, 64); Pl += __shfl_xor(Pl, 1, 64);
     int num = -1, den = 0;
-    if (!bad) {
+    if (!bad) flow::with_words<MAXW>(c.n, [&](auto words) {
+        flow::Flow<M, words.value> f(c);
         if (Pl * G < 0x7fffffffll) {
-            flow::exact_density(c, load, (int)Pl, &num, &den);
+            flow::exact_density(f, load, (int)Pl, &num, &den);
             int a = num, b = den;                     // reduce by the greatest common divisor
             while (b != 0) { const int t = a % b; a = b; b = t; }
             if (a > 1) { num /= a; den /= a; }
             if (num == 0) den = 1;
         } else {
-            flow::start_on_first_replicas(c, load);
-            num = flow::optimum_value(c, (int)min(Pl, 0x7fffffffll));
+            flow::start_on_first_replicas(f, load);
+            num = flow::optimum_value(f, (int)min(Pl, 0x7fffffffll));
             den = 1;
         }
-    }
+    });
     if (l == 0) {
         m_num[cand] = num;
         m_den[cand] = den;
@@ -627,10 +628,10 @@ int launch_eval_placements(const fine_shape& s, int n, const uint8_t* place, con
     if (n == 0) return FINE_OK;
     if (s.G > kMaxEnumG) {
         const size_t rest = 2 * (size_t)s.E * 4;
+        if (!flow::size_allowed(s.E, s.G, 64 * 1024 - rest)) return FINE_UNSUPPORTED;
         const int xs = flow::x_stride(s.E, s.G, 64 * 1024 - rest);
         const size_t lds = flow::ctx_bytes(s.E, s.G, xs) + rest;
-        if (lds > 64 * 1024) return FINE_UNSUPPORTED;
-        auto k = s.G <= 32 ? k_score_flow<false, uint32_t> : k_score_flow<false, u64>;
+        auto k = flow::by_size(s.E, s.G, [](auto words, auto m) { return k_score_flow<false, decltype(m), words.value>; });
         hipLaunchKernelGGL(k, dim3(n), dim3(64), lds, st, load, (const int32_t*)nullptr, place, s.E, s.G, 0,
                            0u, xs, m_num, m_den);
         FINE_LAUNCH_CHECK();
@@ -643,10 +644,10 @@ int launch_place_search(const fine_shape& s, const int32_t* load, const int32_t*
                         int64_t* m_num, int32_t* m_den, int32_t* best, uint8_t* place, hipStream_t st) {
     if (s.G > kMaxEnumG) {
         const size_t rest = 2 * (size_t)s.E * 4;
+        if (!flow::size_allowed(s.E, s.G, 64 * 1024 - rest)) return FINE_UNSUPPORTED;
         const int xs = flow::x_stride(s.E, s.G, 64 * 1024 - rest);
         const size_t lds = flow::ctx_bytes(s.E, s.G, xs) + rest;
-        if (lds > 64 * 1024) return FINE_UNSUPPORTED;
-        auto k = s.G <= 32 ? k_score_flow<true, uint32_t> : k_score_flow<true, u64>;
+        auto k = flow::by_size(s.E, s.G, [](auto words, auto m) { return k_score_flow<true, decltype(m), words.value>; });
         hipLaunchKernelGGL(k, dim3(n), dim3(64), lds, st, load, counts, (const uint8_t*)nullptr, s.E, s.G,
                            slots, seed, xs, m_num, m_den);
     } else {

@@ -417,7 +417,7 @@ SchedWs sched_ws_layout(const fine_shape& s) {
 }
 
 int launch_general_x(const fine_shape& s, const uint8_t* place, const int32_t* load, const int32_t* x_prev,
-                     int32_t* x_eg, int32_t* max_load, hipStream_t st);
+                     int32_t* x_eg, int32_t* max_load, int32_t* seg_off, int32_t* rank_off, hipStream_t st);
 
 namespace {
 
@@ -491,12 +491,12 @@ int launch_sched(const fine_shape& s, const int32_t* topk_idx, const uint8_t* pl
         };
         if (place == nullptr) return run(k_sched_small<0>);
         FINE_TRY(run(k_sched_small<1>));
-        FINE_TRY(launch_general_x(s, place, load, x_prev, x_eg, max_load, st));
+        FINE_TRY(launch_general_x(s, place, load, x_prev, x_eg, max_load, nullptr, nullptr, st));
         return run(k_sched_small<2>);
     }
     FINE_TRY(launch_sched_tables(s, topk_idx, load, input_eg, ws, st));
     if (place != nullptr) {
-        FINE_TRY(launch_general_x(s, place, load, x_prev, x_eg, max_load, st));
+        FINE_TRY(launch_general_x(s, place, load, x_prev, x_eg, max_load, nullptr, nullptr, st));
         return launch_sched_routing(s, topk_idx, 0, load, input_eg, x_eg, pair_dst, row_of_pair, pair_of_row, seg_off,
                                     rank_off, ws, st);
     }

@@ -85,8 +85,7 @@ struct SchedWs {
     size_t bitmap;     // uint64 [E][W]    bit t%64 of word t/64: token t chose expert e
     size_t cum;        // int32  [E][W+1]  exclusive prefix of popcounts over words
     size_t inpre;      // int32  [E][G]    pairs of expert e on source ranks < g
-    size_t Y;          // int32  [E][G][G] Algorithm 1 transfer table
-    size_t Ypre;       // int32  [E][G][G] Ypre[e][g][h] = sum_{g'<g} Y[e][g'][h]
+    size_t route;      // RouteTables (route.h)
     size_t total;
     int W;
 };

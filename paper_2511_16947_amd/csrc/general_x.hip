@@ -22,7 +22,7 @@
 // replica the units came from.  When no such path exists x[e][g] is maximal given the
 // earlier variables, i.e. the result is the lexicographically greatest optimum, which is
 // unique: the order in which paths are found does not change it.
-#include "flow_wave.h"
+#include "route.h"
 
 namespace fine {
 
@@ -151,7 +151,8 @@ __host__ __device__ inline size_t x_bytes(int E, int G, int xs, int mask_bytes) 
 template <typename M, int MAXW>
 __global__ __launch_bounds__(kXThreads) void k_general_x(const uint8_t* __restrict__ place, const int32_t* __restrict__ load,
                                                          const int32_t* prev, int E, int G, int xs, int P, int32_t* x_out,
-                                                         int32_t* __restrict__ max_load, int32_t* __restrict__ seg_off,
+                                                         int32_t* __restrict__ max_load, const int32_t* __restrict__ input_eg,
+                                                         int locality, RouteTables route, int32_t* __restrict__ seg_off,
                                                          int32_t* __restrict__ rank_off) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     Problem<M> c;
@@ -181,6 +182,7 @@ __global__ __launch_bounds__(kXThreads) void k_general_x(const uint8_t* __restri
         for (int i = tid; i < E * G; i += kXThreads) x_out[i] = 0;
         if (seg_off != nullptr) {
             for (int i = tid; i < G * (E + 1); i += kXThreads) seg_off[i] = 0;
+            for (int i = tid; i < E * G; i += kXThreads) route.wait[i] = route.room_end[i] = 0;
             for (int i = tid; i <= G; i += kXThreads) rank_off[i] = 0;
         }
         if (tid == 0) max_load[0] = -1;
@@ -252,22 +254,33 @@ __global__ __launch_bounds__(kXThreads) void k_general_x(const uint8_t* __restri
     __syncthreads();
     int run = c.t[q];
     for (int w = 0; w < wave; ++w) run += sums[w * G + q];
-    for (int i = 0; i < count; ++i) {
-        const int v = units(i);
-        if (l < G) {
-            x_out[(size_t)(e0 + i) * G + l] = v;
-            if (seg_off != nullptr) seg_off[(size_t)l * (E + 1) + e0 + i] = run;
+    for (int i0 = 0; i0 < count; i0 += 4) {
+        int in[4] = {0, 0, 0, 0};
+        if (seg_off != nullptr)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) in[k] = input_eg[(size_t)(e0 + min(i0 + k, count - 1)) * G + q];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int i = i0 + k, e = e0 + i;
+            if (i >= count) break;
+            const int v = units(i);
+            if (l < G) x_out[(size_t)e * G + l] = v;
+            if (seg_off != nullptr) {
+                write_route(route, e, G, 0, locality, l < G ? in[k] : 0, l < G ? v : 0);
+                if (l < G) seg_off[(size_t)l * (E + 1) + e] = run;
+            }
+            run += v;
         }
-        run += v;
     }
     if (seg_off != nullptr && l < G && e0 + count == E && count > 0) seg_off[(size_t)l * (E + 1) + E] = run;
 }
 
 }  // namespace
 
-// seg_off, rank_off: written too, unless NULL
+// seg_off, rank_off: written too, with the queues of Algorithm 1 (route.h), unless NULL
 int launch_general_x(const fine_shape& s, const uint8_t* place, const int32_t* load, const int32_t* x_prev,
-                     int32_t* x_eg, int32_t* max_load, int32_t* seg_off, int32_t* rank_off, hipStream_t st) {
+                     int32_t* x_eg, int32_t* max_load, const int32_t* input_eg, const RouteTables& t, int32_t* seg_off,
+                     int32_t* rank_off, hipStream_t st) {
     const int mask_bytes = s.G <= 32 ? 4 : 8;
     const size_t limit = 160 * 1024;
     if (!flow::size_allowed(s.E, s.G, limit)) return FINE_UNSUPPORTED;
@@ -278,7 +291,7 @@ int launch_general_x(const fine_shape& s, const uint8_t* place, const int32_t* l
     auto k = flow::by_size(s.E, s.G, [](auto words, auto m) { return k_general_x<decltype(m), words.value>; });
     FINE_TRY(raise_lds_limit((const void*)k, (int)limit, lds_set[s.G <= 32][flow::words_for(s.E)]));
     hipLaunchKernelGGL(k, dim3(1), dim3(kXThreads), lds, st, place, load, x_prev, s.E, s.G, xs, s.T * s.K, x_eg, max_load,
-                       seg_off, rank_off);
+                       input_eg, (s.flags & FINE_FLAG_LOCALITY) ? 1 : 0, t, seg_off, rank_off);
     FINE_LAUNCH_CHECK();
     return FINE_OK;
 }

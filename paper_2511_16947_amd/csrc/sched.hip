@@ -3,7 +3,7 @@
 // Integer only; every result is independent of thread timing (no order-dependent
 // atomics), so two runs and two devices give the same bits, which the paper's
 // distributed scheduling relies on (Section 4.3).
-#include "flow_wave.h"
+#include "route.h"
 
 namespace fine {
 
@@ -12,22 +12,6 @@ namespace {
 constexpr int kWave = 64;
 
 __device__ inline int lane_id() { return threadIdx.x & (kWave - 1); }
-
-__device__ inline int wave_incl_scan(int v) {
-    const int lane = lane_id();
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-        int o = __shfl_up(v, off, kWave);
-        if (lane >= off) v += o;
-    }
-    return v;
-}
-
-__device__ inline int wave_sum(int v) {
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
-    return v;
-}
 
 // ---------------------------------------------------------------------------
 // 1. One wave per 64-token word: for every expert the mask of tokens that chose it.
@@ -65,9 +49,9 @@ __global__ __launch_bounds__(64) void k_scan(const unsigned long long* __restric
     for (int base = 0; base < W; base += kWave) {
         int w = base + lane;
         int c = (w < W) ? __popcll(bm[w]) : 0;
-        int inc = wave_incl_scan(c);
+        int inc = flow::wave_incl_scan_i(c);
         if (w < W) s_cum[w] = carry + inc - c;
-        carry += __shfl(inc, kWave - 1, kWave);
+        carry += __builtin_amdgcn_readlane(inc, kWave - 1);
     }
     if (lane == 0) s_cum[W] = carry;
     __syncthreads();
@@ -89,75 +73,46 @@ __device__ inline int overlap(int a0, int alen, int b0, int blen) {
 }
 
 // ---------------------------------------------------------------------------
-// 3. One wave per expert: replica loads (closed form when every expert is on every
-//    rank) and Algorithm 1.  The local pass gives min(input, x) to the own rank; the
-//    global pass walks sources and replicas in ascending order handing out
-//    min(remaining input, remaining load), which is the overlap of the two
-//    prefix-summed remaining sequences.
+// 3. One wave per expert: the queues of Algorithm 1 (route.h) from the replica loads.  FULL: every expert on every rank,
+//    the replica loads have a closed form (the expert-sorted sequence of pairs in chunks of M) and with them the segment
+//    offsets, which are written too.
 // ---------------------------------------------------------------------------
 template <bool FULL>
 __global__ __launch_bounds__(64) void k_tables(const int32_t* __restrict__ load, const int32_t* __restrict__ input_eg,
                                                int E, int G, int P, int locality, int rpn,
-                                               int32_t* __restrict__ x_eg, int32_t* __restrict__ max_load,
-                                               int32_t* __restrict__ Y, int32_t* __restrict__ Ypre) {
-    __shared__ int s_loc[kWave], s_ri[kWave], s_rx[kWave], s_RI[kWave], s_RX[kWave];
-    __shared__ int s_nri[kWave], s_nrx[kWave], s_nI[kWave], s_nX[kWave];
+                                               int32_t* __restrict__ x_eg, int32_t* __restrict__ max_load, RouteTables t,
+                                               int32_t* __restrict__ seg_off, int32_t* __restrict__ rank_off) {
     const int e = blockIdx.x, lane = lane_id();
     int xg = 0;
     if (FULL) {
-        int part = 0;
-        for (int i = lane; i < e; i += kWave) part += load[i];
-        const int off = wave_sum(part);
+        int before = 0, all = 0;
+        for (int i = lane; i < E; i += kWave) {
+            const int v = load[i];
+            before += i < e ? v : 0;
+            all += v;
+        }
+        const int off = flow::wave_sum_i(before), total = flow::wave_sum_i(all);
         const int M = (P + G - 1) / G;
         if (lane < G) {
             xg = overlap(off, load[e], lane * M, M);
             x_eg[(size_t)e * G + lane] = xg;
+            const int lo = min(lane * M, total), hi = min(lane * M + M, total);      // the rows of this rank
+            seg_off[(size_t)lane * (E + 1) + e] = min(max(off, lo), hi);
+            if (e == E - 1) {
+                seg_off[(size_t)lane * (E + 1) + E] = hi;
+                rank_off[lane] = lo;
+                if (lane == G - 1) rank_off[G] = hi;
+            }
         }
         if (e == 0 && lane == 0) max_load[0] = M;
     } else {
         if (lane < G) xg = x_eg[(size_t)e * G + lane];
     }
-    int in_g = (lane < G) ? input_eg[(size_t)e * G + lane] : 0;
-    int loc = locality ? min(in_g, xg) : 0;
-    int ri = in_g - loc, rx = xg - loc;
-    // Pass inside the nodes (Appendix A.1's routing order: same GPU, same node, then any GPU; rpn
-    // consecutive ranks form a node, rpn <= 1: no such pass).  Inside a node the sources' waiting
-    // tokens and the replicas' free loads are two queues paired head to head, so source g meets
-    // replica h on the overlap of their intervals of the node's prefix sums, and what a rank has
-    // left afterwards is what lies beyond the other queue's end.
-    const bool nodes = rpn > 1;
-    int nI = 0, nX = 0, tI = 0, tX = 0;      // prefix inside the node, totals of the node
-    if (nodes) {
-        const int first = (lane / rpn) * rpn, last = min(first + rpn, kWave) - 1;
-        const int sI = wave_incl_scan(ri), sX = wave_incl_scan(rx);
-        const int bI = __shfl(sI, first, kWave) - __shfl(ri, first, kWave);
-        const int bX = __shfl(sX, first, kWave) - __shfl(rx, first, kWave);
-        nI = sI - ri - bI; nX = sX - rx - bX;
-        tI = __shfl(sI, last, kWave) - bI; tX = __shfl(sX, last, kWave) - bX;
-    }
-    const int ri2 = nodes ? ri - overlap(nI, ri, 0, tX) : ri;      // left for the pass over all ranks
-    const int rx2 = nodes ? rx - overlap(nX, rx, 0, tI) : rx;
-    int RI = wave_incl_scan(ri2) - ri2, RX = wave_incl_scan(rx2) - rx2;
-    s_loc[lane] = loc; s_ri[lane] = ri2; s_rx[lane] = rx2; s_RI[lane] = RI; s_RX[lane] = RX;
-    s_nri[lane] = ri; s_nrx[lane] = rx; s_nI[lane] = nI; s_nX[lane] = nX;
-    __syncthreads();
-    int32_t* Ye = Y + (size_t)e * G * G;
-    int32_t* Yp = Ypre + (size_t)e * G * G;
-    if (lane < G) {
-        const int h = lane;            // destination rank
-        int run = 0;
-        for (int g = 0; g < G; ++g) {
-            int y = overlap(s_RI[g], s_ri[g], s_RX[h], s_rx[h]) + (g == h ? s_loc[g] : 0);
-            if (nodes && g / rpn == h / rpn) y += overlap(s_nI[g], s_nri[g], s_nX[h], s_nrx[h]);
-            Ye[g * G + h] = y;
-            Yp[g * G + h] = run;
-            run += y;
-        }
-    }
+    write_route(t, e, G, rpn, locality, lane < G ? input_eg[(size_t)e * G + lane] : 0, xg);
 }
 
 // ---------------------------------------------------------------------------
-// 4. One block per rank: first row of every (rank, expert) segment.
+// 4. One block per rank: first row of every (rank, expert) segment (replica loads that came from the host).
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_segoff(const int32_t* __restrict__ x_eg, int E, int G,
                                                 int32_t* __restrict__ seg_off, int32_t* __restrict__ rank_off) {
@@ -181,7 +136,7 @@ __global__ __launch_bounds__(256) void k_segoff(const int32_t* __restrict__ x_eg
     for (int e0 = 0; e0 < E; e0 += 256) {
         int e = e0 + tid;
         int v = (e < E) ? x_eg[(size_t)e * G + g] : 0;
-        int inc = wave_incl_scan(v);
+        int inc = flow::wave_incl_scan_i(v);
         if (lane_id() == kWave - 1) s_wave[tid / kWave] = inc;
         __syncthreads();
         int wbase = 0;
@@ -204,43 +159,27 @@ __global__ __launch_bounds__(256) void k_segoff(const int32_t* __restrict__ x_eg
 __global__ __launch_bounds__(256) void k_pairs(const int32_t* __restrict__ topk_idx, int T, int K, int E, int G, int W,
                                                int locality, int rpn, const unsigned long long* __restrict__ bitmap,
                                                const int32_t* __restrict__ cum, const int32_t* __restrict__ inpre,
-                                               const int32_t* __restrict__ Y, const int32_t* __restrict__ Ypre,
-                                               const int32_t* __restrict__ seg_off,
+                                               const int32_t* __restrict__ input_eg, const int32_t* __restrict__ x_eg,
+                                               RouteTables t, const int32_t* __restrict__ seg_off,
                                                int32_t* __restrict__ pair_dst, int32_t* __restrict__ row_of_pair,
                                                int32_t* __restrict__ pair_of_row) {
     const int p = blockIdx.x * 256 + threadIdx.x;
     if (p >= T * K) return;
-    const int t = p / K;
+    const int tok = p / K;
     const int e = topk_idx[p];
     // A pair without a destination (an expert index out of range; no schedule exists because an
     // expert with load has no replica) keeps its own place: row p <-> pair p.  pair_dst = -1 marks
     // it, and the movement kernels that run on these indices afterwards stay inside their buffers.
-    if (e < 0 || e >= E) { pair_dst[p] = -1; row_of_pair[p] = p; pair_of_row[p] = p; return; }
-    const int g = t / (T / G);
-    const int w = t >> 6;
-    int r = cum[(size_t)e * (W + 1) + w] + __popcll(bitmap[(size_t)e * W + w] & ((1ull << (t & 63)) - 1ull))
-            - inpre[(size_t)e * G + g];           // rank of this token among (expert e, source g)
-    const int32_t* Yrow = Y + ((size_t)e * G + g) * G;
-    // the hand-outs of source g in the order they were made: its own rank (locality), the ranks
-    // of its node in ascending order (rpn > 1), then the other ranks in ascending order
-    int dst = -1, within = 0;
-    if (locality) {
-        int c = Yrow[g];
-        if (r < c) { dst = g; within = r; } else r -= c;
+    int dst = -1, row = p;
+    if (e >= 0 && e < E) {
+        const int g = tok / (T / G), w = tok >> 6;
+        const size_t row0 = (size_t)e * G;
+        const int r = cum[(size_t)e * (W + 1) + w] + __popcll(bitmap[(size_t)e * W + w] & ((1ull << (tok & 63)) - 1ull)) -
+                      inpre[row0 + g];           // rank of this token among (expert e, source g)
+        int place = 0;
+        dst = route_token(t, input_eg + row0, x_eg + row0, row0, G, rpn, locality, g, r, &place);
+        if (dst >= 0) row = seg_off[(size_t)dst * (E + 1) + e] + place;
     }
-    const int n0 = rpn > 1 ? (g / rpn) * rpn : 0, n1 = rpn > 1 ? min(n0 + rpn, G) : 0;      // the node of g
-    for (int h = n0; h < n1 && dst < 0; ++h) {
-        if (locality && h == g) continue;
-        int c = Yrow[h];
-        if (r < c) { dst = h; within = r; } else r -= c;
-    }
-    for (int h = 0; h < G && dst < 0; ++h) {
-        if ((locality && h == g) || (h >= n0 && h < n1)) continue;
-        int c = Yrow[h];
-        if (r < c) { dst = h; within = r; } else r -= c;
-    }
-    if (dst < 0) { pair_dst[p] = -1; row_of_pair[p] = p; pair_of_row[p] = p; return; }   // no schedule exists
-    const int row = seg_off[(size_t)dst * (E + 1) + e] + Ypre[((size_t)e * G + g) * G + dst] + within;
     pair_dst[p] = dst;
     row_of_pair[p] = row;
     pair_of_row[row] = p;
@@ -410,40 +349,41 @@ SchedWs sched_ws_layout(const fine_shape& s) {
     w.bitmap = o; o = align_up(o + (size_t)s.E * w.W * 8, 256);
     w.cum = o;    o = align_up(o + (size_t)s.E * (w.W + 1) * 4, 256);
     w.inpre = o;  o = align_up(o + (size_t)s.E * s.G * 4, 256);
-    w.Y = o;      o = align_up(o + (size_t)s.E * s.G * s.G * 4, 256);
-    w.Ypre = o;   o = align_up(o + (size_t)s.E * s.G * s.G * 4, 256);
+    w.route = o;
+    // (the contract's size, from when these were two tables of [E][G][G]; at least what the four of [E][G] take when there
+    // are nodes, i.e. more than one rank, and the two without)
+    o = align_up(o + (size_t)s.E * s.G * s.G * 4, 256);
+    o = align_up(o + (size_t)s.E * s.G * s.G * 4, 256);
     w.total = o;
     return w;
 }
 
 int launch_general_x(const fine_shape& s, const uint8_t* place, const int32_t* load, const int32_t* x_prev,
-                     int32_t* x_eg, int32_t* max_load, int32_t* seg_off, int32_t* rank_off, hipStream_t st);
+                     int32_t* x_eg, int32_t* max_load, const int32_t* input_eg, const RouteTables& t, int32_t* seg_off, int32_t* rank_off,
+                     hipStream_t st);
 
 namespace {
 
 struct SchedArrays {
     unsigned long long* bitmap;
-    int32_t *cum, *inpre, *Y, *Ypre;
+    int32_t *cum, *inpre;
+    RouteTables route;
     int W;
 };
 SchedArrays sched_arrays(const fine_shape& s, char* ws) {
     const SchedWs L = sched_ws_layout(s);
+    int32_t* r = reinterpret_cast<int32_t*>(ws + L.route);
+    const size_t n = (size_t)s.E * s.G;
     return {reinterpret_cast<unsigned long long*>(ws + L.bitmap), reinterpret_cast<int32_t*>(ws + L.cum),
-            reinterpret_cast<int32_t*>(ws + L.inpre), reinterpret_cast<int32_t*>(ws + L.Y),
-            reinterpret_cast<int32_t*>(ws + L.Ypre), L.W};
+            reinterpret_cast<int32_t*>(ws + L.inpre), RouteTables{r, r + n, r + 2 * n, r + 3 * n}, L.W};
 }
 
-// segment offsets and per-pair indices from the routing tables in the workspace
-int launch_sched_indices(const fine_shape& s, const int32_t* topk_idx, int rpn, const int32_t* x_eg, const SchedArrays& a,
-                         int32_t* pair_dst, int32_t* row_of_pair, int32_t* pair_of_row, int32_t* seg_off,
-                         int32_t* rank_off, hipStream_t st) {
-    const int P = s.T * s.K;
-    const int locality = (s.flags & FINE_FLAG_LOCALITY) ? 1 : 0;
-    hipLaunchKernelGGL(k_segoff, dim3(s.G), dim3(256), 0, st, x_eg, s.E, s.G, seg_off, rank_off);
-    FINE_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_pairs, dim3(cdiv(P, 256)), dim3(256), 0, st,
-                       topk_idx, s.T, s.K, s.E, s.G, a.W, locality, rpn, a.bitmap, a.cum, a.inpre, a.Y, a.Ypre, seg_off,
-                       pair_dst, row_of_pair, pair_of_row);
+int launch_pairs(const fine_shape& s, const int32_t* topk_idx, int rpn, const int32_t* input_eg, const int32_t* x_eg,
+                 const SchedArrays& a, int32_t* pair_dst, int32_t* row_of_pair, int32_t* pair_of_row, const int32_t* seg_off,
+                 hipStream_t st) {
+    hipLaunchKernelGGL(k_pairs, dim3(cdiv(s.T * s.K, 256)), dim3(256), 0, st,
+                       topk_idx, s.T, s.K, s.E, s.G, a.W, (s.flags & FINE_FLAG_LOCALITY) ? 1 : 0, rpn, a.bitmap, a.cum,
+                       a.inpre, input_eg, x_eg, a.route, seg_off, pair_dst, row_of_pair, pair_of_row);
     FINE_LAUNCH_CHECK();
     return FINE_OK;
 }
@@ -469,11 +409,13 @@ int launch_sched_routing(const fine_shape& s, const int32_t* topk_idx, int ranks
                          int32_t* pair_of_row, int32_t* seg_off, int32_t* rank_off, char* ws, hipStream_t st) {
     const SchedArrays a = sched_arrays(s, ws);
     const int locality = (s.flags & FINE_FLAG_LOCALITY) ? 1 : 0;
-    hipLaunchKernelGGL(k_tables<false>, dim3(s.E), dim3(64), 0, st,
-                       load, input_eg, s.E, s.G, s.T * s.K, locality, ranks_per_node, x_eg, (int32_t*)nullptr, a.Y, a.Ypre);
+    const int rpn = s.G > 1 ? ranks_per_node : 0;
+    hipLaunchKernelGGL(k_tables<false>, dim3(s.E), dim3(64), 0, st, load, input_eg, s.E, s.G, s.T * s.K, locality, rpn, x_eg,
+                       (int32_t*)nullptr, a.route, (int32_t*)nullptr, (int32_t*)nullptr);
     FINE_LAUNCH_CHECK();
-    return launch_sched_indices(s, topk_idx, ranks_per_node, x_eg, a, pair_dst, row_of_pair, pair_of_row, seg_off,
-                                rank_off, st);
+    hipLaunchKernelGGL(k_segoff, dim3(s.G), dim3(256), 0, st, x_eg, s.E, s.G, seg_off, rank_off);
+    FINE_LAUNCH_CHECK();
+    return launch_pairs(s, topk_idx, rpn, input_eg, x_eg, a, pair_dst, row_of_pair, pair_of_row, seg_off, st);
 }
 
 int launch_sched(const fine_shape& s, const int32_t* topk_idx, const uint8_t* place, const int32_t* x_prev,
@@ -491,21 +433,19 @@ int launch_sched(const fine_shape& s, const int32_t* topk_idx, const uint8_t* pl
         };
         if (place == nullptr) return run(k_sched_small<0>);
         FINE_TRY(run(k_sched_small<1>));
-        FINE_TRY(launch_general_x(s, place, load, x_prev, x_eg, max_load, nullptr, nullptr, st));
+        FINE_TRY(launch_general_x(s, place, load, x_prev, x_eg, max_load, nullptr, RouteTables{}, nullptr, nullptr, st));
         return run(k_sched_small<2>);
     }
     FINE_TRY(launch_sched_tables(s, topk_idx, load, input_eg, ws, st));
-    if (place != nullptr) {
-        FINE_TRY(launch_general_x(s, place, load, x_prev, x_eg, max_load, nullptr, nullptr, st));
-        return launch_sched_routing(s, topk_idx, 0, load, input_eg, x_eg, pair_dst, row_of_pair, pair_of_row, seg_off,
-                                    rank_off, ws, st);
-    }
     const SchedArrays a = sched_arrays(s, ws);
-    const int locality = (s.flags & FINE_FLAG_LOCALITY) ? 1 : 0;
-    hipLaunchKernelGGL(k_tables<true>, dim3(s.E), dim3(64), 0, st,
-                       load, input_eg, s.E, s.G, s.T * s.K, locality, 0, x_eg, max_load, a.Y, a.Ypre);
-    FINE_LAUNCH_CHECK();
-    return launch_sched_indices(s, topk_idx, 0, x_eg, a, pair_dst, row_of_pair, pair_of_row, seg_off, rank_off, st);
+    if (place != nullptr) {
+        FINE_TRY(launch_general_x(s, place, load, x_prev, x_eg, max_load, input_eg, a.route, seg_off, rank_off, st));
+    } else {
+        hipLaunchKernelGGL(k_tables<true>, dim3(s.E), dim3(64), 0, st, load, input_eg, s.E, s.G, s.T * s.K,
+                           (s.flags & FINE_FLAG_LOCALITY) ? 1 : 0, 0, x_eg, max_load, a.route, seg_off, rank_off);
+        FINE_LAUNCH_CHECK();
+    }
+    return launch_pairs(s, topk_idx, 0, input_eg, x_eg, a, pair_dst, row_of_pair, pair_of_row, seg_off, st);
 }
 
 // ---------------------------------------------------------------------------

@@ -168,6 +168,124 @@ __global__ __launch_bounds__(256, 3) void k_ffn_f32(const float* __restrict__ A,
     }
 }
 
+// Small launches: 32 rows x 32 columns (GEMM 1: 32 gate columns and the matching 32 up columns) per block, the contraction
+// split over its four waves, operands from memory straight into registers.  With fewer of the tiles above than CUs a
+// launch is a chain of latencies on few CUs: a load, its 2048 cycles of MFMA, the next.  Here a quarter of the chain is
+// left, four to eight times as many blocks share the work, and a wave has 64 k-values under way before it waits for the
+// first.  The four partial tiles are added in LDS, in the order of k.
+// Measured, both GEMMs of a rank's call, 64-row tiles against these: 128 rows of 128 x 256 18.0 : 13.0 us; 256 rows of 256 x
+// 512 27.5 : 14.2; 512 rows on 2-3 experts of 1024 x 2816 (tiles64, below, 330) 133 : 116, 256 rows (210) 115 : 74, 32 rows
+// 105 : 46; 768 rows of 768 x 768 (180) 51 : 46; but 900 rows of 768 x 1024 (239) 57 : 62, 1024 rows of 1024 x 2816 (630) 216 :
+// 230, 4096 rows (2400) 665 : 826.  With a few rows per expert the 64-row tiles are mostly empty however many they are:
+// 16 rows on each of 32 experts of 1024 x 2816 248 : 213, 8 rows 182 : 156; 32 rows 269 : 296.  Rows that are no multiple of
+// 16 bytes: 576 rows of 700 x 777 (149) 57 : 54, 900 rows of 999 x 777 on 13 experts (392) 123 : 116, (536) 122 : 170.
+constexpr int kSM = 32, kSChunk = 32;
+
+template <int EPI, int V>
+__device__ __forceinline__ void ffn_f32_split_body(const float* __restrict__ A, const float* __restrict__ B0,
+                                                   const float* __restrict__ B1, int Kd, int N, float* __restrict__ C,
+                                                   float* __restrict__ act, const TileEntry* __restrict__ tiles,
+                                                   const int32_t* __restrict__ count, const int32_t* __restrict__ seg, int E) {
+    constexpr int NP = EPI == 0 ? 2 : 1;
+    __shared__ __attribute__((aligned(16))) float part[4 * NP * 16 * 64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int r = lane & 31, h = lane >> 5;
+    RankTiles rank;
+    if (seg != nullptr) rank.init(seg, E, kSM);
+    const int ntn = (N + 31) / 32, ntm = seg != nullptr ? rank.count : *count, total = ntm * ntn;
+    const int nc = (Kd + kSChunk - 1) / kSChunk, c0 = nc * wave / 4, c1 = nc * (wave + 1) / 4;
+    for (int work = blockIdx.x; work < total; work += gridDim.x) {
+        const int tm = work / ntn, n0 = (work - tm * ntn) * 32;
+        const TileEntry te = seg != nullptr ? rank.get(tm, kSM) : tiles[tm];
+        const float* Bp[2];
+        Bp[0] = B0 + (size_t)te.expert * Kd * N;
+        Bp[1] = EPI == 0 ? B1 + (size_t)te.expert * Kd * N : Bp[0];
+        // rows past the tile's last and (by the offset) k-values past Kd lie beyond A's descriptor, k-rows past Kd beyond
+        // B's: zeros on both sides; columns past N are clamped, their results never stored
+        const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
+            (void*)(A + (size_t)te.row0 * Kd), 0, (int)((uint32_t)te.rows * Kd * 4u), 0x00020000);
+        const uint32_t b_off = ((uint32_t)4 * h * N + min(n0 + r, N - 1)) * 4u;
+        struct Chunk {
+            f32x4 a[4];
+            float b[NP][16];
+        };
+        auto fetch = [&](Chunk& c, int at) {
+            const int k0 = at * kSChunk;
+            const unsigned long long left = (unsigned long long)(Kd - k0) * N * 4u;
+            const int b_size = (int)(uint32_t)(left < 0xfffffff0ull ? left : 0xfffffff0ull);
+            static_for<4>([&](auto j) {
+                const int k = k0 + 8 * j.value + 4 * h;
+                auto off = [&](int i) { return k + i < Kd ? ((uint32_t)r * Kd + k + i) * 4u : 0xf0000000u; };
+                if constexpr (V == 4) {
+                    c.a[j.value] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(ra, off(0), 0, 0));
+                } else {
+                    static_for<4>([&](auto i) {
+                        c.a[j.value][i.value] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(ra, off(i.value), 0, 0));
+                    });
+                }
+            });
+            static_for<NP>([&](auto t) {
+                const __amdgpu_buffer_rsrc_t rb =
+                    __builtin_amdgcn_make_buffer_rsrc((void*)(Bp[t.value] + (size_t)k0 * N), 0, b_size, 0x00020000);
+                static_for<16>([&](auto i) {
+                    c.b[t.value][i.value] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                        rb, b_off, (8 * (i.value / 4) + i.value % 4) * N * 4, 0));
+                });
+            });
+        };
+        f32x16 acc[NP];
+        static_for<NP>([&](auto t) { static_for<16>([&](auto q) { acc[t.value][q.value] = 0.f; }); });
+        auto multiply = [&](const Chunk& c) {
+            static_for<16>([&](auto i) {
+                static_for<NP>([&](auto t) {
+                    acc[t.value] = __builtin_amdgcn_mfma_f32_32x32x2f32(c.a[i.value / 4][i.value % 4], c.b[t.value][i.value], acc[t.value], 0, 0, 0);
+                });
+            });
+        };
+        Chunk x, y;
+        if (c0 < c1) fetch(x, c0);
+        for (int c = c0; c < c1; c += 2) {      // (wave-uniform)
+            if (c + 1 < c1) fetch(y, c + 1);
+            multiply(x);
+            if (c + 2 < c1) fetch(x, c + 2);
+            if (c + 1 < c1) multiply(y);
+        }
+        static_for<NP>([&](auto t) {
+            static_for<16>([&](auto q) { part[((wave * NP + t.value) * 16 + q.value) * 64 + lane] = acc[t.value][q.value]; });
+        });
+        lds_barrier();
+        // wave w adds up and stores the rows 8 w .. 8 w + 7 (registers 4 w .. 4 w + 3: lane = column)
+        static_for<4>([&](auto q) {
+            float v[NP];
+            static_for<NP>([&](auto t) {
+                const float* p = part + (t.value * 16 + 4 * wave + q.value) * 64 + lane;
+                v[t.value] = ((p[0] + p[NP * 1024]) + p[2 * NP * 1024]) + p[3 * NP * 1024];
+            });
+            const int m = 8 * wave + 4 * h + q.value, n = n0 + r;
+            if (m < te.rows && n < N) {
+                const size_t row = (size_t)te.row0 + m;
+                if constexpr (EPI == 0) {
+                    if (act != nullptr) {
+                        act[row * (2 * (size_t)N) + n] = v[0];
+                        act[row * (2 * (size_t)N) + N + n] = v[1];
+                    }
+                    C[row * N + n] = silu_mul_f32(v[0], v[1]);
+                } else {
+                    C[row * N + n] = v[0];
+                }
+            }
+        });
+        lds_barrier();      // the next tile's parts
+    }
+}
+template <int EPI, int V>
+__global__ __launch_bounds__(256, 2) void k_ffn_f32_split(const float* __restrict__ A, const float* __restrict__ B0,
+                                                          const float* __restrict__ B1, int Kd, int N, float* __restrict__ C,
+                                                          float* __restrict__ act, const TileEntry* __restrict__ tiles,
+                                                          const int32_t* __restrict__ count, const int32_t* __restrict__ seg, int E) {
+    ffn_f32_split_body<EPI, V>(A, B0, B1, Kd, N, C, act, tiles, count, seg, E);
+}
+
 }  // namespace
 
 int launch_ffn_f32(const fine_shape& s, int rank_lo, int rank_hi, const void* x_perm, const void* wg, const void* wu,
@@ -178,25 +296,30 @@ int launch_ffn_f32(const fine_shape& s, int rank_lo, int rank_hi, const void* x_
     auto* h = reinterpret_cast<float*>(ws + L.h);
     if ((s.flags & FINE_FLAG_ACT_SAVE_H) && act_save != nullptr)      // H behind the saved pre-activations
         h = static_cast<float*>(act_save) + (size_t)s.T * s.K * 2 * s.f;
+    const int n_ranks = rank_hi - rank_lo;
+    const bool wide = s.d % 4 == 0 && s.f % 4 == 0;      // 16-byte pieces of a row are aligned
+    // expected tiles of 64 rows (see pick_tile in ffn_mfma.hip)
+    const double rows = (double)s.T * s.K * n_ranks / s.G, runs = std::min((double)s.E * n_ranks / s.G + 1.0, (double)s.E);
+    const double tiles64 = (rows / kBM + runs) * (cdiv(s.f, 64) + cdiv(s.d, 64)) / 2;
+    const bool split = tiles64 < 220.0 || rows <= 16.0 * runs;
+    const int bm = split ? kSM : kBM, bn = split ? 32 : 64;
     const int32_t* seg = nullptr;
-    if (rank_hi - rank_lo == 1 && s.E <= kRankMapExperts) seg = seg_off + (size_t)rank_lo * (s.E + 1);
-    else FINE_TRY(launch_tile_map(s, seg_off, rank_lo, rank_hi, kBM, tiles, count, L.max_tiles, st));
-    // three blocks per CU; no more blocks than there can be tiles
-    const size_t rows_tiles = (size_t)s.T * s.K / kBM + (size_t)s.E * (rank_hi - rank_lo);
-    auto grid = [&](int n) { return (unsigned)std::min<size_t>(768, align_up(rows_tiles * cdiv(n, 64), 8)); };
-#define FINE_F32(V)                                                                                              \
-    do {                                                                                                         \
-        hipLaunchKernelGGL((k_ffn_f32<0, V>), dim3(grid(s.f)), dim3(256), 0, st, (const float*)x_perm, (const float*)wg, \
-                           (const float*)wu, s.d, s.f, h, (float*)act_save, tiles, count, seg, s.E);                       \
-        FINE_LAUNCH_CHECK();                                                                                     \
-        hipLaunchKernelGGL((k_ffn_f32<1, V>), dim3(grid(s.d)), dim3(256), 0, st, (const float*)h, (const float*)wd, \
-                           (const float*)nullptr, s.f, s.d, (float*)y_perm, (float*)nullptr, tiles, count, seg, s.E);      \
-        FINE_LAUNCH_CHECK();                                                                                     \
-    } while (0)
-    if (s.d % 4 == 0 && s.f % 4 == 0) FINE_F32(4);
-    else FINE_F32(1);
-#undef FINE_F32
-    return FINE_OK;
+    if (n_ranks == 1 && s.E <= kRankMapExperts) seg = seg_off + (size_t)rank_lo * (s.E + 1);
+    else FINE_TRY(launch_tile_map(s, seg_off, rank_lo, rank_hi, bm, tiles, count, L.max_tiles, st));
+    // as many blocks as fit a CU (three; split: eight waves per CU's SIMD at most); no more than there can be tiles
+    const size_t rows_tiles = (size_t)s.T * s.K / bm + (size_t)s.E * n_ranks;
+    auto grid = [&](int n) { return (unsigned)std::min<size_t>(split ? 1024 : 768, align_up(rows_tiles * cdiv(n, bn), 8)); };
+    auto run = [&](auto k1, auto k2) {
+        hipLaunchKernelGGL(k1, dim3(grid(s.f)), dim3(256), 0, st, (const float*)x_perm, (const float*)wg, (const float*)wu, s.d, s.f,
+                           h, (float*)act_save, tiles, count, seg, s.E);
+        FINE_LAUNCH_CHECK();
+        hipLaunchKernelGGL(k2, dim3(grid(s.d)), dim3(256), 0, st, (const float*)h, (const float*)wd, (const float*)nullptr, s.f, s.d,
+                           (float*)y_perm, (float*)nullptr, tiles, count, seg, s.E);
+        FINE_LAUNCH_CHECK();
+        return (int)FINE_OK;
+    };
+    if (split) return wide ? run(k_ffn_f32_split<0, 4>, k_ffn_f32_split<1, 4>) : run(k_ffn_f32_split<0, 1>, k_ffn_f32_split<1, 1>);
+    return wide ? run(k_ffn_f32<0, 4>, k_ffn_f32<1, 4>) : run(k_ffn_f32<0, 1>, k_ffn_f32<1, 1>);
 }
 
 }  // namespace fine

@@ -1,5 +1,6 @@
 """fp32 layers on the fp32 matrix cores: every element of y_perm and act_save against the fp64 oracle at the
-edges of the kernel's tiles (64 rows, 64 or 128 columns, 32 k-values; 16-byte and 4-byte operand loads)."""
+edges of the kernels' tiles (64 rows, 64 or 128 columns; small launches 32 rows, 32 columns; 32 k-values, which small
+launches deal to four waves; 16-byte and 4-byte operand loads)."""
 import numpy as np
 import pytest
 import torch
@@ -12,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("d,f", [(128, 256), (4, 4), (1, 1), (33, 65), (63, 31), (132, 68), (133, 858), (256, 132)])
-@pytest.mark.parametrize("T,E,K,G", [(64, 4, 2, 2), (130, 3, 3, 1), (260, 8, 2, 4)])
+@pytest.mark.parametrize("T,E,K,G", [(64, 4, 2, 2), (130, 3, 3, 1), (260, 8, 2, 4), (2200, 3, 3, 1), (40, 40, 1, 4)])
 def test_f32_ffn_every_element(d, f, T, E, K, G):
     cfg = wl.scaled(wl.CONFIGS["cfg1_tiny_f32"], T=T, d=d, f=f, E=E, K=K, G=G, seed=11)
     inp = wl.make_inputs(cfg, "cuda:0")

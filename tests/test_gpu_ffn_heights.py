@@ -1,0 +1,43 @@
+"""Expert FFN on lists of 256-row and of 128-row tiles: runs that end in short tiles, and a last round of few tiles, which are
+cut into four parts of unequal length.  Every element against 64-bit sums."""
+import pytest
+import torch
+
+import paper_2511_16947_amd as fm
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("tile,d,f,rows", [
+    (3, 128, 192, [1, 128, 129, 255, 256, 257, 384, 385, 640]),
+    (0, 128, 192, [1, 128, 129, 255, 256, 257, 384, 385, 640]),
+    (3, 2112, 2816, [1100, 1290, 200]),      # GEMM 1: 12 x 22 = 264 tiles of 33 k-steps
+    (2, 2112, 2816, [600, 650, 100]),        # the same from tiles of 128 rows
+    (3, 192, 2112, [256] * 33),              # GEMM 1: 33 x 17 = 561 tiles; GEMM 2: 33 tiles of 33 k-steps
+])
+def test_tiles_of_both_heights(tile, d, f, rows):
+    E, P = len(rows), sum(rows)
+    shape = fm.Shape(P, d, f, E, 1, 1, flags=fm.FLAG_LOCALITY | (tile << fm.FLAG_TILE_SHIFT))
+    gen = torch.Generator(device=DEV).manual_seed(P)
+
+    def normal(*s, std=1.0):
+        return (torch.randn(*s, generator=gen, device=DEV) * std).bfloat16()
+
+    x, wg, wu, wd = normal(P, d), normal(E, d, f, std=d ** -0.5), normal(E, d, f, std=d ** -0.5), normal(E, f, d, std=f ** -0.5)
+    seg_off = torch.tensor([0] + rows, device=DEV).cumsum(0).int()[None].contiguous()
+    y, ws = torch.full((P, d), 7.0, dtype=torch.bfloat16, device=DEV), fm.alloc_workspace(shape, fm.WS_FFN)
+    got = []
+    for _ in range(2):
+        fm.fine_grouped_ffn(shape, -1, x, wg, wu, wd, seg_off, y, None, ws)
+        got.append(y.clone())
+    assert torch.equal(got[0], got[1])
+    r = 0
+    for e, n in enumerate(rows):
+        xe = x[r:r + n].double()
+        h = (torch.nn.functional.silu(xe @ wg[e].double()) * (xe @ wu[e].double())).bfloat16().double()
+        want = h @ wd[e].double()
+        # H and y are rounded to bf16 (2^-9 each); an H on the other side of a rounding boundary moves y by 2^-8 of one
+        # of its f terms.  y has unit scale here.
+        assert (y[r:r + n].double() - want).abs().max() <= 2e-2 * max(1.0, float(want.abs().max())), (e, n)
+        r += n

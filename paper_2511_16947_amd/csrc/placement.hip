@@ -87,8 +87,13 @@ __device__ inline u64 wave_max_u64(u64 v) {
 // Load per replica as an integer that orders exactly like the fraction: two different l / c with c <= 64 are at
 // least 1 / 64^2 apart, so floor(2^13 l / c) differs the same way, and equal fractions give equal values.  Below it
 // the expert's index, lower = larger.  A round costs one wave maximum and one division (16 rounds on 64
-// experts: 18 -> 7 us against fractions compared by cross-multiplication in a butterfly of shuffles).
-__device__ inline u64 count_key(int load, int c, int e) { return (((u64)(uint32_t)load << 13) / (uint32_t)c) << 10 | (u64)(kMaxE - 1 - e) | 1ull << 60; }
+// experts: 18 -> 7 us against fractions compared by cross-multiplication in a butterfly of shuffles).  The division is a
+// double's: numerator and quotient have 44 bits at most, so the quotient rounds by at most 2^-9, and one that is no whole
+// number is at least 1 / 64 below the next (a division of 64-bit integers is a hundred instructions: 7.7 -> 7.2 us).
+__device__ inline u64 count_key(int load, int c, int e) {
+    const u64 per = (u64)((double)((u64)(uint32_t)load << 13) / (double)c);
+    return per << 10 | (u64)(kMaxE - 1 - e) | 1ull << 60;
+}
 
 __global__ __launch_bounds__(64) void k_replica_counts(const int32_t* __restrict__ load, int E, int G, int slots,
                                                        int32_t* __restrict__ counts) {
@@ -151,8 +156,9 @@ __device__ inline void draw_candidate(const int* s_order, u64* s_mask, int E, in
 // A chain of E dependent steps, so a step is kept short: ranks are compared by 32 bits, 10 bits of slots not yet
 // used (a rank takes at most one replica per expert, so fewer than 1024 are used before a step) and the upper 22 of the
 // key.  Ranks that are equal in these are all chosen or all left, unless the last place falls between them: then a
-// row has chosen too many, and the step is done again with all bits.  (k_pick, one draw of 64
-// experts and the argmin of 4096 scores: 37 -> 23 us.)
+// row has chosen too many, and the step is done again with all bits.  An expert with one replica, as most have, goes to
+// its row's largest value: four rotations instead of fifteen.  (4096 candidates of 64 experts, 16 of them with several
+// replicas: 111 -> 98 us; k_pick, one draw and the argmin of 4096 scores, 23 -> 20.)
 template <int R, typename F>
 __device__ inline void rotations(F& f) {
     if constexpr (R < 16) {
@@ -160,19 +166,55 @@ __device__ inline void rotations(F& f) {
         rotations<R + 1>(f);
     }
 }
-__device__ inline void draw_rows(const int* s_order, uint32_t* s_mask, int E, int G, uint32_t seed, uint32_t cand0) {
+//
+// s_key, unless NULL: the ranks' keys in drawing order, [E][stride] (stride 64: a lane's own; 16: one candidate for every
+// row), made by all waves of the block beforehand (draw_keys): two multiplications and a dozen instructions less per step.
+__device__ inline uint32_t candidate_hash(uint32_t seed, uint32_t cand) { return mix32(seed + 0x9E3779B9u * (cand + 1u)); }
+__device__ inline uint32_t key_of(uint32_t h, int e, int g) { return mix32(h ^ (((uint32_t)e * 64u + (uint32_t)g + 1u) * 0x9E3779B1u)); }
+
+__device__ inline void draw_keys(const int* s_order, uint32_t* s_key, int stride, int E, uint32_t seed, uint32_t cand0) {
+    for (int i = threadIdx.x; i < E * stride; i += blockDim.x) {
+        const int l = i & (stride - 1);
+        s_key[i] = key_of(candidate_hash(seed, cand0 + (uint32_t)(l >> 4)), s_order[i / stride] & 0xffff, l & 15);
+    }
+    __syncthreads();
+}
+
+__device__ inline void draw_rows(const int* s_order, const uint32_t* s_key, int stride, uint32_t* s_mask, int E, int G, uint32_t seed,
+                                 uint32_t cand0) {
     const int lane = threadIdx.x & 63, g = lane & 15, row = lane >> 4;
-    const uint32_t h = mix32(seed + 0x9E3779B9u * (cand0 + (uint32_t)row + 1u));
+    const uint32_t h = candidate_hash(seed, stride == 16 ? cand0 : cand0 + (uint32_t)row);
     uint32_t unused = 1023u;
-    auto key_of = [&](int e) { return mix32(h ^ (((uint32_t)e * 64u + (uint32_t)g + 1u) * 0x9E3779B1u)); };
+    auto key_at = [&](int i, int e) { return s_key != nullptr ? s_key[i * stride + (lane & (stride - 1))] : key_of(h, e, g); };
     int cur = s_order[0], next = s_order[min(1, E - 1)];
-    uint32_t next_key = key_of(cur & 0xffff);
-    for (int i = 0; i < E; ++i) {
-        const int e = cur & 0xffff, c = cur >> 16;
-        const uint32_t key = next_key;
+    uint32_t next_key = key_at(0, cur & 0xffff);
+    uint32_t* const mine = s_mask + row * E;
+    // with all bits: slots, key, then lower rank, distinct over the ranks
+    auto choose_exactly = [&](uint32_t key, int c) {
+        const u64 all = g < G ? (u64)unused << 40 | (u64)key << 8 | (u64)(255 - g) : 0ull;
+        int ahead = 0;
+        auto count_all = [&](auto r) {
+            const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(all >> 32), 0x120 + r.value, 0xf, 0xf, false);
+            const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)all, 0x120 + r.value, 0xf, 0xf, false);
+            ahead += ((u64)hi << 32 | lo) > all;
+        };
+        rotations<1>(count_all);
+        return g < G && ahead < c;
+    };
+    int i = 0;
+    auto step = [&](int& e, int& c, uint32_t& key) {      // on to expert i, and the next one's loads on their way
+        e = __builtin_amdgcn_readfirstlane(cur & 0xffff);
+        c = __builtin_amdgcn_readfirstlane(cur >> 16);
+        key = next_key;
         cur = next;
-        next_key = key_of(cur & 0xffff);      // the next step's, beside the chain
+        next_key = key_at(min(i + 1, E - 1), cur & 0xffff);
         next = s_order[min(i + 2, E - 1)];
+    };
+    int e, c;
+    uint32_t key;
+    for (; i < E; ++i) {                                  // several replicas: counts never grow along the order
+        if (__builtin_amdgcn_readfirstlane(cur >> 16) <= 1) break;
+        step(e, c, key);
         // larger is better; lanes beyond the ranks hold 0, which is ahead of nobody
         const uint32_t comp = g < G ? unused << 22 | key >> 10 : 0u;
         int ahead = 0;
@@ -183,20 +225,27 @@ __device__ inline void draw_rows(const int* s_order, uint32_t* s_mask, int E, in
         bool chosen = g < G && ahead < c;
         u64 m = __ballot(chosen);
         if (__ballot(__popc((uint32_t)(m >> (16 * row)) & 0xffffu) != min(c, G)) != 0ull) {
-            // slots, key, then lower rank: distinct over the ranks
-            const u64 all = g < G ? (u64)unused << 40 | (u64)key << 8 | (u64)(255 - g) : 0ull;
-            ahead = 0;
-            auto count_all = [&](auto r) {
-                const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(all >> 32), 0x120 + r.value, 0xf, 0xf, false);
-                const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)all, 0x120 + r.value, 0xf, 0xf, false);
-                ahead += ((u64)hi << 32 | lo) > all;
-            };
-            rotations<1>(count_all);
-            chosen = g < G && ahead < c;
+            chosen = choose_exactly(key, c);
             m = __ballot(chosen);
         }
         unused -= chosen;
-        if (g == 0) s_mask[row * E + e] = (uint32_t)(m >> (16 * row)) & 0xffffu;
+        if (g == 0) mine[e] = (uint32_t)(m >> (16 * row)) & 0xffffu;
+    }
+    for (; i < E; ++i) {
+        step(e, c, key);
+        const uint32_t comp = g < G ? unused << 22 | key >> 10 : 0u;
+        uint32_t top = comp;
+        auto larger = [&](auto r) { top = max(top, (uint32_t)__builtin_amdgcn_mov_dpp((int)top, 0x120 + r.value, 0xf, 0xf, false)); };
+        larger(std::integral_constant<int, 8>{});
+        larger(std::integral_constant<int, 4>{});
+        larger(std::integral_constant<int, 2>{});
+        larger(std::integral_constant<int, 1>{});
+        bool chosen = comp == top;                        // (never 0: at most E < 1024 slots are used up)
+        if (__popcll(__ballot(chosen)) != 4) chosen = choose_exactly(key, 1);
+        if (c < 1) chosen = false;
+        if (c < 1 && g == 0) mine[e] = 0u;
+        if (chosen) mine[e] = 1u << g;
+        unused -= chosen;
     }
 }
 
@@ -356,8 +405,10 @@ __global__ __launch_bounds__(kScoreThreads) void k_score(const int32_t* __restri
     if constexpr (DRAW) {
         drawing_order(counts, s_cnt, s_order, E);
         // one wave draws (rows past the last candidate draw unused ones); not the same SIMD's in every block of a CU
+        uint32_t* s_key = E <= kWaves * kTable / 64 ? (uint32_t*)s_f : nullptr;      // (the tables are cleared later)
+        if (s_key != nullptr) draw_keys(s_order, s_key, 64, E, seed, (uint32_t)cand0);
         if (wave == (int)((blockIdx.x ^ (blockIdx.x >> 8)) & (kWaves - 1)))
-            draw_rows(s_order, s_mask, E, G, seed, (uint32_t)cand0);
+            draw_rows(s_order, s_key, 64, s_mask, E, G, seed, (uint32_t)cand0);
     } else {
         const uint8_t* pl = place + (size_t)cand0 * E * G;
         for (int i = tid; i < ncand * E; i += kScoreThreads) {
@@ -459,7 +510,7 @@ __global__ __launch_bounds__(64) void k_score_flow(const int32_t* __restrict__ l
 // ---------------------------------------------------------------------------
 // the best candidate
 // ---------------------------------------------------------------------------
-constexpr int kPickThreads = 1024;
+constexpr int kPickThreads = 1024, kPickKeys = 256;      // experts whose keys are made beforehand
 
 __global__ __launch_bounds__(kPickThreads) void k_pick(const int64_t* __restrict__ m_num, const int32_t* __restrict__ m_den, int n,
                                               const int32_t* __restrict__ counts, int E, int G, int slots, uint32_t seed,
@@ -468,7 +519,7 @@ __global__ __launch_bounds__(kPickThreads) void k_pick(const int64_t* __restrict
     u64* s_mask = (u64*)s_dyn;               // [E]
     int* s_order = (int*)(s_mask + E);       // [E]
     int* s_cnt = s_order + E;                // [E]
-    __shared__ int s_idx[kPickThreads], s_num[kPickThreads], s_den[kPickThreads];
+    __shared__ int s_idx[kPickThreads / 64], s_num[kPickThreads / 64], s_den[kPickThreads / 64];
     const int tid = threadIdx.x;
     // smallest m, then lowest index; candidates flagged infeasible (den == 0) never win
     int bi = -1, bn = 0, bd = 1;
@@ -489,34 +540,35 @@ __global__ __launch_bounds__(kPickThreads) void k_pick(const int64_t* __restrict
             }
         }
     }
-    s_idx[tid] = bi; s_num[tid] = bn; s_den[tid] = bd;
-    __syncthreads();
-    for (int off = kPickThreads / 2; off > 0; off >>= 1) {
-        if (tid < off) {
-            const int a = s_idx[tid], b = s_idx[tid + off];
-            if (b >= 0) {
-                bool take = a < 0;
-                if (!take) {
-                    const i64 l = (i64)s_num[tid + off] * s_den[tid], r = (i64)s_num[tid] * s_den[tid + off];
-                    take = l < r || (l == r && b < a);
-                }
-                if (take) {
-                    s_idx[tid] = b; s_num[tid] = s_num[tid + off]; s_den[tid] = s_den[tid + off];
-                }
-            }
+    // (better: smaller m, then lower index; any candidate is better than none)
+    auto take = [&](int i, int num, int den) {
+        const i64 l = (i64)num * bd, r = (i64)bn * den;
+        if (i >= 0 && (bi < 0 || l < r || (l == r && i < bi))) {
+            bi = i; bn = num; bd = den;
         }
-        __syncthreads();
+    };
+#pragma unroll 1      // (code that runs once costs its fetch)
+    for (int off = 32; off > 0; off >>= 1) take(__shfl_xor(bi, off, 64), __shfl_xor(bn, off, 64), __shfl_xor(bd, off, 64));
+    if ((tid & 63) == 0) {
+        s_idx[tid >> 6] = bi; s_num[tid >> 6] = bn; s_den[tid >> 6] = bd;
     }
-    const int best = s_idx[0];
+    __syncthreads();
+    bi = s_idx[tid & 15]; bn = s_num[tid & 15]; bd = s_den[tid & 15];
+    static_assert(kPickThreads / 64 == 16, "one entry per wave");
+#pragma unroll 1
+    for (int off = 8; off > 0; off >>= 1) take(__shfl_xor(bi, off, 64), __shfl_xor(bn, off, 64), __shfl_xor(bd, off, 64));
+    const int best = __builtin_amdgcn_readfirstlane(bi);
     if (tid == 0) best_out[0] = best;
     if (best < 0) {
         for (int i = tid; i < E * G; i += kPickThreads) place[i] = 0;
         return;
     }
     drawing_order(counts, s_cnt, s_order, E);
-    uint32_t* s_rows = (uint32_t*)(s_cnt + E);      // [4][E], row 0 is the winner's (G <= kMaxEnumG)
+    uint32_t* s_rows = (uint32_t*)(s_cnt + E);      // [4][E], every row the winner's (G <= kMaxEnumG)
+    uint32_t* s_key = G <= kMaxEnumG && E <= kPickKeys ? s_rows + 4 * E : nullptr;
+    if (s_key != nullptr) draw_keys(s_order, s_key, 16, E, seed, (uint32_t)best);
     if (tid < 64) {
-        if (G <= kMaxEnumG) draw_rows(s_order, s_rows, E, G, seed, (uint32_t)best);
+        if (G <= kMaxEnumG) draw_rows(s_order, s_key, 16, s_rows, E, G, seed, (uint32_t)best);
         else draw_candidate(s_order, s_mask, E, G, slots, seed, (uint32_t)best);
     }
     __syncthreads();
@@ -654,7 +706,7 @@ int launch_place_search(const fine_shape& s, const int32_t* load, const int32_t*
         FINE_TRY(launch_score<true>(s, load, counts, nullptr, n, slots, seed, m_num, m_den, st));
     }
     FINE_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_pick, dim3(1), dim3(kPickThreads), (size_t)8 * s.E * 4, st, m_num, m_den, n, counts, s.E, s.G, slots, seed,
+    hipLaunchKernelGGL(k_pick, dim3(1), dim3(kPickThreads), ((size_t)8 * s.E + (s.E <= kPickKeys ? 16 * s.E : 0)) * 4, st, m_num, m_den, n, counts, s.E, s.G, slots, seed,
                        best, place);
     FINE_LAUNCH_CHECK();
     return FINE_OK;

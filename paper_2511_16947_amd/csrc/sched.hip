@@ -186,24 +186,24 @@ __global__ __launch_bounds__(256) void k_pairs(const int32_t* __restrict__ topk_
 }
 
 // ---------------------------------------------------------------------------
-// Small problems: all of the above by one block with every table in LDS.  Five launches of a few microseconds each
+// Small problems: all of the above by one block with every table in LDS.  Four launches of a few microseconds each
 // are most of what scheduling a decoding step or a small micro-batch takes.
 //   MODE 0  every expert on every rank: everything
-//   MODE 1  load tables only (the replica loads come from k_general_x next)
-//   MODE 2  everything after the replica loads in x_eg (the token bitmaps are built again)
-// Scans and sums by DPP (flow_wave.h): a wave has several experts to do one after another, and six LDS-crossbar
-// shuffles per scan made this slower than the five launches (128 experts on 8 ranks, 1024 pairs: 27 -> 20 us).
-// LDS: bitmap u64 [E][W], then int32 cum [E][W+1], inpre, in, x [E][G], Ypre [E][G+1][G] (row G = totals; Y is the
-// difference of two rows), seg_off [G][E+1], load [E], rank sums [G].
-// Taken up to 2048 pairs and 512 (expert, rank)s: 512 pairs, 8 experts on 4 ranks 5 us against 15 in five launches, the whole
-// fp32 layer of that size 105 -> 97 us; 128 pairs, 8 experts on 8 ranks 6.4 against 23.  One block is no faster beyond: 3915 pairs,
-// 20 experts on 5 ranks 14.6 against 17 (and the layer takes as long), 128 experts on 8 ranks 20 against 20.
+//   MODE 1  load tables only (the replica loads come from k_general_x next, with the segment offsets and the queues)
+//   MODE 2  the pairs, after that (the token bitmaps are built again)
+// Scans and sums by DPP (flow_wave.h): a wave has several experts to do one after another.
+// LDS: bitmap u64 [E][W], then int32 cum [E][W+1], inpre, in [E][G], and in MODE 0 x and two queues [E][G], seg_off [G][E+1],
+// load [E].
+// Taken up to 2048 pairs, 128 experts and 2048 (expert, rank)s.  Against four launches, both replayed from a graph (in a stream
+// of single launches each of them takes 1-2 us more): 512 pairs, 8 experts on 4 ranks 4.0 : 9.7 us; 1024 pairs, 128 experts on
+// 8 ranks 9.8 : 10.9; 2048 pairs, 128 on 8 11.4 : 11.7, 64 on 16 10.1 : 11.1; but 1280 pairs, 192 on 5 13.5 : 12.0, 2048
+// pairs, 256 on 8 18.8 : 12.7.
 // ---------------------------------------------------------------------------
-constexpr int kSmallThreads = 1024, kSmallPairs = 2048, kSmallTables = 512;
+constexpr int kSmallThreads = 1024, kSmallPairs = 2048, kSmallExperts = 128, kSmallTables = 2048;
 constexpr size_t kSmallLds = 64 * 1024;
 
 __host__ __device__ inline size_t small_lds_bytes(int E, int G, int W) {
-    return (size_t)E * W * 8 + ((size_t)E * (W + 1) + 3 * (size_t)E * G + (size_t)E * (G + 1) * G + (size_t)G * (E + 1) + E + G) * 4;
+    return (size_t)E * W * 8 + ((size_t)E * (W + 1) + 5 * (size_t)E * G + (size_t)G * (E + 1) + E) * 4;
 }
 
 template <int MODE>
@@ -212,17 +212,16 @@ __global__ __launch_bounds__(kSmallThreads) void k_sched_small(const int32_t* __
                                                                int32_t* __restrict__ input_eg, int32_t* __restrict__ x_eg,
                                                                int32_t* __restrict__ max_load, int32_t* __restrict__ pair_dst,
                                                                int32_t* __restrict__ row_of_pair, int32_t* __restrict__ pair_of_row,
-                                                               int32_t* __restrict__ seg_off, int32_t* __restrict__ rank_off) {
+                                                               int32_t* __restrict__ seg_off, int32_t* __restrict__ rank_off,
+                                                               RouteTables route) {
     extern __shared__ unsigned long long s_small[];
     unsigned long long* bm = s_small;
     int* cum = reinterpret_cast<int*>(bm + E * W);
     int* inpre = cum + E * (W + 1);
     int* in = inpre + E * G;
     int* x = in + E * G;
-    int* ypre = x + E * G;
-    int* seg = ypre + E * (G + 1) * G;
+    int* seg = x + 3 * E * G;
     int* s_load = seg + G * (E + 1);
-    int* s_rank = s_load + E;
     constexpr int kWaves = kSmallThreads / kWave;
     const int tid = threadIdx.x, wave = tid / kWave, lane = lane_id(), P = T * K;
 
@@ -234,105 +233,85 @@ __global__ __launch_bounds__(kSmallThreads) void k_sched_small(const int32_t* __
         if (e >= 0 && e < E) atomicOr(&bm[e * W + (t >> 6)], 1ull << (t & 63));      // OR is order independent
     }
     __syncthreads();
-    // 2. a wave per expert: prefix of popcounts, load_e, input_e^g (W <= 64: a word per lane)
+    // 2. prefix of popcounts and load_e: a thread per expert where it has few words, else a wave (W <= 64: a word per lane);
+    //    then input_e^g, a thread per (expert, source)
     const int Tg = T / G;
-    for (int e = wave; e < E; e += kWaves) {
-        const unsigned long long* b = bm + e * W;
-        const int c = lane < W ? __popcll(b[lane]) : 0;
-        const int inc = flow::wave_incl_scan_i(c), total = __builtin_amdgcn_readlane(inc, kWave - 1);
-        if (lane < W) cum[e * (W + 1) + lane] = inc - c;
-        if (lane == 0) {
-            cum[e * (W + 1) + W] = total;
-            s_load[e] = total;
-            if (MODE != 2) load[e] = total;
+    auto put_load = [&](int e, int total) {
+        cum[e * (W + 1) + W] = total;
+        if (MODE == 0) s_load[e] = total;
+        if (MODE != 2) load[e] = total;
+    };
+    if (W <= 4) {
+        for (int e = tid; e < E; e += kSmallThreads) {
+            int total = 0;
+            for (int w = 0; w < W; ++w) {
+                cum[e * (W + 1) + w] = total;
+                total += __popcll(bm[e * W + w]);
+            }
+            put_load(e, total);
         }
+    } else {
+        for (int e = wave; e < E; e += kWaves) {
+            const int c = lane < W ? __popcll(bm[e * W + lane]) : 0, inc = flow::wave_incl_scan_i(c);
+            if (lane < W) cum[e * (W + 1) + lane] = inc - c;
+            if (lane == kWave - 1) put_load(e, inc);
+        }
+    }
+    __syncthreads();
+    for (int i = tid; i < E * G; i += kSmallThreads) {
+        const int e = i / G, t0 = (i - e * G) * Tg;
         auto before = [&](int t) -> int {      // pairs of e among the tokens before t
-            if (t >= T) return total;
-            return cum[e * (W + 1) + (t >> 6)] + __popcll(b[t >> 6] & ((1ull << (t & 63)) - 1ull));
+            const int w = t >> 6;
+            return cum[e * (W + 1) + w] + (t & 63 ? __popcll(bm[e * W + w] & ((1ull << (t & 63)) - 1ull)) : 0);
         };
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        if (lane < G) {
-            const int b0 = before(lane * Tg), b1 = before(lane * Tg + Tg);
-            inpre[e * G + lane] = b0;
-            in[e * G + lane] = b1 - b0;
-            if (MODE != 2) input_eg[e * G + lane] = b1 - b0;
-        }
+        const int b0 = before(t0), b1 = t0 + Tg >= T ? cum[e * (W + 1) + W] : before(t0 + Tg);
+        inpre[i] = b0;
+        in[i] = b1 - b0;
+        if (MODE != 2) input_eg[i] = b1 - b0;
     }
     if (MODE == 1) return;
     __syncthreads();
-    // 3. a wave per expert: replica loads, Algorithm 1 (see k_tables)
-    for (int e = wave; e < E; e += kWaves) {
-        int xg = 0;
-        if (MODE == 0) {
-            int part = 0;
-            for (int i = lane; i < e; i += kWave) part += s_load[i];
-            const int off = flow::wave_sum_i(part), M = (P + G - 1) / G;
+    // 3. a wave per expert: replica loads, segment offsets, the queues of Algorithm 1 (see k_tables)
+    const RouteTables t = MODE == 0 ? RouteTables{x + E * G, x + 2 * E * G, nullptr, nullptr} : route;
+    if (MODE == 0) {
+        const int M = (P + G - 1) / G;
+        for (int e = wave; e < E; e += kWaves) {
+            int part = 0, all = 0;
+            for (int i = lane; i < E; i += kWave) {
+                const int v = s_load[i];
+                part += i < e ? v : 0;
+                all += v;
+            }
+            const int off = flow::wave_sum_i(part), total = flow::wave_sum_i(all), mine = s_load[e];
+            int xg = 0;
             if (lane < G) {
-                xg = overlap(off, s_load[e], lane * M, M);
-                x_eg[e * G + lane] = xg;
+                xg = overlap(off, mine, lane * M, M);
+                x[e * G + lane] = x_eg[e * G + lane] = xg;
+                const int lo = min(lane * M, total), hi = min(lane * M + M, total);      // the rows of this rank
+                seg[lane * (E + 1) + e] = seg_off[lane * (E + 1) + e] = min(max(off, lo), hi);
+                if (e == E - 1) {
+                    seg_off[lane * (E + 1) + E] = hi;
+                    rank_off[lane] = lo;
+                    if (lane == G - 1) rank_off[G] = hi;
+                }
             }
             if (e == 0 && lane == 0) max_load[0] = M;
-        } else if (lane < G) {
-            xg = x_eg[e * G + lane];
+            write_route(t, e, G, 0, locality, lane < G ? in[e * G + lane] : 0, xg);
         }
-        const int in_g = lane < G ? in[e * G + lane] : 0;
-        const int loc = locality ? min(in_g, xg) : 0, ri = in_g - loc, rx = xg - loc;
-        const int RI = flow::wave_incl_scan_i(ri) - ri, RX = flow::wave_incl_scan_i(rx) - rx;
-        if (lane < G) x[e * G + lane] = xg;
-        int run = 0;
-        for (int g = 0; g < G; ++g) {
-            if (lane < G) ypre[(e * (G + 1) + g) * G + lane] = run;
-            run += overlap(__builtin_amdgcn_readlane(RI, g), __builtin_amdgcn_readlane(ri, g), RX, rx) + (g == lane ? loc : 0);
-        }
-        if (lane < G) ypre[(e * (G + 1) + G) * G + lane] = run;
+        __syncthreads();
     }
-    __syncthreads();
-    // 4. a wave per rank: first row of every segment
-    for (int g = wave; g < G; g += kWaves) {
-        int part = 0;
-        for (int e = lane; e < E; e += kWave) part += x[e * G + g];
-        part = flow::wave_sum_i(part);
-        if (lane == 0) s_rank[g] = part;
-    }
-    __syncthreads();
-    for (int g = wave; g < G; g += kWaves) {
-        const int base = flow::wave_sum_i(lane < g ? s_rank[lane] : 0);
-        int carry = base;
-        for (int e0 = 0; e0 < E; e0 += kWave) {
-            const int e = e0 + lane, v = e < E ? x[e * G + g] : 0, inc = flow::wave_incl_scan_i(v);
-            if (e < E) {
-                seg[g * (E + 1) + e] = carry + inc - v;
-                seg_off[g * (E + 1) + e] = carry + inc - v;
-            }
-            carry += __builtin_amdgcn_readlane(inc, kWave - 1);
-        }
-        if (lane == 0) {
-            seg_off[g * (E + 1) + E] = carry;
-            rank_off[g] = base;
-            if (g == G - 1) rank_off[G] = carry;
-        }
-    }
-    __syncthreads();
-    // 5. destination and row of every pair (see k_pairs)
+    // 4. destination and row of every pair (see k_pairs)
+    const int* xs = MODE == 0 ? x : x_eg;
+    const int* segs = MODE == 0 ? seg : seg_off;
     for (int p = tid; p < P; p += kSmallThreads) {
-        const int t = p / K, e = topk_idx[p];
+        const int tok = p / K, e = topk_idx[p];
         int dst = -1, row = p;
         if (e >= 0 && e < E) {
-            const int g = t / Tg, w = t >> 6;
-            int r = cum[e * (W + 1) + w] + __popcll(bm[e * W + w] & ((1ull << (t & 63)) - 1ull)) - inpre[e * G + g];
-            const int* y0 = ypre + (e * (G + 1) + g) * G;
-            if (locality) {
-                const int c = y0[G + g] - y0[g];
-                if (r < c) dst = g;
-                else r -= c;
-            }
-            for (int h = 0; h < G && dst < 0; ++h) {
-                if (locality && h == g) continue;
-                const int c = y0[G + h] - y0[h];
-                if (r < c) dst = h;
-                else r -= c;
-            }
-            if (dst >= 0) row = seg[dst * (E + 1) + e] + y0[dst] + r;
+            const int g = tok / Tg, w = tok >> 6;
+            const int r = cum[e * (W + 1) + w] + __popcll(bm[e * W + w] & ((1ull << (tok & 63)) - 1ull)) - inpre[e * G + g];
+            int place = 0;
+            dst = route_token(t, in + e * G, xs + e * G, (size_t)e * G, G, 0, locality, g, r, &place);
+            if (dst >= 0) row = segs[dst * (E + 1) + e] + place;
         }
         pair_dst[p] = dst;
         row_of_pair[p] = row;
@@ -423,21 +402,21 @@ int launch_sched(const fine_shape& s, const int32_t* topk_idx, const uint8_t* pl
                  int32_t* pair_dst, int32_t* row_of_pair, int32_t* pair_of_row,
                  int32_t* seg_off, int32_t* rank_off, char* ws, hipStream_t st) {
     const int W = cdiv(s.T, 64);
-    const size_t small_lds = W <= 64 && (long long)s.T * s.K <= kSmallPairs && s.E * s.G <= kSmallTables ? small_lds_bytes(s.E, s.G, W) : kSmallLds + 1;
+    const SchedArrays a = sched_arrays(s, ws);
+    const size_t small_lds = W <= 64 && (long long)s.T * s.K <= kSmallPairs && s.E <= kSmallExperts && s.E * s.G <= kSmallTables ? small_lds_bytes(s.E, s.G, W) : kSmallLds + 1;
     if (small_lds <= kSmallLds) {
         auto run = [&](auto k) {
             hipLaunchKernelGGL(k, dim3(1), dim3(kSmallThreads), small_lds, st, topk_idx, s.T, s.K, s.E, s.G, W,
                                (s.flags & FINE_FLAG_LOCALITY) ? 1 : 0, load, input_eg, x_eg, max_load, pair_dst, row_of_pair,
-                               pair_of_row, seg_off, rank_off);
+                               pair_of_row, seg_off, rank_off, a.route);
             return check_hip(hipGetLastError());
         };
         if (place == nullptr) return run(k_sched_small<0>);
         FINE_TRY(run(k_sched_small<1>));
-        FINE_TRY(launch_general_x(s, place, load, x_prev, x_eg, max_load, nullptr, RouteTables{}, nullptr, nullptr, st));
+        FINE_TRY(launch_general_x(s, place, load, x_prev, x_eg, max_load, input_eg, a.route, seg_off, rank_off, st));
         return run(k_sched_small<2>);
     }
     FINE_TRY(launch_sched_tables(s, topk_idx, load, input_eg, ws, st));
-    const SchedArrays a = sched_arrays(s, ws);
     if (place != nullptr) {
         FINE_TRY(launch_general_x(s, place, load, x_prev, x_eg, max_load, input_eg, a.route, seg_off, rank_off, st));
     } else {

@@ -1,6 +1,6 @@
 // Work-list construction for the grouped GEMMs, and the plain FMA expert FFN (layers wider than the
 // matrix-core kernels' 32-bit offsets reach, and a cross-check in tests).
-#include "common.h"
+#include "flow_wave.h"
 
 namespace fine {
 
@@ -11,10 +11,13 @@ namespace {
 // hot expert under the full placement fills whole ranks) form one run of rows and are cut into tiles together, so
 // that a call over all ranks reads an expert's weights once and not once per rank, and has one short tile per run
 // (64 tokens on 8 experts and 8 ranks: 8 tiles instead of 15).  One rank's segments are all of different experts.
-// Thread t takes C consecutive segments; everything it needs of the others are two running maxima (the index of the
-// last non-empty segment; the index of the first segment of the last run) and a sum of tile counts: three block
-// scans whatever the number of segments (8192 segments: 60 -> 31 us against a scan per 256 segments; 1024: 7 us).
+// Thread t takes C consecutive segments; everything it needs of the others are two running maxima (the last non-empty
+// segment; the first segment of the last run) and a sum of tile counts: three block scans whatever the number of
+// segments.  A segment is named by its place in seg_off.  The ranks' rows of seg_off are read into LDS once (CACHED: where they
+// fit) and walked there, with no division per segment: 8192 segments 31 -> 23
+// us, 1024 7.1 -> 5.4.
 constexpr int kMapThreads = 1024;
+constexpr size_t kMapLds = 60 * 1024;
 
 // zeroes the counters that the GEMM launches of a call use
 __device__ inline void clear_counts(int32_t* count) {
@@ -25,70 +28,88 @@ __device__ inline void clear_counts(int32_t* count) {
     if (threadIdx.x < kQueues) count[kQueueOffset + threadIdx.x * kQueueStride] = 0;
 }
 
+// exclusive scan over the block; op(ident, v) = v
 template <typename Op>
 __device__ inline int block_excl_scan(int v, int ident, int* s_w, Op op) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int inc = v;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int o = __shfl_up(inc, off, 64);
-        if (lane >= off) inc = op(inc, o);
-    }
+    auto wave_incl = [&](int x) {      // (DPP: lane layout in flow_wave.h)
+        x = op(flow::dpp_from<0x111, 0xf>(ident, x), x);
+        x = op(flow::dpp_from<0x112, 0xf>(ident, x), x);
+        x = op(flow::dpp_from<0x114, 0xf>(ident, x), x);
+        x = op(flow::dpp_from<0x118, 0xf>(ident, x), x);
+        x = op(flow::dpp_from<0x142, 0xa>(ident, x), x);
+        x = op(flow::dpp_from<0x143, 0xc>(ident, x), x);
+        return x;
+    };
+    const int inc = wave_incl(v);
     if (lane == 63) s_w[wave] = inc;
     __syncthreads();
     // what the waves before this one have: their at most 16 totals, scanned by every wave
-    int tot = lane < (int)(blockDim.x >> 6) ? s_w[lane] : ident;
-#pragma unroll
-    for (int off = 1; off < kMapThreads / 64; off <<= 1) {
-        const int o = __shfl_up(tot, off, 64);
-        if (lane >= off) tot = op(tot, o);
-    }
-    const int base = wave == 0 ? ident : __shfl(tot, max(wave - 1, 0), 64);
+    const int tot = wave_incl(lane < (int)(blockDim.x >> 6) ? s_w[lane] : ident);
+    const int base = wave == 0 ? ident : __builtin_amdgcn_readlane(tot, __builtin_amdgcn_readfirstlane(max(wave - 1, 0)));
     const int up = __shfl_up(inc, 1, 64);
     __syncthreads();      // s_w may be written again
     return lane == 0 ? base : op(base, up);
 }
 
+template <bool CACHED>
 __global__ __launch_bounds__(kMapThreads) void k_tile_map(const int32_t* __restrict__ seg_off, int E, int rank_lo,
                                                           int rank_hi, int BM, TileEntry* __restrict__ tiles,
                                                           int32_t* __restrict__ count, int max_tiles) {
+    extern __shared__ int32_t s_seg[];
     __shared__ int s_w[kMapThreads / 64];
     const int tid = threadIdx.x;
     clear_counts(count);
+    const int32_t* from = seg_off + (size_t)rank_lo * (E + 1);
+    if (CACHED) {
+        for (int i = tid; i < (rank_hi - rank_lo) * (E + 1); i += blockDim.x) s_seg[i] = from[i];
+        __syncthreads();
+    }
+    auto first_row = [&](int at) { return CACHED ? s_seg[at] : from[at]; };
+    auto end_row = [&](int at) { return CACHED ? s_seg[at + 1] : from[at + 1]; };
     const int nseg = (rank_hi - rank_lo) * E, C = (nseg + (int)blockDim.x - 1) / (int)blockDim.x;
-    const int s0 = min(tid * C, nseg), s1 = min(s0 + C, nseg);
+    const int s0 = min(tid * C, nseg), s1 = min(s0 + C, nseg), g0 = s0 / E;
+    // f(place, expert) for this thread's non-empty segments
+    auto each = [&](auto f) {
+        int at = g0 * (E + 1) + (s0 - g0 * E), e = s0 - g0 * E;
+        for (int s = s0; s < s1; ++s) {
+            if (end_row(at) > first_row(at)) f(at, e);
+            ++at;
+            if (++e == E) {
+                e = 0;
+                ++at;
+            }
+        }
+    };
     auto max_op = [](int a, int b) { return max(a, b); };
-    auto first_row = [&](int s) { return seg_off[(size_t)(rank_lo + s / E) * (E + 1) + s % E]; };
-    auto end_row = [&](int s) { return seg_off[(size_t)(rank_lo + s / E) * (E + 1) + s % E + 1]; };
     // last non-empty segment in front of this thread's
     int last = -1;
-    for (int s = s0; s < s1; ++s)
-        if (end_row(s) > first_row(s)) last = s;
-    const int before = block_excl_scan(last, -1, s_w, max_op);
-    // goes on the run of segment `prev`: the same expert, and its rows follow
-    auto continues = [&](int s, int prev) { return prev >= 0 && prev % E == s % E && end_row(prev) == first_row(s); };
-    int head = -1, prev = before;
-    for (int s = s0; s < s1; ++s) {
-        if (end_row(s) <= first_row(s)) continue;
-        if (!continues(s, prev)) head = s;
-        prev = s;
-    }
-    const int head_seg = block_excl_scan(head, -1, s_w, max_op);
-    const int head_before = head_seg < 0 ? 0 : first_row(head_seg);      // (ranks' rows may lie in any order)
+    each([&](int at, int) { last = at; });
+    const int before = block_excl_scan(last, -1, s_w, max_op), before_e = before < 0 ? -1 : before % (E + 1);
+    // goes on the run of the segment at `prev` (expert prev_e): the same expert, and its rows follow
+    auto continues = [&](int at, int e, int prev, int prev_e) { return prev >= 0 && prev_e == e && end_row(prev) == first_row(at); };
+    int head = -1, prev = before, prev_e = before_e;
+    each([&](int at, int e) {
+        if (!continues(at, e, prev, prev_e)) head = at;
+        prev = at;
+        prev_e = e;
+    });
+    const int head_at = block_excl_scan(head, -1, s_w, max_op);
+    const int head_before = head_at < 0 ? 0 : first_row(head_at);      // (ranks' rows may lie in any order)
     // A run's tiles start at its first row + multiples of BM; each belongs to the segment that its first row lies in.
-    // visit(s, r): a tile starts at row r of segment s; closed(end, head): the run from row `head` has ended at `end`.
+    // visit(e, r): a tile starts at row r of expert e; closed(end, head): the run from row `head` has ended at `end`.
     auto walk = [&](auto visit, auto closed) {
-        int h = head_before, p = before;
-        for (int s = s0; s < s1; ++s) {
-            const int r0 = first_row(s), r1 = end_row(s);
-            if (r1 <= r0) continue;
-            if (!continues(s, p)) {
+        int h = head_before, p = before, pe = before_e;
+        each([&](int at, int e) {
+            const int r0 = first_row(at), r1 = end_row(at);
+            if (!continues(at, e, p, pe)) {
                 if (p >= 0) closed(end_row(p), h);
                 h = r0;
             }
-            p = s;
-            for (int r = h + (r0 - h + BM - 1) / BM * BM; r < r1; r += BM) visit(s, r);
-        }
+            p = at;
+            pe = e;
+            for (int r = h + (r0 - h + BM - 1) / BM * BM; r < r1; r += BM) visit(e, r);
+        });
         if (tid == (int)blockDim.x - 1 && p >= 0) closed(end_row(p), h);
     };
     int nt = 0;
@@ -96,8 +117,8 @@ __global__ __launch_bounds__(kMapThreads) void k_tile_map(const int32_t* __restr
     const int at0 = block_excl_scan(nt, 0, s_w, [](int a, int b) { return a + b; });
     int at = at0;
     walk(
-        [&](int s, int r) {
-            if (at < max_tiles) tiles[at] = TileEntry{s % E, r, BM, 0};
+        [&](int e, int r) {
+            if (at < max_tiles) tiles[at] = TileEntry{e, r, BM, 0};
             ++at;
         },
         [](int, int) {});
@@ -219,8 +240,13 @@ int launch_tile_map(const fine_shape& s, const int32_t* seg_off, int rank_lo, in
     if (rank_hi - rank_lo == 1 && s.E <= kMapThreads)
         hipLaunchKernelGGL(k_tile_map_rank, dim3(1), dim3((unsigned)align_up(s.E, 64)), 0, st,
                            seg_off + (size_t)rank_lo * (s.E + 1), s.E, BM, tiles, count, max_tiles);
-    else
-        hipLaunchKernelGGL(k_tile_map, dim3(1), dim3((unsigned)std::min<size_t>(kMapThreads, align_up((size_t)(rank_hi - rank_lo) * s.E, 64))), 0, st, seg_off, s.E, rank_lo, rank_hi, BM, tiles, count, max_tiles);
+    else {
+        const int n_ranks = rank_hi - rank_lo;
+        const size_t lds = (size_t)n_ranks * (s.E + 1) * 4;
+        hipLaunchKernelGGL(lds <= kMapLds ? k_tile_map<true> : k_tile_map<false>, dim3(1),
+                           dim3((unsigned)std::min<size_t>(kMapThreads, align_up((size_t)n_ranks * s.E, 64))), lds <= kMapLds ? lds : 0, st,
+                           seg_off, s.E, rank_lo, rank_hi, BM, tiles, count, max_tiles);
+    }
     FINE_LAUNCH_CHECK();
     return FINE_OK;
 }

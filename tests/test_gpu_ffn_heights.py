@@ -41,3 +41,29 @@ def test_tiles_of_both_heights(tile, d, f, rows):
         # of its f terms.  y has unit scale here.
         assert (y[r:r + n].double() - want).abs().max() <= 2e-2 * max(1.0, float(want.abs().max())), (e, n)
         r += n
+
+
+@pytest.mark.parametrize("E,G", [(1024, 14), (1024, 15), (200, 9)])
+def test_work_list_of_many_segments(E, G):
+    """One call over all ranks (segment table in LDS up to 60 KB, 14 x 1025 entries) against one call per rank."""
+    gen = torch.Generator().manual_seed(E + G)
+    n = torch.randint(0, 4, (G, E), generator=gen) * (torch.rand(G, E, generator=gen) < 0.3)
+    n[1:, E // 2] += 70                      # a run of one expert over ranks only where nothing lies between
+    n[3] = 0                                 # a rank without rows
+    n[3, 5] = 200
+    n[4] = 0
+    n[4, 5] = 90
+    off = torch.zeros(G, E + 1, dtype=torch.int64)
+    off[:, 1:] = n.cumsum(1)
+    off += (n.sum(1).cumsum(0) - n.sum(1))[:, None]
+    P = int(n.sum())
+    shape = fm.Shape(P * G, 64, 64, E, 1, G)
+    x = torch.randn(P, 64, generator=gen).bfloat16().to(DEV)
+    wg, wu, wd = [(torch.randn(E, 64, 64, generator=gen) / 8).bfloat16().to(DEV) for _ in range(3)]
+    seg_off, ws = off.int().to(DEV), fm.alloc_workspace(shape, fm.WS_FFN)
+    ys = [torch.full((P, 64), 7.0, dtype=torch.bfloat16, device=DEV) for _ in range(2)]
+    fm.fine_grouped_ffn(shape, -1, x, wg, wu, wd, seg_off, ys[0], None, ws)
+    for rank in range(G):
+        fm.fine_grouped_ffn(shape, rank, x, wg, wu, wd, seg_off, ys[1], None, ws)
+    assert torch.isfinite(ys[0]).all()
+    assert torch.equal(ys[0], ys[1])         # a row's sums do not depend on the tile it lies in

@@ -193,17 +193,21 @@ __global__ __launch_bounds__(256) void k_pairs(const int32_t* __restrict__ topk_
 //   MODE 2  the pairs, after that (the token bitmaps are built again)
 // Scans and sums by DPP (flow_wave.h): a wave has several experts to do one after another.
 // LDS: bitmap u64 [E][W], then int32 cum [E][W+1], inpre, in [E][G], and in MODE 0 x and two queues [E][G], seg_off [G][E+1],
-// load [E].
+// load [E], and a byte per pair, its expert (kSmallExperts: none).
+// The pairs' experts are loaded once, all loads of a thread before the first use, and read again from LDS (4096 pairs: 0.4 us).
 // Taken up to 2048 pairs, 128 experts and 2048 (expert, rank)s.  Against four launches, both replayed from a graph (in a stream
 // of single launches each of them takes 1-2 us more): 512 pairs, 8 experts on 4 ranks 4.0 : 9.7 us; 1024 pairs, 128 experts on
 // 8 ranks 9.8 : 10.9; 2048 pairs, 128 on 8 11.4 : 11.7, 64 on 16 10.1 : 11.1; but 1280 pairs, 192 on 5 13.5 : 12.0, 2048
-// pairs, 256 on 8 18.8 : 12.7.
+// pairs, 256 on 8 18.8 : 12.7.  With every expert on every rank and at most 32 experts up to 4096 pairs, here in a stream of single
+// launches: 3000 pairs, 8 on 4 7.1 : 13.5; 4096 pairs, 16 on 4 9.3 : 13.9, 32 on 8 10.9 : 13.4 (graph 11.1 : 10.8); but 64 on
+// 8 12.5 : 13.4 (graph 12.7 : 11.1), and 8192 pairs, 8 on 4 15.6 : 14.5.  A restricted placement has the bitmaps built twice
+// here: 8192 pairs, 16 on 8 46 : 27.
 // ---------------------------------------------------------------------------
-constexpr int kSmallThreads = 1024, kSmallPairs = 2048, kSmallExperts = 128, kSmallTables = 2048;
+constexpr int kSmallThreads = 1024, kSmallPairs = 4096, kSmallExperts = 128, kSmallTables = 2048;
 constexpr size_t kSmallLds = 64 * 1024;
 
-__host__ __device__ inline size_t small_lds_bytes(int E, int G, int W) {
-    return (size_t)E * W * 8 + ((size_t)E * (W + 1) + 5 * (size_t)E * G + (size_t)G * (E + 1) + E) * 4;
+__host__ __device__ inline size_t small_lds_bytes(int E, int G, int W, int P) {
+    return (size_t)E * W * 8 + ((size_t)E * (W + 1) + 5 * (size_t)E * G + (size_t)G * (E + 1) + E) * 4 + P;
 }
 
 template <int MODE>
@@ -222,15 +226,22 @@ __global__ __launch_bounds__(kSmallThreads) void k_sched_small(const int32_t* __
     int* x = in + E * G;
     int* seg = x + 3 * E * G;
     int* s_load = seg + G * (E + 1);
+    unsigned char* expert = reinterpret_cast<unsigned char*>(s_load + E);
     constexpr int kWaves = kSmallThreads / kWave;
     const int tid = threadIdx.x, wave = tid / kWave, lane = lane_id(), P = T * K;
 
     // 1. token bitmaps
     for (int i = tid; i < E * W; i += kSmallThreads) bm[i] = 0ull;
     __syncthreads();
-    for (int p = tid; p < P; p += kSmallThreads) {
-        const int e = topk_idx[p], t = p / K;
-        if (e >= 0 && e < E) atomicOr(&bm[e * W + (t >> 6)], 1ull << (t & 63));      // OR is order independent
+    int own[kSmallPairs / kSmallThreads];      // all loads before the first use
+#pragma unroll
+    for (int u = 0; u < kSmallPairs / kSmallThreads; ++u) own[u] = tid + u * kSmallThreads < P ? topk_idx[tid + u * kSmallThreads] : -1;
+#pragma unroll
+    for (int u = 0; u < kSmallPairs / kSmallThreads; ++u) {
+        const int p = tid + u * kSmallThreads, t = p / K;
+        const bool ok = own[u] >= 0 && own[u] < E;
+        if (p < P) expert[p] = (unsigned char)(ok ? own[u] : kSmallExperts);
+        if (ok) atomicOr(&bm[own[u] * W + (t >> 6)], 1ull << (t & 63));      // OR is order independent
     }
     __syncthreads();
     // 2. prefix of popcounts and load_e: a thread per expert where it has few words, else a wave (W <= 64: a word per lane);
@@ -304,9 +315,9 @@ __global__ __launch_bounds__(kSmallThreads) void k_sched_small(const int32_t* __
     const int* xs = MODE == 0 ? x : x_eg;
     const int* segs = MODE == 0 ? seg : seg_off;
     for (int p = tid; p < P; p += kSmallThreads) {
-        const int tok = p / K, e = topk_idx[p];
+        const int tok = p / K, e = expert[p];
         int dst = -1, row = p;
-        if (e >= 0 && e < E) {
+        if (e < E) {
             const int g = tok / Tg, w = tok >> 6;
             const int r = cum[e * (W + 1) + w] + __popcll(bm[e * W + w] & ((1ull << (tok & 63)) - 1ull)) - inpre[e * G + g];
             int place = 0;
@@ -403,7 +414,9 @@ int launch_sched(const fine_shape& s, const int32_t* topk_idx, const uint8_t* pl
                  int32_t* seg_off, int32_t* rank_off, char* ws, hipStream_t st) {
     const int W = cdiv(s.T, 64);
     const SchedArrays a = sched_arrays(s, ws);
-    const size_t small_lds = W <= 64 && (long long)s.T * s.K <= kSmallPairs && s.E <= kSmallExperts && s.E * s.G <= kSmallTables ? small_lds_bytes(s.E, s.G, W) : kSmallLds + 1;
+    const bool small = W <= 64 && (long long)s.T * s.K <= (place == nullptr && s.E <= 32 ? kSmallPairs : kSmallPairs / 2) &&
+                       s.E <= kSmallExperts && s.E * s.G <= kSmallTables;
+    const size_t small_lds = small ? small_lds_bytes(s.E, s.G, W, s.T * s.K) : kSmallLds + 1;
     if (small_lds <= kSmallLds) {
         auto run = [&](auto k) {
             hipLaunchKernelGGL(k, dim3(1), dim3(kSmallThreads), small_lds, st, topk_idx, s.T, s.K, s.E, s.G, W,

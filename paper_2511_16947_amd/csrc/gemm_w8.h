@@ -11,7 +11,9 @@
 // Both operand tiles reach LDS by DMA (buffer_load_dwordx4 ... lds: 16 bytes per lane straight
 // into LDS, no registers, no LDS write instructions).  Measured: lane i's 16 bytes land at
 // LDS base + 16 i, a lane whose offset passes the descriptor's size writes zeros, and the
-// instruction's scalar offset takes part in that check.  Since the LDS side of such an
+// instruction's scalar offset takes part in that check: what counts is the sum of both, also
+// where the scalar offset by itself is past the size (b32, b128 and LDS-DMA loads; it is for the
+// second half of a ragged 64-row k-tile).  Since the LDS side of such an
 // instruction is fixed, the XOR swizzles that keep the fragment reads free of bank conflicts
 // are applied by choosing WHICH global 16 bytes each lane fetches.  Two operand kinds:
 //

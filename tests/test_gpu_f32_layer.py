@@ -35,3 +35,32 @@ def test_f32_ffn_every_element(d, f, T, E, K, G):
         # 1e-5: the library's bound for fp32 outputs (sums of up to 858 products: eps sqrt(858) = 1.7e-6)
         assert max_rel_err(act, want_act) <= 1e-5
         assert max_rel_err(y, want) <= 1e-5
+
+
+@pytest.mark.parametrize("rows", [[5, 0, 40], [8000, 0, 6500]])      # launches of 32-row and of 64-row tiles
+@pytest.mark.parametrize("d,f", [(1, 33), (33, 63), (63, 1), (65, 133), (4, 132), (36, 4)])
+def test_f32_ffn_reads_no_weights_of_others(d, f, rows):
+    """k-ranges that end inside a 32-value step: what follows an expert's weights (an expert without rows, and behind the
+    last expert the rest of the buffer) is NaN, which no factor of zero would hide."""
+    E, P = len(rows), sum(rows)
+    shape = fm.Shape(P, d, f, E, 1, 1, fm.FINE_F32)
+    gen = torch.Generator(device="cuda").manual_seed(d * f)
+    x = torch.randn(P, d, generator=gen, device="cuda")
+    weights = []
+    for n, m in ((d, f), (d, f), (f, d)):
+        buf = torch.full(((E + 40) * n * m + 64,), float("nan"), device="cuda")
+        w = buf[:E * n * m].view(E, n, m)
+        for e in range(E):
+            if rows[e]:
+                w[e] = torch.randn(n, m, generator=gen, device="cuda") * n ** -0.5
+        weights.append(w)
+    seg_off = torch.tensor([0] + rows, device="cuda").cumsum(0).int()[None].contiguous()
+    y = torch.full((P, d), float("nan"), device="cuda")
+    fm.fine_grouped_ffn(shape, -1, x, *weights, seg_off, y, None, fm.alloc_workspace(shape, fm.WS_FFN))
+    r = 0
+    for e, n in enumerate(rows):
+        xe, (wg, wu, wd) = x[r:r + n].double(), [w[e].double() for w in weights]
+        want = (torch.nn.functional.silu(xe @ wg) * (xe @ wu)) @ wd
+        if n:      # 1e-5: as above
+            assert max_rel_err(to64(y[r:r + n]), to64(want)) <= 1e-5
+        r += n

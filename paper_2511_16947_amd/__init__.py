@@ -12,6 +12,7 @@ from __future__ import annotations
 import ctypes
 import os
 from dataclasses import dataclass
+from functools import cached_property
 from typing import Optional
 
 import torch
@@ -122,15 +123,16 @@ class Shape:
     def torch_dtype(self) -> torch.dtype:
         return torch.float32 if self.dtype == FINE_F32 else torch.bfloat16
 
-    def __post_init__(self):
-        # what every call passes on: made once, since a Shape never changes
-        object.__setattr__(self, "_ref", ctypes.byref(self.c()))
+    @cached_property
+    def _ref(self):
+        # what every call passes on: made by the first one, since a Shape never changes
+        return ctypes.byref(self.c())
 
     def c(self) -> _Shape:
         return _Shape(self.T, self.d, self.f, self.E, self.K, self.G, self.dtype, self.flags)
 
-    def __reduce__(self):      # (a ctypes reference cannot be copied: copies make their own)
-        return Shape, (self.T, self.d, self.f, self.E, self.K, self.G, self.dtype, self.flags)
+    def __getstate__(self):      # (a ctypes reference cannot be copied: copies make their own)
+        return {k: v for k, v in self.__dict__.items() if k != "_ref"}
 
 
 def _ptr(t: Optional[torch.Tensor]):

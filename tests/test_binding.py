@@ -42,3 +42,32 @@ def test_shapes_that_no_call_can_take_can_be_made():
     assert fm.Shape(2.5, *ARGS[1:]).P == 5.0
     with pytest.raises(TypeError):
         fm.fine_workspace_bytes(fm.Shape(2.5, *ARGS[1:]), fm.WS_FFN)
+
+
+class TestStream:
+    """The stream handle comes from torch.cuda.current_stream() wherever the shorter way is not the same."""
+
+    class Stream:
+        cuda_stream = 1234
+
+    @pytest.fixture(autouse=True)
+    def initialised(self, monkeypatch):
+        monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+        monkeypatch.setattr(torch.cuda, "current_stream", lambda: self.Stream)
+
+    @pytest.mark.parametrize("name", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
+    def test_without_the_functions(self, monkeypatch, name):
+        monkeypatch.delattr(torch._C, name, raising=False)
+        assert fm._stream() == 1234
+
+    def test_with_them(self, monkeypatch):
+        monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 3, raising=False)
+        monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 100 + device, raising=False)
+        assert fm._stream() == 103
+
+    def test_not_initialised(self, monkeypatch):
+        """Before the first use of the GPU, and in a child forked after it: torch decides (it refuses the child)."""
+        monkeypatch.setattr(torch.cuda, "is_initialized", lambda: False)
+        monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 3, raising=False)
+        monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 100 + device, raising=False)
+        assert fm._stream() == 1234

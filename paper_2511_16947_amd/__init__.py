@@ -144,14 +144,14 @@ def _ptr(t: Optional[torch.Tensor]):
 
 # The handle that torch.cuda.current_stream() wraps, without the wrapper (2.9 us a call, this 0.3).  Small layers are bound by
 # the host: one pass of a 256-token fp32 layer on four ranks, eight calls and twelve launches, kept it busy for 91 us, with
-# this, plain integers for pointers and the shape converted once 63 us.  The wrapper also initialises the GPU and refuses a
-# child forked after that, and the functions are private to torch: where it is not the same, the wrapper it is.
+# this, plain integers for pointers and the shape converted once 63 us.  The wrapper also refuses a child forked after the GPU
+# was initialised, and the functions are private to torch: there it is the wrapper.
 def _stream():
-    if torch.cuda.is_initialized():
-        try:
+    try:
+        if not torch._C._cuda_isInBadFork():
             return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
-        except AttributeError:
-            pass
+    except AttributeError:
+        pass
     return torch.cuda.current_stream().cuda_stream
 
 

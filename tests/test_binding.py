@@ -51,23 +51,21 @@ class TestStream:
         cuda_stream = 1234
 
     @pytest.fixture(autouse=True)
-    def initialised(self, monkeypatch):
-        monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    def functions(self, monkeypatch):
+        monkeypatch.setattr(torch._C, "_cuda_isInBadFork", lambda: False, raising=False)
+        monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 3, raising=False)
+        monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 100 + device, raising=False)
         monkeypatch.setattr(torch.cuda, "current_stream", lambda: self.Stream)
 
-    @pytest.mark.parametrize("name", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
+    @pytest.mark.parametrize("name", ["_cuda_isInBadFork", "_cuda_getCurrentRawStream", "_cuda_getDevice"])
     def test_without_the_functions(self, monkeypatch, name):
-        monkeypatch.delattr(torch._C, name, raising=False)
+        monkeypatch.delattr(torch._C, name)
         assert fm._stream() == 1234
 
-    def test_with_them(self, monkeypatch):
-        monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 3, raising=False)
-        monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 100 + device, raising=False)
+    def test_with_them(self):
         assert fm._stream() == 103
 
-    def test_not_initialised(self, monkeypatch):
-        """Before the first use of the GPU, and in a child forked after it: torch decides (it refuses the child)."""
-        monkeypatch.setattr(torch.cuda, "is_initialized", lambda: False)
-        monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 3, raising=False)
-        monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 100 + device, raising=False)
+    def test_in_a_forked_child(self, monkeypatch):
+        """Forked after the GPU was initialised: torch decides (it refuses)."""
+        monkeypatch.setattr(torch._C, "_cuda_isInBadFork", lambda: True)
         assert fm._stream() == 1234

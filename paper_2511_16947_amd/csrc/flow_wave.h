@@ -22,6 +22,7 @@ struct Problem {
     int* x;        // [n][XS] units of listed expert j on every rank
     PM* pm;        // [n] replica masks of the listed experts (before compact(): of all experts)
     int* t;        // [G] scratch
+    int* A;        // long lists: [G][G | 1] sums of the edges
     int E, G;
     int XS;        // row stride (odd where it fits, so that a column's entries fall into different banks)
     int n;         // listed experts
@@ -68,21 +69,65 @@ __device__ inline int wave_incl_scan_i(int v) {
 }
 __device__ inline int wave_sum_i(int v) { return __builtin_amdgcn_readlane(wave_incl_scan_i(v), kW - 1); }
 
-// What a search and a move need is in the registers of the ranks' lanes: sets of ranks (M: 32 bits where that is enough;
-// the search is a chain of instructions of one wavefront, and 64-bit shifts and selects are several each) and sets of
-// listed experts (NW words of 64).  An edge from a to b exists while some free expert has units on a and a free replica
-// on b, i.e. while units_a and free_b meet; how much may move along it is added up from x where it is used.  (Keeping the
-// edges' sums, or each rank's set of neighbours as a union over its experts, cost every move and every variable that
-// stops being free a chain of updates or of wave-wide reductions; here they are a few instructions.)
-template <typename M, int NW, typename PM = u64>
-struct Flow : Problem<PM> {
+// What a search needs, in the registers of the ranks' lanes: sets of ranks (M: 32 bits where that is enough; the search is a
+// chain of instructions of one wavefront, and 64-bit shifts and selects are several each).
+template <typename M, typename PM>
+struct Ranks : Problem<PM> {
     int ld;                      // lane = rank: its load
     M me;                        // this rank as a set (no rank: the empty set)
     M in;                        // the ranks from which units may move here
+
+    __device__ inline Ranks(const Problem<PM>& p) : Problem<PM>(p) {}
+    // loads from c.t, no edges
+    __device__ inline void load_ranks() {
+        const int l = lane();
+        wave_sync();
+        me = l < this->G ? (M)1 << (l & (8 * (int)sizeof(M) - 1)) : (M)0;
+        ld = l < this->G ? this->t[l] : 0;
+        in = 0;
+    }
+    // Breadth-first search from `src`.  Stops at the first level that holds a rank of `want`.  The sets of ranks are scalar;
+    // what the way back needs is one set per level.
+    struct Way {
+        int src, target, levels;     // target: lowest rank of `want` on the first level that has one, or -1
+        M visited;                   // every rank reached
+        M trail;                     // lane = level: the ranks first reached there
+    };
+    __device__ inline Way bfs(int src, M want) const {
+        const int b = lane();
+        Way w{src, -1, 0, (M)1 << src, 0};
+        M level = w.visited;
+        while (true) {
+            if (b == w.levels) w.trail = level;
+            level = (M)__ballot((in & level) != 0) & ~w.visited;      // (lanes that are no ranks have nothing in `in`)
+            if (level == 0) break;
+            w.visited |= level;
+            const M good = level & want;
+            if (good) { w.target = first_of(good); break; }
+            ++w.levels;
+        }
+        return w;
+    }
+    // where the search came to `rank` from, on level `level` (lowest such rank)
+    __device__ inline int before(const Way& w, int rank, int level) const {
+        return first_of(readlane_set(in, rank) & readlane_set(w.trail, level));
+    }
+};
+
+// Short lists: a move works on sets of listed experts (NW words of 64) in the registers of the ranks' lanes.  An edge from a
+// to b exists while some free expert has units on a and a free replica on b, i.e. while units_a and free_b meet; how much
+// may move along it is added up from x where it is used.  (Keeping the edges' sums, or each rank's set of neighbours as a
+// union over its experts, costs every move and every variable that stops being free a chain of updates or of wave-wide
+// reductions; here they are a few instructions per word.)
+template <typename M, int NW, typename PM = u64>
+struct Flow : Ranks<M, PM> {
+    using Ranks<M, PM>::me;
+    using Ranks<M, PM>::in;
+    using Ranks<M, PM>::ld;
     u64 free[NW];                // experts that have a free replica here
     u64 units[NW];               // those of them that have units on it
 
-    __device__ inline Flow(const Problem<PM>& p) : Problem<PM>(p) {}
+    __device__ inline Flow(const Problem<PM>& p) : Ranks<M, PM>(p) {}
     // whether free experts of `set` (scalar words) have a replica on the lane's rank
     __device__ inline bool meets_free(const u64 (&set)[NW]) const {
         u64 v = 0ull;
@@ -100,18 +145,21 @@ struct Flow : Problem<PM> {
         const bool edge = meets_free(set) && (me & bit) == 0;
         in = (in & ~bit) | (edge ? bit : (M)0);
     }
-    // expert j has free units / a free replica on the lane's rank
+    // expert j has free units on the lane's rank
     __device__ inline bool has_units(int j) const {
         bool v = false;
 #pragma unroll
         for (int w = 0; w < NW; ++w) v = v || (NW == 1 || w == j >> 6) && ((units[w] >> (j & 63)) & 1ull);
         return v;
     }
-    __device__ inline bool is_free(int j) const {
+    // how many (here: has_units)
+    __device__ inline int units_of(int j, bool here) const { return here ? this->x[j * this->XS + lane()] : 0; }
+    // the free replicas of expert j, whose turn it is
+    __device__ inline M begin(int j) const {
         bool v = false;
 #pragma unroll
         for (int w = 0; w < NW; ++w) v = v || (NW == 1 || w == j >> 6) && ((free[w] >> (j & 63)) & 1ull);
-        return v;
+        return (M)__ballot(v);
     }
     // expert j has no units left on the lane's rank, where `here`
     __device__ inline void clear_units(int j, bool here) {
@@ -137,13 +185,23 @@ struct Flow : Problem<PM> {
         const M from = (M)__ballot(v != 0ull) & ~((M)1 << g);
         if (here) in = from;
     }
+    // the lane's rank has given `given` of its `had` units of expert j
+    __device__ inline void gave(int j, int given, int had) {
+        const bool none_left = given > 0 && given == had;
+        clear_units(j, none_left);
+        M gone = (M)__ballot(none_left);
+        while (gone) {
+            const int a = first_of(gone);
+            gone &= gone - 1;
+            u64 set[NW];
+            read_units(a, set);
+            set_out(a, set);
+        }
+    }
     // the registers from c.t (loads), the masks and x: everything free
     __device__ inline void load_registers() {
         const int l = lane();
-        wave_sync();
-        me = l < this->G ? (M)1 << (l & (8 * (int)sizeof(M) - 1)) : (M)0;
-        ld = l < this->G ? this->t[l] : 0;
-        in = 0;
+        this->load_ranks();
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
             free[w] = units[w] = 0ull;
@@ -223,67 +281,160 @@ struct Flow : Problem<PM> {
         }
         return wave_sum_i(sum);
     }
-    // Breadth-first search from `src`.  Stops at the first level that holds a rank of `want`.  The sets of ranks are scalar;
-    // what the way back needs is one set per level.
-    struct Way {
-        int src, target, levels;     // target: lowest rank of `want` on the first level that has one, or -1
-        M visited;                   // every rank reached
-        M trail;                     // lane = level: the ranks first reached there
-    };
-    __device__ inline Way bfs(int src, M want) const {
-        const int b = lane();
-        Way w{src, -1, 0, (M)1 << src, 0};
-        M level = w.visited;
-        while (true) {
-            if (b == w.levels) w.trail = level;
-            level = (M)__ballot((in & level) != 0) & ~w.visited;      // (lanes that are no ranks have nothing in `in`)
-            if (level == 0) break;
-            w.visited |= level;
-            const M good = level & want;
-            if (good) { w.target = first_of(good); break; }
-            ++w.levels;
-        }
-        return w;
-    }
-    // where the search came to `rank` from, on level `level` (lowest such rank)
-    __device__ inline int before(const Way& w, int rank, int level) const {
-        return first_of(readlane_set(in, rank) & readlane_set(w.trail, level));
-    }
-    // smallest capacity on the way
-    __device__ inline int way_capacity(const Way& w) const {
-        int cap = 0x7fffffff, cur = w.target;
-        for (int level = w.levels; level >= 0; --level) {
-            const int p = before(w, cur, level);
-            cap = min(cap, edge_capacity(p, cur));
-            cur = p;
-        }
-        return cap;
-    }
-    // Moves up to `amount` units along the way, last edge first, and returns how many left its source (at least one).  An
-    // edge takes what the edge after it took, or less if it has not as many: a rank on the way never ends with more than
-    // it had.  (The edges not yet used are as the search found them: the ranks of a shortest way are distinct.)
-    __device__ inline int push(const Way& w, int amount) {
-        int cur = w.target;
-        for (int level = w.levels; level >= 0; --level) {
-            const int p = before(w, cur, level);
-            amount = move_units(p, cur, amount);
-            cur = p;
-        }
-        return amount;
-    }
 };
 
-// Calls f(number of words) with one that n listed experts fit, at most MAXW, which is words_for(E): a kernel for many
-// experts needs the registers for as many words, whatever the list's length.
-constexpr int words_for(int E) { return E <= 64 ? 1 : E <= 128 ? 2 : E <= 256 ? 4 : 16; }
+// Long lists: the sums of the edges instead of sets, A[b][a] = units that may move from a to b, kept up to date.  A move
+// looks through the list, 64 experts at a time, and then changes the entries of every rank that is a replica of a giving
+// expert, summed over the givers in that rank's lane.  What a variable that stops being free costs does not depend on the
+// length of the list.
+template <typename M, typename PM>
+struct Flow<M, 0, PM> : Ranks<M, PM> {
+    using Ranks<M, PM>::me;
+    using Ranks<M, PM>::in;
+    using Ranks<M, PM>::ld;
+    int cur = -1;                // the expert whose turn it is: those before it can no longer move
+    M later = 0;                 // its free replicas
+    int mine = 0;                // its units on the lane's
+
+    __device__ inline Flow(const Problem<PM>& p) : Ranks<M, PM>(p) {}
+    __device__ inline int& sum(int a, int b) const { return this->A[b * (this->G | 1) + a]; }
+    __device__ inline M begin(int j) {
+        cur = j;
+        later = readlane_set((M)this->pm[j], 0);
+        return later;
+    }
+    __device__ inline bool has_units(int j) {
+        mine = 0;
+        if ((later & me) != 0) mine = this->x[j * this->XS + lane()];
+        return mine > 0;
+    }
+    __device__ inline int units_of(int, bool) const { return mine; }
+    __device__ inline void fix(int j, int g) {
+        const int l = lane(), *row = this->x + j * this->XS;
+        later &= ~((M)1 << g);
+        int back = 0;
+        if ((later & me) != 0) {      // lane = one of the other replicas
+            const int to_me = sum(g, l) - row[g];
+            back = sum(l, g) - row[l];
+            sum(g, l) = to_me;
+            sum(l, g) = back;
+            in = (in & ~((M)1 << g)) | (M)(to_me > 0) << g;
+        }
+        const M still = (M)__ballot(back > 0);
+        if (l == g) in = (in & ~later) | still;
+        wave_sync();
+    }
+    __device__ inline void gave(int, int given, int) {
+        const int q = lane();
+        M givers = (M)__ballot(given > 0);
+        while (givers) {
+            const int a = first_of(givers);
+            givers &= givers - 1;
+            const int t = __builtin_amdgcn_readlane(given, a);
+            if (q != a && (later & me) != 0) {
+                const int v = sum(a, q) - t;
+                sum(a, q) = v;
+                in = (in & ~((M)1 << a)) | (M)(v > 0) << a;
+            }
+        }
+        wave_sync();
+    }
+    __device__ inline void load_registers() {
+        const int l = lane();
+        this->load_ranks();
+        for (int i = l; i < this->G * (this->G | 1); i += kW) this->A[i] = 0;
+        wave_sync();
+        for (int j = l; j < this->n; j += kW) {
+            const M m = (M)this->pm[j];
+            for (M r = m; r; r &= r - 1) {
+                const int a = first_of(r), units = this->x[j * this->XS + a];
+                if (units > 0)
+                    for (M o = m & ~((M)1 << a); o; o &= o - 1) atomicAdd(&sum(a, first_of(o)), units);
+            }
+        }
+        wave_sync();
+        if (l < this->G)
+            for (int a = 0; a < this->G; ++a) in |= (M)(sum(a, l) > 0) << a;
+    }
+    __device__ inline int move_units(int a, int b, int amount) {
+        const int q = lane();
+        int remaining = amount, D = 0;
+        for (int base = max(cur, 0); base < this->n && remaining > 0; base += kW) {
+            // (a lane past the last expert reads the last one's entries and takes no part: the reads go out together)
+            const int j = base + q, jj = min(j, this->n - 1);
+            const M pm = (M)this->pm[jj];
+            int* row = this->x + jj * this->XS;
+            const int xa = row[a], xb = row[b];
+            const M F = j == cur ? later : pm;
+            const int m = j < this->n && has(F, a) && has(F, b) ? xa : 0;
+            if (__ballot(m > 0) == 0ull) continue;
+            const int inc = wave_incl_scan_i(m), t = max(0, min(m, remaining - (inc - m)));
+            if (t > 0) {
+                row[a] = xa - t;
+                row[b] = xb + t;
+            }
+            u64 givers = __ballot(t > 0);
+            while (givers) {
+                const int src = first_of(givers);
+                givers &= givers - 1;
+                const int ts = __builtin_amdgcn_readlane(t, src);
+                if ((readlane_set(F, src) & me) != 0) D += ts;
+            }
+            remaining -= min(remaining, __builtin_amdgcn_readlane(inc, kW - 1));
+        }
+        if (D > 0) {
+            const int va = q != a ? sum(a, q) - D : 0, vb = q != b ? sum(b, q) + D : 0;
+            if (q != a) sum(a, q) = va;
+            if (q != b) sum(b, q) = vb;
+            in = (in & ~((M)1 << a) & ~((M)1 << b)) | (M)(va > 0) << a | (M)(vb > 0) << b;
+        }
+        const int moved = amount - remaining;
+        ld += q == b ? moved : q == a ? -moved : 0;
+        wave_sync();
+        return moved;
+    }
+    __device__ inline int edge_capacity(int a, int b) const { return __builtin_amdgcn_readfirstlane(sum(a, b)); }
+};
+
+// smallest capacity on the way
+template <typename F, typename W>
+__device__ inline int way_capacity(const F& c, const W& w) {
+    int cap = 0x7fffffff, cur = w.target;
+    for (int level = w.levels; level >= 0; --level) {
+        const int p = c.before(w, cur, level);
+        cap = min(cap, c.edge_capacity(p, cur));
+        cur = p;
+    }
+    return cap;
+}
+// Moves up to `amount` units along the way, last edge first, and returns how many left its source (at least one).  An
+// edge takes what the edge after it took, or less if it has not as many: a rank on the way never ends with more than
+// it had.  (The edges not yet used are as the search found them: the ranks of a shortest way are distinct.)
+template <typename F, typename W>
+__device__ inline int push(F& c, const W& w, int amount) {
+    int cur = w.target;
+    for (int level = w.levels; level >= 0; --level) {
+        const int p = c.before(w, cur, level);
+        amount = c.move_units(p, cur, amount);
+        cur = p;
+    }
+    return amount;
+}
+
+// Calls f(number of words; 0: sums of the edges) with what suits n listed experts; MAXW = words_for(E).  Every word costs every
+// step of the sets, while the sums hardly feel the length.  Whole scheduler, 4096 tokens x 8, us (geometric mean of six
+// placements; started from first replicas / warm), sets of 4 or 16 words : sums.  On 8 ranks 129 experts of two replicas 267 :
+// 265 / 155 : 136, of four 357 : 328 / 259 : 224; 256 of two 398 : 359 / 256 : 211, of eight 1078 : 968 / 1007 : 847; 512 of four
+// 3116 : 1170 / 2382 : 802; on 32 ranks 256 of four 1253 : 1224 / 794 : 719; 1024 of two 5619 : 3083 / 3095 : 1342.  The sets
+// stay ahead only from first replicas with two each on many ranks (256 on 32 697 : 748 / 453 : 437, on 64 749 : 837 / 516 : 514).
+constexpr int kMaxWords = 2;
+constexpr int words_for(int E) { return E <= 64 ? 1 : E <= 64 * kMaxWords ? kMaxWords : 0; }
 template <int MAXW, typename F>
 __device__ inline void with_words(int n, F f) {
-    if constexpr (MAXW > 4)
-        if (n > 256) { f(std::integral_constant<int, 16>{}); return; }
-    if constexpr (MAXW > 2)
-        if (n > 128) { f(std::integral_constant<int, 4>{}); return; }
-    if constexpr (MAXW > 1)
-        if (n > 64) { f(std::integral_constant<int, 2>{}); return; }
+    if constexpr (MAXW == 0)
+        if (n > 64 * kMaxWords) { f(std::integral_constant<int, 0>{}); return; }
+    if constexpr (MAXW != 1)
+        if (n > 64) { f(std::integral_constant<int, kMaxWords>{}); return; }
     f(std::integral_constant<int, 1>{});
 }
 // pick(words_for(E), a value of the type for sets of ranks), on the host
@@ -292,9 +443,8 @@ inline auto by_size(int E, int G, F pick) {
     auto with = [&](auto m) {
         switch (words_for(E)) {
             case 1: return pick(std::integral_constant<int, 1>{}, m);
-            case 2: return pick(std::integral_constant<int, 2>{}, m);
-            case 4: return pick(std::integral_constant<int, 4>{}, m);
-            default: return pick(std::integral_constant<int, 16>{}, m);
+            case kMaxWords: return pick(std::integral_constant<int, kMaxWords>{}, m);
+            default: return pick(std::integral_constant<int, 0>{}, m);
         }
     };
     return G <= 32 ? with(uint32_t{}) : with(u64{});
@@ -373,7 +523,7 @@ __device__ inline int optimum_value(Flow<M, NW, PM>& c, int P) {
             continue;
         }
         const int amount = min(__builtin_amdgcn_readlane(mine, a) - best, best - __builtin_amdgcn_readlane(mine, way.target));
-        c.push(way, amount);
+        push(c, way, amount);
     }
     return best;
 }
@@ -406,7 +556,7 @@ __device__ inline void exact_density(Flow<M, NW, PM>& c, const int32_t* __restri
                 moved = true;
                 break;
             }
-            c.push(way, min(__builtin_amdgcn_readlane(mine, a) - num, num - __builtin_amdgcn_readlane(mine, way.target)));
+            push(c, way, min(__builtin_amdgcn_readlane(mine, a) - num, num - __builtin_amdgcn_readlane(mine, way.target)));
         }
         if (!moved) break;
     }
@@ -415,10 +565,11 @@ __device__ inline void exact_density(Flow<M, NW, PM>& c, const int32_t* __restri
 }
 
 // bytes of LDS behind a Problem for E experts on G ranks, with x in rows of `xs`
+__host__ __device__ inline size_t edge_bytes(int E, int G) { return words_for(E) == 0 ? (size_t)G * (G | 1) * 4 : 0; }
 __host__ __device__ inline size_t ctx_bytes(int E, int G, int xs) {
-    return (((size_t)E * 8 + 15) & ~(size_t)15) + ((size_t)E * xs + G) * 4;
+    return (((size_t)E * 8 + 15) & ~(size_t)15) + edge_bytes(E, G) + ((size_t)E * xs + G) * 4;
 }
-// The contract's limit on (E, G), stated for a table of G x G more than the solver keeps: what it refuses stays refused.
+// The contract's limit on (E, G): with the edges' sums, whether they are kept or not.
 inline bool size_allowed(int E, int G, size_t limit) {
     return (((size_t)E * 8 + 15) & ~(size_t)15) + ((size_t)G * (G | 1) + (size_t)E * G + G) * 4 <= limit;
 }
@@ -430,7 +581,8 @@ __device__ inline Problem<> make_problem(char* smem, int E, int G, int xs) {
     Problem<> c;
     c.E = E; c.G = G; c.XS = xs;
     c.pm = reinterpret_cast<u64*>(smem);
-    c.x = reinterpret_cast<int*>(smem + (((size_t)E * 8 + 15) & ~(size_t)15));
+    c.A = reinterpret_cast<int*>(smem + (((size_t)E * 8 + 15) & ~(size_t)15));
+    c.x = c.A + edge_bytes(E, G) / 4;
     c.t = c.x + (size_t)E * xs;
     c.n = 0; c.listed = 0ull; c.single = 0;
     return c;

@@ -49,15 +49,7 @@ __device__ inline void pull_expert(Flow<M, NW, PM>& c, int j, int g, M from, int
         c.ld += amount;
     }
     wave_sync();
-    c.clear_units(j, t > 0 && t == m);
-    M gone = (M)__ballot(t > 0 && t == m);
-    while (gone) {
-        const int a = first_of(gone);
-        gone &= gone - 1;
-        u64 set[NW];
-        c.read_units(a, set);
-        c.set_out(a, set);
-    }
+    c.gave(j, t, m);
 }
 
 // Phases 1 and 2 by one wavefront; returns M*.  On return c.ld are the ranks' loads.
@@ -69,7 +61,7 @@ __device__ inline int solve(Flow<M, NW, PM>& c, int P) {
     const int cap_rank = optimum_value(c, P);      // M*
     // ---- phase 2: the lexicographically greatest optimum ------------------------------------
     for (int j = 0; j < c.n; ++j) {
-        M later = (M)__ballot(c.is_free(j));       // free replicas of j (including the one being removed next)
+        M later = c.begin(j);                      // free replicas of j (including the one being removed next)
         while (true) {
             const int g = first_of(later);
             later &= later - 1;
@@ -78,24 +70,23 @@ __device__ inline int solve(Flow<M, NW, PM>& c, int P) {
             while (true) {
                 const bool mine = c.has_units(j);
                 if (__ballot(mine) == 0ull) break;
-                const int* row = c.x + j * c.XS;
                 const int room = cap_rank - __builtin_amdgcn_readlane(c.ld, g);
                 if (room > 0) {
-                    pull_expert(c, j, g, later, min(room, wave_sum_i(mine ? row[l] : 0)));
+                    pull_expert(c, j, g, later, min(room, wave_sum_i(c.units_of(j, mine))));
                     continue;
                 }
                 const auto way = c.bfs(g, (M)__ballot(l < c.G && c.ld < cap_rank) | (M)__ballot(mine));
                 if (way.target < 0) break;
-                const int avail = mine ? row[l] : 0, room_r = cap_rank - __builtin_amdgcn_readlane(c.ld, way.target);
+                const int avail = c.units_of(j, mine), room_r = cap_rank - __builtin_amdgcn_readlane(c.ld, way.target);
                 if (room_r > 0) {
                     // the path may itself carry units of j between its later replicas, so
                     // the units are taken from whichever later replicas hold them afterwards
-                    const int moved = c.push(way, min(room_r, wave_sum_i(avail)));
+                    const int moved = push(c, way, min(room_r, wave_sum_i(avail)));
                     pull_expert(c, j, g, later, moved);
                 } else {                           // all ranks on the way are full: exactly as much must come as goes
-                    const int amount = min(c.way_capacity(way), __builtin_amdgcn_readlane(avail, way.target));
+                    const int amount = min(way_capacity(c, way), __builtin_amdgcn_readlane(avail, way.target));
                     pull_expert(c, j, g, (M)1 << way.target, amount);
-                    c.push(way, amount);
+                    push(c, way, amount);
                 }
             }
         }
@@ -127,14 +118,17 @@ __device__ inline u64 replica_mask(const uint8_t* __restrict__ place, int e, int
 
 constexpr int kXThreads = 1024, kXWaves = kXThreads / kW;
 
-// LDS behind the arrays of the Problem: for every expert its place in the list or -1 - its only rank, the experts of the list
-// (both 16 bits), which experts are listed, and a flag.  The waves' sums of the output take the place of the masks.
-__host__ __device__ inline size_t x_masks_bytes(int E, int G, int mask_bytes) {
-    const size_t masks = (size_t)E * mask_bytes, sums = (size_t)kXWaves * G * 4;
-    return ((masks > sums ? masks : sums) + 15) & ~(size_t)15;
+// LDS: the replica masks, whose place the experts' places (16 bits) take once the wavefront is done; one region for, in turn,
+// the set-up's arrays (which experts are listed, a flag, the experts of the list in 16 bits), the sums of the edges and the
+// waves' sums of the output; x and t.
+__host__ __device__ inline size_t x_masks_bytes(int E, int mask_bytes) { return ((size_t)E * mask_bytes + 15) & ~(size_t)15; }
+__host__ __device__ inline size_t x_shared_bytes(int E, int G) {
+    const size_t setup = (size_t)(E + kW - 1) / kW * 8 + 8 + ((size_t)E * 2 + 3 & ~(size_t)3), sums = (size_t)kXWaves * G * 4;
+    const size_t most = setup > sums ? setup : sums;
+    return edge_bytes(E, G) > most ? edge_bytes(E, G) : most;
 }
 __host__ __device__ inline size_t x_bytes(int E, int G, int xs, int mask_bytes) {
-    return x_masks_bytes(E, G, mask_bytes) + ((size_t)E * xs + G + E) * 4 + (size_t)(E + kW - 1) / kW * 8 + 16;
+    return x_masks_bytes(E, mask_bytes) + x_shared_bytes(E, G) + ((size_t)E * xs + G) * 4;
 }
 
 // prev (warm start, Section 4.1: between micro-batches only the loads change, so the previous solution is a good place
@@ -158,13 +152,15 @@ __global__ __launch_bounds__(kXThreads) void k_general_x(const uint8_t* __restri
     Problem<M> c;
     c.E = E; c.G = G; c.XS = xs;
     c.pm = reinterpret_cast<M*>(smem);
-    c.x = reinterpret_cast<int*>(smem + x_masks_bytes(E, G, sizeof(M)));
+    char* const shared = smem + x_masks_bytes(E, sizeof(M));
+    c.A = reinterpret_cast<int*>(shared);
+    c.x = reinterpret_cast<int*>(shared + x_shared_bytes(E, G));
     c.t = c.x + (size_t)E * xs;
-    int16_t* slot = reinterpret_cast<int16_t*>(c.t + G);
-    int16_t* expert = slot + E;
-    u64* listed = reinterpret_cast<u64*>(smem + ((x_masks_bytes(E, G, sizeof(M)) + ((size_t)E * xs + G + E) * 4 + 7) & ~(size_t)7));
+    u64* listed = reinterpret_cast<u64*>(shared);
     int* bad = reinterpret_cast<int*>(listed + (E + kW - 1) / kW);
-    int* sums = reinterpret_cast<int*>(smem);          // [waves][G], once the masks are done with
+    int16_t* expert = reinterpret_cast<int16_t*>(bad + 2);
+    int* sums = reinterpret_cast<int*>(shared);        // [waves][G], after the solution
+    int16_t* slot = reinterpret_cast<int16_t*>(smem);  // the same
     const int tid = threadIdx.x, l = lane(), wave = __builtin_amdgcn_readfirstlane(tid / kW);
 
     // ---- set-up: masks, the list, x, rank loads (a thread per expert: E <= kXThreads) --------------------
@@ -195,12 +191,11 @@ __global__ __launch_bounds__(kXThreads) void k_general_x(const uint8_t* __restri
     }
     c.n = n;
     j += __popcll(in_list & ((1ull << l) - 1ull));
-    if (tid < E) {
-        slot[tid] = (int16_t)(replicas > 1 ? j : -1 - (replicas == 1 ? __ffsll((long long)mask) - 1 : G));      // (G: on no rank)
-        if (replicas > 1) {
-            c.pm[j] = (M)mask;
-            expert[j] = (int16_t)tid;
-        }
+    // this thread's expert: its place in the list, or -1 - its only rank (G: on no rank)
+    const int my_slot = replicas > 1 ? j : -1 - (replicas == 1 ? __ffsll((long long)mask) - 1 : G);
+    if (replicas > 1) {
+        c.pm[j] = (M)mask;
+        expert[j] = (int16_t)tid;
     }
     __syncthreads();
     for (int i = wave; i < n; i += kXWaves) {      // a wave per listed expert, lane = rank
@@ -237,6 +232,8 @@ __global__ __launch_bounds__(kXThreads) void k_general_x(const uint8_t* __restri
             if (rank_off != nullptr && l == G - 1) rank_off[G] = first + loads;
         }
     }
+    __syncthreads();
+    if (tid < E) slot[tid] = (int16_t)my_slot;
     __syncthreads();
 
     // ---- out: a wave per run of experts, lane = rank; the rows of a rank's segments follow one another -------------
@@ -287,7 +284,7 @@ int launch_general_x(const fine_shape& s, const uint8_t* place, const int32_t* l
     const int xs = x_bytes(s.E, s.G, s.G | 1, mask_bytes) <= limit ? s.G | 1 : s.G;
     const size_t lds = x_bytes(s.E, s.G, xs, mask_bytes);
     if (lds > limit) return FINE_UNSUPPORTED;
-    static std::atomic<uint64_t> lds_set[2][17];
+    static std::atomic<uint64_t> lds_set[2][kMaxWords + 1];
     auto k = flow::by_size(s.E, s.G, [](auto words, auto m) { return k_general_x<decltype(m), words.value>; });
     FINE_TRY(raise_lds_limit((const void*)k, (int)limit, lds_set[s.G <= 32][flow::words_for(s.E)]));
     hipLaunchKernelGGL(k, dim3(1), dim3(kXThreads), lds, st, place, load, x_prev, s.E, s.G, xs, s.T * s.K, x_eg, max_load,

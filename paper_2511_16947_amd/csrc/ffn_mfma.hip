@@ -120,10 +120,15 @@ __device__ __forceinline__ void ffn_gemm_body(const uint16_t* __restrict__ A, in
     const int rest_if = total - whole_rounds;
     const bool cut_even = 4 * rest_if >= nblk && (long long)nk * (nblk - rest_if) > (long long)(tall ? 16 : 32) * nblk;
     // A rest of less than a quarter of a round, or one below that break-even, would still cost a whole extra round (24 of
-    // 280 tiles of 32 steps: one more tile time with 232 CUs idle).  Spread over the whole grid each of its tiles would end
-    // in more than four parts for its last block to add up (8 of 264 tiles of 32 steps in 32 parts each: the launch took
-    // 143 us, with four parts 78; 264 tiles of 128 rows and 64 steps 135 and 100); instead every rest tile is cut into 2 or 4 parts
-    // of at least 8 steps, part t + p * rest being k range p of rest tile t ("few parts").
+    // 280 tiles of 32 steps: one more tile time with 232 CUs idle).  Spread over the whole grid each of its tiles would have
+    // four and more parts, up to 32, for its last block to add up; instead every rest tile is cut into p parts ("few parts"),
+    // the more the longer k: a part costs its nk / p steps, and p partial tiles about as much as 5 p steps (4 p on 128 rows).
+    // GEMM 2 in launches of a round and a rest of 8, 16, 24, 32, 48, 56 tiles, us, spread over the grid : p.  256 rows, 32 steps
+    // 153 : 89, 120 : 91, 110 : 94, 107 : 95, 104 : 97, 104 : 96; 128 steps 348 : 254, 292 : 266, 289 : 268, 278 : 267, 290 : 271, 302 :
+    // 279; 224 steps 481 : 417, 436 : 423, 443 : 425, 442 : 430, 473 : 449, 495 : 457; 448 steps 809 : 781, 812 : 793, 857 : 814, 854 : 838,
+    // 913 : 879, 947 : 903.  128 rows, 64 steps 112 : 85, 97 : 87, 94 : 87, 92 : 89, 98 : 91, 99 : 92; 128 steps 179 : 159, 164 : 157, 165 :
+    // 164, 164 : 165, 175 : 172, 179 : 174.  (p = 4 whatever k: 16, 32 tiles of 224 steps 455, 463; 32 of 128 steps on 256 rows 280.)
+    // A tile's parts are consecutive units: on blocks `rest` apart 32 tiles of 64 steps on 128 rows took 99 instead of 89 us.
     // A rest of more than half a round (and GEMMs whose tiles share weight panels: the 256-row tile) is cut in
     // GROUPS instead: q consecutive rest tiles (same column, adjacent rows) share q + 1 parts of q nk / (q + 1)
     // steps, q = ceil(rest / (nblk - rest)), so that every tile is made of exactly two parts (one write, one
@@ -139,9 +144,12 @@ __device__ __forceinline__ void ffn_gemm_body(const uint16_t* __restrict__ A, in
     }
     const bool cut = cut_even && grp == 0;
     int few = 0;
-    if (!cut && grp == 0 && rest_if > 0)
-        for (int p = 4; p >= 2 && few == 0; p >>= 1)
-            if (rest_if * p <= nblk && nk / p >= 8) few = p;
+    if (!cut && grp == 0 && rest_if > 0) {
+        const int fit = nblk / rest_if, most = min(fit >= 4 ? fit : min(fit, 2), nk / 8);      // (at least 8 steps each)
+        int p = 1;
+        while (p < most && (tall ? 5 : 4) * p * (p + 1) < nk) ++p;
+        few = p > 1 ? p : 0;
+    }
     const int full = (cut || few || grp) ? whole_rounds : total;
     const int rest = total - full;
     const int per = (rest * nk + nblk - 1) / nblk;
@@ -200,9 +208,8 @@ __device__ __forceinline__ void ffn_gemm_body(const uint16_t* __restrict__ A, in
         bool finish = true;
         if (kn != nk) {
             const int t = work - full;
-            // the parts that hold pieces of tile t: first, first + step, ... (n_parts of them)
-            const int first = few ? t : grp ? (t / grp) * (grp + 1) + t % grp : (t * nk) / per;
-            const int step = few ? rest : 1;
+            // the parts that hold pieces of tile t: n_parts from `first` on
+            const int first = few ? t * few : grp ? (t / grp) * (grp + 1) + t % grp : (t * nk) / per;
             const int n_parts = few ? few : grp ? 2 : (t * nk + nk - 1) / per - first + 1;
             // Whoever arrives last (everybody else has left its k-loop by then) adds the parts up; the
             // others write theirs to their slots and then count themselves ready.  The tile is
@@ -215,7 +222,7 @@ __device__ __forceinline__ void ffn_gemm_body(const uint16_t* __restrict__ A, in
                          n_parts - 1;
             __syncthreads();
             finish = s_last != 0;
-            const int my_idx = (part - first) / step;
+            const int my_idx = part - first;
             const bool keep = finish && my_idx <= 1;
             if (!keep) {
                 const int mine = slot_of(part, t);
@@ -247,7 +254,7 @@ __device__ __forceinline__ void ffn_gemm_body(const uint16_t* __restrict__ A, in
                 }
                 __syncthreads();
                 auto add_part = [&](int i, auto assign) {
-                    const int sl = slot_of(first + i * step, t);
+                    const int sl = slot_of(first + i, t);
                     static_for<WM * WN / 2>([&](auto mp) {
                         u32x4 v[8];
                         static_for<8>([&](auto g) {
@@ -287,8 +294,8 @@ __device__ __forceinline__ void ffn_gemm_body(const uint16_t* __restrict__ A, in
         if (v < full) {
             piece(v, 0, nk, -1, true);
         } else if (few) {
-            const int part = v - full, kb = nk * (part / rest) / few;
-            piece(full + part % rest, kb, nk * (part / rest + 1) / few - kb, part, true);
+            const int part = v - full, t = part / few, i = part - t * few, kb = nk * i / few;
+            piece(full + t, kb, nk * (i + 1) / few - kb, part, true);
         } else {
             const int part = v - full;
             int u, u1;

@@ -1,5 +1,5 @@
 """Expert FFN on lists of 256-row and of 128-row tiles: runs that end in short tiles, and a last round of few tiles, which are
-cut into four parts of unequal length.  Every element against 64-bit sums."""
+cut into parts of unequal length.  Every element against 64-bit sums."""
 import pytest
 import torch
 
@@ -15,6 +15,8 @@ DEV = "cuda:0"
     (3, 2112, 2816, [1100, 1290, 200]),      # GEMM 1: 12 x 22 = 264 tiles of 33 k-steps
     (2, 2112, 2816, [600, 650, 100]),        # the same from tiles of 128 rows
     (3, 192, 2112, [256] * 33),              # GEMM 1: 33 x 17 = 561 tiles; GEMM 2: 33 tiles of 33 k-steps
+    (3, 1024, 8192, [256] * 3),              # GEMM 1: 192 tiles of 16 k-steps, too many for two parts each; GEMM 2: 12 of 128
+    (2, 1024, 5632, [128] * 3),              # the same from tiles of 128 rows: 132 tiles; 12 of 88
 ])
 def test_tiles_of_both_heights(tile, d, f, rows):
     E, P = len(rows), sum(rows)

@@ -189,20 +189,24 @@ def test_tiles_cut_along_k(tile):
 
 
 @pytest.mark.parametrize("tile,d,f,T,parts", [(3, 1024, 1024, 256, 2), (3, 1024, 1024, 250, 2),
-                                              (2, 2048, 2048, 256, 4), (2, 2048, 2048, 232, 4)])
+                                              (2, 2048, 2048, 256, 3), (2, 2048, 2048, 232, 3),
+                                              (3, 2048, 2048, 256, 3), (3, 4160, 3968, 250, 4), (2, 4096, 3968, 100, 4),
+                                              (3, 14336, 1024, 150, 7)])
 def test_a_small_rest_of_tiles_is_cut_into_few_parts(tile, d, f, T, parts):
     """Fewer tiles than blocks and a k range too short for the cut over the whole grid (16 k-tiles
-    on the 256-row tile, 32 on the 128-row tile): every tile of the rest is cut into `parts` parts,
-    part p of tile t on block t + p * rest, in both GEMMs.  Every element and every row against
-    the oracle, whole and ragged row tiles, and bit-stable from run to run."""
+    on the 256-row tile, 32 on the 128-row tile), or less than a quarter of a round: every tile of the rest is cut
+    into `parts` parts, of equal or unequal length, in GEMM 1 (and in GEMM 2 where it is as wide).  Every element and
+    every row against the oracle, whole and ragged row tiles, and bit-stable from run to run."""
     cfg = wl.LayerConfig("few_parts", T, d, f, 2, 2, 1, "bf16", 11, "scaled_z", 0.5)
-    # both GEMMs take the branch: rest tiles * parts fit the grid of 256 blocks, parts divide the
-    # k-tiles, at least 8 k-tiles per part, and the whole-grid cut does not pay
+    # GEMM 1 takes the branch: the cut over the whole grid is not taken, and as many parts as their partial tiles are worth
+    # (5 steps each on 256 rows, 4 on 128), fit the grid of 256 blocks and have 8 k-tiles each
     bm = 256 if tile == 3 else 128
-    for kd, n_out, bnc in ((d, f, 128), (f, d, 256)):
-        nk, rest = kd // 64, 2 * -(-T // bm) * (n_out // bnc)
-        assert rest * parts <= 256 and nk % parts == 0 and nk // parts >= 8 and (parts == 4 or rest * 4 > 256 or nk // 4 < 8)
-        assert nk * (256 - rest) <= (16 if tile == 3 else 32) * 256
+    nk, rest = d // 64, 2 * -(-T // bm) * (f // 128)
+    assert rest <= 128 and (4 * rest < 256 or nk * (256 - rest) <= (16 if tile == 3 else 32) * 256)
+    p, most = 1, min(256 // rest if 4 * rest <= 256 else min(256 // rest, 2), nk // 8)
+    while p < most and (5 if tile == 3 else 4) * p * (p + 1) < nk:
+        p += 1
+    assert p == parts
     inp = wl.make_inputs(cfg, DEV)
     layer = GpuLayer(cfg, inp, fm.FLAG_LOCALITY | (tile << 8))
     print("few-parts case tile", tile, "T", T, flush=True)

@@ -178,7 +178,8 @@ __global__ __launch_bounds__(256, 3) void k_ffn_f32(const float* __restrict__ A,
 // 105 : 46; 768 rows of 768 x 768 (180) 51 : 46; but 900 rows of 768 x 1024 (239) 57 : 62, 1024 rows of 1024 x 2816 (630) 216 :
 // 230, 4096 rows (2400) 665 : 826.  With a few rows per expert the 64-row tiles are mostly empty however many they are:
 // 16 rows on each of 32 experts of 1024 x 2816 248 : 213, 8 rows 182 : 156; 32 rows 269 : 296.  Rows that are no multiple of
-// 16 bytes: 576 rows of 700 x 777 (149) 57 : 54, 900 rows of 999 x 777 on 13 experts (392) 123 : 116, (536) 122 : 170.
+// 16 bytes need four times the loads: 576 rows of 700 x 777 (149) 57 : 54, 435 rows of 172 x 1515 (173) 56 : 43, but 819 rows of
+// 700 x 777 (196) 57 : 76, 439 rows of 1082 x 1926 (189) 101 : 131, 696 rows of 338 x 907 (198) 47 : 59.
 constexpr int kSM = 32, kSChunk = 32;
 
 template <int EPI, int V>
@@ -301,7 +302,7 @@ int launch_ffn_f32(const fine_shape& s, int rank_lo, int rank_hi, const void* x_
     // expected tiles of 64 rows (see pick_tile in ffn_mfma.hip)
     const double rows = (double)s.T * s.K * n_ranks / s.G, runs = std::min((double)s.E * n_ranks / s.G + 1.0, (double)s.E);
     const double tiles64 = (rows / kBM + runs) * (cdiv(s.f, 64) + cdiv(s.d, 64)) / 2;
-    const bool split = tiles64 < 220.0 || rows <= 16.0 * runs;
+    const bool split = tiles64 < (wide ? 220.0 : 175.0) || rows <= 16.0 * runs;
     const int bm = split ? kSM : kBM, bn = split ? 32 : 64;
     const int32_t* seg = nullptr;
     if (n_ranks == 1 && s.E <= kRankMapExperts) seg = seg_off + (size_t)rank_lo * (s.E + 1);

@@ -216,7 +216,8 @@ int fine_permute(const fine_shape* shape, const void* x, const int32_t* pair_of_
  *        With FINE_FLAG_ACT_SAVE_H the buffer has P*3f elements: [P,2f] as above, followed by
  *        H [P,f].  H then lives there instead of in `ws` (nothing more is written or read than
  *        without the flag), and fine_backward called with the same flag takes it from there.
- * Rows of other ranks are left untouched.
+ * Rows of other ranks are left untouched.  A row's sums may be taken in another order in a rank's call than
+ * in the call for all ranks (equal up to fp32 summation order, not bit by bit).
  */
 int fine_grouped_ffn(const fine_shape* shape, int32_t rank,
                      const void* x_perm, const void* w_gate, const void* w_up, const void* w_down,

@@ -172,7 +172,10 @@ __global__ __launch_bounds__(256, 3) void k_ffn_f32(const float* __restrict__ A,
 // split over its four waves, operands from memory straight into registers.  With fewer of the tiles above than CUs a
 // launch is a chain of latencies on few CUs: a load, its 2048 cycles of MFMA, the next.  Here a quarter of the chain is
 // left, four to eight times as many blocks share the work, and a wave has 64 k-values under way before it waits for the
-// first.  The four partial tiles are added in LDS, in the order of k.
+// first.  The four partial tiles are added in LDS, in the order of k.  That is another order than the one chain of the kernel
+// above (its distance from 64-bit sums is half as large), and which one a row gets depends on the call's ranks: a rank's call
+// and the call over all ranks differ in last bits where one takes this kernel and the other does not.  (The kernel above with
+// its sums in the same four ranges takes 2 % longer, 4 % on short k: 4096 rows of 1024 x 2816 561 -> 573, 8192 of 128 x 256 30 -> 31.)
 // Measured, both GEMMs of a rank's call, 64-row tiles against these: 128 rows of 128 x 256 18.0 : 13.0 us; 256 rows of 256 x
 // 512 27.5 : 14.2; 512 rows on 2-3 experts of 1024 x 2816 (tiles64, below, 330) 133 : 116, 256 rows (210) 115 : 74, 32 rows
 // 105 : 46; 768 rows of 768 x 768 (180) 51 : 46; but 900 rows of 768 x 1024 (239) 57 : 62, 1024 rows of 1024 x 2816 (630) 216 :
@@ -183,10 +186,10 @@ __global__ __launch_bounds__(256, 3) void k_ffn_f32(const float* __restrict__ A,
 constexpr int kSM = 32, kSChunk = 32;
 
 template <int EPI, int V>
-__device__ __forceinline__ void ffn_f32_split_body(const float* __restrict__ A, const float* __restrict__ B0,
-                                                   const float* __restrict__ B1, int Kd, int N, float* __restrict__ C,
-                                                   float* __restrict__ act, const TileEntry* __restrict__ tiles,
-                                                   const int32_t* __restrict__ count, const int32_t* __restrict__ seg, int E) {
+__global__ __launch_bounds__(256, 2) void k_ffn_f32_split(const float* __restrict__ A, const float* __restrict__ B0,
+                                                          const float* __restrict__ B1, int Kd, int N, float* __restrict__ C,
+                                                          float* __restrict__ act, const TileEntry* __restrict__ tiles,
+                                                          const int32_t* __restrict__ count, const int32_t* __restrict__ seg, int E) {
     constexpr int NP = EPI == 0 ? 2 : 1;
     __shared__ __attribute__((aligned(16))) float part[4 * NP * 16 * 64];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -279,13 +282,6 @@ __device__ __forceinline__ void ffn_f32_split_body(const float* __restrict__ A, 
         lds_barrier();      // the next tile's parts
     }
 }
-template <int EPI, int V>
-__global__ __launch_bounds__(256, 2) void k_ffn_f32_split(const float* __restrict__ A, const float* __restrict__ B0,
-                                                          const float* __restrict__ B1, int Kd, int N, float* __restrict__ C,
-                                                          float* __restrict__ act, const TileEntry* __restrict__ tiles,
-                                                          const int32_t* __restrict__ count, const int32_t* __restrict__ seg, int E) {
-    ffn_f32_split_body<EPI, V>(A, B0, B1, Kd, N, C, act, tiles, count, seg, E);
-}
 
 }  // namespace
 
@@ -307,7 +303,7 @@ int launch_ffn_f32(const fine_shape& s, int rank_lo, int rank_hi, const void* x_
     const int32_t* seg = nullptr;
     if (n_ranks == 1 && s.E <= kRankMapExperts) seg = seg_off + (size_t)rank_lo * (s.E + 1);
     else FINE_TRY(launch_tile_map(s, seg_off, rank_lo, rank_hi, bm, tiles, count, L.max_tiles, st));
-    // as many blocks as fit a CU (three; split: eight waves per CU's SIMD at most); no more than there can be tiles
+    // three blocks per CU, four of the split kernel (whose registers let two to four in); no more than there can be tiles
     const size_t rows_tiles = (size_t)s.T * s.K / bm + (size_t)s.E * n_ranks;
     auto grid = [&](int n) { return (unsigned)std::min<size_t>(split ? 1024 : 768, align_up(rows_tiles * cdiv(n, bn), 8)); };
     auto run = [&](auto k1, auto k2) {

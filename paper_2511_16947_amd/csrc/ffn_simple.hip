@@ -14,8 +14,8 @@ namespace {
 // Thread t takes C consecutive segments; everything it needs of the others are two running maxima (the last non-empty
 // segment; the first segment of the last run) and a sum of tile counts: three block scans whatever the number of
 // segments.  A segment is named by its place in seg_off.  The ranks' rows of seg_off are read into LDS once (CACHED: where they
-// fit) and walked there, with no division per segment: 8192 segments 31 -> 23
-// us, 1024 7.1 -> 5.4.
+// fit) and walked there, with no division per segment: 8192 segments 31 -> 23 us,
+// 1024 7.1 -> 5.4.
 constexpr int kMapThreads = 1024;
 constexpr size_t kMapLds = 60 * 1024;
 

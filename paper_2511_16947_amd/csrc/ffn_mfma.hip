@@ -122,13 +122,19 @@ __device__ __forceinline__ void ffn_gemm_body(const uint16_t* __restrict__ A, in
     // A rest of less than a quarter of a round, or one below that break-even, would still cost a whole extra round (24 of
     // 280 tiles of 32 steps: one more tile time with 232 CUs idle).  Spread over the whole grid each of its tiles would have
     // four and more parts, up to 32, for its last block to add up; instead every rest tile is cut into p parts ("few parts"),
-    // the more the longer k: a part costs its nk / p steps, and p partial tiles about as much as 5 p steps (4 p on 128 rows).
-    // GEMM 2 in launches of a round and a rest of 8, 16, 24, 32, 48, 56 tiles, us, spread over the grid : p.  256 rows, 32 steps
-    // 153 : 89, 120 : 91, 110 : 94, 107 : 95, 104 : 97, 104 : 96; 128 steps 348 : 254, 292 : 266, 289 : 268, 278 : 267, 290 : 271, 302 :
-    // 279; 224 steps 481 : 417, 436 : 423, 443 : 425, 442 : 430, 473 : 449, 495 : 457; 448 steps 809 : 781, 812 : 793, 857 : 814, 854 : 838,
-    // 913 : 879, 947 : 903.  128 rows, 64 steps 112 : 85, 97 : 87, 94 : 87, 92 : 89, 98 : 91, 99 : 92; 128 steps 179 : 159, 164 : 157, 165 :
-    // 164, 164 : 165, 175 : 172, 179 : 174.  (p = 4 whatever k: 16, 32 tiles of 224 steps 455, 463; 32 of 128 steps on 256 rows 280.)
-    // A tile's parts are consecutive units: on blocks `rest` apart 32 tiles of 64 steps on 128 rows took 99 instead of 89 us.
+    // the more the longer k: a part costs its nk / p steps, and p partial tiles about as much as 5 p steps (4 p on 128 rows; all
+    // alone in the launch, and so at the same time, another rest / 12 each).
+    // Parts go to the XCDs in equal numbers (`dealt`): in eighths of a round, as tiles do, 16 tiles in four parts would be the work
+    // of two XCDs with a fourth of the memory path.  After whole rounds sixteen parts stay on one XCD: with 16 to 24 steps the
+    // launch takes 1 us (3 %) longer otherwise.  More than 7/8 of a round are left as they lie (60 tiles in four parts 4-6 % slower dealt).
+    // A tile's parts are consecutive units after whole rounds (304 tiles of 128 steps 277 us, 292 with its parts `rest` apart), but
+    // `rest` apart where they are all there is (56 tiles of 128 steps 99 consecutive, 81 so; on 128 rows 68 and 60).
+    // GEMM 2, us, spread over the grid : four parts, not dealt : now.  A round and 8, 16, 32, 48, 56 tiles of 256 rows: 32 steps
+    // 151 : 92 : 86, 118 : 99 : 87, 105 : 104 : 89, 103 : 107 : 92, 102 : 104 : 94; 128 steps 346 : 258 : 250, 290 : 277 : 252, 278 : 280 : 261,
+    // 287 : 277 : 274, 297 : 280 : 274; 224 steps 480 : 427 : 408, 431 : 452 : 410, 438 : 456 : 424, 473 : 465 : 448, 492 : 460 : 459; of 128
+    // rows, 128 steps 182 : 165 : 156, 165 : 163 : 155, 164 : 165 : 163, 174 : 166 : 170, 178 : 170 : 172.  8, 16, 32, 48, 56 tiles alone: 256 rows, 64
+    // steps 103 : 51 : 46, 71 : 59 : 47, 63 : 64 : 51, 66 : 67 : 57, 71 : 66 : 61; 224 steps 112 : 98 : 70, 91 : 119 : 75, 114 : 125 : 102, 140 :
+    // 123 : 126, 156 : 127 : 128; 128 rows, 128 steps 59 : 46 : 34, 48 : 45 : 36, 51 : 56 : 40, 62 : 60 : 51, 71 : 63 : 58.
     // A rest of more than half a round (and GEMMs whose tiles share weight panels: the 256-row tile) is cut in
     // GROUPS instead: q consecutive rest tiles (same column, adjacent rows) share q + 1 parts of q nk / (q + 1)
     // steps, q = ceil(rest / (nblk - rest)), so that every tile is made of exactly two parts (one write, one
@@ -146,8 +152,9 @@ __device__ __forceinline__ void ffn_gemm_body(const uint16_t* __restrict__ A, in
     int few = 0;
     if (!cut && grp == 0 && rest_if > 0) {
         const int fit = nblk / rest_if, most = min(fit >= 4 ? fit : min(fit, 2), nk / 8);      // (at least 8 steps each)
-        int p = 1;
-        while (p < most && (tall ? 5 : 4) * p * (p + 1) < nk) ++p;
+        const int price = 12 * (tall ? 5 : 4) + (whole_rounds == 0 ? rest_if : 0);             // of a partial tile, in 1 / 12 steps
+        int p = min(most, 2);
+        while (p < most && price * p * (p + 1) < 12 * nk) ++p;
         few = p > 1 ? p : 0;
     }
     const int full = (cut || few || grp) ? whole_rounds : total;
@@ -155,6 +162,9 @@ __device__ __forceinline__ void ffn_gemm_body(const uint16_t* __restrict__ A, in
     const int per = (rest * nk + nblk - 1) / nblk;
     const int n_groups = grp ? (rest + grp - 1) / grp : 0;
     const int nparts = cut ? nblk : grp ? rest + n_groups : rest * few;
+    // (the units of a round are its 256 places, 32 for each XCD: dealt, the first nparts / 8 of these hold a part)
+    const bool dealt = few && 8 * nparts <= 7 * nblk && (full == 0 || nparts > 16);
+    const int few_step = full == 0 ? rest : 1;      // between the parts of a tile
     int32_t* counters = count + kSkCounterOffset;      // arrivals per rest tile
     int32_t* ready = count + kSkReadyOffset;           // parts written per rest tile
     // steps [u0, u1) of the sequence of rest tiles (tile t = steps [t nk, (t + 1) nk)) that part `part` computes
@@ -194,7 +204,7 @@ __device__ __forceinline__ void ffn_gemm_body(const uint16_t* __restrict__ A, in
     // Who computes what: the units of a launch are its whole tiles [0, full) and then its parts
     // [full, full + nparts), handed out by UnitQueue (counters zeroed by k_tile_map).
     UnitQueue uq;
-    uq.init(count + kQueueOffset + (EPI * 8) * kQueueStride, kQueueStride, full + nparts, bid, true);
+    uq.init(count + kQueueOffset + (EPI * 8) * kQueueStride, kQueueStride, full + (dealt ? nblk : nparts), bid, true);
     auto request = [&]() { uq.request(); };
 
     // k-tiles [kb, kb + kn) of tile `work`; part: the part this piece belongs to (-1: a whole tile);
@@ -208,8 +218,8 @@ __device__ __forceinline__ void ffn_gemm_body(const uint16_t* __restrict__ A, in
         bool finish = true;
         if (kn != nk) {
             const int t = work - full;
-            // the parts that hold pieces of tile t: n_parts from `first` on
-            const int first = few ? t * few : grp ? (t / grp) * (grp + 1) + t % grp : (t * nk) / per;
+            // the parts that hold pieces of tile t: first, first + step, ... (n_parts of them)
+            const int first = few ? (few_step == 1 ? t * few : t) : grp ? (t / grp) * (grp + 1) + t % grp : (t * nk) / per;
             const int n_parts = few ? few : grp ? 2 : (t * nk + nk - 1) / per - first + 1;
             // Whoever arrives last (everybody else has left its k-loop by then) adds the parts up; the
             // others write theirs to their slots and then count themselves ready.  The tile is
@@ -222,7 +232,7 @@ __device__ __forceinline__ void ffn_gemm_body(const uint16_t* __restrict__ A, in
                          n_parts - 1;
             __syncthreads();
             finish = s_last != 0;
-            const int my_idx = part - first;
+            const int step = few ? few_step : 1, my_idx = (part - first) / step;
             const bool keep = finish && my_idx <= 1;
             if (!keep) {
                 const int mine = slot_of(part, t);
@@ -254,7 +264,7 @@ __device__ __forceinline__ void ffn_gemm_body(const uint16_t* __restrict__ A, in
                 }
                 __syncthreads();
                 auto add_part = [&](int i, auto assign) {
-                    const int sl = slot_of(first + i, t);
+                    const int sl = slot_of(first + i * step, t);
                     static_for<WM * WN / 2>([&](auto mp) {
                         u32x4 v[8];
                         static_for<8>([&](auto g) {
@@ -294,8 +304,17 @@ __device__ __forceinline__ void ffn_gemm_body(const uint16_t* __restrict__ A, in
         if (v < full) {
             piece(v, 0, nk, -1, true);
         } else if (few) {
-            const int part = v - full, t = part / few, i = part - t * few, kb = nk * i / few;
-            piece(full + t, kb, nk * (i + 1) / few - kb, part, true);
+            int part = v - full;
+            if (dealt) {
+                const int per_x = nblk / 8, x = part / per_x, at = nparts * x / 8 + part - x * per_x;
+                part = at < nparts * (x + 1) / 8 ? at : -1;
+            }
+            if (part < 0) {
+                request();
+            } else {
+                const int t = few_step == 1 ? part / few : part % rest, i = few_step == 1 ? part - t * few : part / rest;
+                piece(full + t, nk * i / few, nk * (i + 1) / few - nk * i / few, part, true);
+            }
         } else {
             const int part = v - full;
             int u, u1;

@@ -189,9 +189,9 @@ def test_tiles_cut_along_k(tile):
 
 
 @pytest.mark.parametrize("tile,d,f,T,parts", [(3, 1024, 1024, 256, 2), (3, 1024, 1024, 250, 2),
-                                              (2, 2048, 2048, 256, 3), (2, 2048, 2048, 232, 3),
-                                              (3, 2048, 2048, 256, 3), (3, 4160, 3968, 250, 4), (2, 4096, 3968, 100, 4),
-                                              (3, 14336, 1024, 150, 7)])
+                                              (2, 2048, 2048, 256, 2), (2, 2048, 2048, 232, 2),
+                                              (3, 2048, 2048, 256, 2), (3, 4160, 3968, 250, 3), (2, 8192, 3840, 100, 4),
+                                              (3, 14336, 1024, 150, 6)])
 def test_a_small_rest_of_tiles_is_cut_into_few_parts(tile, d, f, T, parts):
     """Fewer tiles than blocks and a k range too short for the cut over the whole grid (16 k-tiles
     on the 256-row tile, 32 on the 128-row tile), or less than a quarter of a round: every tile of the rest is cut
@@ -199,12 +199,13 @@ def test_a_small_rest_of_tiles_is_cut_into_few_parts(tile, d, f, T, parts):
     every row against the oracle, whole and ragged row tiles, and bit-stable from run to run."""
     cfg = wl.LayerConfig("few_parts", T, d, f, 2, 2, 1, "bf16", 11, "scaled_z", 0.5)
     # GEMM 1 takes the branch: the cut over the whole grid is not taken, and as many parts as their partial tiles are worth
-    # (5 steps each on 256 rows, 4 on 128), fit the grid of 256 blocks and have 8 k-tiles each
+    # (5 steps each on 256 rows, 4 on 128, and rest / 12), fit the grid of 256 blocks and have 8 k-tiles each
     bm = 256 if tile == 3 else 128
     nk, rest = d // 64, 2 * -(-T // bm) * (f // 128)
     assert rest <= 128 and (4 * rest < 256 or nk * (256 - rest) <= (16 if tile == 3 else 32) * 256)
-    p, most = 1, min(256 // rest if 4 * rest <= 256 else min(256 // rest, 2), nk // 8)
-    while p < most and (5 if tile == 3 else 4) * p * (p + 1) < nk:
+    most = min(256 // rest if 4 * rest <= 256 else min(256 // rest, 2), nk // 8)
+    p, price = min(most, 2), 12 * (5 if tile == 3 else 4) + rest
+    while p < most and price * p * (p + 1) < 12 * nk:
         p += 1
     assert p == parts
     inp = wl.make_inputs(cfg, DEV)

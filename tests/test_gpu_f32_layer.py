@@ -88,6 +88,7 @@ def test_fewer_rows_take_no_longer():
             t.append(a.elapsed_time(b) * 100)
         return float(np.median(t))
 
+    us(1000)      # (clocks)
     assert us(900) < 1.12 * us(1000)
 
 

@@ -56,21 +56,29 @@ __device__ __forceinline__ void ffn_gemm_body(const uint16_t* __restrict__ A, in
         // and asks memory for nothing (their results are never stored)
         oa.init(A + (size_t)te.row0 * lda, [&](int r) { return (size_t)r * lda; },
                 (uint32_t)((size_t)te.rows * lda * 2), (wave / WAVES_N) * WM * 32);
-        DmaOperand<WN> ob;
         const int wn = wave % WAVES_N;
-        if constexpr (EPI == 0) {
-            // panel 0 = 128 gate columns, panel 1 = the matching up columns; a wave's two
-            // fragments are the same 32 columns of both
-            ob.init(Bg, Bu, [&](int, int c) { return min(n0 + 8 * c, N - 8); }, (size_t)N,
-                    [&](int f) { return 128 * f + 32 * wn; });
-        } else {
-            ob.init(Bg, Bg, [&](int p, int c) { return min(n0 + 128 * p + 8 * c, N - 8); }, (size_t)N,
-                    [&](int f) { return 64 * wn + 32 * f; });
-        }
         // fragments of the wave that hold valid rows (the rest of a short last tile is skipped)
         const int nf = min(WM, max(0, (te.rows - (wave / WAVES_N) * WM * 32 + 31) / 32));
-        if (te.rows == BM) k_loop8<false, 4>(kn, smem, acc, oa, ob, k_tile);
-        else k_loop8<true, 4>(kn, smem, acc, oa, ob, k_tile, nf);
+        auto k_range = [&](auto ragged, auto nt) {
+            DmaOperand<WN, nt.value> ob;
+            if constexpr (EPI == 0) {
+                // panel 0 = 128 gate columns, panel 1 = the matching up columns; a wave's two
+                // fragments are the same 32 columns of both
+                ob.init(Bg, Bu, [&](int, int c) { return min(n0 + 8 * c, N - 8); }, (size_t)N,
+                        [&](int f) { return 128 * f + 32 * wn; });
+            } else {
+                ob.init(Bg, Bg, [&](int p, int c) { return min(n0 + 128 * p + 8 * c, N - 8); }, (size_t)N,
+                        [&](int f) { return 64 * wn + 32 * f; });
+            }
+            k_loop8<ragged.value, 4>(kn, smem, acc, oa, ob, k_tile, nf);
+        };
+        // Weights that no other row tile reads bypass the caches (non-temporal), which leaves those to the activations and
+        // to weights that are read again: 32 rows on each of 64 experts of 7168 x 2048, both GEMMs 985 -> 894 us (5.7 -> 6.3
+        // TB/s); 8192 rows on them (half of the runs one tile) 1254 -> 1219; 10725 rows on 144 of 3776 x 512 394 -> 361; where most
+        // runs have several tiles nothing changes.  (Non-temporal throughout is 7 % slower: then weights are shared.)
+        if (te.rows == BM) k_range(std::false_type{}, std::false_type{});
+        else if (te.alone) k_range(std::true_type{}, std::true_type{});
+        else k_range(std::true_type{}, std::false_type{});
     };
 
     // LDS-staged epilogue of tile te, 8-byte coalesced stores

@@ -83,7 +83,8 @@ __device__ inline void block_barrier() {
 // ---------------------------------------------------------------------------
 enum OperandKind { kRing = 1, kRow = 2 };
 
-template <int NF>
+// NT: fetched with the non-temporal policy (data that this launch reads once).
+template <int NF, bool NT = false>
 struct DmaOperand {
     static constexpr int kKind = kRing;
     static constexpr bool kDma = true;
@@ -127,7 +128,7 @@ struct DmaOperand {
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
             (void*)(src[T] + (size_t)base * (ld2 / 2)), 0, (int)((uint32_t)(end - base) * ld2), 0x00020000);
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, FINE_LDS_PTR(stage + T * 8192 + wave * 1024), 16, voff[T],
-                                                 (uint32_t)((int)k0 - base) * ld2, 0, 0);
+                                                 (uint32_t)((int)k0 - base) * ld2, 0, NT ? 2 : 0);
     }
     template <int J>
     __device__ inline void row_issue(ptrdiff_t, int, char*) const {}      // (the other kind's interface: never called)

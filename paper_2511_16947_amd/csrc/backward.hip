@@ -8,6 +8,8 @@
 //               e on every rank, ranks in ascending order: the replicas' gradients, which the
 //               paper sums with a data-parallel all-reduce, share one fp32 accumulator here)
 //   dX[token] = sum_k dXp[row(token, k)]
+#include <cmath>
+
 #include "gemm_w8.h"
 
 namespace fine {
@@ -15,6 +17,23 @@ namespace fine {
 namespace {
 
 using namespace mfma;
+
+// The k-loop of a data gradient's tile on 8 waves: both operands contiguous along k, init_b sets up the weights'.  On 128 rows
+// weights that no other row tile reads are fetched non-temporal (5196 rows on 93 experts of 1856 x 1728: dH 154 -> 142 us,
+// dXp 238 -> 217; of 256 rows a tile is seldom alone).
+template <int WM, typename OA, typename Tile, typename InitB>
+__device__ __forceinline__ void k_loop_rows(int nk, char* smem, f32x16 (&acc)[WM][2], const TileEntry& te, OA& oa, Tile k_tile, int nf,
+                                            InitB init_b) {
+    auto run = [&](auto ragged, auto nt) {
+        RowDmaOperand<2, 256, nt.value> ob;
+        init_b(ob);
+        if constexpr (WM == 2) k_loop8_rows3<ragged.value>(nk, smem, acc, oa, ob, k_tile, nf);
+        else k_loop8<ragged.value>(nk, smem, acc, oa, ob, k_tile, nf);
+    };
+    if (te.rows == WM * 64) run(std::false_type{}, std::false_type{});
+    else if (WM == 2 && te.alone) run(std::true_type{}, std::integral_constant<bool, WM == 2>{});
+    else run(std::true_type{}, std::false_type{});
+}
 
 // ---- dH = dY Wd^T with the SwiGLU backward epilogue -------------------------------------
 template <int WAVES_M, int WAVES_N, int WM, int WN>
@@ -42,16 +61,15 @@ __device__ __forceinline__ void bwd_dh_body(const uint16_t* __restrict__ dy, con
         auto k_tile = [&](int kt) { return KTile{(ptrdiff_t)kt * BK, (ptrdiff_t)kt * BK, 0, 0}; };
         if constexpr (W8) {
             const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-            RowDmaOperand<WM> oa;
+            RowDmaOperand<WM, BM> oa;
             // rows past the tile's last lie beyond the descriptor's size: zeros by DMA, no memory request
             oa.init(dy + (size_t)te.row0 * d, [&](int r) { return (size_t)r * d; },
                     (uint32_t)((size_t)te.rows * d * 2), (wave / WAVES_N) * WM * 32);
-            RowDmaOperand<WN> ob;
-            ob.init(W, [&](int n) { return (size_t)min(n0 + n, f - 1) * d; }, (uint32_t)((size_t)f * d * 2),
-                    (wave % WAVES_N) * WN * 32);
-            const int nf = min(4, max(0, (te.rows - (wave / WAVES_N) * WM * 32 + 31) / 32));
-            if (te.rows == BM) k_loop8<false>(d / BK, smem, acc, oa, ob, k_tile);
-            else k_loop8<true>(d / BK, smem, acc, oa, ob, k_tile, nf);
+            const int nf = min(WM, max(0, (te.rows - (wave / WAVES_N) * WM * 32 + 31) / 32));
+            k_loop_rows<WM>(d / BK, smem, acc, te, oa, k_tile, nf, [&](auto& ob) {
+                ob.init(W, [&](int n) { return (size_t)min(n0 + n, f - 1) * d; }, (uint32_t)((size_t)f * d * 2),
+                        (wave % WAVES_N) * WN * 32);
+            });
             uq.request();      // the next tile, read after the epilogue
         } else {
             LoaderKC<BM> la;
@@ -168,15 +186,14 @@ __device__ __forceinline__ void bwd_dx_body(const uint16_t* __restrict__ dact, c
         zero_acc<WM, WN>(acc);
         if constexpr (W8) {
             const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-            RowDmaOperand<WM> oa;
+            RowDmaOperand<WM, BM> oa;
             oa.init(dact + (size_t)te.row0 * (2 * f), [&](int r) { return (size_t)r * (2 * f); },
                     (uint32_t)((size_t)te.rows * 2 * f * 2), (wave / WAVES_N) * WM * 32);
-            RowDmaOperand<WN> ob;
-            ob.init(Wg, [&](int n) { return (size_t)min(n0 + n, d - 1) * f; }, (uint32_t)((size_t)d * f * 2),
-                    (wave % WAVES_N) * WN * 32, Wu);
-            const int nf = min(4, max(0, (te.rows - (wave / WAVES_N) * WM * 32 + 31) / 32));
-            if (te.rows == BM) k_loop8<false>(2 * nkf, smem, acc, oa, ob, k_tile);
-            else k_loop8<true>(2 * nkf, smem, acc, oa, ob, k_tile, nf);
+            const int nf = min(WM, max(0, (te.rows - (wave / WAVES_N) * WM * 32 + 31) / 32));
+            k_loop_rows<WM>(2 * nkf, smem, acc, te, oa, k_tile, nf, [&](auto& ob) {
+                ob.init(Wg, [&](int n) { return (size_t)min(n0 + n, d - 1) * f; }, (uint32_t)((size_t)d * f * 2),
+                        (wave % WAVES_N) * WN * 32, Wu);
+            });
             uq.request();
         } else {
             LoaderKC<BM> la;
@@ -338,8 +355,8 @@ int run_dgrad(const fine_shape& s, int rank_lo, int rank_hi, const uint16_t* dy,
               TileEntry* tiles, int32_t* count, int max_tiles, bool run_dh, bool run_dx, hipStream_t st) {
     constexpr int BM = WAVES_M * WM * 32, BN = WAVES_N * WN * 32;
     FINE_TRY(launch_tile_map(s, seg_off, rank_lo, rank_hi, BM, tiles, count, max_tiles, st));      // also zeroes the queues
-    const size_t lds = (size_t)2 * (BM + BN) * 128;
     constexpr bool W8 = WAVES_M * WAVES_N == 8;
+    const size_t lds = (size_t)(W8 && WM == 2 ? 3 : 2) * (BM + BN) * 128;
     constexpr int threads = WAVES_M * WAVES_N * 64;
     auto k1 = [] { if constexpr (W8) return k_bwd_dh_w8<WAVES_M, WAVES_N, WM, WN>; else return k_bwd_dh<WAVES_M, WAVES_N, WM, WN>; }();
     auto k2 = [] { if constexpr (W8) return k_bwd_dx_w8<WAVES_M, WAVES_N, WM, WN>; else return k_bwd_dx<WAVES_M, WAVES_N, WM, WN>; }();
@@ -420,21 +437,34 @@ int launch_backward(const fine_shape& s, int rank_lo, int rank_hi, const void* d
                                       L.max_tiles, reinterpret_cast<float*>(ws + L.sk), true, false, true, st));
         act = act_ws;
     }
-    const double P = (double)s.T * s.K;
-    // expected rows of a (rank, expert) segment; the work list of a call for all ranks joins an expert's segments on
-    // neighbouring ranks, but one rank's call has the segments by themselves and takes the same tile
-    const double seg_rows = (P / s.G) / ((double)s.E / s.G + 1.0);
+    // Row tiles of the data gradients: 256 rows where the launches are long, 128 where tiles of 256 would leave much of a round of
+    // the 256 blocks idle or would mostly lie past the ends of short runs.  Per row 128 cost about a tenth more (65536 rows on 16
+    // experts of 2048 x 8192: dH 2450 : 2730 us, dXp 3650 : 3890); the line lies where a tile of 128 is priced at 1.25 / 2 of one of
+    // 256.  A row tile has f / 256 column tiles of d / 64 steps in dH and d / 256 of 2 f / 64 in dXp; rounds count whole, past four of
+    // them (where blocks that are done take on others' tiles) and a half.  256 : 128 rows, dH and dXp: 12000 rows on 24 experts of
+    // 1600 x 1600 135 + 184 : 114 + 160 us; 20000 on 17 of 640 x 2112 145 + 182 : 139 + 139; 16384 on 16 of 2048 x 8192 672 + 1140 : 718
+    // + 1140; 8192 on 16 of 1024 x 2816 100 + 162 : 118 + 170.  (The 4-wave 128-row tiles, for matrices past the 8-wave kernels' offsets,
+    // take 242 + 340 us where 128 rows here take 202 + 306: 32768 rows on 128 experts of 2048 x 768.)
+    const double n_ranks = rank_hi - rank_lo, rows = (double)s.T * s.K * n_ranks / s.G;
+    const double runs = std::min((double)s.E * n_ranks / s.G + 1.0, (double)s.E);
+    auto cost = [&](int bm) {
+        const double row_tiles = std::max(runs, rows / bm + runs / 2);
+        auto rounds = [&](int n) {
+            const double r = row_tiles * cdiv(n, 256) / 256.0;
+            return r > 4.0 ? r + 0.5 : std::ceil(r);
+        };
+        return (bm == 256 ? 2.0 : 1.25) * (rounds(s.f) * s.d + rounds(s.d) * 2.0 * s.f);
+    };
     int tile = (s.flags & FINE_FLAG_TILE_MASK) >> FINE_FLAG_TILE_SHIFT;
-    // Short segments: 128-row tiles on 4 waves also where most of their rows are empty.  (64-row tiles, dH + dXp against
-    // 128 rows: 5 rows per segment 126 : 101 us, 15 rows 201 : 170, 60 rows 380 : 317, 57 rows on wide experts 192 : 162.)
-    if (tile != 3) tile = tile == 0 && seg_rows >= 384.0 ? 3 : 2;
-    if (!w8_offsets_fit(s)) tile = 2;
+    if (tile == 0) tile = cost(256) <= cost(128) ? 3 : 2;
+    const bool w8 = w8_offsets_fit(s);
 #define FINE_DGRAD(WAM, WAN, WMM, WNN)                                                                        \
     FINE_TRY((run_dgrad<WAM, WAN, WMM, WNN>(s, rank_lo, rank_hi, dy, act, (const uint16_t*)wg, (const uint16_t*)wu, \
                                             (const uint16_t*)wd, seg_off, dact, h_out, dxp, tiles, count, L.max_tiles, \
                                             on(2), on(3), st)))
     if (on(2) || on(3)) {
-        if (tile == 3) FINE_DGRAD(2, 4, 4, 2);
+        if (w8 && tile == 3) FINE_DGRAD(2, 4, 4, 2);
+        else if (w8) FINE_DGRAD(2, 4, 2, 2);
         else FINE_DGRAD(2, 2, 2, 4);
     }
 #undef FINE_DGRAD

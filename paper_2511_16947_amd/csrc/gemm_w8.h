@@ -147,7 +147,7 @@ struct DmaOperand {
 // wave and 64-k tile: instruction j of wave w covers tile rows 64 j + 8 w .. + 7, lane i row
 // (i >> 3) of them and the LDS chunk (i & 7), for which it fetches the global chunk that the
 // swizzle puts there.  No registers, no LDS write instructions, no waits between barriers.
-template <int NF, int ROWS = 256>
+template <int NF, int ROWS = 256, bool NT = false>
 struct RowDmaOperand {
     static constexpr int kKind = kRow;
     static constexpr int kInstr = ROWS / 64;          // DMA instructions per wave and tile
@@ -184,7 +184,7 @@ struct RowDmaOperand {
         const __amdgpu_buffer_rsrc_t rs =
             __builtin_amdgcn_make_buffer_rsrc((void*)(sel ? src[1] : src[0]), 0, (int)bytes, 0x00020000);
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, FINE_LDS_PTR(buf + (64 * J + 8 * wave) * 128), 16, voff[J],
-                                                 (uint32_t)k * 2u, 0, 0);
+                                                 (uint32_t)k * 2u, 0, NT ? 2 : 0);
     }
     template <int T>
     __device__ inline void issue(ptrdiff_t, int, int, char*) const {}      // (the other kind's interface: never called)
@@ -211,29 +211,36 @@ struct SideOp {
     int kind, idx;
 };
 constexpr SideOp kNo{kNone, 0};
-// [half step][slot][up to two operations]; kA, kB = operand kinds; WM = 32-row fragments per wave
+// [half step][slot][up to three operations]; kA, kB = operand kinds; WM = 32-row fragments per wave
 // (a sub-step has WM slots, a half step 2 WM)
 template <int kA, int kB, int WM>
 struct Schedule;
 template <>
 struct Schedule<kRow, kRing, 2> {   // forward, 128-row tile: two slots per sub-step
     static constexpr int kSlots = 4;
-    static constexpr SideOp op[2][4][2] = {
+    static constexpr SideOp op[2][4][3] = {
         {{{kDmaB, 0}, kNo}, {{kDmaB, 1}, kNo}, {kNo, kNo}, {kNo, kNo}},
         {{{kDmaB, 0}, kNo}, {{kDmaB, 1}, kNo}, {{kRowA, 0}, kNo}, {{kRowA, 1}, kNo}}};
 };
 template <>
 struct Schedule<kRow, kRing, 4> {   // activations by row DMA, weights through the ring (forward)
     static constexpr int kSlots = 8;
-    static constexpr SideOp op[2][8][2] = {
+    static constexpr SideOp op[2][8][3] = {
         {{{kDmaB, 0}, kNo}, {{kDmaB, 1}, kNo}, {kNo, kNo}, {kNo, kNo}, {kNo, kNo}, {kNo, kNo}, {kNo, kNo}, {kNo, kNo}},
         {{{kDmaB, 0}, kNo}, {{kDmaB, 1}, kNo}, {kNo, kNo}, {kNo, kNo},
          {{kRowA, 0}, kNo}, {{kRowA, 1}, kNo}, {{kRowA, 2}, kNo}, {{kRowA, 3}, kNo}}};
 };
 template <>
+struct Schedule<kRow, kRow, 2> {    // both by row DMA, 128-row tile: operand A has two instructions, B four
+    static constexpr int kSlots = 4;
+    static constexpr SideOp op[2][4][3] = {
+        {{kNo, kNo}, {kNo, kNo}, {kNo, kNo}, {kNo, kNo}},
+        {{kNo, kNo}, {kNo, kNo}, {{kRowA, 0}, {kRowB, 0}, {kRowB, 1}}, {{kRowA, 1}, {kRowB, 2}, {kRowB, 3}}}};
+};
+template <>
 struct Schedule<kRow, kRow, 4> {    // both by row DMA (data gradients)
     static constexpr int kSlots = 8;
-    static constexpr SideOp op[2][8][2] = {
+    static constexpr SideOp op[2][8][3] = {
         {{kNo, kNo}, {kNo, kNo}, {kNo, kNo}, {kNo, kNo}, {kNo, kNo}, {kNo, kNo}, {kNo, kNo}, {kNo, kNo}},
         {{kNo, kNo}, {kNo, kNo}, {kNo, kNo}, {kNo, kNo},
          {{kRowA, 0}, {kRowB, 0}}, {{kRowA, 1}, {kRowB, 1}}, {{kRowA, 2}, {kRowB, 2}}, {{kRowA, 3}, {kRowB, 3}}}};
@@ -241,16 +248,16 @@ struct Schedule<kRow, kRow, 4> {    // both by row DMA (data gradients)
 template <>
 struct Schedule<kRing, kRing, 4> {  // both through rings (weight gradients)
     static constexpr int kSlots = 8;
-    static constexpr SideOp op[2][8][2] = {
+    static constexpr SideOp op[2][8][3] = {
         {{{kDmaA, 0}, kNo}, {{kDmaA, 1}, kNo}, {{kDmaB, 0}, kNo}, {{kDmaB, 1}, kNo}, {kNo, kNo}, {kNo, kNo}, {kNo, kNo}, {kNo, kNo}},
         {{{kDmaA, 0}, kNo}, {{kDmaA, 1}, kNo}, {{kDmaB, 0}, kNo}, {{kDmaB, 1}, kNo}, {kNo, kNo}, {kNo, kNo}, {kNo, kNo}, {kNo, kNo}}};
 };
 constexpr bool is_dma(SideOp o) { return o.kind == kDmaA || o.kind == kDmaB || o.kind == kRowA || o.kind == kRowB; }
 constexpr bool is_vmem(SideOp o) { return is_dma(o); }
 template <typename S>
-constexpr int slot_vmem(int P, int i) { return (int)is_vmem(S::op[P][i][0]) + (int)is_vmem(S::op[P][i][1]); }
+constexpr int slot_vmem(int P, int i) { return (int)is_vmem(S::op[P][i][0]) + (int)is_vmem(S::op[P][i][1]) + (int)is_vmem(S::op[P][i][2]); }
 template <typename S>
-constexpr bool slot_dma(int P, int i) { return is_dma(S::op[P][i][0]) || is_dma(S::op[P][i][1]); }
+constexpr bool slot_dma(int P, int i) { return slot_vmem<S>(P, i) > 0; }
 
 // How many vector memory instructions may still be outstanding at the barrier of half step h
 // (parity P) when the DMA of stage h + 1 must have landed.  With a ring of RING stages that DMA
@@ -288,7 +295,8 @@ struct Frags {
 //                     MFMAs and fragment reads of the others are skipped
 //   NATURAL           MFMA operands in their natural order (accumulator tiles hold the output tile as it
 //                     lies, see store_tile_f32_direct) instead of swapped (transposed tiles)
-template <int P, bool BARRIER, bool RAGGED_M, int RING, bool ISSUE, int WM, bool NATURAL, typename OA, typename OB>
+//   VM                how many vector memory instructions may be outstanding at the barrier
+template <int P, bool BARRIER, bool RAGGED_M, int VM, bool ISSUE, int WM, bool NATURAL, typename OA, typename OB>
 __device__ inline void half_step8(const char* a_src, const char* b_src, const char* a_next, const char* b_next,
                                   char* a_dst, char* b_dst, f32x16 (&acc)[WM][2], Frags<WM>& f0, Frags<WM>& f1, OA& oa,
                                   OB& ob, ptrdiff_t ka, ptrdiff_t kb, int kbase, int kend, int ksel, int nf) {
@@ -298,7 +306,7 @@ __device__ inline void half_step8(const char* a_src, const char* b_src, const ch
     constexpr int KA1 = ringA ? 1 : 2 * P + 1, KB1 = ringB ? 1 : 2 * P + 1;                 // second sub-step
     constexpr int KA0 = ringA ? 0 : (2 * P + 2) & 3, KB0 = ringB ? 0 : (2 * P + 2) & 3;     // next first
     auto side = [&](auto slot_c) {
-        if constexpr (ISSUE) static_for<2>([&](auto which) {
+        if constexpr (ISSUE) static_for<3>([&](auto which) {
             constexpr SideOp o = S::op[P][slot_c.value][which.value];
             if constexpr (o.kind == kDmaA) oa.template issue<o.idx>(ka, kbase, kend, a_dst);
             else if constexpr (o.kind == kDmaB) ob.template issue<o.idx>(kb, kbase, kend, b_dst);
@@ -341,7 +349,7 @@ __device__ inline void half_step8(const char* a_src, const char* b_src, const ch
         __builtin_amdgcn_sched_barrier(0);
     });
     if constexpr (BARRIER) {
-        wait_vm_lgkm<(ISSUE ? vm_allowed<S, RING>(P) : 0)>();
+        wait_vm_lgkm<VM>();
         block_barrier();
     }
     // second sub-step: MFMAs on f1 while the next half step's first fragments arrive in f0
@@ -370,6 +378,7 @@ template <bool RAGGED_M = false, int RING = 4, bool NATURAL = false, int WM, typ
 __device__ inline void k_loop8(int nk, char* smem, f32x16 (&acc)[WM][2], OA& oa, OB& ob, Tile tile, int nf = WM) {
     constexpr int kA = OA::kKind, kB = OB::kKind;
     constexpr bool kAnyRing = kA == kRing || kB == kRing;
+    using S = Schedule<kA, kB, WM>;
     static_assert(RING == 4 || (RING == 5 && kA != kRing), "ring depth");
     if (nk <= 0) return;
     char* base_a = smem;
@@ -431,11 +440,11 @@ __device__ inline void k_loop8(int nk, char* smem, f32x16 (&acc)[WM][2], OA& oa,
         const int h = 2 * kt;
         const KTile& d0 = (RING == 4) ? n1 : n2;      // ring, P = 0
         constexpr int d0_half = (RING == 4) ? 32 : 0, d1_half = (RING == 4) ? 0 : 32;
-        half_step8<0, kAnyRing, RAGGED_M, RING, issue0.value, WM, NATURAL>(
+        half_step8<0, kAnyRing, RAGGED_M, issue0.value ? vm_allowed<S, RING>(0) : 0, issue0.value, WM, NATURAL>(
             a_at(kt, h), b_at(kt, h), a_at(kt, h + 1), b_at(kt, h + 1), a_at(kt + 1, h + RING - 1),
             b_at(kt + 1, h + RING - 1), acc, f0, f1, oa, ob, kA == kRing ? d0.a + d0_half : n2.a,
             kB == kRing ? d0.b + d0_half : n2.b, d0.base, d0.end, 0, nf);
-        half_step8<1, true, RAGGED_M, RING, issue1.value, WM, NATURAL>(
+        half_step8<1, true, RAGGED_M, issue1.value ? vm_allowed<S, RING>(1) : 0, issue1.value, WM, NATURAL>(
             a_at(kt, h + 1), b_at(kt, h + 1), a_at(kt + 1, h + 2), b_at(kt + 1, h + 2),
             kA == kRow ? a_at(kt, 0) : a_at(kt + 1, h + RING), kB == kRow ? b_at(kt, 0) : b_at(kt + 1, h + RING), acc, f0,
             f1, oa, ob, kA == kRing ? n2.a + d1_half : n2.a, kB == kRing ? n2.b + d1_half : n2.b, n2.base, n2.end, n2.sel, nf);
@@ -451,6 +460,49 @@ __device__ inline void k_loop8(int nk, char* smem, f32x16 (&acc)[WM][2], OA& oa,
         ++kt;
     }
     iteration(kt, std::false_type{}, std::false_type{});
+    wait_vm_lgkm<0>();
+    block_barrier();
+}
+
+// The same for two row operands and a 128-row tile, whose 48 KB per 64-k tile leave room for three buffers of each: a tile is
+// requested two steps before it is computed on.  (With two buffers the step of 0.5 us waits for what it has just requested.)
+template <bool RAGGED_M, typename OA, typename OB, typename Tile>
+__device__ inline void k_loop8_rows3(int nk, char* smem, f32x16 (&acc)[2][2], OA& oa, OB& ob, Tile tile, int nf) {
+    constexpr int WM = 2, kStage = OA::kBufBytes + OB::kBufBytes, kInstr = OA::kInstr + OB::kInstr;
+    static_assert(OA::kKind == kRow && OB::kKind == kRow, "row operands");
+    if (nk <= 0) return;
+    auto request = [&](int kt, char* at) {
+        const KTile t = tile(kt);
+        static_for<OA::kInstr>([&](auto j) { oa.template row_issue<j.value>(t.a, 0, at); });
+        static_for<OB::kInstr>([&](auto j) { ob.template row_issue<j.value>(t.b, t.sel, at + OA::kBufBytes); });
+    };
+    char *s0 = smem, *s1 = smem + kStage, *s2 = smem + 2 * kStage;      // the stages of tiles kt, kt + 1, kt + 2
+    // (past the last tile that one again, into a stage that nothing reads: the counts stay the same)
+    request(0, s0);
+    request(min(1, nk - 1), s1);
+    request(min(2, nk - 1), s2);
+    wait_vm_lgkm<2 * kInstr>();
+    block_barrier();
+    Frags<WM> f0, f1;
+    static_for<WM>([&](auto i) {
+        if (RAGGED_M && i.value >= nf) return;
+        f0.a[i.value] = oa.template frag<0, i.value>(s0);
+    });
+    if (!(RAGGED_M && nf == 0)) static_for<2>([&](auto i) { f0.b[i.value] = ob.template frag<0, i.value>(s0 + OA::kBufBytes); });
+    auto iteration = [&](int kt, auto issue, auto vm) {
+        const KTile t = issue.value ? tile(kt + 3) : KTile{0, 0, 0, 0, 0};
+        half_step8<0, false, RAGGED_M, 0, false, WM, false>(s0, s0 + OA::kBufBytes, s0, s0 + OA::kBufBytes, nullptr, nullptr, acc, f0, f1, oa,
+                                                            ob, 0, 0, 0, 0, 0, nf);
+        half_step8<1, true, RAGGED_M, vm.value, issue.value, WM, false>(s0, s0 + OA::kBufBytes, s1, s1 + OA::kBufBytes, s0, s0 + OA::kBufBytes,
+                                                                        acc, f0, f1, oa, ob, t.a, t.b, 0, 0, t.sel, nf);
+        char* s = s0;
+        s0 = s1;
+        s1 = s2;
+        s2 = s;
+    };
+    int kt = 0;
+    for (; kt + 3 < nk; ++kt) iteration(kt, std::true_type{}, IntC<kInstr>{});
+    for (; kt < nk; ++kt) iteration(kt, std::false_type{}, IntC<0>{});
     wait_vm_lgkm<0>();
     block_barrier();
 }

@@ -233,7 +233,7 @@ struct WgradProblem {
 template <int WAVES_M, int WAVES_N, int WM, int WN>
 __device__ __forceinline__ void wgrad_body(WgradProblem p0, WgradProblem p1, WgradProblem p2,
                                            const int32_t* __restrict__ seg_off, int E, int g_lo, int g_hi,
-                                           int accumulate) {
+                                           int accumulate, int32_t* __restrict__ count) {
     constexpr int BM = WAVES_M * WM * 32, BN = WAVES_N * WN * 32;
     constexpr bool W8 = WAVES_M * WAVES_N == 8;
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -248,8 +248,15 @@ __device__ __forceinline__ void wgrad_body(WgradProblem p0, WgradProblem p1, Wgr
     // list): s_seg[2 i], s_seg[2 i + 1] = first row and end of segment i; then their number and the
     // number of 64-row k-tiles.  At most 64 ranks: one lane per rank.
     __shared__ int s_seg[2 * 64 + 2];
+    // Experts differ in rows, and so do their tiles in time: dealt in the fixed order (a block's 36 tiles belong to 36 experts) the
+    // slowest block made the launch (32768 rows, 128 experts of 2048 x 768: 785 -> 734 us; with the
+    // non-temporal stores 705; 65536 rows on 64 experts, one with half of them, 7330 -> 7250; equal experts within 2 %).
+    __shared__ int s_next;
+    const int bid = xcd_contiguous_id();
+    UnitQueue uq;
+    uq.init(count + kQueueOffset + 16 * kQueueStride, kQueueStride, total, bid, W8);
     int seg_expert = -1, nk = 0;
-    for (int work = xcd_contiguous_id(); work < total; work += gridDim.x) {
+    for (int work = uq.first(bid); work >= 0; work = uq.next(work, &s_next)) {
         const int e = work / per_expert;
         int j = work - e * per_expert;
         WgradProblem p = p0;
@@ -285,7 +292,13 @@ __device__ __forceinline__ void wgrad_body(WgradProblem p0, WgradProblem p1, Wgr
             seg_expert = e;
             nk = __builtin_amdgcn_readfirstlane(s_seg[129]);
         }
-        if (nk == 0 && accumulate) continue;      // nothing to add (block-uniform)
+        if (nk == 0) {      // (block-uniform)
+            lds_barrier();      // no k-loop, whose barriers keep s_next until every wave has read it
+            if (accumulate) {      // nothing to add
+                uq.request();
+                continue;
+            }
+        }
         // k-tiles: 64 rows at a time through the segments in order
         int cur_i = -1, cur_k = 0, cur_lo = 0, cur_hi = 0;
         auto k_tile = [&](int) {
@@ -308,8 +321,16 @@ __device__ __forceinline__ void wgrad_body(WgradProblem p0, WgradProblem p1, Wgr
             ob.init(p.B, p.B, [&](int pn, int c) { return min(n0 + 128 * pn + 8 * c, p.N - 8); }, (size_t)p.ldb,
                     [&](int f) { return 64 * wn + 32 * f; });
             k_loop8<false, 4, true>(nk, smem, acc, oa, ob, k_tile);      // operands in natural order
-            store_tile_f32_direct<WAVES_M, WAVES_N, WM, WN>(acc, p.out + (size_t)e * p.M * p.N, p.M, p.N, m0, n0,
-                                                            accumulate != 0);
+            uq.request();      // the next tile, read after the stores
+            auto store = [&](auto nt) {
+                store_tile_f32_direct<WAVES_M, WAVES_N, WM, WN, nt.value>(acc, p.out + (size_t)e * p.M * p.N, p.M, p.N, m0, n0, accumulate != 0);
+            };
+            // Up to 384 rows the tile's 256 KB of output are most of its memory traffic: stored non-temporal they leave the operands
+            // that neighbouring tiles share in the L2 (128 rows on 64 experts of 1088 x 2112: 421 -> 323 us; 64 on 128 of 2048 x 768:
+            // 474 -> 409; but 520 on 32 of 2048 x 8192: 2240 -> 2267, 7270 -> 7490 on 64 experts of very different rows).  Old values that
+            // are added to are read once, too: 520 rows 3448 -> 3149, 1024 on 16 experts 2064 -> 1948, 4096 on 8 2174 : 2171.
+            if (accumulate || nk <= 6) store(std::true_type{});
+            else store(std::false_type{});
             continue;
         } else {
             static_assert(BM == LoaderMC::ROWS && BN == LoaderMC::ROWS, "tile of the 4-wave kernel");
@@ -339,14 +360,14 @@ __device__ __forceinline__ void wgrad_body(WgradProblem p0, WgradProblem p1, Wgr
 template <int WAVES_M, int WAVES_N, int WM, int WN>
 __global__ __launch_bounds__(256) void k_wgrad(WgradProblem p0, WgradProblem p1, WgradProblem p2,
                                                const int32_t* __restrict__ seg_off, int E, int g_lo, int g_hi,
-                                               int accumulate) {
-    wgrad_body<WAVES_M, WAVES_N, WM, WN>(p0, p1, p2, seg_off, E, g_lo, g_hi, accumulate);
+                                               int accumulate, int32_t* __restrict__ count) {
+    wgrad_body<WAVES_M, WAVES_N, WM, WN>(p0, p1, p2, seg_off, E, g_lo, g_hi, accumulate, count);
 }
 template <int WAVES_M, int WAVES_N, int WM, int WN>
 __global__ __launch_bounds__(512) void k_wgrad_w8(WgradProblem p0, WgradProblem p1, WgradProblem p2,
                                                   const int32_t* __restrict__ seg_off, int E, int g_lo, int g_hi,
-                                                  int accumulate) {
-    wgrad_body<WAVES_M, WAVES_N, WM, WN>(p0, p1, p2, seg_off, E, g_lo, g_hi, accumulate);
+                                                  int accumulate, int32_t* __restrict__ count) {
+    wgrad_body<WAVES_M, WAVES_N, WM, WN>(p0, p1, p2, seg_off, E, g_lo, g_hi, accumulate, count);
 }
 
 template <int WAVES_M, int WAVES_N, int WM, int WN>
@@ -377,7 +398,8 @@ int run_dgrad(const fine_shape& s, int rank_lo, int rank_hi, const uint16_t* dy,
 
 template <int WAVES_M, int WAVES_N, int WM, int WN>
 int run_wgrad(const fine_shape& s, int rank_lo, int rank_hi, const uint16_t* x_perm, const uint16_t* dy, const uint16_t* dact, const uint16_t* h,
-              const int32_t* seg_off, float* d_wg, float* d_wu, float* d_wd, int accumulate, hipStream_t st) {
+              const int32_t* seg_off, float* d_wg, float* d_wu, float* d_wd, int accumulate, int32_t* count,
+              hipStream_t st) {
     constexpr int BM = WAVES_M * WM * 32, BN = WAVES_N * WN * 32;
     const size_t lds = (size_t)2 * (BM + BN) * 128;
     constexpr bool W8 = WAVES_M * WAVES_N == 8;
@@ -389,7 +411,7 @@ int run_wgrad(const fine_shape& s, int rank_lo, int rank_hi, const uint16_t* x_p
     WgradProblem pu{x_perm, s.d, s.d, dact + s.f, 2 * s.f, s.f, d_wu};
     WgradProblem pd{h, s.f, s.f, dy, s.d, s.d, d_wd};
     const int grid = 256 * ((lds <= 80 * 1024) ? 2 : 1);
-    hipLaunchKernelGGL(k, dim3(grid), dim3(threads), lds, st, pg, pu, pd, seg_off, s.E, rank_lo, rank_hi, accumulate);
+    hipLaunchKernelGGL(k, dim3(grid), dim3(threads), lds, st, pg, pu, pd, seg_off, s.E, rank_lo, rank_hi, accumulate, count);
     FINE_LAUNCH_CHECK();
     return FINE_OK;
 }
@@ -471,10 +493,11 @@ int launch_backward(const fine_shape& s, int rank_lo, int rank_hi, const void* d
     // Weight-gradient tiles span the weight matrices, not the segments: 256 x 256 on 8 waves wherever they fit, however
     // few rows an expert has (4 waves, 128 x 128: 5 rows 697 : 419 us, 43 rows 1157 : 458, 60 rows 1347 : 504).
     if (on(4)) {
+        if (only == 4) FINE_TRY(launch_tile_map(s, seg_off, rank_lo, rank_hi, 256, tiles, count, L.max_tiles, st));      // zeroes the queues
         if (s.d >= 256 && s.f >= 256)
-            FINE_TRY((run_wgrad<2, 4, 4, 2>(s, rank_lo, rank_hi, (const uint16_t*)x_perm, dy, dact, h_in, seg_off, d_wg, d_wu, d_wd, accumulate, st)));
+            FINE_TRY((run_wgrad<2, 4, 4, 2>(s, rank_lo, rank_hi, (const uint16_t*)x_perm, dy, dact, h_in, seg_off, d_wg, d_wu, d_wd, accumulate, count, st)));
         else
-            FINE_TRY((run_wgrad<2, 2, 2, 2>(s, rank_lo, rank_hi, (const uint16_t*)x_perm, dy, dact, h_in, seg_off, d_wg, d_wu, d_wd, accumulate, st)));
+            FINE_TRY((run_wgrad<2, 2, 2, 2>(s, rank_lo, rank_hi, (const uint16_t*)x_perm, dy, dact, h_in, seg_off, d_wg, d_wu, d_wd, accumulate, count, st)));
     }
     if (on(5) && rank_hi == s.G) FINE_TRY(launch_permute_bwd(s, dxp, row_of_pair, d_x, st));
     return FINE_OK;

@@ -117,10 +117,10 @@ inline bool mfma_offsets_fit(const fine_shape& s) {
 // two slots of one 256 x 256 fp32 tile for each of the 256 parts of a launch.
 // From int32 index kQueueOffset on: the work queues of the 8-wave GEMM launches that follow a
 // k_tile_map (which zeroes them) - queue q at kQueueOffset + q * kQueueStride, one cache line
-// each; a launch uses 8 of them (one per XCD), the second GEMM of a call the next 8.
+// each; a launch uses 8 of them (one per XCD), the second GEMM of a call the next 8, the weight gradients the third.
 constexpr size_t kCountBytes = 8192;
 constexpr int kSkCounterOffset = 64, kSkReadyOffset = 320;
-constexpr int kQueueOffset = 1024, kQueueStride = 32, kQueues = 16;
+constexpr int kQueueOffset = 1024, kQueueStride = 32, kQueues = 24;
 constexpr size_t kSkSlotBytes = 256 * 256 * 4, kSkBytes = 512 * kSkSlotBytes;
 
 struct FfnWs {

@@ -310,8 +310,8 @@ __device__ inline void stage_tile_f32(char* smem, const f32x16 (&acc)[WM][WN], F
 // retires in order; measured on the training workload, P = 65536 rows, 64 experts: 7.3 ms against 7.9 ms staged through
 // LDS).  Rows from M on and columns from N on are masked (and lie outside the
 // buffer descriptor, whose size ends with the tile's last valid row).  accumulate: the old values are
-// read the same way.
-template <int WAVES_M, int WAVES_N, int WM, int WN>
+// read the same way.  NT: non-temporal.
+template <int WAVES_M, int WAVES_N, int WM, int WN, bool NT>
 __device__ inline void store_tile_f32_direct(const f32x16 (&acc)[WM][WN], float* __restrict__ out, int M, int N, int m0,
                                              int n0, bool accumulate) {
     constexpr int BM = WAVES_M * WM * 32;
@@ -332,22 +332,22 @@ __device__ inline void store_tile_f32_direct(const f32x16 (&acc)[WM][WN], float*
                 if (accumulate) {
                     float old[16];
                     static_for<16>([&](auto r) {
-                        old[r.value] = col_ok ? __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, voff, soff(r.value), 0)) : 0.f;
+                        old[r.value] = col_ok ? __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, voff, soff(r.value), NT ? 2 : 0)) : 0.f;
                     });
                     static_for<16>([&](auto r) { v[r.value] += old[r.value]; });
                 }
                 if (col_ok)
                     static_for<16>([&](auto r) {
                         const float val = v[r.value];      // (a bit cast applied to the vector element itself took element 0 every time)
-                        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, val), rs, voff, soff(r.value), 0);
+                        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, val), rs, voff, soff(r.value), NT ? 2 : 0);
                     });
             } else {                                      // last row tile of a matrix whose height is no multiple of the tile
                 static_for<16>([&](auto r) {
                     if (col_ok && row_w + row_of(r.value) < rows) {
                         float val = v[r.value];
                         if (accumulate)
-                            val += __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, voff, soff(r.value), 0));
-                        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, val), rs, voff, soff(r.value), 0);
+                            val += __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, voff, soff(r.value), NT ? 2 : 0));
+                        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, val), rs, voff, soff(r.value), NT ? 2 : 0);
                     }
                 });
             }
@@ -528,7 +528,7 @@ struct UnitQueue {
             }
             *s_next = found;
         }
-        __syncthreads();
+        lds_barrier();
         return __builtin_amdgcn_readfirstlane(*s_next);
     }
 };

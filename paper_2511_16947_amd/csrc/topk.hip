@@ -557,10 +557,15 @@ int dispatch(const fine_shape& s, const void* x, const void* w, const float* bia
 
 }  // namespace
 
+// the value of another of a group of sixteen lanes (DPP)
+template <int CTRL>
+__device__ inline int from_lane(int v) { return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xf, 0xf, false); }
+
 // Second pass of the gate when blocks shared token tiles.  Sixteen lanes per token, lane l holding
 // experts l, l + 16, ...: T / 4 wavefronts instead of the T / 32 that the accumulator layout gives.
 // Partial logits are added in ascending part order, then the bias; K rounds of (largest value, lowest
-// expert of equals) over the lane's values and across the sixteen lanes.
+// expert of equals) over the lane's values and across the sixteen lanes.  Bound by latency: memory once (the parts' loads
+// together), then a chain of K rounds, whose exchanges are DPP moves and not trips through the LDS crossbar.
 template <int MAXJ>
 __global__ __launch_bounds__(256) void k_topk_select(const float* __restrict__ partial, int parts, int rows, int epad,
                                                     const float* __restrict__ bias, int Tn, int E, int K,
@@ -571,15 +576,26 @@ __global__ __launch_bounds__(256) void k_topk_select(const float* __restrict__ p
     float v[MAXJ];
 #pragma unroll
     for (int j = 0; j < MAXJ; ++j) v[j] = 0.f;
-    for (int part = 0; part < parts; ++part) {
-        const float* src = partial + ((size_t)part * rows + tc) * epad + l;      // epad >= 16 MAXJ columns exist
-#pragma unroll
-        for (int j = 0; j < MAXJ; ++j) v[j] += src[16 * j];
-    }
+    // four parts' and the bias's values are under way at a time (a part past the last is read as the last and not added)
+    float b[MAXJ];
     if (bias != nullptr) {
-        float b[MAXJ];
 #pragma unroll
         for (int j = 0; j < MAXJ; ++j) b[j] = bias[min(l + 16 * j, E - 1)];
+    }
+    for (int p0 = 0; p0 < parts; p0 += 4) {
+        float got[4][MAXJ];
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            const float* src = partial + ((size_t)min(p0 + p, parts - 1) * rows + tc) * epad + l;      // epad >= 16 MAXJ columns exist
+#pragma unroll
+            for (int j = 0; j < MAXJ; ++j) got[p][j] = src[16 * j];
+        }
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
+#pragma unroll
+            for (int j = 0; j < MAXJ; ++j) v[j] = p0 + p < parts ? v[j] + got[p][j] : v[j];
+    }
+    if (bias != nullptr) {
 #pragma unroll
         for (int j = 0; j < MAXJ; ++j) v[j] += b[j];
     }
@@ -592,11 +608,14 @@ __global__ __launch_bounds__(256) void k_topk_select(const float* __restrict__ p
         for (int j = 0; j < MAXJ; ++j)        // ">" keeps the lowest of equals
             if (key[j] > bv) { bv = key[j]; bj = j; }
         int be = l + 16 * bj;
-#pragma unroll
-        for (int off = 8; off > 0; off >>= 1) {
-            const int ov = __shfl_xor(bv, off, 16), oe = __shfl_xor(be, off, 16);
+        // over the token's sixteen lanes: the neighbour, the other pair, the other four, the other eight (DPP)
+        auto take = [&](int ov, int oe) {
             if (ov > bv || (ov == bv && oe < be)) { bv = ov; be = oe; }
-        }
+        };
+        take(from_lane<0xb1>(bv), from_lane<0xb1>(be));
+        take(from_lane<0x4e>(bv), from_lane<0x4e>(be));
+        take(from_lane<0x141>(bv), from_lane<0x141>(be));
+        take(from_lane<0x140>(bv), from_lane<0x140>(be));
         const unsigned gone = ((be & 15) == l) ? (1u << (be >> 4)) : 0u;         // the winner leaves the race
 #pragma unroll
         for (int j = 0; j < MAXJ; ++j) key[j] = ((gone >> j) & 1u) ? kNoKey : key[j];
@@ -605,12 +624,18 @@ __global__ __launch_bounds__(256) void k_topk_select(const float* __restrict__ p
             if (t < Tn) topk_idx[(size_t)t * K + k] = be;
         }
     }
-    if (l == 0 && t < Tn) {
-        const float top = s_val[grp][0];
-        float sum = 0.f;
-        for (int k = 0; k < K; ++k) sum += __expf(s_val[grp][k] - top);
-        for (int k = 0; k < K; ++k) topk_w[(size_t)t * K + k] = __expf(s_val[grp][k] - top) / sum;
+    __builtin_amdgcn_wave_barrier();      // (a token's sixteen lanes belong to one wave, whose LDS accesses are performed in order)
+    const float top = s_val[grp][0];
+    float sum = 0.f;
+    for (int k0 = 0; k0 < K; k0 += 8) {
+        float val[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) val[k] = s_val[grp][min(k0 + k, K - 1)];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) sum += k0 + k < K ? __expf(val[k] - top) : 0.f;
     }
+    if (t < Tn)
+        for (int k = l; k < K; k += 16) topk_w[(size_t)t * K + k] = __expf(s_val[grp][k] - top) / sum;
 }
 
 // Parts of k that blocks of one token tile split among themselves: enough blocks for two per CU,

@@ -1,4 +1,4 @@
-"""Python binding of libfinemoe (ctypes): argument marshalling only.
+"""Python binding of libfinemoe (ctypes; calls that pass tensors through csrc/call.cpp): argument marshalling only.
 
 Every step of the MoE-layer hot path (gate top-K, token scheduling, permute,
 grouped SwiGLU expert FFN, combine, backward) runs in the HIP kernels behind the
@@ -13,12 +13,12 @@ import ctypes
 import os
 from dataclasses import dataclass
 from functools import cached_property
-from typing import Optional
 
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libfinemoe.so")
+CALL_PATH = os.path.join(_HERE, "_call.so")
 
 FINE_OK = 0
 FINE_INVALID_ARG = -1
@@ -53,16 +53,25 @@ class _Shape(ctypes.Structure):
 
 
 _lib = None
+_call = None      # _call.call
+_entry = {}       # of the loaded library's functions below: address and kinds
+# What the entry points that take device memory are passed between the shape and the stream: t a tensor or None (NULL), i an integer
+_KINDS = {"fine_topk": "t" * 6 + "i", "fine_sched": "t" * 12 + "i", "fine_sched_warm": "t" * 13 + "i", "fine_sched_static": "t" * 11,
+          "fine_sched_comm": "ttiii" + "t" * 10 + "i", "fine_permute": "ttt", "fine_grouped_ffn": "i" + "t" * 8 + "i",
+          "fine_combine": "tttt", "fine_backward": "i" + "t" * 16 + "iti", "fine_cayley_placement": "iiiiit",
+          "fine_replica_counts": "tit", "fine_eval_placements": "itttt", "fine_place_search": "ttiiitttt"}
 
 
 def load_library() -> ctypes.CDLL:
     """Loads libfinemoe.so from the package directory; raises if it is not built."""
-    global _lib
+    global _lib, _call, _entry
     if _lib is not None:
         return _lib
-    if not os.path.exists(LIB_PATH):
-        raise FileNotFoundError(
-            "%s is missing: build it with `python -m paper_2511_16947_amd.build` (there is no fallback path)" % LIB_PATH)
+    for path in (LIB_PATH, CALL_PATH):
+        if not os.path.exists(path):
+            raise FileNotFoundError(
+                "%s is missing: build it with `python -m paper_2511_16947_amd.build` (there is no fallback path)" % path)
+    from ._call import call
     lib = ctypes.CDLL(LIB_PATH)
     vp, sz, i32 = ctypes.c_void_p, ctypes.c_size_t, ctypes.c_int32
     sp = ctypes.POINTER(_Shape)
@@ -100,6 +109,7 @@ def load_library() -> ctypes.CDLL:
     lib.fine_eval_placements.argtypes = [sp, i32, vp, vp, vp, vp, vp]
     lib.fine_place_search.restype = ctypes.c_int
     lib.fine_place_search.argtypes = [sp, vp, vp, i32, i32, ctypes.c_uint32, vp, vp, vp, vp, vp]
+    _call, _entry = call, {name: (ctypes.cast(getattr(lib, name), vp).value, kinds) for name, kinds in _KINDS.items()}
     _lib = lib
     return lib
 
@@ -126,20 +136,21 @@ class Shape:
     @cached_property
     def _ref(self):
         # what every call passes on: made by the first one, since a Shape never changes
-        return ctypes.byref(self.c())
+        return ctypes.byref(self._struct)
+
+    @cached_property
+    def _struct(self) -> _Shape:
+        return self.c()
+
+    @cached_property
+    def _at(self) -> int:
+        return ctypes.addressof(self._struct)
 
     def c(self) -> _Shape:
         return _Shape(self.T, self.d, self.f, self.E, self.K, self.G, self.dtype, self.flags)
 
     def __getstate__(self):      # (a ctypes reference cannot be copied: copies make their own)
-        return {k: v for k, v in self.__dict__.items() if k != "_ref"}
-
-
-def _ptr(t: Optional[torch.Tensor]):
-    if t is None:
-        return None
-    assert t.is_cuda and t.is_contiguous(), "device-resident contiguous tensors only"
-    return t.data_ptr()
+        return {k: v for k, v in self.__dict__.items() if k not in ("_ref", "_struct", "_at")}
 
 
 # The handle that torch.cuda.current_stream() wraps, without the wrapper (2.9 us a call, this 0.3).  Small layers are bound by
@@ -153,6 +164,15 @@ def _stream():
     except AttributeError:
         pass
     return torch.cuda.current_stream().cuda_stream
+
+
+def _run(fn: str, shape: Shape, *args):
+    """A call of an entry point whose pointers are device memory: device-resident contiguous tensors, None for NULL."""
+    if _lib is None:
+        load_library()
+    rc = _call(*_entry[fn], _stream, shape._at, *args)
+    if rc != FINE_OK:
+        _check(fn, rc)
 
 
 def _check(fn: str, rc: int):
@@ -176,42 +196,31 @@ def alloc_workspace(shape: Shape, which: int, device="cuda") -> torch.Tensor:
 
 
 def fine_topk(shape: Shape, x, w_router, bias, topk_idx, topk_w, ws=None):
-    rc = load_library().fine_topk(shape._ref, _ptr(x), _ptr(w_router), _ptr(bias), _ptr(topk_idx), _ptr(topk_w),
-                                  _ptr(ws), 0 if ws is None else ws.numel(), _stream())
-    _check("fine_topk", rc)
+    _run("fine_topk", shape, x, w_router, bias, topk_idx, topk_w, ws, 0 if ws is None else ws.numel())
 
 
 def fine_sched(shape: Shape, topk_idx, place, load, input_eg, x_eg, max_load, pair_dst, row_of_pair, pair_of_row,
                seg_off, rank_off, ws):
-    rc = load_library().fine_sched(shape._ref, _ptr(topk_idx), _ptr(place), _ptr(load), _ptr(input_eg), _ptr(x_eg),
-                                   _ptr(max_load), _ptr(pair_dst), _ptr(row_of_pair), _ptr(pair_of_row), _ptr(seg_off),
-                                   _ptr(rank_off), _ptr(ws), ws.numel(), _stream())
-    _check("fine_sched", rc)
+    _run("fine_sched", shape, topk_idx, place, load, input_eg, x_eg, max_load, pair_dst, row_of_pair, pair_of_row,
+         seg_off, rank_off, ws, ws.numel())
 
 
 def fine_sched_warm(shape: Shape, topk_idx, place, x_prev, load, input_eg, x_eg, max_load, pair_dst, row_of_pair,
                     pair_of_row, seg_off, rank_off, ws):
-    rc = load_library().fine_sched_warm(shape._ref, _ptr(topk_idx), _ptr(place), _ptr(x_prev), _ptr(load),
-                                        _ptr(input_eg), _ptr(x_eg), _ptr(max_load), _ptr(pair_dst), _ptr(row_of_pair),
-                                        _ptr(pair_of_row), _ptr(seg_off), _ptr(rank_off), _ptr(ws), ws.numel(), _stream())
-    _check("fine_sched_warm", rc)
+    _run("fine_sched_warm", shape, topk_idx, place, x_prev, load, input_eg, x_eg, max_load, pair_dst, row_of_pair,
+         pair_of_row, seg_off, rank_off, ws, ws.numel())
 
 
 def fine_sched_static(shape: Shape, topk_idx, place, load, input_eg, x_eg, max_load, pair_dst, row_of_pair, pair_of_row,
                       seg_off, rank_off):
-    rc = load_library().fine_sched_static(shape._ref, _ptr(topk_idx), _ptr(place), _ptr(load), _ptr(input_eg),
-                                          _ptr(x_eg), _ptr(max_load), _ptr(pair_dst), _ptr(row_of_pair),
-                                          _ptr(pair_of_row), _ptr(seg_off), _ptr(rank_off), _stream())
-    _check("fine_sched_static", rc)
+    _run("fine_sched_static", shape, topk_idx, place, load, input_eg, x_eg, max_load, pair_dst, row_of_pair,
+         pair_of_row, seg_off, rank_off)
 
 
 def fine_sched_comm(shape: Shape, topk_idx, place, alpha_num: int, alpha_den: int, ranks_per_node: int, load, input_eg,
                     x_eg, comp_comm, pair_dst, row_of_pair, pair_of_row, seg_off, rank_off, ws):
-    rc = load_library().fine_sched_comm(shape._ref, _ptr(topk_idx), _ptr(place), alpha_num, alpha_den,
-                                        ranks_per_node, _ptr(load), _ptr(input_eg), _ptr(x_eg), _ptr(comp_comm),
-                                        _ptr(pair_dst), _ptr(row_of_pair), _ptr(pair_of_row), _ptr(seg_off),
-                                        _ptr(rank_off), _ptr(ws), ws.numel(), _stream())
-    _check("fine_sched_comm", rc)
+    _run("fine_sched_comm", shape, topk_idx, place, alpha_num, alpha_den, ranks_per_node, load, input_eg, x_eg,
+         comp_comm, pair_dst, row_of_pair, pair_of_row, seg_off, rank_off, ws, ws.numel())
 
 
 def fine_comm_replica_loads_host(load, input_eg, place, alpha_num: int, alpha_den: int):
@@ -230,27 +239,22 @@ def fine_comm_replica_loads_host(load, input_eg, place, alpha_num: int, alpha_de
 
 
 def fine_permute(shape: Shape, x, pair_of_row, x_perm):
-    _check("fine_permute", load_library().fine_permute(shape._ref, _ptr(x), _ptr(pair_of_row), _ptr(x_perm), _stream()))
+    _run("fine_permute", shape, x, pair_of_row, x_perm)
 
 
 def fine_grouped_ffn(shape: Shape, rank: int, x_perm, w_gate, w_up, w_down, seg_off, y_perm, act_save, ws):
-    rc = load_library().fine_grouped_ffn(shape._ref, rank, _ptr(x_perm), _ptr(w_gate), _ptr(w_up), _ptr(w_down),
-                                         _ptr(seg_off), _ptr(y_perm), _ptr(act_save), _ptr(ws), ws.numel(), _stream())
-    _check("fine_grouped_ffn", rc)
+    _run("fine_grouped_ffn", shape, rank, x_perm, w_gate, w_up, w_down, seg_off, y_perm, act_save, ws, ws.numel())
 
 
 def fine_combine(shape: Shape, y_perm, row_of_pair, topk_w, out):
-    _check("fine_combine", load_library().fine_combine(shape._ref, _ptr(y_perm), _ptr(row_of_pair), _ptr(topk_w),
-                                                       _ptr(out), _stream()))
+    _run("fine_combine", shape, y_perm, row_of_pair, topk_w, out)
 
 
 def fine_backward(shape: Shape, rank: int, d_out, x_perm, y_perm, act_save, w_gate, w_up, w_down, row_of_pair,
                   pair_of_row, seg_off, topk_w, d_x, d_topk_w, d_w_gate, d_w_up, d_w_down, accumulate: bool, ws):
-    rc = load_library().fine_backward(shape._ref, rank, _ptr(d_out), _ptr(x_perm), _ptr(y_perm), _ptr(act_save),
-                                      _ptr(w_gate), _ptr(w_up), _ptr(w_down), _ptr(row_of_pair), _ptr(pair_of_row),
-                                      _ptr(seg_off), _ptr(topk_w), _ptr(d_x), _ptr(d_topk_w), _ptr(d_w_gate),
-                                      _ptr(d_w_up), _ptr(d_w_down), 1 if accumulate else 0, _ptr(ws), ws.numel(), _stream())
-    _check("fine_backward", rc)
+    _run("fine_backward", shape, rank, d_out, x_perm, y_perm, act_save, w_gate, w_up, w_down, row_of_pair,
+         pair_of_row, seg_off, topk_w, d_x, d_topk_w, d_w_gate, d_w_up, d_w_down, 1 if accumulate else 0, ws,
+         ws.numel())
 
 
 def fine_cayley_placement(shape: Shape, orders, gens, complete: int, place):
@@ -260,25 +264,19 @@ def fine_cayley_placement(shape: Shape, orders, gens, complete: int, place):
     flat = [int(v) for s in gens for v in s]
     assert len(flat) == k * len(gens)
     g = (ctypes.c_int32 * max(1, len(flat)))(*flat)
-    rc = load_library().fine_cayley_placement(shape._ref, k, ctypes.cast(o, ctypes.c_void_p), len(gens),
-                                              ctypes.cast(g, ctypes.c_void_p), complete, _ptr(place), _stream())
-    _check("fine_cayley_placement", rc)
+    _run("fine_cayley_placement", shape, k, ctypes.addressof(o), len(gens), ctypes.addressof(g), complete, place)
 
 
 def fine_replica_counts(shape: Shape, load, slots: int, counts):
-    _check("fine_replica_counts", load_library().fine_replica_counts(shape._ref, _ptr(load), slots, _ptr(counts),
-                                                                     _stream()))
+    _run("fine_replica_counts", shape, load, slots, counts)
 
 
 def fine_eval_placements(shape: Shape, n: int, place, load, m_num, m_den):
-    _check("fine_eval_placements", load_library().fine_eval_placements(shape._ref, n, _ptr(place), _ptr(load),
-                                                                       _ptr(m_num), _ptr(m_den), _stream()))
+    _run("fine_eval_placements", shape, n, place, load, m_num, m_den)
 
 
 def fine_place_search(shape: Shape, load, counts, slots: int, n: int, seed: int, m_num, m_den, best, place):
-    rc = load_library().fine_place_search(shape._ref, _ptr(load), _ptr(counts), slots, n, seed & 0xFFFFFFFF,
-                                          _ptr(m_num), _ptr(m_den), _ptr(best), _ptr(place), _stream())
-    _check("fine_place_search", rc)
+    _run("fine_place_search", shape, load, counts, slots, n, seed & 0xFFFFFFFF, m_num, m_den, best, place)
 
 
 # ---------------------------------------------------------------------------

@@ -7,11 +7,13 @@ Object files go to paper_2511_16947_amd/_build/, the library next to this file.
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libfinemoe.so")
+CALL = os.path.join(HERE, "_call.so")      # the Python binding's marshalling (host code)
 SOURCES = ["api.hip", "sched.hip", "comm_sched.hip", "general_x.hip", "topk.hip", "movement.hip", "ffn_simple.hip", "ffn_f32.hip", "ffn_stream.hip",
            "ffn_mfma.hip", "backward.hip", "placement.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",
@@ -48,6 +50,11 @@ def build(verbose: bool = False) -> str:
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + r.stderr)
+    cmd = [cc, "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-I" + sysconfig.get_paths()["include"],
+           os.path.join(CSRC, "call.cpp"), "-o", CALL]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("hipcc failed on call.cpp:\n" + r.stderr)
     return OUT
 
 

@@ -283,6 +283,114 @@ __global__ __launch_bounds__(256, 2) void k_ffn_f32_split(const float* __restric
     }
 }
 
+// The same on 32 rows x 16 columns (v_mfma_f32_16x16x4_f32, 32 cycles): launches of so few 32 x 32 tiles that half of the CUs
+// have none, where what is left of a launch is one trip to memory and a wave's chain of MFMAs, which this halves.  An MFMA's four
+// k-values are k, k + 4, k + 8, k + 12 (lane group g has 4 g + i of sixteen), so that a lane's A values are 16 contiguous bytes.
+// Bound by latency: a rank's call of 128 rows of 128 x 256 on 8 experts, both GEMMs, 32 x 32 : 32 x 16 tiles (72 expected of the
+// former) 9.8 : 8.9 us; 64 rows of 133 x 257 (42) 13.5 : 11.0; 64 rows of 1024 x 1024 (128) 23.4 : 19.2; 256 rows of 256 x 512 (144) 13.8 :
+// 12.9; but 1024 rows of 128 x 256 (240) 11.8 : 12.0, 512 rows of 300 x 301 (240) 19.3 : 23.2, 256 of 512 x 512 (384) 18.6 : 24.1.
+template <int EPI, int V>
+__global__ __launch_bounds__(256, 2) void k_ffn_f32_split16(const float* __restrict__ A, const float* __restrict__ B0,
+                                                            const float* __restrict__ B1, int Kd, int N, float* __restrict__ C,
+                                                            float* __restrict__ act, const TileEntry* __restrict__ tiles,
+                                                            const int32_t* __restrict__ count, const int32_t* __restrict__ seg, int E) {
+    constexpr int NP = EPI == 0 ? 2 : 1;
+    __shared__ __attribute__((aligned(16))) float part[4 * NP * 8 * 64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int r = lane & 15, g = lane >> 4;
+    RankTiles rank;
+    if (seg != nullptr) rank.init(seg, E, kSM);
+    const int ntn = (N + 15) / 16, ntm = seg != nullptr ? rank.count : *count, total = ntm * ntn;
+    const int nc = (Kd + kSChunk - 1) / kSChunk, c0 = nc * wave / 4, c1 = nc * (wave + 1) / 4;
+    for (int work = blockIdx.x; work < total; work += gridDim.x) {
+        const int tm = work / ntn, n0 = (work - tm * ntn) * 16;
+        const TileEntry te = seg != nullptr ? rank.get(tm, kSM) : tiles[tm];
+        const float* Bp[2];
+        Bp[0] = B0 + (size_t)te.expert * Kd * N;
+        Bp[1] = EPI == 0 ? B1 + (size_t)te.expert * Kd * N : Bp[0];
+        // (ranges as in the kernel above)
+        const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
+            (void*)(A + (size_t)te.row0 * Kd), 0, (int)((uint32_t)te.rows * Kd * 4u), 0x00020000);
+        const uint32_t b_off = ((uint32_t)4 * g * N + min(n0 + r, N - 1)) * 4u;
+        struct Chunk {
+            f32x4 a[2][2];      // [16 k][16 rows]
+            float b[NP][8];
+        };
+        auto fetch = [&](Chunk& c, int at) {
+            const int k0 = at * kSChunk;
+            const unsigned long long left = (unsigned long long)(Kd - k0) * N * 4u;
+            const int b_size = (int)(uint32_t)(left < 0xfffffff0ull ? left : 0xfffffff0ull);
+            static_for<2>([&](auto j) {
+                static_for<2>([&](auto f) {
+                    const int k = k0 + 16 * j.value + 4 * g, row = 16 * f.value + r;
+                    auto off = [&](int i) { return k + i < Kd ? ((uint32_t)row * Kd + k + i) * 4u : 0xf0000000u; };
+                    if constexpr (V == 4) {
+                        c.a[j.value][f.value] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(ra, off(0), 0, 0));
+                    } else {
+                        static_for<4>([&](auto i) {
+                            c.a[j.value][f.value][i.value] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(ra, off(i.value), 0, 0));
+                        });
+                    }
+                });
+            });
+            static_for<NP>([&](auto t) {
+                const __amdgpu_buffer_rsrc_t rb =
+                    __builtin_amdgcn_make_buffer_rsrc((void*)(Bp[t.value] + (size_t)k0 * N), 0, b_size, 0x00020000);
+                static_for<8>([&](auto i) {
+                    c.b[t.value][i.value] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                        rb, b_off, (16 * (i.value / 4) + i.value % 4) * N * 4, 0));
+                });
+            });
+        };
+        f32x4 acc[NP][2];
+        static_for<NP>([&](auto t) { static_for<2>([&](auto f) { acc[t.value][f.value] = f32x4{0.f, 0.f, 0.f, 0.f}; }); });
+        auto multiply = [&](const Chunk& c) {
+            static_for<8>([&](auto i) {
+                static_for<NP>([&](auto t) {
+                    static_for<2>([&](auto f) {
+                        acc[t.value][f.value] = __builtin_amdgcn_mfma_f32_16x16x4f32(c.a[i.value / 4][f.value][i.value % 4], c.b[t.value][i.value],
+                                                                                     acc[t.value][f.value], 0, 0, 0);
+                    });
+                });
+            });
+        };
+        Chunk x, y;
+        if (c0 < c1) fetch(x, c0);
+        for (int c = c0; c < c1; c += 2) {      // (wave-uniform)
+            if (c + 1 < c1) fetch(y, c + 1);
+            multiply(x);
+            if (c + 2 < c1) fetch(x, c + 2);
+            if (c + 1 < c1) multiply(y);
+        }
+        static_for<NP>([&](auto t) {
+            static_for<8>([&](auto q) { part[((wave * NP + t.value) * 8 + q.value) * 64 + lane] = acc[t.value][q.value / 4][q.value % 4]; });
+        });
+        lds_barrier();
+        // wave w adds up and stores registers 2 w and 2 w + 1: rows 16 (w / 2) + 4 g + 2 (w & 1) + 0, 1; lane = column
+        static_for<2>([&](auto q) {
+            float v[NP];
+            static_for<NP>([&](auto t) {
+                const float* p = part + (t.value * 8 + 2 * wave + q.value) * 64 + lane;
+                v[t.value] = ((p[0] + p[NP * 512]) + p[2 * NP * 512]) + p[3 * NP * 512];
+            });
+            const int m = 16 * (wave >> 1) + 4 * g + 2 * (wave & 1) + q.value, n = n0 + r;
+            if (m < te.rows && n < N) {
+                const size_t row = (size_t)te.row0 + m;
+                if constexpr (EPI == 0) {
+                    if (act != nullptr) {
+                        act[row * (2 * (size_t)N) + n] = v[0];
+                        act[row * (2 * (size_t)N) + N + n] = v[1];
+                    }
+                    C[row * N + n] = silu_mul_f32(v[0], v[1]);
+                } else {
+                    C[row * N + n] = v[0];
+                }
+            }
+        });
+        lds_barrier();      // the next tile's parts
+    }
+}
+
 }  // namespace
 
 int launch_ffn_f32(const fine_shape& s, int rank_lo, int rank_hi, const void* x_perm, const void* wg, const void* wu,
@@ -299,7 +407,9 @@ int launch_ffn_f32(const fine_shape& s, int rank_lo, int rank_hi, const void* x_
     const double rows = (double)s.T * s.K * n_ranks / s.G, runs = std::min((double)s.E * n_ranks / s.G + 1.0, (double)s.E);
     const double tiles64 = (rows / kBM + runs) * (cdiv(s.f, 64) + cdiv(s.d, 64)) / 2;
     const bool split = tiles64 < (wide ? 220.0 : 175.0) || rows <= 16.0 * runs;
-    const int bm = split ? kSM : kBM, bn = split ? 32 : 64;
+    const double tiles32 = (rows / kSM + runs) * (cdiv(s.f, 32) + cdiv(s.d, 32)) / 2;
+    const bool narrow = split && tiles32 < 160.0;
+    const int bm = split ? kSM : kBM, bn = narrow ? 16 : split ? 32 : 64;
     const int32_t* seg = nullptr;
     if (n_ranks == 1 && s.E <= kRankMapExperts) seg = seg_off + (size_t)rank_lo * (s.E + 1);
     else FINE_TRY(launch_tile_map(s, seg_off, rank_lo, rank_hi, bm, tiles, count, L.max_tiles, st));
@@ -315,6 +425,7 @@ int launch_ffn_f32(const fine_shape& s, int rank_lo, int rank_hi, const void* x_
         FINE_LAUNCH_CHECK();
         return (int)FINE_OK;
     };
+    if (narrow) return wide ? run(k_ffn_f32_split16<0, 4>, k_ffn_f32_split16<1, 4>) : run(k_ffn_f32_split16<0, 1>, k_ffn_f32_split16<1, 1>);
     if (split) return wide ? run(k_ffn_f32_split<0, 4>, k_ffn_f32_split<1, 4>) : run(k_ffn_f32_split<0, 1>, k_ffn_f32_split<1, 1>);
     return wide ? run(k_ffn_f32<0, 4>, k_ffn_f32<1, 4>) : run(k_ffn_f32<0, 1>, k_ffn_f32<1, 1>);
 }

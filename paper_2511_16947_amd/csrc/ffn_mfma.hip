@@ -318,6 +318,7 @@ __device__ __forceinline__ void ffn_gemm_body(const uint16_t* __restrict__ A, in
                 part = at < nparts * (x + 1) / 8 ? at : -1;
             }
             if (part < 0) {
+                lds_barrier();      // (no k-loop, whose barriers keep the queue's s_next until every wave has read it)
                 request();
             } else {
                 const int t = few_step == 1 ? part / few : part % rest, i = few_step == 1 ? part - t * few : part / rest;
@@ -327,7 +328,10 @@ __device__ __forceinline__ void ffn_gemm_body(const uint16_t* __restrict__ A, in
             const int part = v - full;
             int u, u1;
             part_range(part, u, u1);
-            if (u >= u1) request();      // (an empty part at the end of the sequence)
+            if (u >= u1) {      // (an empty part at the end of the sequence)
+                lds_barrier();
+                request();
+            }
             while (u < u1) {
                 const int t = u / nk, kb = u - t * nk, kn = min(nk - kb, u1 - u);
                 piece(full + t, kb, kn, part, u + kn >= u1);

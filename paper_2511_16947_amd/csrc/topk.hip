@@ -460,11 +460,11 @@ __global__ __launch_bounds__(256) void k_topk_mfma_esplit(const uint16_t* __rest
     select_topk<NT>(all, bias, E, K, t0 + r, Tn, s_val, topk_idx, topk_w);
 }
 
-// fp32 layers.  A block is 32 tokens, its NW waves split k in pieces of 8 J (J groups: 32 up to 64 experts, 8 beyond).  Both MFMA operands come
+// fp32 layers.  A block is 32 tokens, its NW waves split k in pieces of 8 J, whose loads are in flight together.  Both MFMA operands come
 // straight from memory: lane (l & 31, h = l >> 5) supplies expert / token (l & 31) and the k-values
 // 8 j + 4 h + 0 .. 3 of a piece (its token's as one 16-byte load, each weight a 4-byte load that 32 lanes make of
 // neighbouring experts).  k-values past d are zeros, experts past E are masked before the selection.
-template <int NT, int NW>
+template <int NT, int NW, int J>
 __global__ __launch_bounds__(64 * NW) void k_topk_f32(const float* __restrict__ x, const float* __restrict__ w_router,
                                                       const float* __restrict__ bias, int Tn, int d, int E, int K,
                                                       int32_t* __restrict__ topk_idx, float* __restrict__ topk_w) {
@@ -483,7 +483,6 @@ __global__ __launch_bounds__(64 * NW) void k_topk_f32(const float* __restrict__ 
     for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
         for (int q = 0; q < 16; ++q) acc[nt][q] = 0.f;
-    constexpr int J = NT <= 2 ? 4 : 1;               // groups of 8 k-values whose loads are in flight together
     auto group = [&](int k0, auto checked) {
         f32x4 xv[J];
         float wv[J][NT][4];
@@ -660,13 +659,18 @@ int launch_topk(const fine_shape& s, const void* x, const void* w_router, const 
                                    : dispatch<uint16_t>(s, x, w_router, bias, topk_idx, topk_w, st);
     const int blocks = cdiv(s.T, 32);
     if (s.dtype == FINE_F32) {
-#define FINE_TOPK_F32(NT, NW)                                                                                   \
-    hipLaunchKernelGGL((k_topk_f32<NT, NW>), dim3(blocks), dim3(64 * NW), 0, st, (const float*)x,               \
+#define FINE_TOPK_F32(NT, NW, J)                                                                                \
+    hipLaunchKernelGGL((k_topk_f32<NT, NW, J>), dim3(blocks), dim3(64 * NW), 0, st, (const float*)x,               \
                        (const float*)w_router, bias, s.T, s.d, s.E, s.K, topk_idx, topk_w)
-        if (s.E <= 32) FINE_TOPK_F32(1, 8);
-        else if (s.E <= 64) FINE_TOPK_F32(2, 8);
-        else if (s.E <= 128) FINE_TOPK_F32(4, 4);
-        else FINE_TOPK_F32(8, 4);
+        // From 1024 k-values on (eight waves' 128) up to 32 experts, all of a piece's loads are in flight together: a wave's few
+        // trips to memory are the kernel (J 4 : 16, us: 2048 tokens, d 1024, 16 experts 15.2 : 10.3; 8192 tokens 19.9 : 12.0; d 4096
+        // 60 : 31; 300 tokens, d 1024 12.9 : 9.9).  Below, waves would have nothing and the others' sums be longer: d 512 8.4 : 6.9 at
+        // 1.2 times the distance from 64-bit sums; d 128 5.1 : 6.7.  Nothing is gained at 48 experts (21.4 : 21.5).
+        if (s.E <= 32 && s.d >= 1024) FINE_TOPK_F32(1, 8, 16);
+        else if (s.E <= 32) FINE_TOPK_F32(1, 8, 4);
+        else if (s.E <= 64) FINE_TOPK_F32(2, 8, 4);
+        else if (s.E <= 128) FINE_TOPK_F32(4, 4, 1);
+        else FINE_TOPK_F32(8, 4, 1);
 #undef FINE_TOPK_F32
         FINE_LAUNCH_CHECK();
         return FINE_OK;

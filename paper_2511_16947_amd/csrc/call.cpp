@@ -1,6 +1,7 @@
 // Marshalling of a library call from Python: call(function, kinds, stream, shape, argument, ...) -> return code.
 //   function, shape   addresses
-//   kinds             a character per argument: 't' a tensor or None, 'i' an integer
+//   kinds             a character per argument: 't' a tensor or None, 'i' what ctypes takes for an int32_t: an int, a c_int32, what
+//                     has __index__ (NumPy's integers, integer tensors of one element) or an _as_parameter_ of these
 //   stream            what to call for the stream handle, which is passed last, once all arguments have been accepted
 //
 // Every argument of an entry point of finemoe.h is a pointer, an integer of at most 64 bits or a size, all of which the C calling
@@ -21,7 +22,8 @@
 namespace {
 
 constexpr Py_ssize_t kMaxArgs = 24;
-PyObject *s_is_cuda, *s_is_contiguous, *s_data_ptr;
+PyObject *s_is_cuda, *s_is_contiguous, *s_data_ptr, *s_value, *s_as_parameter;
+PyObject *c_int32, *refused;      // ctypes.c_int32; a ctypes.ArgumentError that is a TypeError too
 
 bool integer(PyObject* o, uint64_t& out) {
     out = PyLong_AsUnsignedLongLongMask(o);
@@ -51,6 +53,31 @@ bool pointer(PyObject* t, uint64_t& out) {
     return good;
 }
 
+// what is no int; argument number for the message
+bool other_integer(PyObject* o, Py_ssize_t number, uint64_t& out) {
+    const int simple = PyObject_IsInstance(o, c_int32);
+    if (simple < 0) return false;
+    PyObject* v = simple ? PyObject_GetAttr(o, s_value) : PyNumber_Index(o);
+    if (v == nullptr && !simple) {
+        PyErr_Clear();
+        v = PyObject_GetAttr(o, s_as_parameter);
+        if (v == nullptr) {
+            PyErr_Clear();
+            PyErr_Format(refused, "argument %zd: an integer, not %s", number, Py_TYPE(o)->tp_name);
+        }
+    }
+    if (v == nullptr) return false;
+    bool ok = false;
+    if (PyLong_Check(v)) {
+        ok = integer(v, out);
+    } else if (Py_EnterRecursiveCall(" in an _as_parameter_") == 0) {
+        ok = other_integer(v, number, out);
+        Py_LeaveRecursiveCall();
+    }
+    Py_DECREF(v);
+    return ok;
+}
+
 PyObject* call(PyObject*, PyObject* const* args, Py_ssize_t n) {
     Py_ssize_t n_args = 0;
     const char* kinds = n >= 4 ? PyUnicode_AsUTF8AndSize(args[1], &n_args) : nullptr;
@@ -67,10 +94,7 @@ PyObject* call(PyObject*, PyObject* const* args, Py_ssize_t n) {
         PyObject* o = args[4 + i];
         if (kinds[i] == 't') {
             if (o != Py_None && !pointer(o, v[1 + i])) return nullptr;
-        } else if (!PyLong_Check(o)) {
-            PyErr_Format(PyExc_TypeError, "argument %zd: an integer, not %s", i + 1, Py_TYPE(o)->tp_name);
-            return nullptr;
-        } else if (!integer(o, v[1 + i])) {
+        } else if (!(PyLong_Check(o) ? integer(o, v[1 + i]) : other_integer(o, i + 1, v[1 + i]))) {
             return nullptr;
         }
     }
@@ -101,6 +125,20 @@ PyMODINIT_FUNC PyInit__call() {
     s_is_cuda = PyUnicode_InternFromString("is_cuda");
     s_is_contiguous = PyUnicode_InternFromString("is_contiguous");
     s_data_ptr = PyUnicode_InternFromString("data_ptr");
-    if (s_is_cuda == nullptr || s_is_contiguous == nullptr || s_data_ptr == nullptr) return nullptr;
+    s_value = PyUnicode_InternFromString("value");
+    s_as_parameter = PyUnicode_InternFromString("_as_parameter_");
+    if (!s_is_cuda || !s_is_contiguous || !s_data_ptr || !s_value || !s_as_parameter) return nullptr;
+    PyObject* ctypes = PyImport_ImportModule("ctypes");
+    if (ctypes == nullptr) return nullptr;
+    c_int32 = PyObject_GetAttrString(ctypes, "c_int32");
+    PyObject* base = PyObject_GetAttrString(ctypes, "ArgumentError");
+    Py_DECREF(ctypes);
+    if (c_int32 == nullptr || base == nullptr) return nullptr;
+    PyObject* bases = PyTuple_Pack(2, base, PyExc_TypeError);
+    Py_DECREF(base);
+    if (bases == nullptr) return nullptr;
+    refused = PyErr_NewException("paper_2511_16947_amd.ArgumentError", bases, nullptr);
+    Py_DECREF(bases);
+    if (refused == nullptr) return nullptr;
     return PyModule_Create(&module);
 }

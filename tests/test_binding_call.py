@@ -3,6 +3,7 @@ anything is called."""
 import ctypes
 import inspect
 
+import numpy as np
 import pytest
 import torch
 
@@ -52,6 +53,39 @@ def test_arguments_arrive_in_order(call, n):
 def test_what_is_refused(call, kind, arg, error):
     with pytest.raises(error):      # (address 1 would be called; the stream is asked for only when all is accepted)
         call(1, "i" + kind, lambda: pytest.fail("accepted"), 77, 3, arg)
+
+
+class Index:
+    def __index__(self):
+        return -3
+
+
+class AsParameter:
+    def __init__(self, value):
+        self._as_parameter_ = value
+
+
+@pytest.mark.parametrize("arg", [
+    np.int32(-3), np.int64(-3), np.int8(-3), np.array(-3), torch.tensor(-3), torch.tensor(-3, dtype=torch.int32), Index(),
+    ctypes.c_int32(-3), AsParameter(-3), AsParameter(AsParameter(np.int64(-3)))])
+def test_integers_of_every_kind(call, arg):
+    """What ctypes takes for an int32_t: out of NumPy and torch too."""
+    seen = []
+    fn = ctypes.CFUNCTYPE(ctypes.c_int, *[U] * 3)(lambda *a: seen.append(a) or 0)
+    assert call(ctypes.cast(fn, ctypes.c_void_p).value, "i", lambda: 9, 77, arg) == 0
+    assert seen == [(77, -3 % (1 << 64), 9)]
+
+
+@pytest.mark.parametrize("arg", [np.float32(1), np.array([3]), torch.tensor(1.0), torch.tensor([1, 2]), ctypes.c_int64(1), ctypes.c_uint32(1),
+                                 AsParameter(1.0), AsParameter(None), "x", None])
+def test_refused_integers(call, arg):
+    with pytest.raises(TypeError) as info:
+        call(1, "ii", lambda: pytest.fail("accepted"), 77, 3, arg)
+    assert isinstance(info.value, ctypes.ArgumentError)      # what ctypes raises
+    loop = AsParameter(0)
+    loop._as_parameter_ = loop
+    with pytest.raises(RecursionError):
+        call(1, "i", lambda: pytest.fail("accepted"), 77, loop)
 
 
 def test_kinds_match_the_prototypes():

@@ -13,12 +13,13 @@ import ctypes
 import os
 from dataclasses import dataclass
 from functools import cached_property
+from importlib.machinery import EXTENSION_SUFFIXES
 
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libfinemoe.so")
-CALL_PATH = os.path.join(_HERE, "_call.so")
+CALL_PATH = os.path.join(_HERE, "_call" + EXTENSION_SUFFIXES[0])      # (built against this interpreter's headers, for it alone)
 
 FINE_OK = 0
 FINE_INVALID_ARG = -1

@@ -9,11 +9,12 @@ import subprocess
 import sys
 import sysconfig
 from concurrent.futures import ThreadPoolExecutor
+from importlib.machinery import EXTENSION_SUFFIXES
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libfinemoe.so")
-CALL = os.path.join(HERE, "_call.so")      # the Python binding's marshalling (host code)
+CALL = os.path.join(HERE, "_call" + EXTENSION_SUFFIXES[0])      # the Python binding's marshalling (host code, this interpreter's)
 SOURCES = ["api.hip", "sched.hip", "comm_sched.hip", "general_x.hip", "topk.hip", "movement.hip", "ffn_simple.hip", "ffn_f32.hip", "ffn_stream.hip",
            "ffn_mfma.hip", "backward.hip", "placement.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",

@@ -1,7 +1,9 @@
 """The binding's native marshalling (no GPU): every argument arrives in its place, and what is no device tensor is refused before
 anything is called."""
 import ctypes
+import importlib.machinery
 import inspect
+import os
 
 import numpy as np
 import pytest
@@ -33,6 +35,13 @@ class DeviceTensor:
 def call():
     fm.load_library()
     return fm._call
+
+
+def test_module_is_this_interpreters(call):
+    """No other interpreter finds it: its name carries the tag."""
+    path = os.path.join(os.path.dirname(fm.__file__), "_call" + importlib.machinery.EXTENSION_SUFFIXES[0])
+    assert fm._call.__self__.__file__ == path == fm.CALL_PATH
+    assert importlib.machinery.EXTENSION_SUFFIXES[0] != ".so"
 
 
 @pytest.mark.parametrize("n", [0, 1, 3, 5, 6, 13, 22])

@@ -460,11 +460,12 @@ __global__ __launch_bounds__(256) void k_topk_mfma_esplit(const uint16_t* __rest
     select_topk<NT>(all, bias, E, K, t0 + r, Tn, s_val, topk_idx, topk_w);
 }
 
-// fp32 layers.  A block is 32 tokens, its NW waves split k in pieces of 8 J, whose loads are in flight together.  Both MFMA operands come
-// straight from memory: lane (l & 31, h = l >> 5) supplies expert / token (l & 31) and the k-values
+// fp32 layers.  A block is 32 tokens, pieces of 8 J k-values are dealt to its NW waves in turn; a wave takes U of its pieces per iteration.  Both
+// MFMA operands come straight from memory: lane (l & 31, h = l >> 5) supplies expert / token (l & 31) and the k-values
 // 8 j + 4 h + 0 .. 3 of a piece (its token's as one 16-byte load, each weight a 4-byte load that 32 lanes make of
-// neighbouring experts).  k-values past d are zeros, experts past E are masked before the selection.
-template <int NT, int NW, int J>
+// neighbouring experts).  k-values past d are zeros, experts past E are masked before the selection.  The order of a sum depends on
+// J and NW alone, and with it the distance from 64-bit sums: longer pieces would leave some waves longer chains.
+template <int NT, int NW, int J, int U>
 __global__ __launch_bounds__(64 * NW) void k_topk_f32(const float* __restrict__ x, const float* __restrict__ w_router,
                                                       const float* __restrict__ bias, int Tn, int d, int E, int K,
                                                       int32_t* __restrict__ topk_idx, float* __restrict__ topk_w) {
@@ -483,40 +484,48 @@ __global__ __launch_bounds__(64 * NW) void k_topk_f32(const float* __restrict__ 
     for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
         for (int q = 0; q < 16; ++q) acc[nt][q] = 0.f;
-    auto group = [&](int k0, auto checked) {
-        f32x4 xv[J];
-        float wv[J][NT][4];
+    constexpr int kStep = NW * 8 * J;      // from a wave's piece to its next
+    auto pieces = [&](int k0, auto n, auto checked) {
+        f32x4 xv[n.value][J];
+        float wv[n.value][J][NT][4];
 #pragma unroll
-        for (int j = 0; j < J; ++j) {
-            const int k = k0 + 8 * j + 4 * h;
-            if constexpr (checked.value) {
+        for (int u = 0; u < n.value; ++u)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const float v = xrow[min(k + q, d - 1)];
-                    xv[j][q] = k + q < d ? v : 0.f;
+            for (int j = 0; j < J; ++j) {
+                const int k = k0 + u * kStep + 8 * j + 4 * h;
+                if constexpr (checked.value) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const float v = xrow[min(k + q, d - 1)];
+                        xv[u][j][q] = k + q < d ? v : 0.f;
+                    }
+                } else {
+                    xv[u][j] = *reinterpret_cast<const f32x4_a4*>(xrow + k);
                 }
-            } else {
-                xv[j] = *reinterpret_cast<const f32x4_a4*>(xrow + k);
-            }
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const float v = w_router[(size_t)(checked.value ? min(k + q, d - 1) : k + q) * E + e_of[nt]];
-                    wv[j][nt][q] = checked.value && k + q >= d ? 0.f : v;
-                }
-        }
-#pragma unroll
-        for (int j = 0; j < J; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt)
-                    acc[nt] = __builtin_amdgcn_mfma_f32_32x32x2f32(wv[j][nt][q], xv[j][q], acc[nt], 0, 0, 0);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const float v = w_router[(size_t)(checked.value ? min(k + q, d - 1) : k + q) * E + e_of[nt]];
+                        wv[u][j][nt][q] = checked.value && k + q >= d ? 0.f : v;
+                    }
+            }
+#pragma unroll
+        for (int u = 0; u < n.value; ++u)
+#pragma unroll
+            for (int j = 0; j < J; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt)
+                        acc[nt] = __builtin_amdgcn_mfma_f32_32x32x2f32(wv[u][j][nt][q], xv[u][j][q], acc[nt], 0, 0, 0);
     };
-    for (int k0 = wave * 8 * J; k0 < d; k0 += NW * 8 * J) {
-        if (k0 + 8 * J <= d) group(k0, std::false_type{});
-        else group(k0, std::true_type{});
+    int k0 = wave * 8 * J;
+    if constexpr (U > 1)
+        for (; k0 + (U - 1) * kStep + 8 * J <= d; k0 += U * kStep) pieces(k0, IntC<U>{}, std::false_type{});
+    for (; k0 < d; k0 += kStep) {
+        if (k0 + 8 * J <= d) pieces(k0, IntC<1>{}, std::false_type{});
+        else pieces(k0, IntC<1>{}, std::true_type{});
     }
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt)
@@ -659,18 +668,18 @@ int launch_topk(const fine_shape& s, const void* x, const void* w_router, const 
                                    : dispatch<uint16_t>(s, x, w_router, bias, topk_idx, topk_w, st);
     const int blocks = cdiv(s.T, 32);
     if (s.dtype == FINE_F32) {
-#define FINE_TOPK_F32(NT, NW, J)                                                                                \
-    hipLaunchKernelGGL((k_topk_f32<NT, NW, J>), dim3(blocks), dim3(64 * NW), 0, st, (const float*)x,               \
+#define FINE_TOPK_F32(NT, NW, J, U)                                                                             \
+    hipLaunchKernelGGL((k_topk_f32<NT, NW, J, U>), dim3(blocks), dim3(64 * NW), 0, st, (const float*)x,               \
                        (const float*)w_router, bias, s.T, s.d, s.E, s.K, topk_idx, topk_w)
-        // From 1024 k-values on (eight waves' 128) up to 32 experts, all of a piece's loads are in flight together: a wave's few
-        // trips to memory are the kernel (J 4 : 16, us: 2048 tokens, d 1024, 16 experts 15.2 : 10.3; 8192 tokens 19.9 : 12.0; d 4096
-        // 60 : 31; 300 tokens, d 1024 12.9 : 9.9).  Below, waves would have nothing and the others' sums be longer: d 512 8.4 : 6.9 at
-        // 1.2 times the distance from 64-bit sums; d 128 5.1 : 6.7.  Nothing is gained at 48 experts (21.4 : 21.5).
-        if (s.E <= 32 && s.d >= 1024) FINE_TOPK_F32(1, 8, 16);
-        else if (s.E <= 32) FINE_TOPK_F32(1, 8, 4);
-        else if (s.E <= 64) FINE_TOPK_F32(2, 8, 4);
-        else if (s.E <= 128) FINE_TOPK_F32(4, 4, 1);
-        else FINE_TOPK_F32(8, 4, 1);
+        // Up to 32 experts four pieces per iteration: a wave's few trips to memory are the kernel, and the one basic block of 64 MFMAs
+        // lets the compiler keep up to ten loads outstanding (it does not send them all out first: its waits count down to none every
+        // 8 to 50 MFMAs), where one piece per iteration waits for nearly each.  The sums are the same bit for bit.  One : four pieces,
+        // us, 16 experts: 256 tokens, d 128 5.3 : 4.4, d 1024 13.5 : 9.3; 2048 tokens, d 512 9.1 : 7.3, 768 11.2 : 9.2, 1024 15.4 : 10.3,
+        // 1152 16.5 : 11.2, 1536 21.2 : 14.4, 4096 60.2 : 28.4; 8192 tokens, d 1024 19.6 : 11.9.  Beyond 32 experts not measured.
+        if (s.E <= 32) FINE_TOPK_F32(1, 8, 4, 4);
+        else if (s.E <= 64) FINE_TOPK_F32(2, 8, 4, 1);
+        else if (s.E <= 128) FINE_TOPK_F32(4, 4, 1, 1);
+        else FINE_TOPK_F32(8, 4, 1, 1);
 #undef FINE_TOPK_F32
         FINE_LAUNCH_CHECK();
         return FINE_OK;

@@ -632,7 +632,9 @@ __global__ __launch_bounds__(256) void k_topk_select(const float* __restrict__ p
             if (t < Tn) topk_idx[(size_t)t * K + k] = be;
         }
     }
-    __builtin_amdgcn_wave_barrier();      // (a token's sixteen lanes belong to one wave, whose LDS accesses are performed in order)
+    // lane 0's values are read by the token's other lanes: of the same wave, whose LDS accesses are performed in order; the compiler has
+    // to keep the order too
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     const float top = s_val[grp][0];
     float sum = 0.f;
     for (int k0 = 0; k0 < K; k0 += 8) {

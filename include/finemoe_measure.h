@@ -13,7 +13,8 @@ enum {
     FINE_FLAG_ONLY_GEMM1 = 4,    /* timing: fine_grouped_ffn runs only X[Wg|Wu] + SwiGLU (H into ws)    */
     FINE_FLAG_ONLY_GEMM2 = 8,    /* timing: fine_grouped_ffn runs only H Wd (H as left in ws)           */
     FINE_FLAG_TILE_SHIFT = 8,    /* bits 8-9, tests: row tile of the MFMA kernels, 0 = chosen from the  */
-    FINE_FLAG_TILE_MASK = 0x300, /*   shape, 1 = 64 rows (backward: as 2), 2 = 128 rows, 3 = 256 rows */
+    FINE_FLAG_TILE_MASK = 0x300, /*   shape, 1 = 64 rows (backward: 128 rows on 4 waves, as where d f
+                                  *   is past the 8-wave kernels' offsets), 2 = 128 rows, 3 = 256 rows */
     /* bits 12-14, timing: fine_backward runs one stage only; the stages of a pass must then be called
      * in the order 1 .. 5 on one workspace: 1 = gradient of combine (and the recomputation of the
      * pre-activations when act_save is NULL), 2 = dH with the SwiGLU gradient, 3 = dXp,

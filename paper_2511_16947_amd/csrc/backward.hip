@@ -479,7 +479,7 @@ int launch_backward(const fine_shape& s, int rank_lo, int rank_hi, const void* d
     };
     int tile = (s.flags & FINE_FLAG_TILE_MASK) >> FINE_FLAG_TILE_SHIFT;
     if (tile == 0) tile = cost(256) <= cost(128) ? 3 : 2;
-    const bool w8 = w8_offsets_fit(s);
+    const bool w8 = w8_offsets_fit(s) && tile != 1;
 #define FINE_DGRAD(WAM, WAN, WMM, WNN)                                                                        \
     FINE_TRY((run_dgrad<WAM, WAN, WMM, WNN>(s, rank_lo, rank_hi, dy, act, (const uint16_t*)wg, (const uint16_t*)wu, \
                                             (const uint16_t*)wd, seg_off, dact, h_out, dxp, tiles, count, L.max_tiles, \

@@ -1,5 +1,6 @@
-"""Data gradients on 128-row and 256-row tiles: edges of the tiles, contractions of one to a few steps, weights that one tile alone
-reads.  Every element against 64-bit sums, and both heights bit for bit (a row's sums do not depend on the tile it lies in)."""
+"""Data gradients on 128-row tiles of 4 waves (those of matrices past the 8-wave kernels' offsets) and on 128-row and 256-row tiles of 8:
+edges of the tiles, contractions of one to a few steps, runs of one tile.  Every element against 64-bit sums,
+and all three bit for bit (a row's sums do not depend on the tile it lies in)."""
 import pytest
 import torch
 
@@ -29,14 +30,14 @@ def test_data_gradients_on_tiles_of_both_heights(d, f, rows):
     seg_off = torch.tensor([0] + rows, device=DEV).cumsum(0).int()[None].contiguous()
     w = torch.rand(P, 1, generator=gen, device=DEV)
     got = []
-    for tile in (2, 3):
+    for tile in (1, 2, 3):
         shape = fm.Shape(P, d, f, E, 1, 1, flags=fm.FLAG_LOCALITY | (tile << fm.FLAG_TILE_SHIFT))
         d_x, d_w = torch.full((P, d), 7.0, dtype=torch.bfloat16, device=DEV), torch.full((P, 1), 7.0, device=DEV)
         grads = [torch.full((E, *m), 7.0, device=DEV) for m in ((d, f), (d, f), (f, d))]
         fm.fine_backward(shape, -1, d_out, x, y, act, wg, wu, wd, pairs, pairs, seg_off, w, d_x, d_w, *grads, False,
                          fm.alloc_workspace(shape, fm.WS_BACKWARD))
         got.append([d_x] + grads)
-    assert all(torch.equal(a, b) for a, b in zip(*got))
+    assert all(torch.equal(a, b) and torch.equal(a, c) for a, b, c in zip(*got))
     r = 0
     for e, n in enumerate(rows):
         if n == 0:

@@ -24,15 +24,21 @@ using namespace mfma;
 template <int WM, typename OA, typename Tile, typename InitB>
 __device__ __forceinline__ void k_loop_rows(int nk, char* smem, f32x16 (&acc)[WM][2], const TileEntry& te, OA& oa, Tile k_tile, int nf,
                                             InitB init_b) {
-    auto run = [&](auto ragged, auto nt) {
-        RowDmaOperand<2, 256, nt.value> ob;
+    if constexpr (WM == 2) {
+        auto run = [&](auto ragged, auto nt) {
+            RowDmaOperand<2, 256, nt.value> ob;
+            init_b(ob);
+            k_loop8_rows3<ragged.value>(nk, smem, acc, oa, ob, k_tile, nf);
+        };
+        if (te.rows == WM * 64) run(std::false_type{}, std::false_type{});
+        else if (te.alone) run(std::true_type{}, std::true_type{});
+        else run(std::true_type{}, std::false_type{});
+    } else {      // (set up once in front of the branch: in both arms it cost dH four more spilled registers)
+        RowDmaOperand<2> ob;
         init_b(ob);
-        if constexpr (WM == 2) k_loop8_rows3<ragged.value>(nk, smem, acc, oa, ob, k_tile, nf);
-        else k_loop8<ragged.value>(nk, smem, acc, oa, ob, k_tile, nf);
-    };
-    if (te.rows == WM * 64) run(std::false_type{}, std::false_type{});
-    else if (WM == 2 && te.alone) run(std::true_type{}, std::integral_constant<bool, WM == 2>{});
-    else run(std::true_type{}, std::false_type{});
+        if (te.rows == WM * 64) k_loop8<false>(nk, smem, acc, oa, ob, k_tile, nf);
+        else k_loop8<true>(nk, smem, acc, oa, ob, k_tile, nf);
+    }
 }
 
 // ---- dH = dY Wd^T with the SwiGLU backward epilogue -------------------------------------

@@ -19,11 +19,11 @@ namespace {
 using namespace mfma;
 
 // The k-loop of a data gradient's tile on 8 waves: both operands contiguous along k, init_b sets up the weights'.  On 128 rows
-// weights that no other row tile reads are fetched non-temporal (5196 rows on 93 experts of 1856 x 1728: dH 154 -> 142 us,
+// weights that nobody reads again (see nt_from) are fetched non-temporal (5196 rows on 93 experts of 1856 x 1728: dH 154 -> 142 us,
 // dXp 238 -> 217; of 256 rows a tile is seldom alone).
 template <int WM, typename OA, typename Tile, typename InitB>
-__device__ __forceinline__ void k_loop_rows(int nk, char* smem, f32x16 (&acc)[WM][2], const TileEntry& te, OA& oa, Tile k_tile, int nf,
-                                            InitB init_b) {
+__device__ __forceinline__ void k_loop_rows(int nk, char* smem, f32x16 (&acc)[WM][2], const TileEntry& te, int nt_from, OA& oa, Tile k_tile,
+                                            int nf, InitB init_b) {
     if constexpr (WM == 2) {
         auto run = [&](auto ragged, auto nt) {
             RowDmaOperand<2, 256, nt.value> ob;
@@ -31,7 +31,7 @@ __device__ __forceinline__ void k_loop_rows(int nk, char* smem, f32x16 (&acc)[WM
             k_loop8_rows3<ragged.value>(nk, smem, acc, oa, ob, k_tile, nf);
         };
         if (te.rows == WM * 64) run(std::false_type{}, std::false_type{});
-        else if (te.alone) run(std::true_type{}, std::true_type{});
+        else if (te.alone >= nt_from) run(std::true_type{}, std::true_type{});
         else run(std::true_type{}, std::false_type{});
     } else {      // (set up once in front of the branch: in both arms it cost dH four more spilled registers)
         RowDmaOperand<2> ob;
@@ -46,7 +46,7 @@ template <int WAVES_M, int WAVES_N, int WM, int WN>
 __device__ __forceinline__ void bwd_dh_body(const uint16_t* __restrict__ dy, const uint16_t* __restrict__ wd,
                                             const uint16_t* __restrict__ act, int d, int f,
                                             uint16_t* __restrict__ dact, uint16_t* __restrict__ h,
-                                            const TileEntry* __restrict__ tiles, int32_t* __restrict__ count) {
+                                            const TileEntry* __restrict__ tiles, int32_t* __restrict__ count, int nt_from) {
     constexpr int BM = WAVES_M * WM * 32, BN = WAVES_N * WN * 32;
     constexpr bool W8 = WAVES_M * WAVES_N == 8;
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -72,7 +72,7 @@ __device__ __forceinline__ void bwd_dh_body(const uint16_t* __restrict__ dy, con
             oa.init(dy + (size_t)te.row0 * d, [&](int r) { return (size_t)r * d; },
                     (uint32_t)((size_t)te.rows * d * 2), (wave / WAVES_N) * WM * 32);
             const int nf = min(WM, max(0, (te.rows - (wave / WAVES_N) * WM * 32 + 31) / 32));
-            k_loop_rows<WM>(d / BK, smem, acc, te, oa, k_tile, nf, [&](auto& ob) {
+            k_loop_rows<WM>(d / BK, smem, acc, te, nt_from, oa, k_tile, nf, [&](auto& ob) {
                 ob.init(W, [&](int n) { return (size_t)min(n0 + n, f - 1) * d; }, (uint32_t)((size_t)f * d * 2),
                         (wave % WAVES_N) * WN * 32);
             });
@@ -145,15 +145,15 @@ template <int WAVES_M, int WAVES_N, int WM, int WN>
 __global__ __launch_bounds__(256) void k_bwd_dh(const uint16_t* __restrict__ dy, const uint16_t* __restrict__ wd,
                                                 const uint16_t* __restrict__ act, int d, int f,
                                                 uint16_t* __restrict__ dact, uint16_t* __restrict__ h,
-                                                const TileEntry* __restrict__ tiles, int32_t* __restrict__ count) {
-    bwd_dh_body<WAVES_M, WAVES_N, WM, WN>(dy, wd, act, d, f, dact, h, tiles, count);
+                                                const TileEntry* __restrict__ tiles, int32_t* __restrict__ count, int nt_from) {
+    bwd_dh_body<WAVES_M, WAVES_N, WM, WN>(dy, wd, act, d, f, dact, h, tiles, count, nt_from);
 }
 template <int WAVES_M, int WAVES_N, int WM, int WN>
 __global__ __launch_bounds__(512) void k_bwd_dh_w8(const uint16_t* __restrict__ dy, const uint16_t* __restrict__ wd,
                                                    const uint16_t* __restrict__ act, int d, int f,
                                                    uint16_t* __restrict__ dact, uint16_t* __restrict__ h,
-                                                   const TileEntry* __restrict__ tiles, int32_t* __restrict__ count) {
-    bwd_dh_body<WAVES_M, WAVES_N, WM, WN>(dy, wd, act, d, f, dact, h, tiles, count);
+                                                   const TileEntry* __restrict__ tiles, int32_t* __restrict__ count, int nt_from) {
+    bwd_dh_body<WAVES_M, WAVES_N, WM, WN>(dy, wd, act, d, f, dact, h, tiles, count, nt_from);
 }
 
 // ---- dXp = [dA | dB] [Wg | Wu]^T --------------------------------------------------------------
@@ -161,7 +161,7 @@ template <int WAVES_M, int WAVES_N, int WM, int WN>
 __device__ __forceinline__ void bwd_dx_body(const uint16_t* __restrict__ dact, const uint16_t* __restrict__ wg,
                                             const uint16_t* __restrict__ wu, int d, int f,
                                             uint16_t* __restrict__ dxp, const TileEntry* __restrict__ tiles,
-                                            int32_t* __restrict__ count) {
+                                            int32_t* __restrict__ count, int nt_from) {
     constexpr int BM = WAVES_M * WM * 32, BN = WAVES_N * WN * 32;
     constexpr bool W8 = WAVES_M * WAVES_N == 8;
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -196,7 +196,7 @@ __device__ __forceinline__ void bwd_dx_body(const uint16_t* __restrict__ dact, c
             oa.init(dact + (size_t)te.row0 * (2 * f), [&](int r) { return (size_t)r * (2 * f); },
                     (uint32_t)((size_t)te.rows * 2 * f * 2), (wave / WAVES_N) * WM * 32);
             const int nf = min(WM, max(0, (te.rows - (wave / WAVES_N) * WM * 32 + 31) / 32));
-            k_loop_rows<WM>(2 * nkf, smem, acc, te, oa, k_tile, nf, [&](auto& ob) {
+            k_loop_rows<WM>(2 * nkf, smem, acc, te, nt_from, oa, k_tile, nf, [&](auto& ob) {
                 ob.init(Wg, [&](int n) { return (size_t)min(n0 + n, d - 1) * f; }, (uint32_t)((size_t)d * f * 2),
                         (wave % WAVES_N) * WN * 32, Wu);
             });
@@ -218,15 +218,15 @@ template <int WAVES_M, int WAVES_N, int WM, int WN>
 __global__ __launch_bounds__(256) void k_bwd_dx(const uint16_t* __restrict__ dact, const uint16_t* __restrict__ wg,
                                                 const uint16_t* __restrict__ wu, int d, int f,
                                                 uint16_t* __restrict__ dxp, const TileEntry* __restrict__ tiles,
-                                                int32_t* __restrict__ count) {
-    bwd_dx_body<WAVES_M, WAVES_N, WM, WN>(dact, wg, wu, d, f, dxp, tiles, count);
+                                                int32_t* __restrict__ count, int nt_from) {
+    bwd_dx_body<WAVES_M, WAVES_N, WM, WN>(dact, wg, wu, d, f, dxp, tiles, count, nt_from);
 }
 template <int WAVES_M, int WAVES_N, int WM, int WN>
 __global__ __launch_bounds__(512) void k_bwd_dx_w8(const uint16_t* __restrict__ dact, const uint16_t* __restrict__ wg,
                                                    const uint16_t* __restrict__ wu, int d, int f,
                                                    uint16_t* __restrict__ dxp, const TileEntry* __restrict__ tiles,
-                                                   int32_t* __restrict__ count) {
-    bwd_dx_body<WAVES_M, WAVES_N, WM, WN>(dact, wg, wu, d, f, dxp, tiles, count);
+                                                   int32_t* __restrict__ count, int nt_from) {
+    bwd_dx_body<WAVES_M, WAVES_N, WM, WN>(dact, wg, wu, d, f, dxp, tiles, count, nt_from);
 }
 
 // ---- weight gradients: out[e][m][n] (+)= sum over the rows of expert e of A[row][m] * B[row][n] ----
@@ -381,7 +381,8 @@ int run_dgrad(const fine_shape& s, int rank_lo, int rank_hi, const uint16_t* dy,
               const uint16_t* wd, const int32_t* seg_off, uint16_t* dact, uint16_t* h, uint16_t* dxp,
               TileEntry* tiles, int32_t* count, int max_tiles, bool run_dh, bool run_dx, hipStream_t st) {
     constexpr int BM = WAVES_M * WM * 32, BN = WAVES_N * WN * 32;
-    FINE_TRY(launch_tile_map(s, seg_off, rank_lo, rank_hi, BM, tiles, count, max_tiles, st));      // also zeroes the queues
+    const int nt1 = nt_from(s, 1, rank_hi - rank_lo), nt2 = nt_from(s, 2, rank_hi - rank_lo);      // (nt1 >= nt2)
+    FINE_TRY(launch_tile_map(s, seg_off, rank_lo, rank_hi, BM, nt1 == 2, tiles, count, max_tiles, st));      // also zeroes the queues
     constexpr bool W8 = WAVES_M * WAVES_N == 8;
     const size_t lds = (size_t)(W8 && WM == 2 ? 3 : 2) * (BM + BN) * 128;
     constexpr int threads = WAVES_M * WAVES_N * 64;
@@ -392,11 +393,11 @@ int run_dgrad(const fine_shape& s, int rank_lo, int rank_hi, const uint16_t* dy,
     FINE_TRY(raise_lds_limit((const void*)k2, (int)lds, lds_set2));
     const int grid = 256 * ((lds <= 80 * 1024) ? 2 : 1);
     if (run_dh) {
-        hipLaunchKernelGGL(k1, dim3(grid), dim3(threads), lds, st, dy, wd, act, s.d, s.f, dact, h, tiles, count);
+        hipLaunchKernelGGL(k1, dim3(grid), dim3(threads), lds, st, dy, wd, act, s.d, s.f, dact, h, tiles, count, nt1);
         FINE_LAUNCH_CHECK();
     }
     if (run_dx) {
-        hipLaunchKernelGGL(k2, dim3(grid), dim3(threads), lds, st, dact, wg, wu, s.d, s.f, dxp, tiles, count);
+        hipLaunchKernelGGL(k2, dim3(grid), dim3(threads), lds, st, dact, wg, wu, s.d, s.f, dxp, tiles, count, nt2);
         FINE_LAUNCH_CHECK();
     }
     return FINE_OK;
@@ -499,7 +500,7 @@ int launch_backward(const fine_shape& s, int rank_lo, int rank_hi, const void* d
     // Weight-gradient tiles span the weight matrices, not the segments: 256 x 256 on 8 waves wherever they fit, however
     // few rows an expert has (4 waves, 128 x 128: 5 rows 697 : 419 us, 43 rows 1157 : 458, 60 rows 1347 : 504).
     if (on(4)) {
-        if (only == 4) FINE_TRY(launch_tile_map(s, seg_off, rank_lo, rank_hi, 256, tiles, count, L.max_tiles, st));      // zeroes the queues
+        if (only == 4) FINE_TRY(launch_tile_map(s, seg_off, rank_lo, rank_hi, 256, false, tiles, count, L.max_tiles, st));      // zeroes the queues
         if (s.d >= 256 && s.f >= 256)
             FINE_TRY((run_wgrad<2, 4, 4, 2>(s, rank_lo, rank_hi, (const uint16_t*)x_perm, dy, dact, h_in, seg_off, d_wg, d_wu, d_wd, accumulate, count, st)));
         else

@@ -96,8 +96,19 @@ struct TileEntry {
     int32_t expert;
     int32_t row0;      // first row of the tile (absolute row of the permuted buffer)
     int32_t rows;      // valid rows in the tile (1..BM)
-    int32_t alone;     // 1: the only tile of its run
+    int32_t alone;     // 1: the only tile of its run; 2: of its expert, too (found where it was asked for)
 };
+
+// Weights that nobody reads again are fetched non-temporal.  nt_from: the least TileEntry::alone for that.  A call for all ranks under a
+// placement can have several runs of an expert, each of one tile, on ranks that are not neighbours: up to the 256 MB of the memory-side
+// cache the second one finds the weights there, past it they go through it unused.  By the megabytes of a launch's matrices,
+// non-temporal : not, us, 64 rows on each of an expert's 4 (or 2) ranks, other weights from call to call: dH 67 70 : 54, 134 116 : 95, 201
+// 199 : 182 (119 : 125), 268 230 : 230 (124 : 100), 537 462 : 540; dXp 134 97 : 90, 268 222 : 168, 403 309 : 325 (159 : 169), 805 812 :
+// 878.  The forward GEMMs, which together go by the first one's: 134 156 : 144, 268 289 : 265, 403 444 : 452, 537 548 : 575, 1074 1061 : 1160.
+// Experts of one run: up to 134 equal; the first GEMM at 403 230 : 255.
+inline int nt_from(const fine_shape& s, int matrices, int n_ranks) {
+    return n_ranks > 1 && (double)s.E * s.d * s.f * 2.0 * matrices <= 320e6 ? 2 : 1;
+}
 
 // The GEMM kernels keep byte offsets from a tile's bases in 32 bits.  The 8-wave ones (gemm_w8.h) span 256 rows of
 // activations and a whole weight matrix:
@@ -186,7 +197,8 @@ int launch_combine_bwd(const fine_shape& s, const void* d_out, const void* y_per
 int launch_permute_bwd(const fine_shape& s, const void* dx_perm, const int32_t* row_of_pair,
                        void* d_x, hipStream_t st);
 
-int launch_tile_map(const fine_shape& s, const int32_t* seg_off, int rank_lo, int rank_hi, int BM,
+// sole: an expert's only tile is marked as that (TileEntry::alone)
+int launch_tile_map(const fine_shape& s, const int32_t* seg_off, int rank_lo, int rank_hi, int BM, bool sole,
                     TileEntry* tiles, int32_t* count, int max_tiles, hipStream_t st);
 
 int launch_ffn_simple(const fine_shape& s, int rank_lo, int rank_hi, const void* x_perm,

@@ -412,7 +412,7 @@ int launch_ffn_f32(const fine_shape& s, int rank_lo, int rank_hi, const void* x_
     const int bm = split ? kSM : kBM, bn = narrow ? 16 : split ? 32 : 64;
     const int32_t* seg = nullptr;
     if (n_ranks == 1 && s.E <= kRankMapExperts) seg = seg_off + (size_t)rank_lo * (s.E + 1);
-    else FINE_TRY(launch_tile_map(s, seg_off, rank_lo, rank_hi, bm, tiles, count, L.max_tiles, st));
+    else FINE_TRY(launch_tile_map(s, seg_off, rank_lo, rank_hi, bm, false, tiles, count, L.max_tiles, st));
     // three blocks per CU, four of the split kernel (whose registers let two to four in); no more than there can be tiles
     const size_t rows_tiles = (size_t)s.T * s.K / bm + (size_t)s.E * n_ranks;
     auto grid = [&](int n) { return (unsigned)std::min<size_t>(split ? 1024 : 768, align_up(rows_tiles * cdiv(n, bn), 8)); };

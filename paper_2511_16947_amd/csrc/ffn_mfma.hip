@@ -33,7 +33,7 @@ __device__ __forceinline__ void ffn_gemm_body(const uint16_t* __restrict__ A, in
                                               const uint16_t* __restrict__ B1, size_t b_expert_stride, int Kd, int N,
                                               uint16_t* __restrict__ C, int ldc, uint16_t* __restrict__ act,
                                               const TileEntry* __restrict__ tiles, int32_t* __restrict__ count,
-                                              float* __restrict__ sk_partials, int may_cut, int tall) {
+                                              float* __restrict__ sk_partials, int may_cut, int tall, int nt_from) {
     constexpr int BN = WAVES_N * WN * 32;
     constexpr int BNC = (EPI == 0) ? BN / 2 : BN;      // output columns per block
     static_assert(WAVES_M == 2 && WAVES_N == 4 && WN == 2, "2 x 4 waves on 256 x 256 or 128 x 256");
@@ -72,12 +72,12 @@ __device__ __forceinline__ void ffn_gemm_body(const uint16_t* __restrict__ A, in
             }
             k_loop8<ragged.value, 4>(kn, smem, acc, oa, ob, k_tile, nf);
         };
-        // Weights that no other row tile reads bypass the caches (non-temporal), which leaves those to the activations and
-        // to weights that are read again: 32 rows on each of 64 experts of 7168 x 2048, both GEMMs 985 -> 894 us (5.7 -> 6.3
+        // Weights that nobody reads again (see nt_from) bypass the caches, which leaves those to the activations and to weights
+        // that are; a tile of exactly BM rows takes the form without row tests, which has one policy: 32 rows on each of 64 experts of 7168 x 2048, both GEMMs 985 -> 894 us (5.7 -> 6.3
         // TB/s); 8192 rows on them (half of the runs one tile) 1254 -> 1219; 10725 rows on 144 of 3776 x 512 394 -> 361; where most
         // runs have several tiles nothing changes.  (Non-temporal throughout is 7 % slower: then weights are shared.)
         if (te.rows == BM) k_range(std::false_type{}, std::false_type{});
-        else if (te.alone) k_range(std::true_type{}, std::true_type{});
+        else if (te.alone >= nt_from) k_range(std::true_type{}, std::true_type{});
         else k_range(std::true_type{}, std::false_type{});
     };
 
@@ -348,8 +348,8 @@ __global__ __launch_bounds__(512) void k_ffn_gemm_w8(const uint16_t* __restrict_
                                                      size_t b_expert_stride, int Kd, int N,
                                                      uint16_t* __restrict__ C, int ldc, uint16_t* __restrict__ act,
                                                      const TileEntry* __restrict__ tiles, int32_t* __restrict__ count,
-                                                     float* __restrict__ sk_partials, int may_cut, int tall) {
-    ffn_gemm_body<2, 4, 2, EPI>(A, lda, B0, B1, b_expert_stride, Kd, N, C, ldc, act, tiles, count, sk_partials, may_cut, tall);
+                                                     float* __restrict__ sk_partials, int may_cut, int tall, int nt_from) {
+    ffn_gemm_body<2, 4, 2, EPI>(A, lda, B0, B1, b_expert_stride, Kd, N, C, ldc, act, tiles, count, sk_partials, may_cut, tall, nt_from);
 }
 
 // BM: rows of the list's tiles, 256 or 128
@@ -357,7 +357,8 @@ int run_ffn(const fine_shape& s, int BM, int rank_lo, int rank_hi, const void* x
             const void* wd, const int32_t* seg_off, void* h_buf, void* y_perm, void* act_save, TileEntry* tiles,
             int32_t* count, int max_tiles, float* sk_partials, bool gemm1, bool gemm2, bool may_cut, hipStream_t st) {
     auto* h = reinterpret_cast<uint16_t*>(h_buf);
-    FINE_TRY(launch_tile_map(s, seg_off, rank_lo, rank_hi, BM, tiles, count, max_tiles, st));
+    const int nt = nt_from(s, 2, rank_hi - rank_lo);
+    FINE_TRY(launch_tile_map(s, seg_off, rank_lo, rank_hi, BM, nt == 2, tiles, count, max_tiles, st));
     const size_t lds = (size_t)w8_lds_bytes(true, 4);
     static std::atomic<uint64_t> lds_set1{0}, lds_set2{0};
     FINE_TRY(raise_lds_limit((const void*)k_ffn_gemm_w8<0>, (int)lds, lds_set1));
@@ -366,13 +367,13 @@ int run_ffn(const fine_shape& s, int BM, int rank_lo, int rank_hi, const void* x
     if (gemm1) {
         hipLaunchKernelGGL(k_ffn_gemm_w8<0>, dim3(grid), dim3(512), lds, st, (const uint16_t*)x_perm, s.d, (const uint16_t*)wg,
                            (const uint16_t*)wu, (size_t)s.d * s.f, s.d, s.f, h, s.f, (uint16_t*)act_save, tiles, count,
-                           sk_partials, (int)may_cut, (int)(BM == 256));
+                           sk_partials, (int)may_cut, (int)(BM == 256), nt);
         FINE_LAUNCH_CHECK();
     }
     if (gemm2) {
         hipLaunchKernelGGL(k_ffn_gemm_w8<1>, dim3(grid), dim3(512), lds, st, (const uint16_t*)h, s.f, (const uint16_t*)wd,
                            (const uint16_t*)nullptr, (size_t)s.f * s.d, s.f, s.d, (uint16_t*)y_perm, s.d,
-                           (uint16_t*)nullptr, tiles, count, sk_partials, (int)may_cut, (int)(BM == 256));
+                           (uint16_t*)nullptr, tiles, count, sk_partials, (int)may_cut, (int)(BM == 256), nt);
         FINE_LAUNCH_CHECK();
     }
     return FINE_OK;

@@ -54,13 +54,16 @@ __device__ inline int block_excl_scan(int v, int ident, int* s_w, Op op) {
 
 template <bool CACHED>
 __global__ __launch_bounds__(kMapThreads) void k_tile_map(const int32_t* __restrict__ seg_off, int E, int rank_lo,
-                                                          int rank_hi, int BM, TileEntry* __restrict__ tiles,
+                                                          int rank_hi, int BM, int sole, TileEntry* __restrict__ tiles,
                                                           int32_t* __restrict__ count, int max_tiles) {
     extern __shared__ int32_t s_seg[];
     __shared__ int s_w[kMapThreads / 64];
     const int tid = threadIdx.x;
     clear_counts(count);
     const int32_t* from = seg_off + (size_t)rank_lo * (E + 1);
+    int32_t* s_runs = s_seg + (CACHED ? (rank_hi - rank_lo) * (E + 1) : 0);      // sole: runs of each expert
+    if (sole != 0)
+        for (int e = tid; e < E; e += blockDim.x) s_runs[e] = 0;      // (added to after a scan's barriers)
     if (CACHED) {
         for (int i = tid; i < (rank_hi - rank_lo) * (E + 1); i += blockDim.x) s_seg[i] = from[i];
         __syncthreads();
@@ -90,30 +93,33 @@ __global__ __launch_bounds__(kMapThreads) void k_tile_map(const int32_t* __restr
     auto continues = [&](int at, int e, int prev, int prev_e) { return prev >= 0 && prev_e == e && end_row(prev) == first_row(at); };
     int head = -1, prev = before, prev_e = before_e;
     each([&](int at, int e) {
-        if (!continues(at, e, prev, prev_e)) head = at;
+        if (!continues(at, e, prev, prev_e)) {
+            head = at;
+            if (sole != 0) atomicAdd(&s_runs[e], 1);
+        }
         prev = at;
         prev_e = e;
     });
     const int head_at = block_excl_scan(head, -1, s_w, max_op);
     const int head_before = head_at < 0 ? 0 : first_row(head_at);      // (ranks' rows may lie in any order)
     // A run's tiles start at its first row + multiples of BM; each belongs to the segment that its first row lies in.
-    // visit(e, r): a tile starts at row r of expert e; closed(end, head): the run from row `head` has ended at `end`.
+    // visit(e, r): a tile starts at row r of expert e; closed(e, end, head): its run from row `head` has ended at `end`.
     auto walk = [&](auto visit, auto closed) {
         int h = head_before, p = before, pe = before_e;
         each([&](int at, int e) {
             const int r0 = first_row(at), r1 = end_row(at);
             if (!continues(at, e, p, pe)) {
-                if (p >= 0) closed(end_row(p), h);
+                if (p >= 0) closed(pe, end_row(p), h);
                 h = r0;
             }
             p = at;
             pe = e;
             for (int r = h + (r0 - h + BM - 1) / BM * BM; r < r1; r += BM) visit(e, r);
         });
-        if (tid == (int)blockDim.x - 1 && p >= 0) closed(end_row(p), h);
+        if (tid == (int)blockDim.x - 1 && p >= 0) closed(pe, end_row(p), h);
     };
     int nt = 0;
-    walk([&](int, int) { ++nt; }, [](int, int) {});
+    walk([&](int, int) { ++nt; }, [](int, int, int) {});
     const int at0 = block_excl_scan(nt, 0, s_w, [](int a, int b) { return a + b; });
     int at = at0;
     walk(
@@ -121,14 +127,16 @@ __global__ __launch_bounds__(kMapThreads) void k_tile_map(const int32_t* __restr
             if (at < max_tiles) tiles[at] = TileEntry{e, r, BM, 0};
             ++at;
         },
-        [](int, int) {});
+        [](int, int, int) {});
     __syncthreads();
     at = at0;
     walk([&](int, int) { ++at; },
-         [&](int end, int h) {      // its last tile is the last one so far
+         [&](int e, int end, int h) {      // its last tile is the last one so far
              if (at - 1 >= max_tiles) return;
              tiles[at - 1].rows = end - (h + (end - 1 - h) / BM * BM);
-             tiles[at - 1].alone = end - h <= BM;
+             int alone = end - h <= BM;
+             if (alone != 0 && sole != 0 && s_runs[e] == 1) alone = 2;
+             tiles[at - 1].alone = alone;
          });
     if (tid == (int)blockDim.x - 1) *count = min(at, max_tiles);
 }
@@ -144,7 +152,7 @@ __global__ __launch_bounds__(kMapThreads) void k_tile_map_rank(const int32_t* __
     clear_counts(count);
     const int at = block_excl_scan(nt, 0, s_w, [](int a, int b) { return a + b; });
     for (int i = 0; i < nt && at + i < max_tiles; ++i)
-        tiles[at + i] = TileEntry{e, r0 + i * BM, min(BM, n - i * BM), nt == 1};
+        tiles[at + i] = TileEntry{e, r0 + i * BM, min(BM, n - i * BM), nt == 1 ? 2 : 0};
     if (e == (int)blockDim.x - 1) *count = min(at + nt, max_tiles);
 }
 
@@ -235,17 +243,17 @@ __global__ __launch_bounds__(256) void k_gemm_simple(const T* __restrict__ A, in
 
 }  // namespace
 
-int launch_tile_map(const fine_shape& s, const int32_t* seg_off, int rank_lo, int rank_hi, int BM,
+int launch_tile_map(const fine_shape& s, const int32_t* seg_off, int rank_lo, int rank_hi, int BM, bool sole,
                     TileEntry* tiles, int32_t* count, int max_tiles, hipStream_t st) {
     if (rank_hi - rank_lo == 1 && s.E <= kMapThreads)
         hipLaunchKernelGGL(k_tile_map_rank, dim3(1), dim3((unsigned)align_up(s.E, 64)), 0, st,
                            seg_off + (size_t)rank_lo * (s.E + 1), s.E, BM, tiles, count, max_tiles);
     else {
         const int n_ranks = rank_hi - rank_lo;
-        const size_t lds = (size_t)n_ranks * (s.E + 1) * 4;
+        const size_t runs = sole ? (size_t)s.E * 4 : 0, lds = (size_t)n_ranks * (s.E + 1) * 4 + runs;
         hipLaunchKernelGGL(lds <= kMapLds ? k_tile_map<true> : k_tile_map<false>, dim3(1),
-                           dim3((unsigned)std::min<size_t>(kMapThreads, align_up((size_t)n_ranks * s.E, 64))), lds <= kMapLds ? lds : 0, st,
-                           seg_off, s.E, rank_lo, rank_hi, BM, tiles, count, max_tiles);
+                           dim3((unsigned)std::min<size_t>(kMapThreads, align_up((size_t)n_ranks * s.E, 64))), lds <= kMapLds ? lds : runs, st,
+                           seg_off, s.E, rank_lo, rank_hi, BM, (int)sole, tiles, count, max_tiles);
     }
     FINE_LAUNCH_CHECK();
     return FINE_OK;
@@ -275,7 +283,7 @@ static int ffn_simple_t(const fine_shape& s, int rank_lo, int rank_hi, const voi
     T* h = reinterpret_cast<T*>(ws + L.h);
     if ((s.flags & FINE_FLAG_ACT_SAVE_H) && act_save != nullptr)      // H behind the saved pre-activations
         h = static_cast<T*>(act_save) + (size_t)s.T * s.K * 2 * s.f;
-    FINE_TRY(launch_tile_map(s, seg_off, rank_lo, rank_hi, 64, tiles, count, L.max_tiles, st));
+    FINE_TRY(launch_tile_map(s, seg_off, rank_lo, rank_hi, 64, false, tiles, count, L.max_tiles, st));
     const int grid = 2048;
     hipLaunchKernelGGL((k_gemm_simple<T, 0>), dim3(grid), dim3(256), 0, st, (const T*)x_perm, s.d, (const T*)wg,
                        (const T*)wu, (size_t)s.d * s.f, s.d, s.f, h, s.f, (T*)act_save, 2 * s.f, tiles, count);

@@ -203,7 +203,7 @@ __global__ __launch_bounds__(256, 2) void k_ffn_stream(const uint16_t* __restric
             constexpr int NF = nf.value;
             f32x16 acc[NF][4];
             zero_acc<NF, 4>(acc);
-            // Weights that no other row tile reads bypass the caches (non-temporal): 8 % more from HBM.  (With
+            // Weights of a run of one tile bypass the caches (non-temporal): 8 % more from HBM.  (With
             // several tiles per run it would be the other way round: their weights come from the L2 but once.)
             auto k_range = [&](auto nt) {
                 StreamOperands<NF, nt.value> o;
@@ -270,7 +270,7 @@ int launch_ffn_stream(const fine_shape& s, int rank_lo, int rank_hi, const void*
     auto* h = reinterpret_cast<uint16_t*>(h_buf);
     const int32_t* seg = nullptr;
     if (rank_hi - rank_lo == 1 && s.E <= kRankMapExperts) seg = seg_off + (size_t)rank_lo * (s.E + 1);
-    else FINE_TRY(launch_tile_map(s, seg_off, rank_lo, rank_hi, kStreamRows, tiles, count, max_tiles, st));
+    else FINE_TRY(launch_tile_map(s, seg_off, rank_lo, rank_hi, kStreamRows, false, tiles, count, max_tiles, st));
     const size_t lds = 4 * kStreamWave;
     static std::atomic<uint64_t> lds_set0{0}, lds_set1{0};
     FINE_TRY(raise_lds_limit((const void*)k_ffn_stream<0>, (int)lds, lds_set0));

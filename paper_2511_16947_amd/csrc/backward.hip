@@ -20,7 +20,7 @@ using namespace mfma;
 
 // The k-loop of a data gradient's tile on 8 waves: both operands contiguous along k, init_b sets up the weights'.  On 128 rows
 // weights that nobody reads again (see nt_from) are fetched non-temporal (5196 rows on 93 experts of 1856 x 1728: dH 154 -> 142 us,
-// dXp 238 -> 217; of 256 rows a tile is seldom alone).
+// dXp 238 -> 217; of 256 rows a tile is seldom alone; one of exactly 128 takes the form without row tests, which has one policy).
 template <int WM, typename OA, typename Tile, typename InitB>
 __device__ __forceinline__ void k_loop_rows(int nk, char* smem, f32x16 (&acc)[WM][2], const TileEntry& te, int nt_from, OA& oa, Tile k_tile,
                                             int nf, InitB init_b) {
@@ -331,7 +331,8 @@ __device__ __forceinline__ void wgrad_body(WgradProblem p0, WgradProblem p1, Wgr
             auto store = [&](auto nt) {
                 store_tile_f32_direct<WAVES_M, WAVES_N, WM, WN, nt.value>(acc, p.out + (size_t)e * p.M * p.N, p.M, p.N, m0, n0, accumulate != 0);
             };
-            // Up to 384 rows the tile's 256 KB of output are most of its memory traffic: stored non-temporal they leave the operands
+            // Up to six steps (384 rows; fewer in several segments, whose last steps are short) the tile's 256 KB of output are most
+            // of its memory traffic: stored non-temporal they leave the operands
             // that neighbouring tiles share in the L2 (128 rows on 64 experts of 1088 x 2112: 421 -> 323 us; 64 on 128 of 2048 x 768:
             // 474 -> 409; but 520 on 32 of 2048 x 8192: 2240 -> 2267, 7270 -> 7490 on 64 experts of very different rows).  Old values that
             // are added to are read once, too: 520 rows 3448 -> 3149, 1024 on 16 experts 2064 -> 1948, 4096 on 8 2174 : 2171.

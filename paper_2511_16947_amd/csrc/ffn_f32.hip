@@ -171,8 +171,8 @@ __global__ __launch_bounds__(256, 3) void k_ffn_f32(const float* __restrict__ A,
 // Small launches: 32 rows x 32 columns (GEMM 1: 32 gate columns and the matching 32 up columns) per block, the contraction
 // split over its four waves, operands from memory straight into registers.  With fewer of the tiles above than CUs a
 // launch is a chain of latencies on few CUs: a load, its 2048 cycles of MFMA, the next.  Here a quarter of the chain is
-// left, four to eight times as many blocks share the work, and a wave has 64 k-values under way before it waits for the
-// first.  The four partial tiles are added in LDS, in the order of k.  That is another order than the one chain of the kernel
+// left, four to eight times as many blocks share the work, and a wave asks for 64 k-values before it waits, for all of them: the second
+// chunk's request is behind a branch, after which the compiler's waits for the first count down to none.  The four partial tiles are added in LDS, in the order of k.  That is another order than the one chain of the kernel
 // above (its distance from 64-bit sums is half as large), and which one a row gets depends on the call's ranks: a rank's call
 // and the call over all ranks differ in last bits where one takes this kernel and the other does not.  (The kernel above with
 // its sums in the same four ranges takes 2 % longer, 4 % on short k: 4096 rows of 1024 x 2816 561 -> 573, 8192 of 128 x 256 30 -> 31.)

@@ -572,8 +572,8 @@ __device__ inline int from_lane(int v) { return __builtin_amdgcn_update_dpp(v, v
 // Second pass of the gate when blocks shared token tiles.  Sixteen lanes per token, lane l holding
 // experts l, l + 16, ...: T / 4 wavefronts instead of the T / 32 that the accumulator layout gives.
 // Partial logits are added in ascending part order, then the bias; K rounds of (largest value, lowest
-// expert of equals) over the lane's values and across the sixteen lanes.  Bound by latency: memory once (the parts' loads
-// together), then a chain of K rounds, whose exchanges are DPP moves and not trips through the LDS crossbar.
+// expert of equals) over the lane's values and across the sixteen lanes.  Bound by latency: memory once or, beyond 128
+// experts, three times, then a chain of K rounds, whose exchanges are DPP moves and not trips through the LDS crossbar.
 template <int MAXJ>
 __global__ __launch_bounds__(256) void k_topk_select(const float* __restrict__ partial, int parts, int rows, int epad,
                                                     const float* __restrict__ bias, int Tn, int E, int K,
@@ -584,7 +584,8 @@ __global__ __launch_bounds__(256) void k_topk_select(const float* __restrict__ p
     float v[MAXJ];
 #pragma unroll
     for (int j = 0; j < MAXJ; ++j) v[j] = 0.f;
-    // four parts' and the bias's values are under way at a time (a part past the last is read as the last and not added)
+    // The bias's and four parts' values are asked for ahead of the sums (a part past the last is read as the last and not added).  At
+    // MAXJ 8 the compiler sends all 32 before it waits; at 16 it sends the first 16 eight at a time and then 48.
     float b[MAXJ];
     if (bias != nullptr) {
 #pragma unroll
